@@ -386,7 +386,6 @@ struct Layout {
     uint32_t *tick = nullptr;
     uint32_t *state = nullptr;  // [0] error bits, [1] name count
     uint32_t *split = nullptr;
-    uint32_t *packed = nullptr, *sepmask = nullptr, *wordcnt = nullptr;
     SortBufs sb{};
 };
 
@@ -421,9 +420,6 @@ void carve_dc3(Carver &c, int64_t n, const Tune &t, uint32_t *top_out, Layout *L
     L->tick = c.take<uint32_t>(64);
     L->state = c.take<uint32_t>(64);
     L->split = c.take<uint32_t>((n + kMgTile - 1) / kMgTile + 2);
-    L->packed = c.take<uint32_t>(packed_words(n));
-    L->sepmask = c.take<uint32_t>(sepmask_words(n));
-    L->wordcnt = c.take<uint32_t>(sepmask_words(n));
     carve_sort(c, items, 64, t, &L->sb, true);
 }
 
@@ -583,7 +579,7 @@ struct Dc3 {
 
     int run(int64_t n, int32_t *levels_out) {
         SA_TRY(launch_fill_u32(L.state, 64, 0, st));
-        SA_TRY(launch_pack(text, n, L.packed, L.sepmask, L.wordcnt, L.state, st));
+        SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, nullptr, L.state, st));  // validation
         int depth = 0;
         for (;; ++depth) {
             Level &v = L.lev[depth];

@@ -111,12 +111,11 @@ void timing_pause(bool on);  // calling thread: no events while a stream is bein
 int64_t packed_words(int64_t n);
 int64_t sepmask_words(int64_t n);
 
-// pack: packed/sepmask/per-word separator counts; err bits OR-ed into *err.
+// pack: validates the text (err bits OR-ed into *err) and writes those of its forms that are
+// asked for (NULL: not): the 2-bit codes, the separator bits, the separators per word, and the
+// records for random-access windows (text.hpp; sepmask_words(n) of them).
 int launch_pack(const uint8_t *text, int64_t n, uint32_t *packed, uint32_t *sepmask,
-                uint32_t *wordcnt, uint32_t *err, hipStream_t s);
-// block layout for random-access windows (text.hpp): nrec = sepmask_words(n) records
-int launch_blocks(const uint32_t *packed, const uint32_t *sepmask, uint4 *blk, int64_t nrec,
-                  hipStream_t s);
+                uint32_t *wordcnt, uint4 *blk, uint32_t *err, hipStream_t s);
 // exclusive scan of uint32 values into int32 (out[i] = sum of in[0..i)); total -> *total_out
 int64_t scan_flags_words(int64_t n);
 int launch_scan_u32_i32(const uint32_t *in, int32_t *out, int64_t n, int32_t *total_out,
@@ -161,8 +160,10 @@ int launch_hist(const SortBufs &b, int cur, int64_t n, int bit_lo, int bits, con
                 hipStream_t s, int *nparts);
 // Runs the passes over n items (or, when count_dev is given, over the count read from device
 // memory, at most n); returns the buffer index holding the sorted data in *cur_out.
+// index_vals: vals[cur] is not read, each item's value is its index.
 int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, int bit_lo,
-             int bits, const Tune &t, int nparts, hipStream_t s, int *cur_out);
+             int bits, const Tune &t, int nparts, hipStream_t s, int *cur_out,
+             bool index_vals = false);
 
 // Device-side round state of a suffix-array build (words of a uint32 array).
 constexpr int kStErr = 0;      // error bits
@@ -175,13 +176,30 @@ constexpr int kStBig = 6;      // 1: some group entering the round has more than
 constexpr int kStRadixN = 7;   // items of large groups the round sorts by radix passes
 constexpr int kStBigNext = 8;  // set by the rank update for the next round
 constexpr int kStBigLast = 9;  // kStRadixN of the round that ended (read back for timing)
+constexpr int kStLongRun = 10; // first round: a run of equal top key bits is too long for LDS
+constexpr int kStNoExt = 11;   // first round: some group is equal on the h0 symbols of its key only
 constexpr int kStWords = 16;   // state words the host reads back
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
-// key builders (fused with the histogram of the sort that follows)
-int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0,
-                const int64_t *set_off_dev, int n_sets, int key_bits, const SortBufs &b, int cur,
-                const Tune &t, hipStream_t s, int *nparts);
+// key builders (fused with the histogram of the sort that follows, over key bits
+// [lo_bit, key_bits)); a value is its item's index and is left to the first pass
+int launch_key0(const uint4 *blk, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
+                int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
+                hipStream_t s, int *nparts);
+// First round (first_round.hip): from items ordered by key bits [lo_bit, ..), which tell their
+// first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the items of
+// runs too long for it, taken out.
+constexpr int kExtBases = 61;
+constexpr int kFirstMinTile = 1792;
+int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint4 *blk, int64_t n,
+                      int lo_bit, int top_d, int h0, bool mixed, int32_t *sa, uint32_t *rank,
+                      uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags, int64_t lb_words,
+                      uint32_t *tick, uint32_t *state, hipStream_t s);
+int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,
+                         int key_bits,
+                         const SortBufs &b, uint32_t *idx, uint64_t *lbflags, int64_t lb_words,
+                         uint32_t *tick, uint32_t *state, const Tune &t, hipStream_t s,
+                         int *nparts);
 // Keys of the items in groups of more than kRunMax members (sa_build.hip's doubling rounds),
 // into b.keys[0]/b.vals[0] with their list indices in bigidx, fused with the histograms.
 int launch_big_extract(const uint32_t *P, const uint32_t *S, const uint32_t *rank, int64_t n,

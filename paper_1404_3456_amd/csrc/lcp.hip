@@ -148,9 +148,6 @@ __global__ void k_lcp_flag(const uint32_t *err, int32_t *lcp) {
 int64_t lcp_ws_bytes(int64_t n) {
     if (n < 1) return -1;
     Carver c(nullptr, INT64_MAX);
-    c.take<uint32_t>(packed_words(n));
-    c.take<uint32_t>(sepmask_words(n));
-    c.take<uint32_t>(sepmask_words(n));
     c.take<uint4>(sepmask_words(n));
     c.take<uint32_t>(64);
     if (n >= g_plcp_min_n) c.take<int32_t>(n);
@@ -161,9 +158,6 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
             void *ws, int64_t ws_bytes, hipStream_t stream, int32_t *flag, int64_t span) {
     if (ws_bytes < lcp_ws_bytes(n)) return fail(SA_ERR_NOMEM, "sa_lcp: workspace too small");
     Carver c(ws, ws_bytes);
-    uint32_t *packed = c.take<uint32_t>(packed_words(n));
-    uint32_t *sepmask = c.take<uint32_t>(sepmask_words(n));
-    uint32_t *wordcnt = c.take<uint32_t>(sepmask_words(n));
     uint4 *blk = c.take<uint4>(sepmask_words(n));
     uint32_t *err = c.take<uint32_t>(64);
     // the scattered writes of one text stay inside its own block of the array: with texts of
@@ -171,8 +165,7 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
     const bool plcp = (span > 0 && span < n ? span : n) >= g_plcp_min_n;
     int32_t *pl = plcp ? c.take<int32_t>(n) : nullptr;
     SA_TRY(launch_fill_u32(err, 1, 0, stream));
-    SA_TRY(launch_pack(text, n, packed, sepmask, wordcnt, err, stream));
-    SA_TRY(launch_blocks(packed, sepmask, blk, sepmask_words(n), stream));
+    SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, blk, err, stream));
     const uint32_t chunk = g_lcp_chunk;
     const int64_t threads = (n + chunk - 1) / chunk;
     const dim3 grid(unsigned((threads + 255) / 256));

@@ -134,9 +134,6 @@ using namespace saasm;
 extern "C" int64_t sa_lookup_ws_bytes(int64_t n, int64_t pat_total) {
     if (n < 1 || pat_total < 0) return -1;
     Carver c(nullptr, INT64_MAX);
-    c.take<uint32_t>(packed_words(n));
-    c.take<uint32_t>(sepmask_words(n));
-    c.take<uint32_t>(sepmask_words(n));
     c.take<uint4>(sepmask_words(n));
     c.take<uint32_t>(pat_words(pat_total));
     c.take<uint32_t>(64);
@@ -155,15 +152,11 @@ extern "C" int sa_lookup(const uint8_t *text, int64_t n, const int32_t *sa, cons
         return fail(SA_ERR_NOMEM, "sa_lookup: workspace too small");
     if (n_pat == 0) return SA_OK;
     Carver c(ws, ws_bytes);
-    uint32_t *packed = c.take<uint32_t>(packed_words(n));
-    uint32_t *sepmask = c.take<uint32_t>(sepmask_words(n));
-    uint32_t *wordcnt = c.take<uint32_t>(sepmask_words(n));
     uint4 *blk = c.take<uint4>(sepmask_words(n));
     uint32_t *ppk = c.take<uint32_t>(pat_words(pat_total));
     uint32_t *err = c.take<uint32_t>(64);
     SA_TRY(launch_fill_u32(err, 1, 0, stream));
-    SA_TRY(launch_pack(text, n, packed, sepmask, wordcnt, err, stream));
-    SA_TRY(launch_blocks(packed, sepmask, blk, sepmask_words(n), stream));
+    SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, blk, err, stream));
     const int64_t pw = pat_words(pat_total);
     hipLaunchKernelGGL(k_pack_pat, dim3(unsigned((pw + 255) / 256)), dim3(256), 0, stream, pat,
                        pat_total, ppk, pw, err);

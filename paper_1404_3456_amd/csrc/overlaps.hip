@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_run_write(const uint64_t *__restrict__ 
 }
 
 struct OvlFixed {
-    uint32_t *packed, *sepmask, *wordcnt;
+    uint32_t *sepmask, *wordcnt;
     int32_t *sepcnt, *read_end;
     uint32_t *counts;
     int64_t *offs;
@@ -116,9 +116,8 @@ struct OvlFixed {
     uint32_t *ctr;  // [0] err; [2..3] m (int32 at ctr+2); int64 totals at ctr+8, ctr+10
 };
 
-// Text-sized part (packed text, separator rank structure) then read-sized part (m reads).
+// Text-sized part (separator rank structure) then read-sized part (m reads).
 static void carve_fixed(Carver &c, int64_t n, int64_t m, OvlFixed *F) {
-    F->packed = c.take<uint32_t>(packed_words(n));
     F->sepmask = c.take<uint32_t>(sepmask_words(n));
     F->wordcnt = c.take<uint32_t>(sepmask_words(n));
     F->sepcnt = c.take<int32_t>(sepmask_words(n));
@@ -190,10 +189,10 @@ extern "C" int sa_overlaps(const uint8_t *text, int64_t n, const int32_t *sa, co
     OvlFixed F;
     {
         Carver c0(ws, ws_bytes);
-        carve_fixed(c0, n, 1, &F);  // pack area and counters only; read arrays carved below
+        carve_fixed(c0, n, 1, &F);  // separators and counters only; read arrays carved below
     }
     SA_TRY(launch_fill_u32(F.ctr, 64, 0, s));
-    SA_TRY(launch_pack(text, n, F.packed, F.sepmask, F.wordcnt, F.ctr, s));
+    SA_TRY(launch_pack(text, n, nullptr, F.sepmask, F.wordcnt, nullptr, F.ctr, s));
     const int64_t nw = (n + 31) / 32;
     SA_TRY(launch_scan_u32_i32(F.wordcnt, F.sepcnt, nw, reinterpret_cast<int32_t *>(F.ctr + 2),
                                F.lbflags, F.tick, F.ctr, s));

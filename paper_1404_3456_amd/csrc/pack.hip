@@ -12,12 +12,14 @@ namespace saasm {
 int64_t sepmask_words(int64_t n) { return (n + 31) / 32 + 4; }
 int64_t packed_words(int64_t n) { return 2 * sepmask_words(n); }
 
-// One thread per 32 text positions: one separator-mask word and two packed words.  Words past
-// the end of the text are written as zeros (padding that window reads may touch).
+// One thread per 32 text positions: one separator-mask word, two packed words and one window
+// record (text.hpp), each only where its array is given.  Words past the end of the text are
+// written as zeros (padding that window reads may touch).
 __global__ __launch_bounds__(256) void k_pack(const uint8_t *__restrict__ text, int64_t n,
                                               uint32_t *__restrict__ packed,
                                               uint32_t *__restrict__ sepmask,
-                                              uint32_t *__restrict__ wordcnt, int64_t nwords,
+                                              uint32_t *__restrict__ wordcnt,
+                                              uint4 *__restrict__ blk, int64_t nwords,
                                               uint32_t *err) {
     int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (w >= nwords) return;
@@ -54,38 +56,25 @@ __global__ __launch_bounds__(256) void k_pack(const uint8_t *__restrict__ text, 
             if (b[(n - 1) - p0] != '$') raise_err(err, kErrNoSepEnd);
         }
     }
-    packed[2 * w] = hiw;
-    packed[2 * w + 1] = low;
-    sepmask[w] = sep;
-    wordcnt[w] = __popc(sep);
+    if (packed) {
+        packed[2 * w] = hiw;
+        packed[2 * w + 1] = low;
+    }
+    if (sepmask) sepmask[w] = sep;
+    if (wordcnt) wordcnt[w] = __popc(sep);
+    if (blk) blk[w] = make_uint4(hiw, low, sep, 0u);
     if (bad) raise_err(err, kErrAlphabet);
 }
 
 int launch_pack(const uint8_t *text, int64_t n, uint32_t *packed, uint32_t *sepmask,
-                uint32_t *wordcnt, uint32_t *err, hipStream_t s) {
+                uint32_t *wordcnt, uint4 *blk, uint32_t *err, hipStream_t s) {
     int64_t nw = sepmask_words(n);
-    TimedScope ts("pack", double(n) + double(nw) * 16.0, s, double(n));
+    const double per = (packed ? 8.0 : 0.0) + (sepmask ? 4.0 : 0.0) + (wordcnt ? 4.0 : 0.0) +
+                       (blk ? 16.0 : 0.0);
+    TimedScope ts("pack", double(n) + double(nw) * per, s, double(n));
     hipLaunchKernelGGL(k_pack, dim3(unsigned((nw + 255) / 256)), dim3(256), 0, s, text, n, packed,
-                       sepmask, wordcnt, nw, err);
+                       sepmask, wordcnt, blk, nw, err);
     ts.finish();
-    SA_HIP(hipGetLastError());
-    return SA_OK;
-}
-
-// Block layout of the text for random-access windows (see text.hpp): record b = {codes of
-// positions 32b..32b+15, codes of 32b+16..32b+31, separator bits of 32b..32b+31, 0}.
-__global__ __launch_bounds__(256) void k_blocks(const uint32_t *__restrict__ packed,
-                                                const uint32_t *__restrict__ sepmask,
-                                                uint4 *__restrict__ blk, int64_t nrec) {
-    const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b >= nrec) return;
-    blk[b] = make_uint4(packed[2 * b], packed[2 * b + 1], sepmask[b], 0u);
-}
-
-int launch_blocks(const uint32_t *packed, const uint32_t *sepmask, uint4 *blk, int64_t nrec,
-                  hipStream_t s) {
-    hipLaunchKernelGGL(k_blocks, dim3(unsigned((nrec + 255) / 256)), dim3(256), 0, s, packed,
-                       sepmask, blk, nrec);
     SA_HIP(hipGetLastError());
     return SA_OK;
 }
@@ -274,7 +263,7 @@ extern "C" int sa_pack(const uint8_t *text, int64_t n, uint32_t *packed, uint32_
     uint32_t *tick = c.take<uint32_t>(64);
     uint32_t *ctr = c.take<uint32_t>(64);
     SA_TRY(launch_fill_u32(ctr, 64, 0, stream));
-    SA_TRY(launch_pack(text, n, packed, sepmask, wordcnt, ctr, stream));
+    SA_TRY(launch_pack(text, n, packed, sepmask, wordcnt, nullptr, ctr, stream));
     const int64_t nw = (n + 31) / 32;
     SA_TRY(launch_scan_u32_i32(wordcnt, sepcnt, nw, reinterpret_cast<int32_t *>(ctr + 2), lbflags,
                                tick, ctr, stream));

@@ -22,6 +22,7 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "text.hpp"
 
 namespace saasm {
 
@@ -230,7 +231,8 @@ __device__ __forceinline__ void rank_wave(const uint64_t (&key)[ITEMS], uint32_t
 // One tile per workgroup, tiles numbered by ticket.  The grid covers an upper bound on the
 // item count; the count itself is read from device memory when `count_dev` is given (so the
 // same launch can be recorded in a graph and replayed with whatever count an earlier kernel
-// produced; surplus workgroups exit at once), otherwise it is `n_host`.
+// produced; surplus workgroups exit at once), otherwise it is `n_host`.  vin == nullptr: an
+// item's value is its index.
 template <int D, int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_onesweep(const uint64_t *__restrict__ kin,
                                                     const uint32_t *__restrict__ vin,
@@ -277,14 +279,14 @@ __global__ __launch_bounds__(BLOCK) void k_onesweep(const uint64_t *__restrict__
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 key[k] = kp[k * kWave];
-                val[k] = vp[k * kWave];
+                val[k] = vin ? vp[k * kWave] : wbase + lane + k * kWave;
             }
         } else {
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const uint32_t idx = wbase + k * kWave + lane;
                 key[k] = idx < n ? kin[idx] : 0;
-                val[k] = idx < n ? vin[idx] : 0;
+                val[k] = idx < n ? (vin ? vin[idx] : idx) : 0;
             }
         }
 
@@ -440,9 +442,11 @@ static int launch_pass_d(const Tune &t, int64_t n_max, hipStream_t s, const uint
 }
 
 int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, int bit_lo,
-             int bits, const Tune &t, int nparts, hipStream_t s, int *cur_out) {
+             int bits, const Tune &t, int nparts, hipStream_t s, int *cur_out,
+             bool index_vals) {
     const int P = sort_passes(bits, t);
     *cur_out = cur;
+    if (index_vals && n == 1) SA_TRY(launch_fill_u32(b.vals[cur], 1, 0, s));
     if (P == 0 || n <= 1) return SA_OK;
     const int R = t.radix();
     switch (t.dbits) {
@@ -459,15 +463,16 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
         const int width = (bits - lo) < t.dbits ? (bits - lo) : t.dbits;
         const uint32_t shift = uint32_t(bit_lo + lo);
         const uint32_t dmask = (1u << width) - 1u;
+        const uint32_t *vin = index_vals && p == 0 ? nullptr : b.vals[cur];
         TimedScope ts = count_dev ? TimedScope("radix_pass", 0.0, 24.0, s)
-                                  : TimedScope("radix_pass", double(n) * 24.0, s, double(n));
+                                  : TimedScope("radix_pass", double(n) * (vin ? 24.0 : 20.0), s, double(n));
         int rc = SA_OK;
         uint32_t *fl = b.flags + size_t(p) * tiles * R;
         switch (t.dbits) {
-            case 4: rc = launch_pass_d<4>(t, n, s, b.keys[cur], b.vals[cur], b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 8: rc = launch_pass_d<8>(t, n, s, b.keys[cur], b.vals[cur], b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 9: rc = launch_pass_d<9>(t, n, s, b.keys[cur], b.vals[cur], b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 11: rc = launch_pass_d<11>(t, n, s, b.keys[cur], b.vals[cur], b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 4: rc = launch_pass_d<4>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 8: rc = launch_pass_d<8>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 9: rc = launch_pass_d<9>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 11: rc = launch_pass_d<11>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
             default: rc = fail(SA_ERR_INVALID, "unsupported digit width");
         }
         ts.finish();
@@ -479,27 +484,37 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
 }
 
 // ---- key builders ---------------------------------------------------------------------------
-// First-round key of suffix p (prefix length h0 <= 29): the 2-bit codes of T[p .. p+min(L_p, h0)),
-// zero-padded to h0 bases, followed by min(L_p, h0) in 5 bits, where L_p is the distance from p
-// to the next separator.  Comparing two such keys as integers orders the suffixes by their
-// first h0 symbols with the separator below every base; keys equal with a length below h0
-// belong to suffixes that end at different separators at the same offset, whose order is
-// their position order (kept by the stable sort, since values are positions).  For a batch of
-// independent texts the text's index is placed above these bits, so every text's suffixes
-// form one contiguous block of the order.
-__device__ __forceinline__ uint64_t key0_of(const uint32_t *__restrict__ packed,
-                                            const uint32_t *__restrict__ sepmask, uint32_t p,
-                                            uint32_t h0) {
-    const uint32_t w = p >> 4, o = p & 15;
-    uint64_t x = (uint64_t(packed[w]) << 32) | packed[w + 1];
-    x <<= 2 * o;
-    if (o) x |= uint64_t(packed[w + 2]) >> (32 - 2 * o);
-    const uint32_t sw = p >> 5, so = p & 31;
-    const uint64_t sm = ((uint64_t(sepmask[sw]) << 32) | sepmask[sw + 1]) << so;
-    uint32_t L = sm ? uint32_t(__clzll((long long)sm)) : 64u;
+// First-round key of suffix p (prefix length h0 <= 29), from the top: where the string of its
+// first D bases stands among all strings of at most D bases in sorted order (2D + 1 bits), the
+// 2-bit codes of its next h0 - D bases, and min(L_p, h0) in 5 bits, where L_p is the distance
+// from p to the next separator; bases past the separator count as zero.  Comparing two such
+// keys as integers orders the suffixes by their first h0 symbols with the separator below every
+// base; keys equal with a length below h0 belong to suffixes that end at different separators
+// at the same offset, whose order is their position order (kept by the stable sort, since
+// values are positions).  D = 0 leaves the codes of all h0 bases and the length.  With D > 0 a
+// suffix of fewer than D bases shares its top bits only with its equals, not, as in plain
+// codes, with every suffix that goes on in A's.  For a batch of independent texts the text's
+// index is placed above these bits, so every text's suffixes form one contiguous block of the
+// order.
+// The standing of w, |w| <= D: its |w| proper prefixes and, for every base w_i, the w_i
+// smaller subtrees of (4^(D-i) - 1) / 3 strings each: |w| + sum w_i (4^(D-i) - 1) / 3, which is
+// |w| + (4 c - sum w_i) / 3 for the code c of w padded with zeros to D bases.
+__device__ __forceinline__ uint64_t key0_of(const uint4 *__restrict__ blk, uint32_t p,
+                                            uint32_t h0, uint32_t D) {
+    const Window x = window_at(blk, p);
+    uint32_t L = x.sep ? uint32_t(__clz(x.sep)) : 32u;
     if (L > h0) L = h0;
-    uint64_t code = x >> (64 - 2 * h0);
+    uint64_t code = x.code >> (64 - 2 * h0);
     if (L < h0) code &= ~((uint64_t(1) << (2 * (h0 - L))) - 1);
+    if (D) {
+        const uint32_t rest = 2 * (h0 - D);
+        const uint64_t c = code >> rest;
+        const uint64_t sum = uint64_t(popc64(c & 0x5555555555555555ull)) +
+                             2u * uint64_t(popc64(c & 0xaaaaaaaaaaaaaaaaull));
+        // the difference is a multiple of 3, so this product with 3's inverse is the quotient
+        const uint64_t at = (L < D ? L : D) + (4 * c - sum) * 0xaaaaaaaaaaaaaaabull;
+        code = (at << rest) | (code & ((uint64_t(1) << rest) - 1));
+    }
     return (code << 5) | L;
 }
 
@@ -518,42 +533,41 @@ __device__ __forceinline__ uint32_t set_of(const int64_t *__restrict__ set_off, 
 constexpr int kK0Block = 1024;  // threads per key0 workgroup (grid-stride, one partial each)
 
 template <int D>
-__global__ __launch_bounds__(kK0Block) void k_key0(const uint32_t *__restrict__ packed,
-                                              const uint32_t *__restrict__ sepmask, uint32_t n,
-                                              uint32_t h0, const int64_t *__restrict__ set_off,
-                                              uint32_t n_sets, uint64_t *__restrict__ keys,
-                                              uint32_t *__restrict__ vals, int passes,
+__global__ __launch_bounds__(kK0Block) void k_key0(const uint4 *__restrict__ blk, uint32_t n,
+                                              uint32_t h0, uint32_t top_d,
+                                              const int64_t *__restrict__ set_off,
+                                              uint32_t n_sets, int set_shift,
+                                              uint64_t *__restrict__ keys, int lo_bit, int passes,
                                               uint32_t *__restrict__ hist) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
-    const int set_shift = int(2 * h0 + 5);
     for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-        uint64_t k = key0_of(packed, sepmask, p, h0);
+        uint64_t k = key0_of(blk, p, h0, top_d);
         if (set_off) k |= uint64_t(set_of(set_off, n_sets, p)) << set_shift;
         keys[p] = k;
-        vals[p] = p;
-        hist_add<D>(s_h, k, passes);
+        hist_add<D>(s_h, k >> lo_bit, passes);
     }
     __syncthreads();
     hist_flush<D>(s_h, hist, passes);
 }
 
-int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0,
-                const int64_t *set_off_dev, int n_sets, int key_bits, const SortBufs &b, int cur,
-                const Tune &t, hipStream_t s, int *nparts) {
-    const int P = sort_passes(key_bits, t);
+int launch_key0(const uint4 *blk, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
+                int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
+                hipStream_t s, int *nparts) {
+    const int set_shift = 2 * h0 + 5 + (top_d ? 1 : 0);
+    const int P = sort_passes(key_bits - lo_bit, t);
     *nparts = int(hist_grid(n));
     size_t lds = size_t(P) * t.radix() * 4;
-    TimedScope ts("key0", double(n) * (12.0 + 0.375), s, double(n));
+    TimedScope ts("key0", double(n) * (8.0 + 0.5), s, double(n));
     const unsigned g = hist_grid(n);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(n), uint32_t(h0), set_off_dev, uint32_t(n_sets), b.keys[cur], b.vals[cur], P, b.hist); break;
-        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(n), uint32_t(h0), set_off_dev, uint32_t(n_sets), b.keys[cur], b.vals[cur], P, b.hist); break;
-        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(n), uint32_t(h0), set_off_dev, uint32_t(n_sets), b.keys[cur], b.vals[cur], P, b.hist); break;
-        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(n), uint32_t(h0), set_off_dev, uint32_t(n_sets), b.keys[cur], b.vals[cur], P, b.hist); break;
+        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
+        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
+        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
+        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();

@@ -33,10 +33,11 @@ namespace saasm {
 constexpr int kRuBlock = 1024;
 constexpr int kRuItems = 8;
 constexpr int kRuTile = kRuBlock * kRuItems;
-// Smallest tile of a kernel that takes the build's tile look-back words (the rank update; the
-// large-group extraction's tiles are larger): the array holds one word per tile of this size,
-// and every launcher checks its tile count against that on the host.
-constexpr int kLbMinTile = kRuTile;
+// Smallest tile of a kernel that takes the build's tile look-back words: the array holds one
+// word per tile of this size, and every launcher checks its tile count against that on the host.
+constexpr int kLbMinTile = kFirstMinTile < kRuTile ? kFirstMinTile : kRuTile;
+
+constexpr int64_t kTopMinN = 16384;  // the default radix tile (choose_first_round)
 
 // Rank update over the sorted active items (K, V) of a round, whose suffix-array slots are
 // S[0..A) (S == nullptr: identity, round 0).  For item i:
@@ -211,14 +212,16 @@ __global__ __launch_bounds__(kRuBlock) void k_rank_update(
     }
 }
 
-// Advances the round state after a rank update (one thread).
-__global__ void k_round_end(uint32_t *state, uint32_t h_first) {
+// Advances the round state after a rank update (one thread).  h_ext: symbols the first round's
+// groups are equal on unless it met one too large to be extended past h_first (0: none was).
+__global__ void k_round_end(uint32_t *state, uint32_t h_first, uint32_t h_ext) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     state[kStBigLast] = state[kStRadixN];  // the round's large-group items (0 when none)
     state[kStRadixN] = 0;
     if (state[kStActive] == 0) return;  // the round had nothing to do
     const uint32_t rounds = state[kStRounds];
-    state[kStH] = rounds == 0 ? h_first : state[kStH] * 2u;
+    if (rounds > 0) state[kStH] *= 2u;
+    else state[kStH] = h_ext && !state[kStNoExt] ? h_ext : h_first;
     state[kStRounds] = rounds + 1;
     state[kStActive] = state[kStNext];
     // the next round sorts the items of groups too large for the run sort by radix passes
@@ -250,7 +253,7 @@ static int bits_for(int64_t v) {  // bits needed to hold 0..v
 }
 
 struct BuildLayout {
-    uint32_t *packed, *sepmask, *wordcnt;
+    uint4 *blk;            // packed text (window records)
     uint32_t *rank;        // used when the caller gives no isa buffer
     uint32_t *slots[2];
     uint32_t *pos;         // active text positions in the last round's order (bit 31: run start)
@@ -267,12 +270,11 @@ struct BuildLayout {
 
 static void carve_build(Carver &c, int64_t n, int n_sets, const Tune &t, BuildLayout *L) {
     const int bits = 63 > 2 * bits_for(n) ? 63 : 2 * bits_for(n);
-    L->packed = c.take<uint32_t>(packed_words(n));
-    L->sepmask = c.take<uint32_t>(sepmask_words(n));
-    L->wordcnt = c.take<uint32_t>(sepmask_words(n));
+    L->blk = c.take<uint4>(sepmask_words(n));
     L->rank = c.take<uint32_t>(n);
-    L->slots[0] = c.take<uint32_t>(n);
-    L->slots[1] = c.take<uint32_t>(n);
+    const int64_t n64 = (n + 63) & ~int64_t(63);
+    L->slots[0] = c.take<uint32_t>(2 * n64);  // one piece: the first round sorts keys there
+    L->slots[1] = L->slots[0] ? L->slots[0] + n64 : nullptr;
     L->pos = c.take<uint32_t>(n);
     L->bigidx = c.take<uint32_t>(n);
     carve_sort(c, n, bits, t, &L->sb, true);
@@ -433,6 +435,7 @@ struct Build {
     int h0 = kH0;
     int key0_bits = 2 * kH0 + 5;
     int rbits = 1;
+    int top_d = 0, top_bits = 0;  // bases and key bits the first round sorts by passes (0: all)
 
     // copies the state words to pinned slot k and records its event (stream order)
     int snapshot(PinnedState &ps, int k) {
@@ -448,28 +451,85 @@ struct Build {
         return SA_OK;
     }
 
-    int round0() {
+    // Keys and the passes over their bits [lo_bit, key0_bits): the sorted items end up in
+    // buffer *cur.
+    int first_sort(int lo_bit, int *cur) {
+        const int64_t *set_off_dev = n_sets > 0 ? L.set_off : nullptr;
+        const int bits = key0_bits - lo_bit;
+        SA_TRY(sort_prepare(L.sb, n, bits, t, s));
+        int nparts = 0;
+        SA_TRY(launch_key0(L.blk, n, h0, top_d, set_off_dev, n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
+        return sort_run(L.sb, 0, nullptr, n, lo_bit, bits, t, nparts, s, cur, true);
+    }
+
+    int round_end() {
+        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, L.state, uint32_t(h0),
+                           top_bits ? uint32_t(h0 + kExtBases) : 0u);
+        SA_HIP(hipGetLastError());
+        return SA_OK;
+    }
+
+    // Waits for the state words as they are now (stream order): into pinned slot 0, host[].
+    int wait_state(PinnedState &ps, uint32_t host[kStWords]) {
+        SA_TRY(snapshot(ps, 0));
+        SA_HIP(hipEventSynchronize(ps.ev[0]));
+        memcpy(host, ps.h, sizeof(uint32_t) * kStWords);
+        return SA_OK;
+    }
+
+    // The first round, and the state after it (pinned slot 0, host[]).
+    int round0(PinnedState &ps, uint32_t host[kStWords]) {
         SA_TRY(launch_fill_u32(L.state, 64, 0, s));
         SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
-        SA_TRY(launch_pack(text, n, L.packed, L.sepmask, L.wordcnt, L.state + kStErr, s));
-        const int64_t *set_off_dev = nullptr;
+        SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, L.blk, L.state + kStErr, s));
         if (n_sets > 0) {
             SA_HIP(hipMemcpyAsync(L.set_off, set_off_h, size_t(n_sets + 1) * 8, hipMemcpyHostToDevice, s));
             hipLaunchKernelGGL(k_check_sets, dim3(unsigned((n_sets + 255) / 256)), dim3(256), 0, s,
                                text, L.set_off, uint32_t(n_sets), L.state + kStErr);
             SA_HIP(hipGetLastError());
-            set_off_dev = L.set_off;
         }
-        SA_TRY(sort_prepare(L.sb, n, key0_bits, t, s));
-        int nparts = 0;
-        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, set_off_dev, n_sets, key0_bits, L.sb, 0, t, s, &nparts));
         int cur = 0;
-        SA_TRY(sort_run(L.sb, 0, nullptr, n, 0, key0_bits, t, nparts, s, &cur));
-        SA_TRY(launch_rank_update(L.sb.keys[cur], L.sb.vals[cur], nullptr, n, n, true, h0, rbits,
-                                  sa, rank, L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets,
-                                  L.state, s));
-        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, L.state, uint32_t(h0));
-        SA_HIP(hipGetLastError());
+        if (top_bits == 0) {
+            SA_TRY(first_sort(0, &cur));
+            SA_TRY(launch_rank_update(L.sb.keys[cur], L.sb.vals[cur], nullptr, n, n, true, h0, rbits,
+                                      sa, rank, L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets,
+                                      L.state, s));
+            SA_TRY(round_end());
+            return wait_state(ps, host);
+        }
+        const int lo_bit = key0_bits - top_bits;
+        SA_TRY(first_sort(lo_bit, &cur));
+        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.blk, n, lo_bit, top_d, h0, false, sa, rank,
+                                 L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
+        SA_TRY(round_end());
+        SA_TRY(wait_state(ps, host));
+        if (host[kStLongRun] == 0) return SA_OK;
+        // Some run of equal top bits is too long for the run sort: its items are taken out,
+        // sorted by their whole keys and put back, and the round's end runs again.  The passes
+        // work between the idle half of the sort's buffers and the slot and position arrays,
+        // which nothing has filled yet.
+        SA_TRY(launch_fill_u32(L.state + 1, kStWords - 1, 0, s));
+        SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
+        SortBufs b = L.sb;
+        b.keys[0] = L.sb.keys[cur ^ 1];
+        b.vals[0] = L.sb.vals[cur ^ 1];
+        b.keys[1] = reinterpret_cast<uint64_t *>(L.slots[0]);  // slots[0] and slots[1] in one
+        b.vals[1] = L.pos;
+        SA_TRY(sort_prepare(b, n, key0_bits, t, s));
+        int nparts = 0, bc = 0;
+        const int64_t tag = timing_round_begin();
+        timing_scope_mode(kModeRadix);
+        SA_TRY(launch_first_extract(L.sb.keys[cur], L.sb.vals[cur], n, lo_bit, top_d, key0_bits, b, L.bigidx,
+                                    L.lbflags, L.lb_words, L.tickets, L.state, t, s, &nparts));
+        SA_TRY(sort_run(b, 0, L.state + kStRadixN, n, 0, key0_bits, t, nparts, s, &bc));
+        SA_TRY(launch_big_place(b.keys[bc], b.vals[bc], L.bigidx, n, L.state, L.sb.keys[cur],
+                                L.sb.vals[cur], L.state + kStErr, s));
+        timing_scope_mode(kModeAny);
+        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.blk, n, lo_bit, top_d, h0, true, sa, rank,
+                                 L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
+        SA_TRY(round_end());
+        SA_TRY(wait_state(ps, host));
+        timing_round_items(tag, n, host[kStBigLast]);
         return SA_OK;
     }
 
@@ -507,20 +567,56 @@ struct Build {
         SA_TRY(launch_rank_update(K, V, L.slots[sl], a_bound, n, false, h0, rbits, sa, rank,
                                   L.slots[sl ^ 1], L.pos, L.lbflags, L.lb_words, L.tickets,
                                   L.state, s));
-        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, L.state, uint32_t(h0));
-        SA_HIP(hipGetLastError());
-        return SA_OK;
+        return round_end();
+    }
+
+    // How the first round sorts: by the first top_d bases of every key by passes over HBM and
+    // by the rest run by run in LDS, where a run is the suffixes equal on those bases.  Whole
+    // digits' worth of bases, so many that a random text of the longest one's size would hold
+    // sixteen suffixes a run at most: reads lie as many deep as their coverage, so a run then
+    // holds the copies of one or two genome stretches.  More bases only add passes; fewer make
+    // runs of several stretches, which cost the run sort their square and pass its limit
+    // sooner.  Texts below one radix tile keep the passes over the whole key: one workgroup
+    // does each of them.
+    void choose_first_round() {
+        int sb = 0;
+        while ((int64_t(1) << sb) < n_sets) ++sb;
+        h0 = (63 - 5 - sb) / 2 < kH0 ? (63 - 5 - sb) / 2 : kH0;
+        key0_bits = 2 * h0 + 5 + sb;
+        top_d = top_bits = 0;
+        if (n < kTopMinN) return;
+        int64_t longest = n_sets > 0 ? 0 : n;
+        for (int k = 0; k < n_sets; ++k)
+            longest = set_off_h[k + 1] - set_off_h[k] > longest ? set_off_h[k + 1] - set_off_h[k] : longest;
+        const int h = (63 - 6 - sb) / 2 < kH0 - 1 ? (63 - 6 - sb) / 2 : kH0 - 1;
+        int d = 1;
+        while (d < h && (int64_t(16) << (2 * d)) < longest) ++d;
+        d = (sort_passes(sb + 2 * d + 1, t) * t.dbits - sb - 1) / 2;
+        if (d > h) d = h;
+        if (d < 1) return;
+        top_d = d;
+        h0 = h;
+        top_bits = sb + 2 * d + 1;
+        key0_bits = 2 * h0 + 6 + sb;
     }
 
     int run(bool use_graph, int *rounds_out) {
         rbits = bits_for(n - 1);
-        SA_TRY(round0());
+        choose_first_round();
+        if (h0 < 1) return fail(SA_ERR_INVALID, "too many texts in one batch");
+        PinnedState &ps = pinned_state();
+        if (!ps.ok) return fail(SA_ERR_HIP, "sa_build: no pinned host memory for round state");
         uint32_t host[kStWords];
-        if (use_graph) {
-            SA_TRY(read_state(host));
-            SA_TRY(check_err(host[kStErr]));
+        // Round 1 waits for round 0's state: whether its groups are all small (then no round
+        // needs the radix passes again), and how many suffixes are left.
+        SA_TRY(round0(ps, host));
+        timing_poll();
+        SA_TRY(check_err(host[kStErr]));
+        if (host[kStActive] == 0) {
+            timing_flush();
+        } else if (use_graph) {
             int64_t A = host[kStActive];
-            if (A > 0) {
+            {
                 // Record two rounds (the slot buffers alternate) once and replay until done.
                 // Capture on a private stream (the caller's may be the legacy default stream,
                 // which cannot be captured); the graph is then launched on the caller's stream.
@@ -572,15 +668,9 @@ struct Build {
             // work.  A round enqueued after the last useful one finds no active suffix and every
             // kernel of it returns at once.  A round's bounds (grid and fill sizes) use the last
             // count the host has seen, which can only be larger than the true one.
-            PinnedState &ps = pinned_state();
-            if (!ps.ok) return fail(SA_ERR_HIP, "sa_build: no pinned host memory for round state");
             int cur = 0, sl = 0;
-            int64_t bound = n;
-            SA_TRY(snapshot(ps, cur));  // state after round 0
-            // Round 1 waits for round 0's state: if its groups are all small, no round needs
-            // the radix passes again.
-            SA_HIP(hipEventSynchronize(ps.ev[cur]));
-            bool runs_only = ps.h[kStWords * cur + kStBig] == 0;
+            int64_t bound = host[kStActive];
+            bool runs_only = host[kStBig] == 0;
             // A round's units of work are known one round late: its active count from the
             // state before it, its large-group item count from the state after it.
             int64_t prev_tag = -1, prev_active = 0;
@@ -639,13 +729,6 @@ static int build_common(const uint8_t *text, int64_t n, const int64_t *set_off_h
     carve_build(c, n, n_sets, t, &B.L);
     B.L.sb.err = B.L.state + kStErr;
     B.rank = isa_or_null ? reinterpret_cast<uint32_t *>(isa_or_null) : B.L.rank;
-    if (n_sets > 0) {
-        int sb = 0;
-        while ((int64_t(1) << sb) < n_sets) ++sb;
-        B.h0 = (63 - 5 - sb) / 2 < kH0 ? (63 - 5 - sb) / 2 : kH0;
-        if (B.h0 < 1) return fail(SA_ERR_INVALID, "too many texts in one batch");
-        B.key0_bits = 2 * B.h0 + 5 + sb;
-    }
     int rounds = 0;
     SA_TRY(B.run(use_graph, &rounds));
     if (lcp_or_null) {

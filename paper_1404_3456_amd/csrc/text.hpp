@@ -2,7 +2,7 @@
 //
 // Record b of the block layout holds the 2-bit codes of positions 32b .. 32b+31 (two words,
 // position 32b in the top bits of the first) and their separator bits (position 32b in bit
-// 31), padded to 16 bytes; launch_blocks builds it from the packed words and separator mask.
+// 31), padded to 16 bytes; launch_pack writes it.
 // A window starting anywhere is then two aligned 16-byte loads.
 #pragma once
 #include <hip/hip_runtime.h>
