@@ -544,7 +544,7 @@ KERNEL_NAMES = {
     "radix_pass": "k_onesweep (one LSD radix pass)",
     "rank_update": "k_rank_update (group labels; random 4-byte scatter)",
     "kasai": "k_kasai (LCP; random gathers)",
-    "keyruns": "k_keys_runs (doubling keys sorted group by group in LDS)",
+    "keyruns": "k_first_runs, k_keys_runs (keys sorted run by run in LDS)",
     "keybuild": "k_big_extract (doubling keys of the large groups' items)",
     "key0": "k_key0 (first-round keys + digit histograms)",
     "overlap_walk": "k_ovl_walk (LCP-interval walks)",

@@ -115,8 +115,9 @@ int sa_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int32_t bit_lo, int
 
 /* ---------------------------------------------------------------------------------------- */
 /* Suffix array (Sec. IV), by prefix doubling over LSD radix sorts of rank-pair keys.          */
-/* A doubling round whose groups all have at most 32 members orders each group in on-chip    */
-/* memory instead of running radix passes over all its keys; the result is the same.         */
+/* The first round sends only the top bits of its keys through radix passes and orders the   */
+/* short runs they leave in on-chip memory; a doubling round does so with groups of at most   */
+/* 32 members.  The result is that of radix passes over all keys.                             */
 /* ---------------------------------------------------------------------------------------- */
 
 /* Workspace bytes for sa_build on a text of n bytes. */
@@ -426,8 +427,9 @@ int asm_server_destroy(asm_server *server);
 /* ---------------------------------------------------------------------------------------- */
 
 /* Per-kernel timing with HIP events recorded on the launch stream around every instrumented
- * launch.  Keys: "radix_pass", "key0" (first-round keys), "keybuild" (doubling keys in text
- * order), "keyruns" (doubling keys sorted run by run), "rank_update", "kasai", "lcp_gather",
+ * launch.  Keys: "radix_pass", "key0" (first-round keys), "keybuild" (doubling keys of
+ * large groups), "keyruns" (keys sorted run by run, the first round's and the doubling rounds'),
+ * "first_extract" (first-round items in runs too long for that), "rank_update", "kasai", "lcp_gather",
  * "overlap_walk", "pack", "lookup".
  * sa_timing_get returns launches, summed duration (ms) and summed algorithmic bytes (the
  * bytes each launch must move at minimum, as documented per kernel). */
@@ -436,8 +438,8 @@ int sa_timing_reset(void);
 int sa_timing_get(const char *key, int64_t *launches_h, double *total_ms_h, double *bytes_h);
 
 /* sa_timing_items: summed units of work of the timed launches under `key` (suffixes for
- * "pack", "key0", "kasai" and "lcp_gather"; items sorted for "radix_pass"; active suffixes
- * for "rank_update", "keyruns" and "keybuild"; reads for
+ * "pack", "key0", "first_extract", "kasai" and "lcp_gather"; items sorted for "radix_pass";
+ * active suffixes for "rank_update", "keyruns" and "keybuild"; reads for
  * "overlap_walk"; patterns for "lookup"), so that bytes per unit of any other model can be
  * applied to the same launches. */
 int sa_timing_items(const char *key, double *items_h);

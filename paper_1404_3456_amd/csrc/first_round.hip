@@ -19,43 +19,43 @@
 // runs the other form, which takes such runs as sorted.
 #include "device.hpp"
 #include "internal.hpp"
-#include "text.hpp"
 
 namespace saasm {
 
 constexpr int kFrRun = 128;                      // longest run sorted in LDS
-constexpr int kFrBlock = 512;
-constexpr int kFrItems = 4;
+constexpr int kFrBlock = 1024;
+constexpr int kFrItems = 2;
 constexpr int kFrSpan = kFrBlock * kFrItems;     // items loaded per tile
 constexpr int kFrTile = kFrSpan - 2 * kFrRun;    // items a tile finishes
 constexpr int kFrRows = kFrSpan / kWave;
 constexpr int kFrWaves = kFrBlock / kWave;
 constexpr int kFrRow0 = kFrRun / kWave;              // first and last + 1 row of the tile's own items
 constexpr int kFrRow1 = kFrRows - kFrRun / kWave;
-static_assert(kFrRun % kWave == 0 && kFrRun == 2 * kWave, "the bounds of a run are sought two words away");
+constexpr int kFrReach = kFrRun / kWave;             // words of a mask a run can reach into
+static_assert(kFrRun % kWave == 0 && kFrRun <= 128, "7 bits tell the members of a group apart");
 static_assert(kFrTile >= kFirstMinTile, "look-back words are sized for tiles of kFirstMinTile items");
 
 // First item of the run that holds item x, from a mask of run starts (bit x % 64 of word
-// x / 64): the nearest start at or before x, sought two words back; -1 if there is none.
+// x / 64): the nearest start at or before x, sought kFrReach words back; -1 if there is none.
 __device__ __forceinline__ int run_start(const uint64_t *m, int x) {
     const int w = x >> 6, b = x & 63;
     const uint64_t le = b == 63 ? ~uint64_t(0) : ((uint64_t(2) << b) - 1);
     uint64_t v = m[w] & le;
     int at = w;
-    for (int k = 1; k <= 2 && !v && w - k >= 0; ++k) {
+    for (int k = 1; k <= kFrReach && !v && w - k >= 0; ++k) {
         v = m[w - k];
         at = w - k;
     }
     return v ? at * 64 + 63 - int(__clzll((long long)v)) : -1;
 }
 
-// First item after the run that holds item x: the next start, sought two words on; -1 if none.
+// First item after the run that holds item x: the next start, sought kFrReach words on; -1 if none.
 __device__ __forceinline__ int run_end(const uint64_t *m, int x) {
     const int w = x >> 6, b = x & 63;
     const uint64_t le = b == 63 ? ~uint64_t(0) : ((uint64_t(2) << b) - 1);
     uint64_t v = m[w] & ~le;
     int at = w;
-    for (int k = 1; k <= 2 && !v && w + k < kFrRows; ++k) {
+    for (int k = 1; k <= kFrReach && !v && w + k < kFrRows; ++k) {
         v = m[w + k];
         at = w + k;
     }
@@ -69,29 +69,79 @@ __device__ __forceinline__ bool run_bounds(const uint64_t *m, int x, int *st, in
     return *st >= 0 && *en >= 0 && *en - *st <= kFrRun;
 }
 
-// The kExtBases symbols from text position a on, as two words that order like them: 32 bases,
-// then 29 bases and, in the last 6 bits, how many there are before the separator (61: all).
+// 128 bases of the packed text from position a on (base 0 in the top bits of b[0]).
+struct Bases {
+    uint64_t b[4];
+};
+struct __attribute__((packed, aligned(4))) Words9 {
+    uint32_t w[9];
+};
+__device__ __forceinline__ Bases bases_at(const uint32_t *__restrict__ packed, uint32_t a) {
+    const Words9 q = *reinterpret_cast<const Words9 *>(packed + (a >> 4));
+    const uint32_t o = 2 * (a & 15);
+    uint32_t r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = __builtin_amdgcn_alignbit(q.w[i], q.w[i + 1], (32 - o) & 31);
+    Bases x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        x.b[i] = o ? (uint64_t(r[2 * i]) << 32) | r[2 * i + 1]
+                   : (uint64_t(q.w[2 * i]) << 32) | q.w[2 * i + 1];
+    return x;
+}
+
+// The kExtStage bases at the top of (w0, w1), of which l are before the separator, as two words
+// that order like the symbols: 32 bases; then 25 bases, l in 6 bits, and 7 bits left zero.
 // Bases past the separator are zero, so a suffix that ends sorts below those that go on.
-__device__ __forceinline__ void ext_key(const uint4 *__restrict__ blk, uint32_t a, uint64_t *c0,
-                                        uint64_t *c1) {
-    const uint32_t b = a >> 5, o = a & 31;
-    const uint4 x = blk[b], y = blk[b + 1], z = blk[b + 2];
-    const uint64_t w0 = (uint64_t(x.x) << 32) | x.y, w1 = (uint64_t(y.x) << 32) | y.y,
-                   w2 = (uint64_t(z.x) << 32) | z.y;
-    uint64_t p0 = o ? (w0 << (2 * o)) | (w1 >> (64 - 2 * o)) : w0;
-    uint64_t p1 = o ? (w1 << (2 * o)) | (w2 >> (64 - 2 * o)) : w1;
-    const uint64_t s01 = (uint64_t(x.z) << 32) | y.z;
-    const uint64_t sm = o ? (s01 << o) | (uint64_t(z.z) >> (32 - o)) : s01;  // bits of a .. a+63
-    uint32_t L = sm ? uint32_t(__clzll((long long)sm)) : 64u;
-    if (L < 32) {
-        p0 &= L ? ~uint64_t(0) << (64 - 2 * L) : 0;
-        p1 = 0;
-    } else if (L < 64) {
-        p1 &= L > 32 ? ~uint64_t(0) << (128 - 2 * L) : 0;
+__device__ __forceinline__ void stage_key(uint64_t w0, uint64_t w1, uint32_t l, uint64_t *c0,
+                                          uint64_t *c1) {
+    if (l > uint32_t(kExtStage)) l = kExtStage;
+    if (l < 32) {
+        w0 &= l ? ~uint64_t(0) << (64 - 2 * l) : 0;
+        w1 = 0;
+    } else {
+        w1 &= l > 32 ? ~uint64_t(0) << (128 - 2 * l) : 0;  // 7 bases and more cleared
     }
-    if (L > uint32_t(kExtBases)) L = kExtBases;
-    *c0 = p0;
-    *c1 = (p1 & ~uint64_t(63)) | L;
+    *c0 = w0;
+    *c1 = w1 | (uint64_t(l) << 7);
+}
+
+// Items y of [st, en) whose word s[y] is below k, four reads at a time (s has four words more
+// than it has items).
+__device__ __forceinline__ int count_below(const uint64_t *s, int st, int en, uint64_t k) {
+    int c = 0;
+    for (int y = st; y < en; y += 4) {
+        uint64_t q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = s[y + i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c += (y + i < en && q[i] < k) ? 1 : 0;
+    }
+    return c;
+}
+
+// The same for two-word keys, whose last 7 bits tell equal symbols apart; *twin: some item
+// below has the same symbols.
+__device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *s1, int st, int en,
+                                            uint64_t k0, uint64_t k1, bool *twin) {
+    int c = 0;
+    bool same = false;
+    for (int y = st; y < en; y += 4) {
+        uint64_t q0[4], q1[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            q0[i] = s0[y + i];
+            q1[i] = s1[y + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = y + i < en, eq = q0[i] == k0, lt1 = q1[i] < k1;
+            c += (in && (q0[i] < k0 || (eq && lt1))) ? 1 : 0;
+            same = same || (in && eq && lt1 && (q1[i] ^ k1) < 128);
+        }
+    }
+    *twin = same;
+    return c;
 }
 
 // One tile of the order by the keys' top bits (bits lo_bit and up): sorts its runs, labels its
@@ -103,17 +153,18 @@ __device__ __forceinline__ void ext_key(const uint4 *__restrict__ blk, uint32_t 
 // that meets it, or meets the item after it, lies in the loaded span, and both tiles that share
 // a run sort it alike.
 template <bool MIXED>
-__global__ __launch_bounds__(kFrBlock) void k_first_runs(
-    const uint64_t *__restrict__ K, const uint32_t *__restrict__ V, const uint4 *__restrict__ blk,
-    uint32_t n, uint32_t lo_bit, uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa,
-    uint32_t *__restrict__ rank, uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new,
-    uint64_t *lbflags, uint32_t *tick, uint32_t *state, uint32_t *err) {
-    __shared__ uint64_t s_k[kFrSpan];     // keys; then the first words of the extension keys
-    __shared__ uint64_t s_c[kFrSpan];     // second words of the extension keys
-    __shared__ uint32_t s_v[kFrSpan];     // text positions; then with bit 31 on group starts
+__global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
+    const uint64_t *__restrict__ K, const uint32_t *__restrict__ V,
+    const uint32_t *__restrict__ packed, uint32_t n, uint32_t lo_bit, uint32_t key_bits,
+    uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
+    uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new, uint64_t *lbflags, uint32_t *tick,
+    uint32_t *state, uint32_t *err) {
+    __shared__ uint64_t s_k[kFrSpan + 4];  // keys; first words of the extension keys; s_p
+    __shared__ uint64_t s_c[kFrSpan + 4];  // (rest of key, item); s_v; second words
+    uint32_t *const s_v = reinterpret_cast<uint32_t *>(s_c);  // text positions in order of the keys
+    uint32_t *const s_p = reinterpret_cast<uint32_t *>(s_k);  // text positions in the final order
     __shared__ uint64_t s_m0[kFrRows];    // starts of runs
-    __shared__ uint64_t s_m1[kFrRows];    // starts of groups equal on the whole key
-    __shared__ uint64_t s_m2[kFrRows];    // starts of the final groups
+    __shared__ uint64_t s_m[kFrRows];     // starts of groups
     __shared__ uint64_t s_row[kFrRows];   // (count, last start) before each row
     __shared__ uint32_t s_tile, s_quit;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
@@ -130,6 +181,7 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
         return;
     }
     const int64_t lo = int64_t(tile) * kFrTile - kFrRun;
+    const uint64_t kmask = (uint64_t(1) << key_bits) - 1;  // key_bits <= kKeyLenShift
     uint64_t k[kFrItems];
     uint32_t v[kFrItems];
 #pragma unroll
@@ -139,8 +191,14 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
         k[j] = in ? K[gi] : 0;
         v[j] = in ? V[gi] : 0;
     }
+    // a run is ordered by the bits below lo_bit (31 at most), equal ones by item
+    const uint64_t rest = (uint64_t(1) << lo_bit) - 1;
 #pragma unroll
-    for (int j = 0; j < kFrItems; ++j) s_k[j * kFrBlock + tid] = k[j];
+    for (int j = 0; j < kFrItems; ++j) {
+        const int x = j * kFrBlock + tid;
+        s_k[x] = k[j];
+        s_c[x] = ((k[j] & rest) << 32) | uint32_t(x);
+    }
     __syncthreads();
     // starts of runs (positions outside the array count as runs of their own, and so does a
     // suffix of fewer than top_d bases: it shares its top bits only with its equals, which are
@@ -151,7 +209,7 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
         const int64_t gi = lo + x;
         bool h = gi <= 0 || gi >= int64_t(n);
         if (!h && x > 0)
-            h = (k[j] >> lo_bit) != (s_k[x - 1] >> lo_bit) || (k[j] & 31u) < uint64_t(top_d);
+            h = ((k[j] ^ s_k[x - 1]) & kmask) >> lo_bit || (k[j] & 31u) < uint64_t(top_d);
         const uint64_t m = ballot(h);
         if (lane == 0) s_m0[x >> 6] = m;
     }
@@ -164,12 +222,7 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
         int st, en;
         pos[j] = x;
         if (run_bounds(s_m0, x, &st, &en)) {
-            int before = 0;
-            for (int y = st; y < en; ++y) {
-                const uint64_t q = s_k[y];
-                before += (q < k[j] || (q == k[j] && y < x)) ? 1 : 0;
-            }
-            pos[j] = st + before;
+            if (en - st > 1) pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
         } else if (!MIXED && x >= kFrRun && x < kFrRun + kFrTile) {
             s_quit = 1;
         }
@@ -190,84 +243,102 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
     __syncthreads();
     // starts of groups equal on the whole key; a key of fewer than h0 symbols is a suffix that
     // ended at its separator, alone in its group
+    uint32_t reach[kFrItems];  // symbols before the separator (511: or more)
 #pragma unroll
     for (int j = 0; j < kFrItems; ++j) {
         const int x = j * kFrBlock + tid;
         const int64_t gi = lo + x;
-        k[j] = s_k[x];
+        const uint64_t key = s_k[x];
         v[j] = s_v[x];
+        reach[j] = uint32_t(key >> kKeyLenShift);
         bool h = gi <= 0 || gi >= int64_t(n);
-        if (!h && x > 0) h = k[j] != s_k[x - 1] || (k[j] & 31u) < uint64_t(h0);
+        if (!h && x > 0) h = ((key ^ s_k[x - 1]) & kmask) != 0 || (key & 31u) < uint64_t(h0);
         const uint64_t m = ballot(h);
-        if (lane == 0) s_m1[x >> 6] = m;
+        if (lane == 0) s_m[x >> 6] = m;
     }
     __syncthreads();
-    // groups that meet the tile or the item after it: their members' next kExtBases symbols
+    // Groups that meet the tile or the item after it are told apart by the text: windows of two
+    // stages, kExtStage bases each, as long as the tile has groups.  en[j] > 0: item j of the
+    // thread is in such a group, at pos[j] in [st[j], en[j]).
     int st[kFrItems], en[kFrItems];
-    uint64_t c0[kFrItems], c1[kFrItems];
+    bool any = false;
 #pragma unroll
     for (int j = 0; j < kFrItems; ++j) {
         const int x = j * kFrBlock + tid;
-        const bool small = run_bounds(s_m1, x, &st[j], &en[j]);
+        const bool small = run_bounds(s_m, x, &st[j], &en[j]);
         if (!small && x >= kFrRun && x < kFrRun + kFrTile) state[kStNoExt] = 1u;
         const bool ext = small && en[j] - st[j] > 1 && st[j] <= kFrRun + kFrTile && en[j] > kFrRun;
-        if (!ext) {
-            en[j] = 0;
-            continue;
-        }
-        const uint32_t a = v[j] + h0;
-        if (a < n) {
-            ext_key(blk, a, &c0[j], &c1[j]);
-        } else {
-            raise_err(err, kErrRange);
-            c0[j] = c1[j] = 0;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        if (en[j]) {
-            s_k[x] = c0[j];
-            s_c[x] = c1[j];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
+        if (!ext) en[j] = 0;
+        any = any || ext;
         pos[j] = x;
-        bool head = (s_m1[x >> 6] >> (x & 63)) & 1u;
-        if (en[j]) {
-            int before = 0;
-            bool first = true;
-            for (int y = st[j]; y < en[j]; ++y) {
-                const uint64_t q0 = s_k[y], q1 = s_c[y];
-                const bool eq = q0 == c0[j] && q1 == c1[j];
-                before += (q0 < c0[j] || (q0 == c0[j] && q1 < c1[j]) || (eq && y < x)) ? 1 : 0;
-                if (eq && y < x) first = false;
+    }
+    uint32_t *const s_m32 = reinterpret_cast<uint32_t *>(s_m);
+    for (int w = 0; w < kExtWindows; ++w) {
+        if (!__syncthreads_or(any)) break;
+        const uint32_t depth = h0 + uint32_t(w) * 2 * kExtStage;
+        Bases q[kFrItems];
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            if (!en[j]) continue;
+            const uint32_t a = v[j] + depth;
+            if (a >= n) {  // inconsistent input: report only
+                raise_err(err, kErrRange);
+                en[j] = 0;
+                continue;
             }
-            pos[j] = st[j] + before;
-            head = first || (c1[j] & 63u) < uint64_t(kExtBases);
+            q[j] = bases_at(packed, a);
         }
-        s_v[pos[j]] = v[j] | (head ? kDone : 0u);
+#pragma unroll
+        for (int stage = 0; stage < 2; ++stage) {
+            uint64_t c0[kFrItems], c1[kFrItems];
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                if (!en[j]) continue;
+                const uint64_t *b = q[j].b;
+                // 57 bases are 114 bits: 50 bits into the second word
+                const uint64_t w0 = stage == 0 ? b[0] : (b[1] << 50) | (b[2] >> 14);
+                const uint64_t w1 = stage == 0 ? b[1] : (b[2] << 50) | (b[3] >> 14);
+                stage_key(w0, w1, reach[j] - depth - uint32_t(stage * kExtStage), &c0[j], &c1[j]);
+                c1[j] |= uint64_t(pos[j] - st[j]);  // equal symbols: in order of their positions
+                s_k[pos[j]] = c0[j];
+                s_c[pos[j]] = c1[j];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                if (!en[j]) continue;
+                bool twin;
+                pos[j] = st[j] + count_below2(s_k, s_c, st[j], en[j], c0[j], c1[j], &twin);
+                if (!twin || ((c1[j] >> 7) & 63u) < uint64_t(kExtStage))
+                    atomicOr(&s_m32[pos[j] >> 5], 1u << (pos[j] & 31));
+            }
+            __syncthreads();
+            any = false;
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                if (!en[j]) continue;
+                st[j] = run_start(s_m, pos[j]);
+                en[j] = run_end(s_m, pos[j]);
+                if (en[j] - st[j] <= 1) en[j] = 0;
+                any = any || en[j] != 0;
+            }
+        }
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        const uint64_t m = ballot((s_v[x] & kDone) != 0);
-        if (lane == 0) s_m2[x >> 6] = m;
-    }
+    for (int j = 0; j < kFrItems; ++j) s_p[pos[j]] = v[j];
     __syncthreads();
-    // per row of 64: suffixes still in groups (neither they nor the next item start a group on
-    // both sides) and the last start; scanned over the tile's rows, then over tiles
+    // Wave 0: per row of 64, the suffixes still in groups (not both they and the next item
+    // start one) and the last start, scanned over the tile's rows and then over tiles.  The
+    // other waves meanwhile write the ranks and the final suffixes, which need only the
+    // starts at hand (unless a long group began before them).
     if (wave == 0) {
         uint64_t mine = 0;
         const int r = kFrRow0 + int(lane);
         if (r < kFrRow1) {
             const int64_t g = lo + r * 64;
-            const uint64_t m = s_m2[r];
-            const uint64_t nxt = (m >> 1) | (s_m2[r + 1] << 63);
+            const uint64_t m = s_m[r];
+            const uint64_t nxt = (m >> 1) | (s_m[r + 1] << 63);
             const int64_t left = int64_t(n) - g;
             const uint64_t in = left >= 64 ? ~uint64_t(0) : left <= 0 ? 0 : ((uint64_t(1) << left) - 1);
             const uint64_t hm = m & in;
@@ -282,40 +353,52 @@ __global__ __launch_bounds__(kFrBlock) void k_first_runs(
         if (r < kFrRow1) s_row[r] = CountLastOp::combine(before, ex);
         if (lane == 0 && tile == ntiles - 1)
             state[kStNext] = uint32_t(CountLastOp::combine(before, agg) >> 31);
+    } else {
+        for (int r = kFrRow0 + int(wave) - 1; r < kFrRow1; r += kFrWaves - 1) {
+            const int64_t gi = lo + r * 64 + lane;
+            if (gi >= int64_t(n)) break;
+            const uint32_t p = s_p[r * 64 + lane];
+            const int st_x = run_start(s_m, r * 64 + int(lane));
+            if (p >= n || st_x < 0 || lo + st_x < 0) continue;  // see below
+            rank[p] = uint32_t(lo + st_x);
+            const uint64_t m = s_m[r];
+            const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63));
+            if ((single >> lane) & 1u) sa[gi] = int32_t(p);
+        }
     }
     __syncthreads();
     for (int r = kFrRow0 + int(wave); r < kFrRow1; r += kFrWaves) {
         const int64_t gi = lo + r * 64 + lane;
         if (gi >= int64_t(n)) break;
         const uint32_t i = uint32_t(gi);
-        const uint64_t m = s_m2[r];
-        const uint64_t nxt = (m >> 1) | (s_m2[r + 1] << 63);
-        const uint64_t single = m & nxt, bit = uint64_t(1) << lane;
-        const uint64_t le = bit | (bit - 1);
-        const uint64_t mb = m & le;
-        const uint32_t head = uint32_t((m >> lane) & 1u);
-        // the last start at or before i: in this row, else in the rows and tiles before
-        const uint32_t g = mb ? uint32_t(lo + r * 64) + 63u - uint32_t(__clzll((long long)mb))
-                              : uint32_t(s_row[r] & CountLastOp::kLastMask) - 1u;
-        const uint32_t p = s_v[r * 64 + lane] & kRankMask;
-        if (p >= n || g > i) {  // inconsistent input: report only (a tile that gave up also
-                                // leaves the tiles after it without a start: not an error)
-            if (MIXED || p >= n) raise_err(err, kErrRange);
+        const uint64_t m = s_m[r];
+        const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63)), bit = uint64_t(1) << lane;
+        const uint32_t p = s_p[r * 64 + lane];
+        if (p >= n) {  // inconsistent input: report only
+            raise_err(err, kErrRange);
             continue;
         }
-        rank[p] = g;
-        if (single & bit) {
-            sa[i] = int32_t(p);
-        } else {
-            const uint32_t o = uint32_t(s_row[r] >> 31) + uint32_t(popc64(~single & (bit - 1)));
-            if (o >= n) {
-                raise_err(err, kErrRange);
+        if (single & bit) continue;
+        // the last start at or before i: within reach of the loaded span, else from the rows
+        // and tiles before
+        const int st_x = run_start(s_m, r * 64 + int(lane));
+        uint32_t g = uint32_t(lo + st_x);
+        if (st_x < 0 || lo + st_x < 0) {
+            g = uint32_t(s_row[r] & CountLastOp::kLastMask) - 1u;
+            if (!MIXED || g > i) {
+                if (MIXED) raise_err(err, kErrRange);
                 continue;
             }
-            S_new[o] = i;
-            P_new[o] = p | (head ? kDone : 0u);
-            if (i - g == uint32_t(kRunMax)) state[kStBigNext] = 1u;
+            rank[p] = g;
         }
+        const uint32_t o = uint32_t(s_row[r] >> 31) + uint32_t(popc64(~single & (bit - 1)));
+        if (o >= n) {
+            raise_err(err, kErrRange);
+            continue;
+        }
+        S_new[o] = i;
+        P_new[o] = p | (m & bit ? kDone : 0u);
+        if (i - g == uint32_t(kRunMax)) state[kStBigNext] = 1u;
     }
 }
 
@@ -332,7 +415,7 @@ static_assert(kFxTile >= kFirstMinTile, "look-back words are sized for tiles of 
 template <int D>
 __global__ __launch_bounds__(kFxBlock) void k_first_extract(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V, uint32_t n, uint32_t lo_bit,
-    uint32_t top_d, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, uint32_t *__restrict__ idx,
+    uint32_t key_bits, uint32_t top_d, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, uint32_t *__restrict__ idx,
     int passes, uint32_t *__restrict__ hist, uint64_t *lbflags, uint32_t *tick, uint32_t *state,
     uint32_t *err) {
     constexpr int R = 1 << D;
@@ -344,6 +427,7 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const uint32_t ntiles = (n + kFxTile - 1) / kFxTile;
     const uint64_t le = lane == 63 ? ~uint64_t(0) : ((uint64_t(2) << lane) - 1);
+    const uint64_t kmask = (uint64_t(1) << key_bits) - 1;
     for (int i = tid; i < passes * R; i += kFxBlock) s_h[i] = 0;
     while (true) {
         __syncthreads();
@@ -357,7 +441,7 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
             bool h = i <= 0 || i >= int64_t(n);
             if (!h) {
                 const uint64_t k = K[i];
-                h = (k >> lo_bit) != (K[i - 1] >> lo_bit) || (k & 31u) < uint64_t(top_d);
+                h = ((k ^ K[i - 1]) & kmask) >> lo_bit || (k & 31u) < uint64_t(top_d);
             }
             const uint64_t m = ballot(h);
             if (lane == 0) s_m[r] = m;
@@ -401,10 +485,10 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
                 raise_err(err, kErrRange);
                 continue;
             }
-            const uint64_t key = K[i];
-            keys[j] = key;
+            keys[j] = K[i];
             vals[j] = V[i];
             idx[j] = i;
+            const uint64_t key = K[i] & kmask;
             for (int p = 0; p < passes; ++p)
                 atomicAdd(&s_h[p * R + uint32_t((key >> (p * D)) & (R - 1))], 1u);
         }
@@ -414,24 +498,26 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
     for (int i = tid; i < passes * R; i += kFxBlock) dst[i] = s_h[i];
 }
 
-int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint4 *blk, int64_t n,
-                      int lo_bit, int top_d, int h0, bool mixed, int32_t *sa, uint32_t *rank,
-                      uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags, int64_t lb_words,
-                      uint32_t *tick, uint32_t *state, hipStream_t s) {
+int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
+                      int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
+                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags,
+                      int64_t lb_words, uint32_t *tick, uint32_t *state, hipStream_t s) {
     const int64_t tiles = (n + kFrTile - 1) / kFrTile;
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
     SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
     SA_TRY(launch_fill_u32(tick, 1, 0, s));
     // per suffix: key 8 and position 4 read; rank 4, and sa 4 or slot and position 8, written;
     // 24 bytes of packed text for a suffix still in a group
-    TimedScope ts("first_runs", double(n) * 24.0, s, double(n));
+    TimedScope ts("keyruns", double(n) * 24.0, s, double(n));
     if (mixed)
-        hipLaunchKernelGGL(k_first_runs<true>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, blk,
-                           uint32_t(n), uint32_t(lo_bit), uint32_t(top_d), uint32_t(h0), sa, rank, S_new, P_new,
+        hipLaunchKernelGGL(k_first_runs<true>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed,
+                           uint32_t(n), uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d),
+                           uint32_t(h0), sa, rank, S_new, P_new,
                            lbflags, tick, state, state + kStErr);
     else
-        hipLaunchKernelGGL(k_first_runs<false>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, blk,
-                           uint32_t(n), uint32_t(lo_bit), uint32_t(top_d), uint32_t(h0), sa, rank, S_new, P_new,
+        hipLaunchKernelGGL(k_first_runs<false>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed,
+                           uint32_t(n), uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d),
+                           uint32_t(h0), sa, rank, S_new, P_new,
                            lbflags, tick, state, state + kStErr);
     ts.finish();
     SA_HIP(hipGetLastError());
@@ -455,10 +541,10 @@ int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo
     // every key read; per item of a long run, its key, value and place written
     TimedScope ts("first_extract", double(n) * 8.0, s, double(n));
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_first_extract<4>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 8: hipLaunchKernelGGL(k_first_extract<8>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 9: hipLaunchKernelGGL(k_first_extract<9>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 11: hipLaunchKernelGGL(k_first_extract<11>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
+        case 4: hipLaunchKernelGGL(k_first_extract<4>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
+        case 8: hipLaunchKernelGGL(k_first_extract<8>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
+        case 9: hipLaunchKernelGGL(k_first_extract<9>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
+        case 11: hipLaunchKernelGGL(k_first_extract<11>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();

@@ -183,18 +183,23 @@ constexpr int kRunMax = 32;    // largest group the run sort handles
 
 // key builders (fused with the histogram of the sort that follows, over key bits
 // [lo_bit, key_bits)); a value is its item's index and is left to the first pass
-int launch_key0(const uint4 *blk, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
+int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
                 int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
                 hipStream_t s, int *nparts);
-// First round (first_round.hip): from items ordered by key bits [lo_bit, ..), which tell their
-// first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the items of
-// runs too long for it, taken out.
-constexpr int kExtBases = 61;
+// First round (first_round.hip): from items ordered by key bits [lo_bit, key_bits), which tell
+// their first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the
+// items of runs too long for it, taken out.
+constexpr int kKeyLenShift = 55;          // a key's top 9 bits: distance to the separator, capped
+constexpr uint32_t kKeyLenMax = 511;
+constexpr int kExtStage = 57;             // bases one comparison of the extension takes
+constexpr int kExtWindows = 4;            // windows of two stages each
+constexpr int kExtBases = 2 * kExtStage * kExtWindows;
+static_assert(kH0 + kExtBases <= int(kKeyLenMax), "the extension needs exact distances");
 constexpr int kFirstMinTile = 1792;
-int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint4 *blk, int64_t n,
-                      int lo_bit, int top_d, int h0, bool mixed, int32_t *sa, uint32_t *rank,
-                      uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags, int64_t lb_words,
-                      uint32_t *tick, uint32_t *state, hipStream_t s);
+int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
+                      int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
+                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags,
+                      int64_t lb_words, uint32_t *tick, uint32_t *state, hipStream_t s);
 int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,
                          int key_bits,
                          const SortBufs &b, uint32_t *idx, uint64_t *lbflags, int64_t lb_words,

@@ -499,23 +499,37 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
 // The standing of w, |w| <= D: its |w| proper prefixes and, for every base w_i, the w_i
 // smaller subtrees of (4^(D-i) - 1) / 3 strings each: |w| + sum w_i (4^(D-i) - 1) / 3, which is
 // |w| + (4 c - sum w_i) / 3 for the code c of w padded with zeros to D bases.
-__device__ __forceinline__ uint64_t key0_of(const uint4 *__restrict__ blk, uint32_t p,
-                                            uint32_t h0, uint32_t D) {
-    const Window x = window_at(blk, p);
-    uint32_t L = x.sep ? uint32_t(__clz(x.sep)) : 32u;
+// D > 0 also leaves min(L_p, 511) in the key's top 9 bits, above the text's index; no pass and no
+// comparison takes those bits, they are there for the extension of the keys (first_round.hip).
+__device__ __forceinline__ uint64_t key0_of(uint64_t bases, uint32_t L, uint32_t h0, uint32_t D) {
+    const uint64_t reach = uint64_t(L < kKeyLenMax ? L : kKeyLenMax) << kKeyLenShift;
     if (L > h0) L = h0;
-    uint64_t code = x.code >> (64 - 2 * h0);
+    uint64_t code = bases >> (64 - 2 * h0);
     if (L < h0) code &= ~((uint64_t(1) << (2 * (h0 - L))) - 1);
-    if (D) {
-        const uint32_t rest = 2 * (h0 - D);
-        const uint64_t c = code >> rest;
-        const uint64_t sum = uint64_t(popc64(c & 0x5555555555555555ull)) +
-                             2u * uint64_t(popc64(c & 0xaaaaaaaaaaaaaaaaull));
-        // the difference is a multiple of 3, so this product with 3's inverse is the quotient
-        const uint64_t at = (L < D ? L : D) + (4 * c - sum) * 0xaaaaaaaaaaaaaaabull;
-        code = (at << rest) | (code & ((uint64_t(1) << rest) - 1));
-    }
-    return (code << 5) | L;
+    if (D == 0) return (code << 5) | L;
+    const uint32_t rest = 2 * (h0 - D);
+    const uint64_t c = code >> rest;
+    const uint64_t sum = uint64_t(popc64(c & 0x5555555555555555ull)) +
+                         2u * uint64_t(popc64(c & 0xaaaaaaaaaaaaaaaaull));
+    // the difference is a multiple of 3, so this product with 3's inverse is the quotient
+    const uint64_t at = (L < D ? L : D) + (4 * c - sum) * 0xaaaaaaaaaaaaaaabull;
+    code = (at << rest) | (code & ((uint64_t(1) << rest) - 1));
+    return (code << 5) | L | reach;
+}
+
+// Distance of every lane's position to the next separator at or after it (at least 512 when
+// there is none within 512), for a wave at positions 32 w .. 32 w + 63: lane j holds word j of
+// the 18 from w on.
+__device__ __forceinline__ uint32_t sep_distance(const uint32_t *__restrict__ sepmask, uint32_t w,
+                                                 uint32_t nwords) {
+    const uint32_t lane = lane_id();
+    const uint32_t mine = lane < 18 && w + lane < nwords ? sepmask[w + lane] : 0u;
+    const uint64_t here = ((uint64_t(__shfl(mine, 0)) << 32) | __shfl(mine, 1)) << lane;
+    const uint64_t later = ballot(mine != 0) >> 2;
+    const uint32_t k = later ? uint32_t(__ffsll((long long)later)) - 1u : 0u;
+    const uint32_t next = __shfl(mine, int(k) + 2);  // every lane takes part
+    if (here) return uint32_t(__clzll((long long)here));
+    return later ? 64u - lane + 32u * k + uint32_t(__clz(next)) : 512u;
 }
 
 // Index of the text of a batch that holds position p: largest s with set_off[s] <= p.
@@ -533,41 +547,50 @@ __device__ __forceinline__ uint32_t set_of(const int64_t *__restrict__ set_off, 
 constexpr int kK0Block = 1024;  // threads per key0 workgroup (grid-stride, one partial each)
 
 template <int D>
-__global__ __launch_bounds__(kK0Block) void k_key0(const uint4 *__restrict__ blk, uint32_t n,
+__global__ __launch_bounds__(kK0Block) void k_key0(const uint32_t *__restrict__ packed,
+                                              const uint32_t *__restrict__ sepmask,
+                                              uint32_t nwords, uint32_t n,
                                               uint32_t h0, uint32_t top_d,
                                               const int64_t *__restrict__ set_off,
                                               uint32_t n_sets, int set_shift,
-                                              uint64_t *__restrict__ keys, int lo_bit, int passes,
+                                              uint64_t *__restrict__ keys, int lo_bit,
+                                              uint64_t key_mask, int passes,
                                               uint32_t *__restrict__ hist) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-        uint64_t k = key0_of(blk, p, h0, top_d);
+    const uint32_t lane = lane_id();
+    // a wave takes 64 positions at a time, all of its lanes while any is in the text
+    for (uint64_t p0 = blockIdx.x * blockDim.x + threadIdx.x - lane; p0 < n; p0 += stride) {
+        const uint32_t p = uint32_t(p0) + lane;
+        const uint32_t L = sep_distance(sepmask, uint32_t(p0) >> 5, nwords);
+        if (p >= n) continue;
+        uint64_t k = key0_of(codes_at(packed, p), L, h0, top_d);
         if (set_off) k |= uint64_t(set_of(set_off, n_sets, p)) << set_shift;
         keys[p] = k;
-        hist_add<D>(s_h, k >> lo_bit, passes);
+        hist_add<D>(s_h, (k & key_mask) >> lo_bit, passes);
     }
     __syncthreads();
     hist_flush<D>(s_h, hist, passes);
 }
 
-int launch_key0(const uint4 *blk, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
+int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
                 int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
                 hipStream_t s, int *nparts) {
     const int set_shift = 2 * h0 + 5 + (top_d ? 1 : 0);
+    const uint64_t key_mask = (uint64_t(1) << key_bits) - 1;  // key_bits <= 63
     const int P = sort_passes(key_bits - lo_bit, t);
     *nparts = int(hist_grid(n));
     size_t lds = size_t(P) * t.radix() * 4;
-    TimedScope ts("key0", double(n) * (8.0 + 0.5), s, double(n));
+    TimedScope ts("key0", double(n) * (8.0 + 0.375), s, double(n));
     const unsigned g = hist_grid(n);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
-        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
-        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
-        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, blk, uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, P, b.hist); break;
+        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
+        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
+        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
+        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();

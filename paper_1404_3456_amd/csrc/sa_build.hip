@@ -253,7 +253,7 @@ static int bits_for(int64_t v) {  // bits needed to hold 0..v
 }
 
 struct BuildLayout {
-    uint4 *blk;            // packed text (window records)
+    uint32_t *packed, *sepmask;
     uint32_t *rank;        // used when the caller gives no isa buffer
     uint32_t *slots[2];
     uint32_t *pos;         // active text positions in the last round's order (bit 31: run start)
@@ -270,7 +270,8 @@ struct BuildLayout {
 
 static void carve_build(Carver &c, int64_t n, int n_sets, const Tune &t, BuildLayout *L) {
     const int bits = 63 > 2 * bits_for(n) ? 63 : 2 * bits_for(n);
-    L->blk = c.take<uint4>(sepmask_words(n));
+    L->packed = c.take<uint32_t>(packed_words(n));
+    L->sepmask = c.take<uint32_t>(sepmask_words(n));
     L->rank = c.take<uint32_t>(n);
     const int64_t n64 = (n + 63) & ~int64_t(63);
     L->slots[0] = c.take<uint32_t>(2 * n64);  // one piece: the first round sorts keys there
@@ -458,7 +459,7 @@ struct Build {
         const int bits = key0_bits - lo_bit;
         SA_TRY(sort_prepare(L.sb, n, bits, t, s));
         int nparts = 0;
-        SA_TRY(launch_key0(L.blk, n, h0, top_d, set_off_dev, n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
+        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev, n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
         return sort_run(L.sb, 0, nullptr, n, lo_bit, bits, t, nparts, s, cur, true);
     }
 
@@ -481,7 +482,7 @@ struct Build {
     int round0(PinnedState &ps, uint32_t host[kStWords]) {
         SA_TRY(launch_fill_u32(L.state, 64, 0, s));
         SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
-        SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, L.blk, L.state + kStErr, s));
+        SA_TRY(launch_pack(text, n, L.packed, L.sepmask, nullptr, nullptr, L.state + kStErr, s));
         if (n_sets > 0) {
             SA_HIP(hipMemcpyAsync(L.set_off, set_off_h, size_t(n_sets + 1) * 8, hipMemcpyHostToDevice, s));
             hipLaunchKernelGGL(k_check_sets, dim3(unsigned((n_sets + 255) / 256)), dim3(256), 0, s,
@@ -499,7 +500,7 @@ struct Build {
         }
         const int lo_bit = key0_bits - top_bits;
         SA_TRY(first_sort(lo_bit, &cur));
-        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.blk, n, lo_bit, top_d, h0, false, sa, rank,
+        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, false, sa, rank,
                                  L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end());
         SA_TRY(wait_state(ps, host));
@@ -525,7 +526,7 @@ struct Build {
         SA_TRY(launch_big_place(b.keys[bc], b.vals[bc], L.bigidx, n, L.state, L.sb.keys[cur],
                                 L.sb.vals[cur], L.state + kStErr, s));
         timing_scope_mode(kModeAny);
-        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.blk, n, lo_bit, top_d, h0, true, sa, rank,
+        SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, true, sa, rank,
                                  L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end());
         SA_TRY(wait_state(ps, host));
@@ -588,14 +589,14 @@ struct Build {
         int64_t longest = n_sets > 0 ? 0 : n;
         for (int k = 0; k < n_sets; ++k)
             longest = set_off_h[k + 1] - set_off_h[k] > longest ? set_off_h[k + 1] - set_off_h[k] : longest;
-        const int h = (63 - 6 - sb) / 2 < kH0 - 1 ? (63 - 6 - sb) / 2 : kH0 - 1;
+        const int h = (kKeyLenShift - 6 - sb) / 2;
         int d = 1;
         while (d < h && (int64_t(16) << (2 * d)) < longest) ++d;
         d = (sort_passes(sb + 2 * d + 1, t) * t.dbits - sb - 1) / 2;
         if (d > h) d = h;
         if (d < 1) return;
         top_d = d;
-        h0 = h;
+        h0 = d + 13 < h ? d + 13 : h;  // the run sort takes 31 bits: 13 bases and the length
         top_bits = sb + 2 * d + 1;
         key0_bits = 2 * h0 + 6 + sb;
     }
