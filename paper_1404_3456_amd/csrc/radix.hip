@@ -231,9 +231,9 @@ __device__ __forceinline__ void rank_wave(const uint64_t (&key)[ITEMS], uint32_t
 // One tile per workgroup, tiles numbered by ticket.  The grid covers an upper bound on the
 // item count; the count itself is read from device memory when `count_dev` is given (so the
 // same launch can be recorded in a graph and replayed with whatever count an earlier kernel
-// produced; surplus workgroups exit at once), otherwise it is `n_host`.  vin == nullptr: an
-// item's value is its index.
-template <int D, int BLOCK, int ITEMS>
+// produced; surplus workgroups exit at once), otherwise it is `n_host`.  INDEX_VALS: an
+// item's value is its index, vin is not read.
+template <int D, int BLOCK, int ITEMS, bool INDEX_VALS>
 __global__ __launch_bounds__(BLOCK) void k_onesweep(const uint64_t *__restrict__ kin,
                                                     const uint32_t *__restrict__ vin,
                                                     uint64_t *__restrict__ kout,
@@ -279,14 +279,14 @@ __global__ __launch_bounds__(BLOCK) void k_onesweep(const uint64_t *__restrict__
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 key[k] = kp[k * kWave];
-                val[k] = vin ? vp[k * kWave] : wbase + lane + k * kWave;
+                val[k] = INDEX_VALS ? wbase + lane + k * kWave : vp[k * kWave];
             }
         } else {
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const uint32_t idx = wbase + k * kWave + lane;
                 key[k] = idx < n ? kin[idx] : 0;
-                val[k] = idx < n ? (vin ? vin[idx] : idx) : 0;
+                val[k] = INDEX_VALS ? idx : idx < n ? vin[idx] : 0;
             }
         }
 
@@ -414,8 +414,14 @@ static int launch_pass_t(int64_t n_max, hipStream_t s, const uint64_t *kin, cons
     constexpr int TILE = BLOCK * ITEMS;
     int64_t grid = (n_max + TILE - 1) / TILE;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_onesweep<D, BLOCK, ITEMS>), dim3(unsigned(grid)), dim3(BLOCK), 0, s, kin,
-                       vin, kout, vout, count_dev, n_host, shift, dmask, gbase, flags, tick, err);
+    if (vin)
+        hipLaunchKernelGGL((k_onesweep<D, BLOCK, ITEMS, false>), dim3(unsigned(grid)), dim3(BLOCK), 0,
+                           s, kin, vin, kout, vout, count_dev, n_host, shift, dmask, gbase, flags,
+                           tick, err);
+    else
+        hipLaunchKernelGGL((k_onesweep<D, BLOCK, ITEMS, true>), dim3(unsigned(grid)), dim3(BLOCK), 0,
+                           s, kin, vin, kout, vout, count_dev, n_host, shift, dmask, gbase, flags,
+                           tick, err);
     SA_HIP(hipGetLastError());
     return SA_OK;
 }
