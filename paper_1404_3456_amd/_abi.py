@@ -354,22 +354,39 @@ def sa_workspace_bytes(n: int, n_reads_upper: int = 0) -> int:
     return int(load().sa_workspace_bytes(int(n), int(n_reads_upper)))
 
 
+def _index_ws_bytes(n: int) -> int:
+    return int(load().sa_build_batched_ws_bytes(n, 1, None, None))
+
+
+def _index(t, ws, stream):
+    """(sa, isa, lcp) of one device text: a batched build of a single set, which takes the LCP
+    array from its own comparisons instead of scanning for it afterwards."""
+    torch = _torch()
+    n = t.numel()
+    sa, isa, lcp = (torch.empty(n, dtype=torch.int32, device=t.device) for _ in range(3))
+    off = (ctypes.c_int64 * 2)(0, n)
+    _check(load().sa_build_batched(_ptr(t), n, off, 1, _ptr(sa), _ptr(isa), _ptr(lcp), _ptr(ws),
+                                   ws.numel(), None, 0, None, _stream(stream)))
+    return sa, isa, lcp
+
+
 def sa_path(text, min_len: int, stream=None, ws=None):
-    """The whole path -- sa_build, sa_lcp, sa_overlaps -- through one workspace of
-    sa_workspace_bytes(n, reads) bytes (allocated here unless `ws` is given): (sa, isa, lcp,
+    """The whole path -- suffix array, LCP array, overlaps -- through one workspace (allocated
+    here unless `ws` is given; sa_workspace_bytes(n, reads) bytes are enough): (sa, isa, lcp,
     overlap rows)."""
     torch = _torch()
     lib = load()
     t = _dev_text(text)
     n = t.numel()
     if ws is None:
-        ws = _ws(sa_workspace_bytes(n, 0), t.device)
-    sa = torch.empty(n, dtype=torch.int32, device=t.device)
-    isa_t = torch.empty(n, dtype=torch.int32, device=t.device)
-    lcp = torch.empty(n, dtype=torch.int32, device=t.device)
+        ws = _ws(max(sa_workspace_bytes(n, 0), _index_ws_bytes(n)), t.device)
     st = _stream(stream)
-    _check(lib.sa_build(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(ws), ws.numel(), None, None, st))
-    _check(lib.sa_lcp(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(lcp), _ptr(ws), ws.numel(), st))
+    if ws.numel() >= _index_ws_bytes(n):
+        sa, isa_t, lcp = _index(t, ws, stream)
+    else:  # a workspace of the three calls' size without the room a build's own LCP takes
+        sa, isa_t, lcp = (torch.empty(n, dtype=torch.int32, device=t.device) for _ in range(3))
+        _check(lib.sa_build(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(ws), ws.numel(), None, None, st))
+        _check(lib.sa_lcp(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(lcp), _ptr(ws), ws.numel(), st))
     cap = max(n // 64, 1024)
     for _ in range(4):
         out = torch.empty((cap, 3), dtype=torch.int32, device=t.device)
@@ -475,8 +492,7 @@ def to_host(*tensors):
 def sa_reconstruct(text, max_steps: int = 10 ** 7, stream=None):
     """Builds SA, ISA and LCP of the fragment text on the GPU, then runs the host search."""
     t = _dev_text(text)
-    sa, isa = sa_build(t, stream=stream)
-    lcp = sa_lcp(t, sa, isa, stream=stream)
+    sa, isa, lcp = _index(t, _ws(_index_ws_bytes(t.numel()), t.device), stream)
     t_h, sa_h, isa_h, lcp_h = to_host(t, sa, isa, lcp)
     return sa_reconstruct_host(t_h, sa_h, isa_h, lcp_h, max_steps)
 
@@ -511,8 +527,7 @@ def sa_strand_rows(rows, m: int, stream=None):
 def sa_overlaps_rc(text, min_len: int, stream=None):
     """Overlaps on both strands: (k, 4) int32 device rows (a, b, strand, l), sorted."""
     t2, m = sa_revcomp_text(text, stream=stream)
-    sa, isa = sa_build(t2, stream=stream)
-    lcp = sa_lcp(t2, sa, isa, stream=stream)
+    sa, isa, lcp = _index(t2, _ws(_index_ws_bytes(t2.numel()), t2.device), stream)
     rows = sa_overlaps(t2, sa, isa, lcp, min_len, stream=stream)
     return sa_strand_rows(rows, m, stream=stream)
 

@@ -144,6 +144,41 @@ __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *
     return c;
 }
 
+// The codes of a key's h0 bases (zeros past its separator).  The string of its first D bases is
+// number at = |w| + (4 c - sum w_i) / 3 among all strings (key0_of), so 4 c - sum w_i is known
+// and rises by at least 3 with every c: steps by a quarter of what is left, rounded away from
+// zero, close in on c (three at most over every case tried up to 20 bases).
+__device__ __forceinline__ uint64_t key_codes(uint64_t key, uint32_t lo_bit, uint32_t top_d,
+                                              uint32_t h0, uint32_t *err) {
+    const uint32_t len = uint32_t(key) & 31u;
+    const uint64_t at = (key >> lo_bit) & ((uint64_t(1) << (2 * top_d + 1)) - 1);
+    const int64_t m = 3 * int64_t(at - (len < top_d ? len : top_d));
+    int64_t c = m >> 2;
+    for (int k = 0;; ++k) {
+        const int64_t d = m - 4 * c + popc64(uint64_t(c) & 0x5555555555555555ull) +
+                          2 * popc64(uint64_t(c) & 0xaaaaaaaaaaaaaaaaull);
+        if (d == 0) break;
+        if (k == 32) {  // not reached by a key that key0_of made
+            raise_err(err, kErrRange);
+            break;
+        }
+        c += d > 0 ? (d + 3) >> 2 : -((3 - d) >> 2);
+    }
+    const uint32_t rest = 2 * (h0 - top_d);
+    return (uint64_t(c) << rest) | ((key >> 5) & ((uint64_t(1) << rest) - 1));
+}
+
+// Common prefix of two suffixes that differ within their first h0 symbols, from their keys.
+__device__ __forceinline__ uint32_t key_lcp(uint64_t a, uint64_t b, uint32_t lo_bit,
+                                            uint32_t top_d, uint32_t h0, uint32_t *err) {
+    const uint32_t la = uint32_t(a) & 31u, lb = uint32_t(b) & 31u;
+    uint32_t l = la < lb ? la : lb;
+    if (l == 0) return 0;
+    const uint64_t d = key_codes(a, lo_bit, top_d, h0, err) ^ key_codes(b, lo_bit, top_d, h0, err);
+    const uint32_t same = d ? (uint32_t(__clzll((long long)d)) - (64 - 2 * h0)) >> 1 : h0;
+    return same < l ? same : l;
+}
+
 // One tile of the order by the keys' top bits (bits lo_bit and up): sorts its runs, labels its
 // groups and writes rank[], the final sa[] entries and the compacted slots and positions of
 // the suffixes still in groups, as k_rank_update does for a doubling round.  MIXED: runs of
@@ -152,13 +187,18 @@ __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *
 // A tile loads kFrRun items of context on either side, so every run of at most kFrRun items
 // that meets it, or meets the item after it, lies in the loaded span, and both tiles that share
 // a run sort it alike.
-template <bool MIXED>
+// LCP: also writes lcp[i] of every suffix told apart from its predecessor here (the keys and
+// windows compared hold their common prefix); for the others, which leave in groups, the
+// negative of one more than the symbols they are known to share.
+template <bool MIXED, bool LCP>
 __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V,
     const uint32_t *__restrict__ packed, uint32_t n, uint32_t lo_bit, uint32_t key_bits,
     uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
-    uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new, uint64_t *lbflags, uint32_t *tick,
-    uint32_t *state, uint32_t *err) {
+    uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new, int32_t *__restrict__ lcp,
+    uint64_t *lbflags, uint32_t *tick, uint32_t *state, uint32_t *err) {
+    __shared__ int16_t s_l[LCP ? kFrSpan : 1];   // lcp entries
+    __shared__ uint16_t s_at[LCP ? kFrSpan : 1]; // where a sorted item's words lie
     __shared__ uint64_t s_k[kFrSpan + 4];  // keys; first words of the extension keys; s_p
     __shared__ uint64_t s_c[kFrSpan + 4];  // (rest of key, item); s_v; second words
     uint32_t *const s_v = reinterpret_cast<uint32_t *>(s_c);  // text positions in order of the keys
@@ -208,8 +248,10 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         const int x = j * kFrBlock + tid;
         const int64_t gi = lo + x;
         bool h = gi <= 0 || gi >= int64_t(n);
-        if (!h && x > 0)
-            h = ((k[j] ^ s_k[x - 1]) & kmask) >> lo_bit || (k[j] & 31u) < uint64_t(top_d);
+        if (!h) {
+            const uint64_t prev = x > 0 ? s_k[x - 1] : K[gi - 1];
+            h = ((k[j] ^ prev) & kmask) >> lo_bit || (k[j] & 31u) < uint64_t(top_d);
+        }
         const uint64_t m = ballot(h);
         if (lane == 0) s_m0[x >> 6] = m;
     }
@@ -253,6 +295,11 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         reach[j] = uint32_t(key >> kKeyLenShift);
         bool h = gi <= 0 || gi >= int64_t(n);
         if (!h && x > 0) h = ((key ^ s_k[x - 1]) & kmask) != 0 || (key & 31u) < uint64_t(h0);
+        if (LCP) {
+            int l = -1 - int(h0);
+            if (h) l = gi <= 0 || x == 0 ? 0 : int(key_lcp(s_k[x - 1], key, lo_bit, top_d, h0, err));
+            s_l[x] = int16_t(l);
+        }
         const uint64_t m = ballot(h);
         if (lane == 0) s_m[x >> 6] = m;
     }
@@ -304,13 +351,41 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
                 s_c[pos[j]] = c1[j];
             }
             __syncthreads();
+            int to[kFrItems];
+            uint32_t heads = 0;
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
                 if (!en[j]) continue;
                 bool twin;
-                pos[j] = st[j] + count_below2(s_k, s_c, st[j], en[j], c0[j], c1[j], &twin);
-                if (!twin || ((c1[j] >> 7) & 63u) < uint64_t(kExtStage))
-                    atomicOr(&s_m32[pos[j] >> 5], 1u << (pos[j] & 31));
+                to[j] = st[j] + count_below2(s_k, s_c, st[j], en[j], c0[j], c1[j], &twin);
+                const bool head = !twin || ((c1[j] >> 7) & 63u) < uint64_t(kExtStage);
+                heads |= uint32_t(head) << j;
+                if (LCP) s_at[to[j]] = uint16_t(pos[j]);
+            }
+            if (LCP) {
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kFrItems; ++j) {
+                    if (!en[j] || to[j] == st[j]) continue;  // a group's first keeps its entry
+                    int l = -1 - int(depth) - (stage + 1) * kExtStage;
+                    if ((heads >> j) & 1u) {
+                        const uint32_t y = s_at[to[j] - 1];
+                        const uint64_t d0 = s_k[y] ^ c0[j], q1 = s_c[y], d1 = (q1 ^ c1[j]) >> 14;
+                        const uint32_t same = d0   ? uint32_t(__clzll((long long)d0)) >> 1
+                                              : d1 ? 32u + ((uint32_t(__clzll((long long)d1)) - 14u) >> 1)
+                                                   : uint32_t(kExtStage);
+                        const uint32_t la = uint32_t(q1 >> 7) & 63u, lb = uint32_t(c1[j] >> 7) & 63u;
+                        const uint32_t most = la < lb ? la : lb;
+                        l = int(depth) + stage * kExtStage + int(same < most ? same : most);
+                    }
+                    s_l[to[j]] = int16_t(l);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                if (!en[j]) continue;
+                pos[j] = to[j];
+                if ((heads >> j) & 1u) atomicOr(&s_m32[pos[j] >> 5], 1u << (pos[j] & 31));
             }
             __syncthreads();
             any = false;
@@ -371,6 +446,7 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         const int64_t gi = lo + r * 64 + lane;
         if (gi >= int64_t(n)) break;
         const uint32_t i = uint32_t(gi);
+        if (LCP) lcp[i] = s_l[r * 64 + lane];
         const uint64_t m = s_m[r];
         const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63)), bit = uint64_t(1) << lane;
         const uint32_t p = s_p[r * 64 + lane];
@@ -500,25 +576,21 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
 
 int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
                       int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
-                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags,
-                      int64_t lb_words, uint32_t *tick, uint32_t *state, hipStream_t s) {
+                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp,
+                      uint64_t *lbflags, int64_t lb_words, uint32_t *tick, uint32_t *state,
+                      hipStream_t s) {
     const int64_t tiles = (n + kFrTile - 1) / kFrTile;
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
     SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
     SA_TRY(launch_fill_u32(tick, 1, 0, s));
     // per suffix: key 8 and position 4 read; rank 4, and sa 4 or slot and position 8, written;
-    // 24 bytes of packed text for a suffix still in a group
-    TimedScope ts("keyruns", double(n) * 24.0, s, double(n));
-    if (mixed)
-        hipLaunchKernelGGL(k_first_runs<true>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed,
-                           uint32_t(n), uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d),
-                           uint32_t(h0), sa, rank, S_new, P_new,
-                           lbflags, tick, state, state + kStErr);
-    else
-        hipLaunchKernelGGL(k_first_runs<false>, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed,
-                           uint32_t(n), uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d),
-                           uint32_t(h0), sa, rank, S_new, P_new,
-                           lbflags, tick, state, state + kStErr);
+    // 36 bytes of packed text per window of a suffix still in a group; lcp 4
+    TimedScope ts("keyruns", double(n) * (lcp ? 28.0 : 24.0), s, double(n));
+    auto k = mixed ? (lcp ? k_first_runs<true, true> : k_first_runs<true, false>)
+                   : (lcp ? k_first_runs<false, true> : k_first_runs<false, false>);
+    hipLaunchKernelGGL(k, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed, uint32_t(n),
+                       uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d), uint32_t(h0), sa, rank,
+                       S_new, P_new, lcp, lbflags, tick, state, state + kStErr);
     ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;

@@ -136,6 +136,14 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
             void *ws, int64_t ws_bytes, hipStream_t stream, int32_t *flag = nullptr,
             int64_t span = 0);
 
+// Finishes an LCP array whose negative entries are -1 - (symbols the suffix is known to share with
+// its predecessor), by comparing on in the text.  Sets *too_long, and may leave entries
+// negative, when some pair shares more than kLcpRestMax symbols past those (then Kasai's scan
+// is the way).
+constexpr uint32_t kLcpRestMax = 2048;
+int launch_lcp_rest(const uint8_t *text, int64_t n, const int32_t *sa, int32_t *lcp, void *ws,
+                    int64_t ws_bytes, uint32_t *too_long, uint32_t *err, hipStream_t s);
+
 // radix sort plumbing
 struct SortBufs {
     uint64_t *keys[2];
@@ -178,6 +186,7 @@ constexpr int kStBigNext = 8;  // set by the rank update for the next round
 constexpr int kStBigLast = 9;  // kStRadixN of the round that ended (read back for timing)
 constexpr int kStLongRun = 10; // first round: a run of equal top key bits is too long for LDS
 constexpr int kStNoExt = 11;   // first round: some group is equal on the h0 symbols of its key only
+constexpr int kStLcpLong = 12; // the LCP array needs Kasai's scan (launch_lcp_rest)
 constexpr int kStWords = 16;   // state words the host reads back
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
@@ -198,8 +207,9 @@ static_assert(kH0 + kExtBases <= int(kKeyLenMax), "the extension needs exact dis
 constexpr int kFirstMinTile = 1792;
 int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
                       int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
-                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, uint64_t *lbflags,
-                      int64_t lb_words, uint32_t *tick, uint32_t *state, hipStream_t s);
+                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp_or_null,
+                      uint64_t *lbflags, int64_t lb_words, uint32_t *tick, uint32_t *state,
+                      hipStream_t s);
 int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,
                          int key_bits,
                          const SortBufs &b, uint32_t *idx, uint64_t *lbflags, int64_t lb_words,

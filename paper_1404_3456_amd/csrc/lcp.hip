@@ -117,6 +117,44 @@ __global__ __launch_bounds__(256) void k_lcp_gather(const int32_t *__restrict__ 
     }
 }
 
+// One entry per thread; see launch_lcp_rest.  A thread that finds the flag set stops: on a text
+// with many long matches the kernel then ends after its first workgroups.
+__global__ __launch_bounds__(256) void k_lcp_rest(const uint4 *__restrict__ blk,
+                                                  const int32_t *__restrict__ sa, uint32_t n,
+                                                  int32_t *__restrict__ lcp, uint32_t *too_long,
+                                                  uint32_t *err) {
+    for (uint64_t g = blockIdx.x * 256u + threadIdx.x; g < n; g += uint64_t(gridDim.x) * 256u) {
+        const uint32_t i = uint32_t(g);
+        const int32_t l = lcp[i];
+        if (l >= 0 || i == 0) continue;
+        if (ld_agent(too_long)) return;
+        const uint32_t p = uint32_t(sa[i]), q = uint32_t(sa[i - 1]);
+        uint32_t h = uint32_t(-1 - l);
+        const uint32_t most = h + kLcpRestMax;
+        while (true) {
+            if (p >= n || q >= n || h >= n - p || h >= n - q) {
+                raise_err(err, kErrRange);
+                break;
+            }
+            if (h >= most) {
+                st_agent(too_long, 1u);
+                break;
+            }
+            const Window a = window_at(blk, p + h), b = window_at(blk, q + h);
+            const uint64_t d = a.code ^ b.code;
+            const uint32_t sp = a.sep | b.sep;
+            const uint32_t md = d ? uint32_t(__clzll((long long)d)) >> 1 : 32u;
+            const uint32_t ms = sp ? uint32_t(__clz(sp)) : 32u;
+            const uint32_t kk = md < ms ? md : ms;
+            h += kk;
+            if (kk < 32) {
+                lcp[i] = int32_t(h);
+                break;
+            }
+        }
+    }
+}
+
 static uint32_t g_lcp_chunk = 4;
 // Texts of at least this many positions take the permuted-LCP form (4 bytes of LCP per
 // position exceed the 256 MB last-level cache from about 64 M on).
@@ -194,6 +232,22 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
         SA_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_lcp_flag, dim3(1), dim3(64), 0, stream, err, flag ? flag : lcp);
+    SA_HIP(hipGetLastError());
+    return SA_OK;
+}
+
+int launch_lcp_rest(const uint8_t *text, int64_t n, const int32_t *sa, int32_t *lcp, void *ws,
+                    int64_t ws_bytes, uint32_t *too_long, uint32_t *err, hipStream_t s) {
+    if (ws_bytes < lcp_ws_bytes(n)) return fail(SA_ERR_NOMEM, "sa_lcp: workspace too small");
+    Carver c(ws, ws_bytes);
+    uint4 *blk = c.take<uint4>(sepmask_words(n));
+    SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, blk, err, s));
+    int64_t g = (n + 255) / 256;
+    if (g > 16384) g = 16384;
+    TimedScope ts("lcp_rest", double(n) * 4.0, s, double(n));
+    hipLaunchKernelGGL(k_lcp_rest, dim3(unsigned(g)), dim3(256), 0, s, blk, sa, uint32_t(n), lcp,
+                       too_long, err);
+    ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;
 }

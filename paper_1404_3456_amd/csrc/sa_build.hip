@@ -430,6 +430,7 @@ struct Build {
     const int64_t *set_off_h;
     int32_t *sa;
     uint32_t *rank;
+    int32_t *lcp = nullptr;  // batched builds: filled as far as the first round tells
     Tune t;
     BuildLayout L;
     hipStream_t s;
@@ -455,7 +456,7 @@ struct Build {
     // Keys and the passes over their bits [lo_bit, key0_bits): the sorted items end up in
     // buffer *cur.
     int first_sort(int lo_bit, int *cur) {
-        const int64_t *set_off_dev = n_sets > 0 ? L.set_off : nullptr;
+        const int64_t *set_off_dev = n_sets > 1 ? L.set_off : nullptr;
         const int bits = key0_bits - lo_bit;
         SA_TRY(sort_prepare(L.sb, n, bits, t, s));
         int nparts = 0;
@@ -483,7 +484,7 @@ struct Build {
         SA_TRY(launch_fill_u32(L.state, 64, 0, s));
         SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
         SA_TRY(launch_pack(text, n, L.packed, L.sepmask, nullptr, nullptr, L.state + kStErr, s));
-        if (n_sets > 0) {
+        if (n_sets > 1) {  // one text's end is checked by the packing
             SA_HIP(hipMemcpyAsync(L.set_off, set_off_h, size_t(n_sets + 1) * 8, hipMemcpyHostToDevice, s));
             hipLaunchKernelGGL(k_check_sets, dim3(unsigned((n_sets + 255) / 256)), dim3(256), 0, s,
                                text, L.set_off, uint32_t(n_sets), L.state + kStErr);
@@ -501,7 +502,7 @@ struct Build {
         const int lo_bit = key0_bits - top_bits;
         SA_TRY(first_sort(lo_bit, &cur));
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, false, sa, rank,
-                                 L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
+                                 L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end());
         SA_TRY(wait_state(ps, host));
         if (host[kStLongRun] == 0) return SA_OK;
@@ -527,7 +528,7 @@ struct Build {
                                 L.sb.vals[cur], L.state + kStErr, s));
         timing_scope_mode(kModeAny);
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, true, sa, rank,
-                                 L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets, L.state, s));
+                                 L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end());
         SA_TRY(wait_state(ps, host));
         timing_round_items(tag, n, host[kStBigLast]);
@@ -601,7 +602,25 @@ struct Build {
         key0_bits = 2 * h0 + 6 + sb;
     }
 
-    int run(bool use_graph, int *rounds_out) {
+    // The rest of the LCP array after the last round: *have_lcp when it is complete.  A build
+    // whose first round left no group has it already; texts with matches far beyond the first
+    // round's reach are left to Kasai's scan, whose work does not depend on their length.
+    int finish_lcp(PinnedState &ps, bool left, bool *have_lcp) {
+        if (!lcp || top_bits == 0) return SA_OK;
+        if (left) {
+            uint32_t host[kStWords];
+            SA_TRY(launch_lcp_rest(text, n, sa, lcp, L.lcp_ws, L.lcp_ws_bytes, L.state + kStLcpLong,
+                                   L.state + kStErr, s));
+            SA_TRY(wait_state(ps, host));
+            timing_flush();
+            SA_TRY(check_err(host[kStErr]));
+            if (host[kStLcpLong]) return SA_OK;
+        }
+        *have_lcp = true;
+        return SA_OK;
+    }
+
+    int run(bool use_graph, int *rounds_out, bool *have_lcp) {
         rbits = bits_for(n - 1);
         choose_first_round();
         if (h0 < 1) return fail(SA_ERR_INVALID, "too many texts in one batch");
@@ -613,7 +632,8 @@ struct Build {
         SA_TRY(round0(ps, host));
         timing_poll();
         SA_TRY(check_err(host[kStErr]));
-        if (host[kStActive] == 0) {
+        const bool left = host[kStActive] != 0;
+        if (!left) {
             timing_flush();
         } else if (use_graph) {
             int64_t A = host[kStActive];
@@ -703,7 +723,7 @@ struct Build {
             }
         }
         if (rounds_out) *rounds_out = int(host[kStRounds]);
-        return SA_OK;
+        return finish_lcp(ps, left, have_lcp);
     }
 };
 
@@ -730,10 +750,13 @@ static int build_common(const uint8_t *text, int64_t n, const int64_t *set_off_h
     carve_build(c, n, n_sets, t, &B.L);
     B.L.sb.err = B.L.state + kStErr;
     B.rank = isa_or_null ? reinterpret_cast<uint32_t *>(isa_or_null) : B.L.rank;
+    if (lcp_or_null && (n_sets < 1 || !B.L.lcp_ws))
+        return fail(SA_ERR_INVALID, "LCP output needs a batched build");
+    B.lcp = lcp_or_null;
     int rounds = 0;
-    SA_TRY(B.run(use_graph, &rounds));
-    if (lcp_or_null) {
-        if (n_sets < 1 || !B.L.lcp_ws) return fail(SA_ERR_INVALID, "LCP output needs a batched build");
+    bool have_lcp = false;  // the array is complete
+    SA_TRY(B.run(use_graph, &rounds, &have_lcp));
+    if (lcp_or_null && !have_lcp) {
         int64_t span = 0;  // the largest text of the batch
         for (int32_t k = 0; k < n_sets; ++k)
             span = set_off_h[k + 1] - set_off_h[k] > span ? set_off_h[k + 1] - set_off_h[k] : span;

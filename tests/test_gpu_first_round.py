@@ -95,3 +95,56 @@ def test_batches(lib, use_graph, kind):
         assert np.array_equal(sa[off[k]:off[k + 1]] - off[k], want)
         assert np.array_equal(lcp[off[k]:off[k + 1]], oracle.lcp_array(t, want))
     assert np.array_equal(isa.cpu().numpy()[sa], np.arange(off[-1]))
+
+
+def lcp_of(lib, text):
+    off = np.array([0, text.size], dtype=np.int64)
+    sa, _, lcp = lib.sa_build_batched(torch.from_numpy(text).cuda(), off, lcp=True)
+    return sa.cpu().numpy(), lcp.cpu().numpy()
+
+
+@pytest.mark.parametrize("read", [24, 25, 80, 81, 82, 137, 138, 139, 481, 2400, 2600])
+def test_lcp_of_the_build(lib, read):
+    """The LCP array a build makes itself: pairs that share about as much as a key, a stage, a
+    window and all windows hold, and more than the scan after them goes on for (then the
+    array is Kasai's), in groups small and large."""
+    rng = np.random.default_rng([synth.SEED_BASE, 803, read])
+    letters = np.frombuffer(b"ACGT", dtype=np.uint8)
+    base = rng.choice(letters, read)
+    reads = []
+    for copies, cut in ((3, 0), (40, 1), (150, 2)):  # copies that end differently
+        for _ in range(copies if read < 1000 else min(copies, 12)):
+            r = base.copy()
+            if r.size > 30:
+                r[int(rng.integers(20, r.size))] = letters[int(rng.integers(0, 4))]
+            reads.append(r[: r.size - cut].tobytes().decode())
+    reads += [rng.choice(letters, int(rng.integers(1, 300))).tobytes().decode() for _ in range(200)]
+    text = synth.text_from_strings([reads[i] for i in rng.permutation(len(reads))])
+    sa, lcp = lcp_of(lib, text)
+    want = oracle.suffix_array(text)
+    assert text.size >= MIN_N
+    assert np.array_equal(sa, want)
+    assert np.array_equal(lcp, oracle.lcp_array(text, want))
+
+
+@pytest.mark.parametrize("kind", ["homopolymer", "tandem", "empty"])
+def test_lcp_of_long_runs(lib, kind):
+    reads = {"homopolymer": ["A" * 9000, "C" * 9000], "tandem": ["ACG" * 150] * 60, "empty": [""] * 17_000}[kind]
+    text = synth.text_from_strings(reads + ["ACGT"])
+    sa, lcp = lcp_of(lib, text)
+    want = oracle.suffix_array(text)
+    assert text.size >= MIN_N
+    assert np.array_equal(sa, want)
+    assert np.array_equal(lcp, oracle.lcp_array(text, want))
+
+
+def test_path_in_a_smaller_workspace(lib):
+    """sa_path in the workspace its documentation asks for, and in its own, gives the same."""
+    text = reads_of_size(9300, 40_000)
+    t = torch.from_numpy(text).cuda()
+    ws = torch.empty(lib.sa_workspace_bytes(text.size, 0), dtype=torch.uint8, device="cuda")
+    want = oracle.suffix_array(text)
+    for got in (lib.sa_path(t, 30, ws=ws), lib.sa_path(t, 30)):
+        assert np.array_equal(got[0].cpu().numpy(), want)
+        assert np.array_equal(got[2].cpu().numpy(), oracle.lcp_array(text, want))
+        assert np.array_equal(got[3].cpu().numpy(), oracle.overlaps(text, 30))
