@@ -28,6 +28,7 @@ constexpr int kFrItems = 2;
 constexpr int kFrSpan = kFrBlock * kFrItems;     // items loaded per tile
 constexpr int kFrTile = kFrSpan - 2 * kFrRun;    // items a tile finishes
 constexpr int kFrRows = kFrSpan / kWave;
+constexpr uint32_t kFrNone = 0xffffffffu;        // no item
 constexpr int kFrWaves = kFrBlock / kWave;
 constexpr int kFrRow0 = kFrRun / kWave;              // first and last + 1 row of the tile's own items
 constexpr int kFrRow1 = kFrRows - kFrRun / kWave;
@@ -197,12 +198,14 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
     uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
     uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new, int32_t *__restrict__ lcp,
     uint64_t *lbflags, uint32_t *tick, uint32_t *state, uint32_t *err) {
+    __shared__ uint64_t s_k[kFrSpan + 4];        // keys; first words of the extension keys
+    __shared__ uint64_t s_c[kFrSpan + 4];        // (rest of key, item); second words
+    __shared__ uint32_t s_v[kFrSpan];            // text positions, in order
+    __shared__ uint16_t s_reach[kFrSpan];        // symbols before the separator (511: or more)
+    __shared__ uint16_t s_list[kFrSpan];         // places of the items in groups
     __shared__ int16_t s_l[LCP ? kFrSpan : 1];   // lcp entries
     __shared__ uint16_t s_at[LCP ? kFrSpan : 1]; // where a sorted item's words lie
-    __shared__ uint64_t s_k[kFrSpan + 4];  // keys; first words of the extension keys; s_p
-    __shared__ uint64_t s_c[kFrSpan + 4];  // (rest of key, item); s_v; second words
-    uint32_t *const s_v = reinterpret_cast<uint32_t *>(s_c);  // text positions in order of the keys
-    uint32_t *const s_p = reinterpret_cast<uint32_t *>(s_k);  // text positions in the final order
+    __shared__ uint32_t s_cnt[kFrRows];
     __shared__ uint64_t s_m0[kFrRows];    // starts of runs
     __shared__ uint64_t s_m[kFrRows];     // starts of groups
     __shared__ uint64_t s_row[kFrRows];   // (count, last start) before each row
@@ -281,18 +284,16 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
     for (int j = 0; j < kFrItems; ++j) {
         s_k[pos[j]] = k[j];
         s_v[pos[j]] = v[j];
+        s_reach[pos[j]] = uint16_t(k[j] >> kKeyLenShift);
     }
     __syncthreads();
     // starts of groups equal on the whole key; a key of fewer than h0 symbols is a suffix that
     // ended at its separator, alone in its group
-    uint32_t reach[kFrItems];  // symbols before the separator (511: or more)
 #pragma unroll
     for (int j = 0; j < kFrItems; ++j) {
         const int x = j * kFrBlock + tid;
         const int64_t gi = lo + x;
         const uint64_t key = s_k[x];
-        v[j] = s_v[x];
-        reach[j] = uint32_t(key >> kKeyLenShift);
         bool h = gi <= 0 || gi >= int64_t(n);
         if (!h && x > 0) h = ((key ^ s_k[x - 1]) & kmask) != 0 || (key & 31u) < uint64_t(h0);
         if (LCP) {
@@ -305,103 +306,145 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
     }
     __syncthreads();
     // Groups that meet the tile or the item after it are told apart by the text: windows of two
-    // stages, kExtStage bases each, as long as the tile has groups.  en[j] > 0: item j of the
-    // thread is in such a group, at pos[j] in [st[j], en[j]).
-    int st[kFrItems], en[kFrItems];
-    bool any = false;
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        const bool small = run_bounds(s_m, x, &st[j], &en[j]);
-        if (!small && x >= kFrRun && x < kFrRun + kFrTile) state[kStNoExt] = 1u;
-        const bool ext = small && en[j] - st[j] > 1 && st[j] <= kFrRun + kFrTile && en[j] > kFrRun;
-        if (!ext) en[j] = 0;
-        any = any || ext;
-        pos[j] = x;
-    }
+    // stages, kExtStage bases each, while there are such groups.  Each window starts by listing
+    // their items, so that a window few items need takes few waves.
     uint32_t *const s_m32 = reinterpret_cast<uint32_t *>(s_m);
+#pragma unroll 1
     for (int w = 0; w < kExtWindows; ++w) {
-        if (!__syncthreads_or(any)) break;
-        const uint32_t depth = h0 + uint32_t(w) * 2 * kExtStage;
-        Bases q[kFrItems];
+        // opaque in the loop: what hangs on it is cheaper made again than kept in registers
+        uint32_t id = tid;
+        asm volatile("" : "+v"(id));
+        uint64_t in[kFrItems];
 #pragma unroll
         for (int j = 0; j < kFrItems; ++j) {
-            if (!en[j]) continue;
-            const uint32_t a = v[j] + depth;
+            const int x = j * kFrBlock + int(id);
+            int st, en;
+            const bool small = run_bounds(s_m, x, &st, &en);
+            if (!small && x >= kFrRun && x < kFrRun + kFrTile) state[kStNoExt] = 1u;
+            in[j] = ballot(small && en - st > 1 && st <= kFrRun + kFrTile && en > kFrRun);
+            if (lane == 0) s_cnt[x >> 6] = uint32_t(popc64(in[j]));
+        }
+        __syncthreads();
+        const uint32_t cnt = lane < uint32_t(kFrRows) ? s_cnt[lane] : 0u;
+        const uint32_t inc = wave_incl_scan<Sum32>(cnt);
+        const uint32_t total = __shfl(inc, kFrRows - 1);
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            const int row = j * kFrWaves + int(id / kWave);
+            const uint32_t before = __shfl(inc - cnt, row);
+            if ((in[j] >> lane) & 1u)
+                s_list[before + uint32_t(popc64(in[j] & lanemask_lt()))] = uint16_t(row * 64 + int(lane));
+        }
+        if (total == 0) break;  // the same for every wave
+        __syncthreads();
+        const uint32_t depth = h0 + uint32_t(w) * 2 * kExtStage;
+        // an item of the thread: its place, where its position and reach lie (its place at the
+        // window's start) and its group's bounds in one word each, 11 bits a place; and the
+        // second stage's words.  What a barrier separates is read again from LDS: registers
+        // bound the waves in flight.
+        uint32_t at[kFrItems], grp[kFrItems];
+        uint64_t d0[kFrItems], d1[kFrItems];
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            const uint32_t t = j * kFrBlock + id;
+            at[j] = kFrNone;
+            if (t >= total) continue;
+            const uint32_t x = s_list[t];
+            at[j] = x | (x << 16);
+            grp[j] = uint32_t(run_start(s_m, int(x))) | (uint32_t(run_end(s_m, int(x))) << 16);
+            uint32_t a = s_v[x] + depth;
             if (a >= n) {  // inconsistent input: report only
                 raise_err(err, kErrRange);
-                en[j] = 0;
-                continue;
+                a = 0;
             }
-            q[j] = bases_at(packed, a);
+            const Bases q = bases_at(packed, a);
+            const uint32_t l = s_reach[x] - depth;
+            uint64_t c0, c1;
+            stage_key(q.b[0], q.b[1], l, &c0, &c1);
+            s_k[x] = c0;
+            s_c[x] = c1 | (x - (grp[j] & 0xffffu));  // equal symbols: in order of their positions
+            // 57 bases are 114 bits: 50 bits into the second word
+            stage_key((q.b[1] << 50) | (q.b[2] >> 14), (q.b[2] << 50) | (q.b[3] >> 14),
+                      l > uint32_t(kExtStage) ? l - kExtStage : 0u, &d0[j], &d1[j]);
         }
 #pragma unroll
         for (int stage = 0; stage < 2; ++stage) {
-            uint64_t c0[kFrItems], c1[kFrItems];
+            if (stage == 1) {
 #pragma unroll
-            for (int j = 0; j < kFrItems; ++j) {
-                if (!en[j]) continue;
-                const uint64_t *b = q[j].b;
-                // 57 bases are 114 bits: 50 bits into the second word
-                const uint64_t w0 = stage == 0 ? b[0] : (b[1] << 50) | (b[2] >> 14);
-                const uint64_t w1 = stage == 0 ? b[1] : (b[2] << 50) | (b[3] >> 14);
-                stage_key(w0, w1, reach[j] - depth - uint32_t(stage * kExtStage), &c0[j], &c1[j]);
-                c1[j] |= uint64_t(pos[j] - st[j]);  // equal symbols: in order of their positions
-                s_k[pos[j]] = c0[j];
-                s_c[pos[j]] = c1[j];
+                for (int j = 0; j < kFrItems; ++j) {
+                    if (at[j] == kFrNone || !grp[j]) continue;
+                    const uint32_t x = at[j] & 0xffffu;
+                    s_k[x] = d0[j];
+                    s_c[x] = d1[j] | (x - (grp[j] & 0xffffu));
+                }
             }
             __syncthreads();
-            int to[kFrItems];
-            uint32_t heads = 0;
+            uint32_t to[kFrItems];  // its place after the stage; top bit: a group's first
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
-                if (!en[j]) continue;
+                if (at[j] == kFrNone || !grp[j]) continue;
+                const uint32_t x = at[j] & 0xffffu;
+                const int st = int(grp[j] & 0xffffu), en = int(grp[j] >> 16);
+                const uint64_t c0 = s_k[x], c1 = s_c[x];
                 bool twin;
-                to[j] = st[j] + count_below2(s_k, s_c, st[j], en[j], c0[j], c1[j], &twin);
-                const bool head = !twin || ((c1[j] >> 7) & 63u) < uint64_t(kExtStage);
-                heads |= uint32_t(head) << j;
-                if (LCP) s_at[to[j]] = uint16_t(pos[j]);
+                to[j] = uint32_t(st + count_below2(s_k, s_c, st, en, c0, c1, &twin));
+                if (LCP) s_at[to[j]] = uint16_t(x);
+                if (!twin || (uint32_t(c1 >> 7) & 63u) < uint32_t(kExtStage)) to[j] |= kDone;
             }
             if (LCP) {
                 __syncthreads();
 #pragma unroll
                 for (int j = 0; j < kFrItems; ++j) {
-                    if (!en[j] || to[j] == st[j]) continue;  // a group's first keeps its entry
+                    if (at[j] == kFrNone || !grp[j]) continue;
+                    const uint32_t y = to[j] & kRankMask;
+                    if (y == (grp[j] & 0xffffu)) continue;  // a group's first keeps its entry
                     int l = -1 - int(depth) - (stage + 1) * kExtStage;
-                    if ((heads >> j) & 1u) {
-                        const uint32_t y = s_at[to[j] - 1];
-                        const uint64_t d0 = s_k[y] ^ c0[j], q1 = s_c[y], d1 = (q1 ^ c1[j]) >> 14;
-                        const uint32_t same = d0   ? uint32_t(__clzll((long long)d0)) >> 1
-                                              : d1 ? 32u + ((uint32_t(__clzll((long long)d1)) - 14u) >> 1)
+                    if (to[j] & kDone) {
+                        const uint32_t x = at[j] & 0xffffu, z = s_at[y - 1];
+                        const uint64_t c1 = s_c[x], e1 = s_c[z], x0 = s_k[x] ^ s_k[z], x1 = (c1 ^ e1) >> 14;
+                        const uint32_t same = x0   ? uint32_t(__clzll((long long)x0)) >> 1
+                                              : x1 ? 32u + ((uint32_t(__clzll((long long)x1)) - 14u) >> 1)
                                                    : uint32_t(kExtStage);
-                        const uint32_t la = uint32_t(q1 >> 7) & 63u, lb = uint32_t(c1[j] >> 7) & 63u;
+                        const uint32_t la = uint32_t(c1 >> 7) & 63u, lb = uint32_t(e1 >> 7) & 63u;
                         const uint32_t most = la < lb ? la : lb;
                         l = int(depth) + stage * kExtStage + int(same < most ? same : most);
                     }
-                    s_l[to[j]] = int16_t(l);
+                    s_l[y] = int16_t(l);
                 }
             }
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
-                if (!en[j]) continue;
-                pos[j] = to[j];
-                if ((heads >> j) & 1u) atomicOr(&s_m32[pos[j] >> 5], 1u << (pos[j] & 31));
+                if (at[j] == kFrNone || !grp[j]) continue;
+                const uint32_t y = to[j] & kRankMask;
+                at[j] = (at[j] & 0xffff0000u) | y;
+                if (to[j] & kDone) atomicOr(&s_m32[y >> 5], 1u << (y & 31));
             }
             __syncthreads();
-            any = false;
+            if (stage == 1) continue;
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
-                if (!en[j]) continue;
-                st[j] = run_start(s_m, pos[j]);
-                en[j] = run_end(s_m, pos[j]);
-                if (en[j] - st[j] <= 1) en[j] = 0;
-                any = any || en[j] != 0;
+                if (at[j] == kFrNone) continue;
+                const int x = int(at[j] & 0xffffu);
+                const uint32_t st = uint32_t(run_start(s_m, x)), en = uint32_t(run_end(s_m, x));
+                grp[j] = en - st > 1 ? st | (en << 16) : 0u;  // 0: alone
             }
         }
-    }
-    __syncthreads();
+        uint32_t v2[kFrItems], r2[kFrItems];
 #pragma unroll
-    for (int j = 0; j < kFrItems; ++j) s_p[pos[j]] = v[j];
+        for (int j = 0; j < kFrItems; ++j) {
+            if (at[j] == kFrNone) continue;
+            v2[j] = s_v[at[j] >> 16];
+            r2[j] = s_reach[at[j] >> 16];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            if (at[j] == kFrNone) continue;
+            s_v[at[j] & 0xffffu] = v2[j];
+            s_reach[at[j] & 0xffffu] = uint16_t(r2[j]);
+        }
+        __syncthreads();
+    }
     __syncthreads();
     // Wave 0: per row of 64, the suffixes still in groups (not both they and the next item
     // start one) and the last start, scanned over the tile's rows and then over tiles.  The
@@ -432,7 +475,7 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         for (int r = kFrRow0 + int(wave) - 1; r < kFrRow1; r += kFrWaves - 1) {
             const int64_t gi = lo + r * 64 + lane;
             if (gi >= int64_t(n)) break;
-            const uint32_t p = s_p[r * 64 + lane];
+            const uint32_t p = s_v[r * 64 + lane];
             const int st_x = run_start(s_m, r * 64 + int(lane));
             if (p >= n || st_x < 0 || lo + st_x < 0) continue;  // see below
             rank[p] = uint32_t(lo + st_x);
@@ -449,7 +492,7 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         if (LCP) lcp[i] = s_l[r * 64 + lane];
         const uint64_t m = s_m[r];
         const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63)), bit = uint64_t(1) << lane;
-        const uint32_t p = s_p[r * 64 + lane];
+        const uint32_t p = s_v[r * 64 + lane];
         if (p >= n) {  // inconsistent input: report only
             raise_err(err, kErrRange);
             continue;
