@@ -23,34 +23,36 @@
 namespace saasm {
 
 constexpr int kFrRun = 128;                      // longest run sorted in LDS
-constexpr int kFrBlock = 1024;
-constexpr int kFrItems = 2;
+constexpr int kFrBlock = 256;
+constexpr int kFrItems = 6;
 constexpr int kFrSpan = kFrBlock * kFrItems;     // items loaded per tile
-constexpr int kFrTile = kFrSpan - 2 * kFrRun;    // items a tile finishes
+constexpr int kFrTile = kFrSpan - kFrRun;        // items whose runs a tile finishes
 constexpr int kFrRows = kFrSpan / kWave;
 constexpr uint32_t kFrNone = 0xffffffffu;        // no item
 constexpr int kFrWaves = kFrBlock / kWave;
-constexpr int kFrRow0 = kFrRun / kWave;              // first and last + 1 row of the tile's own items
-constexpr int kFrRow1 = kFrRows - kFrRun / kWave;
-constexpr int kFrReach = kFrRun / kWave;             // words of a mask a run can reach into
+constexpr int kFrReach = kFrRun / kWave;         // words of a mask a run can reach into
+constexpr int kFrNowhere = -2 * kFrRun;          // no start, no end
 static_assert(kFrRun % kWave == 0 && kFrRun <= 128, "7 bits tell the members of a group apart");
+static_assert(kFrTile % kWave == 0 && kFrRows <= kWave, "rows of the scan");
 static_assert(kFrTile >= kFirstMinTile, "look-back words are sized for tiles of kFirstMinTile items");
 
 // First item of the run that holds item x, from a mask of run starts (bit x % 64 of word
-// x / 64): the nearest start at or before x, sought kFrReach words back; -1 if there is none.
+// x / 64; kFrReach words before word 0 are there too): the nearest start at or before x, sought
+// kFrReach words back; kFrNowhere if there is none.
 __device__ __forceinline__ int run_start(const uint64_t *m, int x) {
     const int w = x >> 6, b = x & 63;
     const uint64_t le = b == 63 ? ~uint64_t(0) : ((uint64_t(2) << b) - 1);
     uint64_t v = m[w] & le;
     int at = w;
-    for (int k = 1; k <= kFrReach && !v && w - k >= 0; ++k) {
+    for (int k = 1; k <= kFrReach && !v; ++k) {
         v = m[w - k];
         at = w - k;
     }
-    return v ? at * 64 + 63 - int(__clzll((long long)v)) : -1;
+    return v ? at * 64 + 63 - int(__clzll((long long)v)) : kFrNowhere;
 }
 
-// First item after the run that holds item x: the next start, sought kFrReach words on; -1 if none.
+// First item after the run that holds item x: the next start, sought kFrReach words on;
+// kFrNowhere if there is none.
 __device__ __forceinline__ int run_end(const uint64_t *m, int x) {
     const int w = x >> 6, b = x & 63;
     const uint64_t le = b == 63 ? ~uint64_t(0) : ((uint64_t(2) << b) - 1);
@@ -60,14 +62,23 @@ __device__ __forceinline__ int run_end(const uint64_t *m, int x) {
         v = m[w + k];
         at = w + k;
     }
-    return v ? at * 64 + int(__ffsll((long long)v)) - 1 : -1;
+    return v ? at * 64 + int(__ffsll((long long)v)) - 1 : kFrNowhere;
 }
 
-// Bounds of the run of item x when it has at most kFrRun items inside the loaded span.
+// Bounds of the run of item x; whether it is known to have at most kFrRun items.
 __device__ __forceinline__ bool run_bounds(const uint64_t *m, int x, int *st, int *en) {
     *st = run_start(m, x);
     *en = run_end(m, x);
-    return *st >= 0 && *en >= 0 && *en - *st <= kFrRun;
+    return *st != kFrNowhere && *en != kFrNowhere && *en - *st <= kFrRun;
+}
+
+// The first start at or after item x (word-aligned) within the span.
+__device__ __forceinline__ int first_start(const uint64_t *m, int x) {
+    for (int w = x >> 6; w < kFrRows; ++w) {
+        const uint64_t v = m[w];
+        if (v) return w * 64 + int(__ffsll((long long)v)) - 1;
+    }
+    return kFrSpan;
 }
 
 // 128 bases of the packed text from position a on (base 0 in the top bits of b[0]).
@@ -107,26 +118,56 @@ __device__ __forceinline__ void stage_key(uint64_t w0, uint64_t w1, uint32_t l, 
     *c1 = w1 | (uint64_t(l) << 7);
 }
 
+// c + 1 in the lanes of `in` whose (q0, q1) is below (k0, k1): the borrow of one 32-bit
+// subtraction chain.  As comparisons this is four 64-bit ones and their logic, twice the
+// instructions, and the compiler turns the chain in C back into them.
+__device__ __forceinline__ uint32_t add_below(uint32_t c, uint64_t q0, uint64_t k0, uint64_t in) {
+    uint32_t t;
+    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
+        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
+        "s_and_b64 vcc, vcc, %6\n\t"
+        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
+        : "=&v"(t), "+v"(c)
+        : "v"(uint32_t(q0)), "v"(uint32_t(k0)), "v"(uint32_t(q0 >> 32)), "v"(uint32_t(k0 >> 32)),
+          "s"(in)
+        : "vcc");
+    return c;
+}
+__device__ __forceinline__ uint32_t add_below2(uint32_t c, uint64_t q0, uint64_t q1, uint64_t k0,
+                                               uint64_t k1, uint64_t in) {
+    uint32_t t;
+    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
+        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
+        "v_subb_co_u32 %0, vcc, %6, %7, vcc\n\t"
+        "v_subb_co_u32 %0, vcc, %8, %9, vcc\n\t"
+        "s_and_b64 vcc, vcc, %10\n\t"
+        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
+        : "=&v"(t), "+v"(c)
+        : "v"(uint32_t(q1)), "v"(uint32_t(k1)), "v"(uint32_t(q1 >> 32)), "v"(uint32_t(k1 >> 32)),
+          "v"(uint32_t(q0)), "v"(uint32_t(k0)), "v"(uint32_t(q0 >> 32)), "v"(uint32_t(k0 >> 32)),
+          "s"(in)
+        : "vcc");
+    return c;
+}
+
 // Items y of [st, en) whose word s[y] is below k, four reads at a time (s has four words more
 // than it has items).
 __device__ __forceinline__ int count_below(const uint64_t *s, int st, int en, uint64_t k) {
-    int c = 0;
+    uint32_t c = 0;
     for (int y = st; y < en; y += 4) {
         uint64_t q[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = s[y + i];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) c += (y + i < en && q[i] < k) ? 1 : 0;
+        for (int i = 0; i < 4; ++i) c = add_below(c, q[i], k, ballot(y + i < en));
     }
-    return c;
+    return int(c);
 }
 
-// The same for two-word keys, whose last 7 bits tell equal symbols apart; *twin: some item
-// below has the same symbols.
+// The same for two-word keys.
 __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *s1, int st, int en,
-                                            uint64_t k0, uint64_t k1, bool *twin) {
-    int c = 0;
-    bool same = false;
+                                            uint64_t k0, uint64_t k1) {
+    uint32_t c = 0;
     for (int y = st; y < en; y += 4) {
         uint64_t q0[4], q1[4];
 #pragma unroll
@@ -135,14 +176,9 @@ __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *
             q1[i] = s1[y + i];
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool in = y + i < en, eq = q0[i] == k0, lt1 = q1[i] < k1;
-            c += (in && (q0[i] < k0 || (eq && lt1))) ? 1 : 0;
-            same = same || (in && eq && lt1 && (q1[i] ^ k1) < 128);
-        }
+        for (int i = 0; i < 4; ++i) c = add_below2(c, q0[i], q1[i], k0, k1, ballot(y + i < en));
     }
-    *twin = same;
-    return c;
+    return int(c);
 }
 
 // The codes of a key's h0 bases (zeros past its separator).  The string of its first D bases is
@@ -169,13 +205,12 @@ __device__ __forceinline__ uint64_t key_codes(uint64_t key, uint32_t lo_bit, uin
     return (uint64_t(c) << rest) | ((key >> 5) & ((uint64_t(1) << rest) - 1));
 }
 
-// Common prefix of two suffixes that differ within their first h0 symbols, from their keys.
-__device__ __forceinline__ uint32_t key_lcp(uint64_t a, uint64_t b, uint32_t lo_bit,
-                                            uint32_t top_d, uint32_t h0, uint32_t *err) {
-    const uint32_t la = uint32_t(a) & 31u, lb = uint32_t(b) & 31u;
-    uint32_t l = la < lb ? la : lb;
-    if (l == 0) return 0;
-    const uint64_t d = key_codes(a, lo_bit, top_d, h0, err) ^ key_codes(b, lo_bit, top_d, h0, err);
+// Common prefix of two suffixes that differ within their first h0 symbols, from their keys'
+// codes and lengths (the last 5 bits of a and b).
+__device__ __forceinline__ uint32_t key_lcp(uint64_t ca, uint64_t cb, uint32_t a, uint32_t b,
+                                            uint32_t h0) {
+    const uint32_t la = a & 31u, lb = b & 31u, l = la < lb ? la : lb;
+    const uint64_t d = ca ^ cb;
     const uint32_t same = d ? (uint32_t(__clzll((long long)d)) - (64 - 2 * h0)) >> 1 : h0;
     return same < l ? same : l;
 }
@@ -185,14 +220,15 @@ __device__ __forceinline__ uint32_t key_lcp(uint64_t a, uint64_t b, uint32_t lo_
 // the suffixes still in groups, as k_rank_update does for a doubling round.  MIXED: runs of
 // more than kFrRun items are in order of the whole key already; otherwise such a run sets
 // state[kStLongRun], after which the tiles give up (the host sees the flag and starts over).
-// A tile loads kFrRun items of context on either side, so every run of at most kFrRun items
-// that meets it, or meets the item after it, lies in the loaded span, and both tiles that share
-// a run sort it alike.
+// A tile finishes the runs that start among its kFrTile items; kFrRun items more are loaded, so
+// they lie in the loaded span as a whole, and of the kFrRun items before it the starts.  In a
+// long run the groups equal on the whole key take the runs' part, and single items where those
+// are long too.
 // LCP: also writes lcp[i] of every suffix told apart from its predecessor here (the keys and
 // windows compared hold their common prefix); for the others, which leave in groups, the
 // negative of one more than the symbols they are known to share.
 template <bool MIXED, bool LCP>
-__global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
+__global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V,
     const uint32_t *__restrict__ packed, uint32_t n, uint32_t lo_bit, uint32_t key_bits,
     uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
@@ -202,12 +238,14 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
     __shared__ uint64_t s_c[kFrSpan + 4];        // (rest of key, item); second words
     __shared__ uint32_t s_v[kFrSpan];            // text positions, in order
     __shared__ uint16_t s_reach[kFrSpan];        // symbols before the separator (511: or more)
-    __shared__ uint16_t s_list[kFrSpan];         // places of the items in groups
+    __shared__ uint16_t s_list[kFrSpan];         // places of the items in groups; s_at
     __shared__ int16_t s_l[LCP ? kFrSpan : 1];   // lcp entries
-    __shared__ uint16_t s_at[LCP ? kFrSpan : 1]; // where a sorted item's words lie
+    uint16_t *const s_at = s_list;               // where a sorted item's words lie
     __shared__ uint32_t s_cnt[kFrRows];
-    __shared__ uint64_t s_m0[kFrRows];    // starts of runs
-    __shared__ uint64_t s_m[kFrRows];     // starts of groups
+    __shared__ uint64_t s_m0w[kFrReach + kFrRows], s_mw[kFrReach + kFrRows];
+    uint64_t *const s_m0 = s_m0w + kFrReach;     // starts of runs
+    uint64_t *const s_m = s_mw + kFrReach;       // starts of groups
+    __shared__ uint64_t s_u[MIXED ? kFrRows : 1];  // starts of what a tile takes as a whole
     __shared__ uint64_t s_row[kFrRows];   // (count, last start) before each row
     __shared__ uint32_t s_tile, s_quit;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
@@ -223,7 +261,7 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         if (tid == 0) st_agent(lbflags + tile, kLb64Inc);
         return;
     }
-    const int64_t lo = int64_t(tile) * kFrTile - kFrRun;
+    const int64_t lo = int64_t(tile) * kFrTile;
     const uint64_t kmask = (uint64_t(1) << key_bits) - 1;  // key_bits <= kKeyLenShift
     uint64_t k[kFrItems];
     uint32_t v[kFrItems];
@@ -241,6 +279,21 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         const int x = j * kFrBlock + tid;
         s_k[x] = k[j];
         s_c[x] = ((k[j] & rest) << 32) | uint32_t(x);
+    }
+    // the rows before the span: their starts (in a long run, in order, also of its groups)
+    if (wave < uint32_t(kFrReach)) {
+        const int64_t gi = lo - kFrRun + int64_t(tid);
+        bool h = gi <= 0, g = gi <= 0;
+        if (!h) {
+            const uint64_t a = K[gi], d = (a ^ K[gi - 1]) & kmask;
+            h = d >> lo_bit || (a & 31u) < uint64_t(top_d);
+            g = d != 0 || (a & 31u) < uint64_t(h0);
+        }
+        const uint64_t mh = ballot(h), mg = ballot(g);
+        if (lane == 0) {
+            s_m0w[wave] = mh;
+            s_mw[wave] = mg;
+        }
     }
     __syncthreads();
     // starts of runs (positions outside the array count as runs of their own, and so does a
@@ -267,8 +320,8 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         int st, en;
         pos[j] = x;
         if (run_bounds(s_m0, x, &st, &en)) {
-            if (en - st > 1) pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
-        } else if (!MIXED && x >= kFrRun && x < kFrRun + kFrTile) {
+            if (st >= 0 && en - st > 1) pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
+        } else if (!MIXED && x < kFrTile) {
             s_quit = 1;
         }
     }
@@ -287,6 +340,14 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         s_reach[pos[j]] = uint16_t(k[j] >> kKeyLenShift);
     }
     __syncthreads();
+    if (LCP) {  // the keys' codes, for the common prefixes of neighbours
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            const int x = j * kFrBlock + tid;
+            s_c[x] = key_codes(s_k[x], lo_bit, top_d, h0, err);
+        }
+        __syncthreads();
+    }
     // starts of groups equal on the whole key; a key of fewer than h0 symbols is a suffix that
     // ended at its separator, alone in its group
 #pragma unroll
@@ -295,19 +356,44 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         const int64_t gi = lo + x;
         const uint64_t key = s_k[x];
         bool h = gi <= 0 || gi >= int64_t(n);
-        if (!h && x > 0) h = ((key ^ s_k[x - 1]) & kmask) != 0 || (key & 31u) < uint64_t(h0);
+        const bool first = h;
+        // before the span: the last item of another run, which differs in its top bits whatever
+        // its order, or one of the same long run, in order
+        const uint64_t prev = first ? 0 : x > 0 ? s_k[x - 1] : K[gi - 1];
+        if (!first) h = ((key ^ prev) & kmask) != 0 || (key & 31u) < uint64_t(h0);
         if (LCP) {
             int l = -1 - int(h0);
-            if (h) l = gi <= 0 || x == 0 ? 0 : int(key_lcp(s_k[x - 1], key, lo_bit, top_d, h0, err));
+            if (h && !first) {
+                const uint64_t before = x > 0 ? s_c[x - 1] : key_codes(prev, lo_bit, top_d, h0, err);
+                l = int(key_lcp(before, s_c[x], uint32_t(prev), uint32_t(key), h0));
+            }
+            if (first) l = 0;
             s_l[x] = int16_t(l);
         }
         const uint64_t m = ballot(h);
         if (lane == 0) s_m[x >> 6] = m;
     }
     __syncthreads();
-    // Groups that meet the tile or the item after it are told apart by the text: windows of two
-    // stages, kExtStage bases each, while there are such groups.  Each window starts by listing
-    // their items, so that a window few items need takes few waves.
+    // the tile's own items: from the first start of a unit on, up to the first after its kFrTile
+    const uint64_t *unit = s_m0;
+    if (MIXED) {
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            const int x = j * kFrBlock + tid;
+            int st, en, gs, ge;
+            bool u = (s_m0[x >> 6] >> (x & 63)) & 1u;
+            if (!u && !run_bounds(s_m0, x, &st, &en) && st < kFrTile)
+                u = ((s_m[x >> 6] >> (x & 63)) & 1u) || !run_bounds(s_m, x, &gs, &ge);
+            const uint64_t m = ballot(u);
+            if (lane == 0) s_u[x >> 6] = m;
+        }
+        __syncthreads();
+        unit = s_u;
+    }
+    const int own0 = first_start(unit, 0), own1 = first_start(unit, kFrTile);
+    // Groups of the tile are told apart by the text: windows of two stages, kExtStage bases
+    // each, while there are such groups.  Each window starts by listing their items, so that a
+    // window few items need takes few waves.
     uint32_t *const s_m32 = reinterpret_cast<uint32_t *>(s_m);
 #pragma unroll 1
     for (int w = 0; w < kExtWindows; ++w) {
@@ -320,8 +406,8 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
             const int x = j * kFrBlock + int(id);
             int st, en;
             const bool small = run_bounds(s_m, x, &st, &en);
-            if (!small && x >= kFrRun && x < kFrRun + kFrTile) state[kStNoExt] = 1u;
-            in[j] = ballot(small && en - st > 1 && st <= kFrRun + kFrTile && en > kFrRun);
+            if (MIXED && !small && x >= own0 && x < own1) state[kStNoExt] = 1u;
+            in[j] = ballot(small && en - st > 1 && st >= own0 && st < own1);
             if (lane == 0) s_cnt[x >> 6] = uint32_t(popc64(in[j]));
         }
         __syncthreads();
@@ -379,45 +465,39 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
                 }
             }
             __syncthreads();
-            uint32_t to[kFrItems];  // its place after the stage; top bit: a group's first
+            uint32_t to[kFrItems];  // its place after the stage
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
                 if (at[j] == kFrNone || !grp[j]) continue;
                 const uint32_t x = at[j] & 0xffffu;
                 const int st = int(grp[j] & 0xffffu), en = int(grp[j] >> 16);
-                const uint64_t c0 = s_k[x], c1 = s_c[x];
-                bool twin;
-                to[j] = uint32_t(st + count_below2(s_k, s_c, st, en, c0, c1, &twin));
-                if (LCP) s_at[to[j]] = uint16_t(x);
-                if (!twin || (uint32_t(c1 >> 7) & 63u) < uint32_t(kExtStage)) to[j] |= kDone;
+                to[j] = uint32_t(st + count_below2(s_k, s_c, st, en, s_k[x], s_c[x]));
+                s_at[to[j]] = uint16_t(x);
             }
-            if (LCP) {
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < kFrItems; ++j) {
-                    if (at[j] == kFrNone || !grp[j]) continue;
-                    const uint32_t y = to[j] & kRankMask;
-                    if (y == (grp[j] & 0xffffu)) continue;  // a group's first keeps its entry
-                    int l = -1 - int(depth) - (stage + 1) * kExtStage;
-                    if (to[j] & kDone) {
-                        const uint32_t x = at[j] & 0xffffu, z = s_at[y - 1];
-                        const uint64_t c1 = s_c[x], e1 = s_c[z], x0 = s_k[x] ^ s_k[z], x1 = (c1 ^ e1) >> 14;
-                        const uint32_t same = x0   ? uint32_t(__clzll((long long)x0)) >> 1
-                                              : x1 ? 32u + ((uint32_t(__clzll((long long)x1)) - 14u) >> 1)
-                                                   : uint32_t(kExtStage);
-                        const uint32_t la = uint32_t(c1 >> 7) & 63u, lb = uint32_t(e1 >> 7) & 63u;
-                        const uint32_t most = la < lb ? la : lb;
-                        l = int(depth) + stage * kExtStage + int(same < most ? same : most);
-                    }
-                    s_l[y] = int16_t(l);
-                }
-            }
+            __syncthreads();
+            // an item starts a group when its symbols are not its predecessor's, or when they
+            // end with a separator (every such suffix is alone)
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
                 if (at[j] == kFrNone || !grp[j]) continue;
-                const uint32_t y = to[j] & kRankMask;
+                const uint32_t x = at[j] & 0xffffu, y = to[j];
                 at[j] = (at[j] & 0xffff0000u) | y;
-                if (to[j] & kDone) atomicOr(&s_m32[y >> 5], 1u << (y & 31));
+                if (y == (grp[j] & 0xffffu)) continue;  // a group's first: known
+                const uint32_t z = s_at[y - 1];
+                const uint64_t c1 = s_c[x], e1 = s_c[z];
+                const uint64_t x0 = s_k[x] ^ s_k[z], x1 = (c1 ^ e1) >> 7;
+                const uint32_t lb = uint32_t(c1 >> 7) & 63u;
+                const bool head = x0 != 0 || x1 != 0 || lb < uint32_t(kExtStage);
+                if (head) atomicOr(&s_m32[y >> 5], 1u << (y & 31));
+                if (LCP) {
+                    // equal words: all the stage's symbols, or those before the separator
+                    const uint32_t same = x0        ? uint32_t(__clzll((long long)x0)) >> 1
+                                          : x1 >> 7 ? 32u + ((uint32_t(__clzll((long long)x1)) - 7u) >> 1)
+                                                    : uint32_t(kExtStage);
+                    const uint32_t la = uint32_t(e1 >> 7) & 63u, most = la < lb ? la : lb;
+                    s_l[y] = int16_t(head ? int(depth) + stage * kExtStage + int(same < most ? same : most)
+                                          : -1 - int(depth) - (stage + 1) * kExtStage);
+                }
             }
             __syncthreads();
             if (stage == 1) continue;
@@ -446,63 +526,68 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
         __syncthreads();
     }
     __syncthreads();
-    // Wave 0: per row of 64, the suffixes still in groups (not both they and the next item
-    // start one) and the last start, scanned over the tile's rows and then over tiles.  The
+    // Wave 0: per row of 64, the tile's suffixes still in groups (not both they and the next
+    // item start one) and the last start, scanned over the rows and then over tiles.  The
     // other waves meanwhile write the ranks and the final suffixes, which need only the
     // starts at hand (unless a long group began before them).
+    const auto own_row = [&](int r) {  // the tile's own items of row r that are in the array
+        int64_t a = own0 - r * 64, b = own1 - r * 64;
+        if (int64_t(n) - lo - r * 64 < b) b = int64_t(n) - lo - r * 64;
+        if (a < 0) a = 0;
+        if (b > 64) b = 64;
+        if (a >= b) return uint64_t(0);
+        const uint64_t to = b == 64 ? ~uint64_t(0) : ((uint64_t(1) << b) - 1);
+        return to & ~((uint64_t(1) << a) - 1);
+    };
+    const auto singles = [&](int r) {  // items alone in their group
+        const uint64_t m = s_m[r];
+        return m & ((m >> 1) | (r + 1 < kFrRows ? s_m[r + 1] << 63 : 0));
+    };
     if (wave == 0) {
         uint64_t mine = 0;
-        const int r = kFrRow0 + int(lane);
-        if (r < kFrRow1) {
-            const int64_t g = lo + r * 64;
-            const uint64_t m = s_m[r];
-            const uint64_t nxt = (m >> 1) | (s_m[r + 1] << 63);
-            const int64_t left = int64_t(n) - g;
-            const uint64_t in = left >= 64 ? ~uint64_t(0) : left <= 0 ? 0 : ((uint64_t(1) << left) - 1);
-            const uint64_t hm = m & in;
-            const uint32_t last = hm ? uint32_t(g) + 64u - uint32_t(__clzll((long long)hm)) : 0u;
-            mine = (uint64_t(popc64(~(m & nxt) & in)) << 31) | last;
+        const int r = int(lane);
+        if (r < kFrRows) {
+            const uint64_t in = own_row(r), hm = s_m[r] & in;
+            const uint32_t last = hm ? uint32_t(lo + r * 64) + 64u - uint32_t(__clzll((long long)hm)) : 0u;
+            mine = (uint64_t(popc64(~singles(r) & in)) << 31) | last;
         }
         const uint64_t inc = wave_incl_scan<CountLastOp>(mine);
         uint64_t ex = __shfl_up(inc, 1);
         if (lane == 0) ex = 0;
         const uint64_t agg = __shfl(inc, kWave - 1);
         const uint64_t before = lookback_tile<CountLastOp>(lbflags, int(tile), agg, err);
-        if (r < kFrRow1) s_row[r] = CountLastOp::combine(before, ex);
+        if (r < kFrRows) s_row[r] = CountLastOp::combine(before, ex);
         if (lane == 0 && tile == ntiles - 1)
             state[kStNext] = uint32_t(CountLastOp::combine(before, agg) >> 31);
     } else {
-        for (int r = kFrRow0 + int(wave) - 1; r < kFrRow1; r += kFrWaves - 1) {
-            const int64_t gi = lo + r * 64 + lane;
-            if (gi >= int64_t(n)) break;
-            const uint32_t p = s_v[r * 64 + lane];
-            const int st_x = run_start(s_m, r * 64 + int(lane));
-            if (p >= n || st_x < 0 || lo + st_x < 0) continue;  // see below
-            rank[p] = uint32_t(lo + st_x);
-            const uint64_t m = s_m[r];
-            const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63));
-            if ((single >> lane) & 1u) sa[gi] = int32_t(p);
+        for (int r = int(wave) - 1; r < kFrRows; r += kFrWaves - 1) {
+            if (!((own_row(r) >> lane) & 1u)) continue;
+            const int x = r * 64 + int(lane);
+            const uint32_t p = s_v[x];
+            const int st = run_start(s_m, x);
+            if (p >= n || st < own0) continue;  // see below
+            rank[p] = uint32_t(lo + st);
+            if ((singles(r) >> lane) & 1u) sa[lo + x] = int32_t(p);
         }
     }
     __syncthreads();
-    for (int r = kFrRow0 + int(wave); r < kFrRow1; r += kFrWaves) {
-        const int64_t gi = lo + r * 64 + lane;
-        if (gi >= int64_t(n)) break;
-        const uint32_t i = uint32_t(gi);
-        if (LCP) lcp[i] = s_l[r * 64 + lane];
-        const uint64_t m = s_m[r];
-        const uint64_t single = m & ((m >> 1) | (s_m[r + 1] << 63)), bit = uint64_t(1) << lane;
-        const uint32_t p = s_v[r * 64 + lane];
+    for (int r = int(wave); r < kFrRows; r += kFrWaves) {
+        const uint64_t in = own_row(r), bit = uint64_t(1) << lane;
+        if (!(in & bit)) continue;
+        const int x = r * 64 + int(lane);
+        const uint32_t i = uint32_t(lo + x);
+        if (LCP) lcp[i] = s_l[x];
+        const uint32_t p = s_v[x];
         if (p >= n) {  // inconsistent input: report only
             raise_err(err, kErrRange);
             continue;
         }
-        if (single & bit) continue;
-        // the last start at or before i: within reach of the loaded span, else from the rows
-        // and tiles before
-        const int st_x = run_start(s_m, r * 64 + int(lane));
-        uint32_t g = uint32_t(lo + st_x);
-        if (st_x < 0 || lo + st_x < 0) {
+        const uint64_t many = ~singles(r) & in;
+        if (!(many & bit)) continue;
+        // the last start at or before i: one of the tile's, else from the rows and tiles before
+        const int st = run_start(s_m, x);
+        uint32_t g = uint32_t(lo + st);
+        if (st < own0) {
             g = uint32_t(s_row[r] & CountLastOp::kLastMask) - 1u;
             if (!MIXED || g > i) {
                 if (MIXED) raise_err(err, kErrRange);
@@ -510,13 +595,13 @@ __global__ __launch_bounds__(kFrBlock, 8) void k_first_runs(
             }
             rank[p] = g;
         }
-        const uint32_t o = uint32_t(s_row[r] >> 31) + uint32_t(popc64(~single & (bit - 1)));
+        const uint32_t o = uint32_t(s_row[r] >> 31) + uint32_t(popc64(many & (bit - 1)));
         if (o >= n) {
             raise_err(err, kErrRange);
             continue;
         }
         S_new[o] = i;
-        P_new[o] = p | (m & bit ? kDone : 0u);
+        P_new[o] = p | (s_m[r] & bit ? kDone : 0u);
         if (i - g == uint32_t(kRunMax)) state[kStBigNext] = 1u;
     }
 }

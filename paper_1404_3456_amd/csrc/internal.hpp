@@ -204,7 +204,7 @@ constexpr int kExtStage = 57;             // bases one comparison of the extensi
 constexpr int kExtWindows = 4;            // windows of two stages each
 constexpr int kExtBases = 2 * kExtStage * kExtWindows;
 static_assert(kH0 + kExtBases <= int(kKeyLenMax), "the extension needs exact distances");
-constexpr int kFirstMinTile = 1792;
+constexpr int kFirstMinTile = 1408;
 int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
                       int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
                       uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp_or_null,

@@ -11,7 +11,7 @@ from paper_1404_3456_amd import synth
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-TILE = 1792      # items a tile of the run sort finishes
+TILE = 1408      # items a tile of the run sort finishes
 LIMIT = 128      # longest run it sorts
 MIN_N = 16384    # shorter texts sort whole keys by passes
 
@@ -83,7 +83,7 @@ def test_long_runs(lib, kind, digit_bits):
 @pytest.mark.parametrize("use_graph", [False, True])
 @pytest.mark.parametrize("kind", ["plain", "repeats"])
 def test_batches(lib, use_graph, kind):
-    texts = [reads_of_size(9100 + k, n) for k, n in enumerate([40, 17_000, 5, 1792, 60_001, 3000])]
+    texts = [reads_of_size(9100 + k, n) for k, n in enumerate([40, 17_000, 5, TILE, 60_001, 3000])]
     if kind == "repeats":
         texts.append(synth.text_from_strings(["ACGT" * 100] * 60 + ["C" * 300] * 3))
     off = np.concatenate([[0], np.cumsum([t.size for t in texts])]).astype(np.int64)
