@@ -26,6 +26,7 @@ int resolve_tuning(const sa_tuning *tu, Tune *out) {
         if (tu->items_per_thread) t.items = tu->items_per_thread;
         if (tu->seg_pack != 0) return fail(SA_ERR_INVALID, "seg_pack must be 0 for this call");
         if (!tu->block_threads && t.dbits > 9) t.block = 512;  // the widest tile needs <= 9 bits
+        t.fixed = tu->block_threads || tu->items_per_thread;
     }
     if (t.dbits != 4 && t.dbits != 8 && t.dbits != 9 && t.dbits != 11)
         return fail(SA_ERR_INVALID, "digit_bits must be 4, 8, 9 or 11");

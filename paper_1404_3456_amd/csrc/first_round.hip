@@ -23,21 +23,25 @@
 namespace saasm {
 
 constexpr int kFrRun = 128;                      // longest run sorted in LDS
-constexpr int kFrBlock = 256;
-constexpr int kFrItems = 6;
-constexpr int kFrSpan = kFrBlock * kFrItems;     // items loaded per tile
-constexpr int kFrTile = kFrSpan - kFrRun;        // items whose runs a tile finishes
-constexpr int kFrRows = kFrSpan / kWave;
 constexpr uint32_t kFrNone = 0xffffffffu;        // no item
-constexpr int kFrWaves = kFrBlock / kWave;
 constexpr int kFrReach = kFrRun / kWave;         // words of a mask a run can reach into
 constexpr int kFrNowhere = -2 * kFrRun;          // no start, no end
 static_assert(kFrRun % kWave == 0 && kFrRun <= 128, "7 bits tell the members of a group apart");
-static_assert(kFrTile % kWave == 0 && kFrRows <= kWave, "rows of the scan");
-static_assert(kFrTile >= kFirstMinTile, "look-back words are sized for tiles of kFirstMinTile items");
+
+// The shape of a workgroup and its tile.
+template <int BLOCK, int ITEMS, int WAVES_PER_SIMD>
+struct FrShape {
+    static constexpr int kBlock = BLOCK, kItems = ITEMS, kOcc = WAVES_PER_SIMD;
+    static constexpr int kSpan = BLOCK * ITEMS;      // items loaded per tile
+    static constexpr int kTile = kSpan - kFrRun;     // items whose runs a tile finishes
+    static constexpr int kRows = kSpan / kWave;
+    static constexpr int kWaves = BLOCK / kWave;
+    static_assert(kTile % kWave == 0 && kRows <= kWave, "rows of the scan");
+    static_assert(kTile >= kFirstMinTile, "look-back words are sized for tiles of kFirstMinTile items");
+};
 
 // First item of the run that holds item x, from a mask of run starts (bit x % 64 of word
-// x / 64; kFrReach words before word 0 are there too): the nearest start at or before x, sought
+// x / 64 of `rows`; kFrReach words before word 0 are there too): the nearest start at or before x, sought
 // kFrReach words back; kFrNowhere if there is none.
 __device__ __forceinline__ int run_start(const uint64_t *m, int x) {
     const int w = x >> 6, b = x & 63;
@@ -53,12 +57,12 @@ __device__ __forceinline__ int run_start(const uint64_t *m, int x) {
 
 // First item after the run that holds item x: the next start, sought kFrReach words on;
 // kFrNowhere if there is none.
-__device__ __forceinline__ int run_end(const uint64_t *m, int x) {
+__device__ __forceinline__ int run_end(const uint64_t *m, int rows, int x) {
     const int w = x >> 6, b = x & 63;
     const uint64_t le = b == 63 ? ~uint64_t(0) : ((uint64_t(2) << b) - 1);
     uint64_t v = m[w] & ~le;
     int at = w;
-    for (int k = 1; k <= kFrReach && !v && w + k < kFrRows; ++k) {
+    for (int k = 1; k <= kFrReach && !v && w + k < rows; ++k) {
         v = m[w + k];
         at = w + k;
     }
@@ -66,19 +70,19 @@ __device__ __forceinline__ int run_end(const uint64_t *m, int x) {
 }
 
 // Bounds of the run of item x; whether it is known to have at most kFrRun items.
-__device__ __forceinline__ bool run_bounds(const uint64_t *m, int x, int *st, int *en) {
+__device__ __forceinline__ bool run_bounds(const uint64_t *m, int rows, int x, int *st, int *en) {
     *st = run_start(m, x);
-    *en = run_end(m, x);
+    *en = run_end(m, rows, x);
     return *st != kFrNowhere && *en != kFrNowhere && *en - *st <= kFrRun;
 }
 
-// The first start at or after item x (word-aligned) within the span.
-__device__ __forceinline__ int first_start(const uint64_t *m, int x) {
-    for (int w = x >> 6; w < kFrRows; ++w) {
+// The first start at or after item x (word-aligned) of the span; the span's size if none.
+__device__ __forceinline__ int first_start(const uint64_t *m, int rows, int x) {
+    for (int w = x >> 6; w < rows; ++w) {
         const uint64_t v = m[w];
         if (v) return w * 64 + int(__ffsll((long long)v)) - 1;
     }
-    return kFrSpan;
+    return rows * 64;
 }
 
 // 128 bases of the packed text from position a on (base 0 in the top bits of b[0]).
@@ -215,6 +219,10 @@ __device__ __forceinline__ uint32_t key_lcp(uint64_t ca, uint64_t cb, uint32_t a
     return same < l ? same : l;
 }
 
+using FrLarge = FrShape<256, 6, 3>;
+using FrSmall = FrShape<512, 2, 4>;
+constexpr int64_t kFrFewItems = int64_t(1) << 21;
+
 // One tile of the order by the keys' top bits (bits lo_bit and up): sorts its runs, labels its
 // groups and writes rank[], the final sa[] entries and the compacted slots and positions of
 // the suffixes still in groups, as k_rank_update does for a doubling round.  MIXED: runs of
@@ -227,13 +235,15 @@ __device__ __forceinline__ uint32_t key_lcp(uint64_t ca, uint64_t cb, uint32_t a
 // LCP: also writes lcp[i] of every suffix told apart from its predecessor here (the keys and
 // windows compared hold their common prefix); for the others, which leave in groups, the
 // negative of one more than the symbols they are known to share.
-template <bool MIXED, bool LCP>
-__global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
+template <class Shape, bool MIXED, bool LCP>
+__global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V,
     const uint32_t *__restrict__ packed, uint32_t n, uint32_t lo_bit, uint32_t key_bits,
     uint32_t top_d, uint32_t h0, int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
     uint32_t *__restrict__ S_new, uint32_t *__restrict__ P_new, int32_t *__restrict__ lcp,
     uint64_t *lbflags, uint32_t *tick, uint32_t *state, uint32_t *err) {
+    constexpr int kFrBlock = Shape::kBlock, kFrItems = Shape::kItems, kFrSpan = Shape::kSpan;
+    constexpr int kFrTile = Shape::kTile, kFrRows = Shape::kRows, kFrWaves = Shape::kWaves;
     __shared__ uint64_t s_k[kFrSpan + 4];        // keys; first words of the extension keys
     __shared__ uint64_t s_c[kFrSpan + 4];        // (rest of key, item); second words
     __shared__ uint32_t s_v[kFrSpan];            // text positions, in order
@@ -319,7 +329,7 @@ __global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
         const int x = j * kFrBlock + tid;
         int st, en;
         pos[j] = x;
-        if (run_bounds(s_m0, x, &st, &en)) {
+        if (run_bounds(s_m0, kFrRows, x, &st, &en)) {
             if (st >= 0 && en - st > 1) pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
         } else if (!MIXED && x < kFrTile) {
             s_quit = 1;
@@ -382,15 +392,15 @@ __global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
             const int x = j * kFrBlock + tid;
             int st, en, gs, ge;
             bool u = (s_m0[x >> 6] >> (x & 63)) & 1u;
-            if (!u && !run_bounds(s_m0, x, &st, &en) && st < kFrTile)
-                u = ((s_m[x >> 6] >> (x & 63)) & 1u) || !run_bounds(s_m, x, &gs, &ge);
+            if (!u && !run_bounds(s_m0, kFrRows, x, &st, &en) && st < kFrTile)
+                u = ((s_m[x >> 6] >> (x & 63)) & 1u) || !run_bounds(s_m, kFrRows, x, &gs, &ge);
             const uint64_t m = ballot(u);
             if (lane == 0) s_u[x >> 6] = m;
         }
         __syncthreads();
         unit = s_u;
     }
-    const int own0 = first_start(unit, 0), own1 = first_start(unit, kFrTile);
+    const int own0 = first_start(unit, kFrRows, 0), own1 = first_start(unit, kFrRows, kFrTile);
     // Groups of the tile are told apart by the text: windows of two stages, kExtStage bases
     // each, while there are such groups.  Each window starts by listing their items, so that a
     // window few items need takes few waves.
@@ -405,7 +415,7 @@ __global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
         for (int j = 0; j < kFrItems; ++j) {
             const int x = j * kFrBlock + int(id);
             int st, en;
-            const bool small = run_bounds(s_m, x, &st, &en);
+            const bool small = run_bounds(s_m, kFrRows, x, &st, &en);
             if (MIXED && !small && x >= own0 && x < own1) state[kStNoExt] = 1u;
             in[j] = ballot(small && en - st > 1 && st >= own0 && st < own1);
             if (lane == 0) s_cnt[x >> 6] = uint32_t(popc64(in[j]));
@@ -437,7 +447,7 @@ __global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
             if (t >= total) continue;
             const uint32_t x = s_list[t];
             at[j] = x | (x << 16);
-            grp[j] = uint32_t(run_start(s_m, int(x))) | (uint32_t(run_end(s_m, int(x))) << 16);
+            grp[j] = uint32_t(run_start(s_m, int(x))) | (uint32_t(run_end(s_m, kFrRows, int(x))) << 16);
             uint32_t a = s_v[x] + depth;
             if (a >= n) {  // inconsistent input: report only
                 raise_err(err, kErrRange);
@@ -505,7 +515,7 @@ __global__ __launch_bounds__(kFrBlock, 3) void k_first_runs(
             for (int j = 0; j < kFrItems; ++j) {
                 if (at[j] == kFrNone) continue;
                 const int x = int(at[j] & 0xffffu);
-                const uint32_t st = uint32_t(run_start(s_m, x)), en = uint32_t(run_end(s_m, x));
+                const uint32_t st = uint32_t(run_start(s_m, x)), en = uint32_t(run_end(s_m, kFrRows, x));
                 grp[j] = en - st > 1 ? st | (en << 16) : 0u;  // 0: alone
             }
         }
@@ -702,26 +712,39 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
     for (int i = tid; i < passes * R; i += kFxBlock) dst[i] = s_h[i];
 }
 
-int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
-                      int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
-                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp,
-                      uint64_t *lbflags, int64_t lb_words, uint32_t *tick, uint32_t *state,
-                      hipStream_t s) {
-    const int64_t tiles = (n + kFrTile - 1) / kFrTile;
+template <class Shape>
+static int launch_first_runs_t(const uint64_t *K, const uint32_t *V, const uint32_t *packed,
+                               int64_t n, int lo_bit, int key_bits, int top_d, int h0, bool mixed,
+                               int32_t *sa, uint32_t *rank, uint32_t *S_new, uint32_t *P_new,
+                               int32_t *lcp, uint64_t *lbflags, int64_t lb_words, uint32_t *tick,
+                               uint32_t *state, hipStream_t s) {
+    const int64_t tiles = (n + Shape::kTile - 1) / Shape::kTile;
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
     SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
     SA_TRY(launch_fill_u32(tick, 1, 0, s));
     // per suffix: key 8 and position 4 read; rank 4, and sa 4 or slot and position 8, written;
     // 36 bytes of packed text per window of a suffix still in a group; lcp 4
     TimedScope ts("keyruns", double(n) * (lcp ? 28.0 : 24.0), s, double(n));
-    auto k = mixed ? (lcp ? k_first_runs<true, true> : k_first_runs<true, false>)
-                   : (lcp ? k_first_runs<false, true> : k_first_runs<false, false>);
-    hipLaunchKernelGGL(k, dim3(unsigned(tiles)), dim3(kFrBlock), 0, s, K, V, packed, uint32_t(n),
+    auto k = mixed ? (lcp ? k_first_runs<Shape, true, true> : k_first_runs<Shape, true, false>)
+                   : (lcp ? k_first_runs<Shape, false, true> : k_first_runs<Shape, false, false>);
+    hipLaunchKernelGGL(k, dim3(unsigned(tiles)), dim3(Shape::kBlock), 0, s, K, V, packed, uint32_t(n),
                        uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d), uint32_t(h0), sa, rank,
                        S_new, P_new, lcp, lbflags, tick, state, state + kStErr);
     ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;
+}
+
+int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
+                      int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
+                      uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp,
+                      uint64_t *lbflags, int64_t lb_words, uint32_t *tick, uint32_t *state,
+                      hipStream_t s) {
+    if (n <= kFrFewItems)
+        return launch_first_runs_t<FrSmall>(K, V, packed, n, lo_bit, key_bits, top_d, h0, mixed, sa, rank,
+                                            S_new, P_new, lcp, lbflags, lb_words, tick, state, s);
+    return launch_first_runs_t<FrLarge>(K, V, packed, n, lo_bit, key_bits, top_d, h0, mixed, sa, rank,
+                                        S_new, P_new, lcp, lbflags, lb_words, tick, state, s);
 }
 
 int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,

@@ -65,12 +65,28 @@ struct Carver {
 };
 
 // ---- tuning --------------------------------------------------------------------------------
+// The shape of a radix pass's workgroup.  Unless the caller fixed it, it depends on the items a
+// sort has: small tiles spread few items over the chip, large ones write longer digit runs and
+// look back less.  One 9-bit pass, 512 x 8 / 512 x 16 / 1024 x 16: 80 k items 12.5 / 15.8 /
+// 21.4 us, 565 k 18.1 / 19.4 / 23.3, 1.6 M 26.3 / 23.4 / 25.7, 3.2 M 38.7 / 32.5 / 28.9, 26 M
+// 243 / 202 / 185.
+constexpr int64_t kTuneSmallN = int64_t(1) << 20, kTuneMidN = int64_t(1) << 21;
 struct Tune {
     int dbits = 9;
     int block = 1024;  // 512 when digits are wider than 9 bits (resolve_tuning)
     int items = 16;
+    bool fixed = false;  // the caller's shape, for any number of items
     int tile() const { return block * items; }
     int radix() const { return 1 << dbits; }
+    Tune at(int64_t n) const {
+        Tune t = *this;
+        if (!fixed && n <= kTuneMidN) {
+            t.block = 512;
+            t.items = n <= kTuneSmallN ? 8 : 16;
+        }
+        t.fixed = true;
+        return t;
+    }
 };
 int resolve_tuning(const sa_tuning *t, Tune *out);
 
@@ -204,7 +220,7 @@ constexpr int kExtStage = 57;             // bases one comparison of the extensi
 constexpr int kExtWindows = 4;            // windows of two stages each
 constexpr int kExtBases = 2 * kExtStage * kExtWindows;
 static_assert(kH0 + kExtBases <= int(kKeyLenMax), "the extension needs exact distances");
-constexpr int kFirstMinTile = 1408;
+constexpr int kFirstMinTile = 896;
 int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *packed, int64_t n,
                       int lo_bit, int key_bits, int top_d, int h0, bool mixed, int32_t *sa,
                       uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp_or_null,

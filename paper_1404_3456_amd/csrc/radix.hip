@@ -29,7 +29,7 @@ namespace saasm {
 int sort_passes(int bits, const Tune &t) { return bits <= 0 ? 0 : (bits + t.dbits - 1) / t.dbits; }
 
 static int64_t sort_tiles(int64_t n, const Tune &t) {
-    int64_t tl = (n + t.tile() - 1) / t.tile();
+    const int64_t tile = t.at(n).tile(), tl = (n + tile - 1) / tile;
     return tl < 1 ? 1 : tl;
 }
 
@@ -47,7 +47,13 @@ void carve_sort(Carver &c, int64_t n, int bits, const Tune &t, SortBufs *b, bool
     }
     b->hist = c.take<uint32_t>(int64_t(kHistParts) * P * t.radix());
     b->gbase = c.take<uint32_t>(int64_t(P) * t.radix());
-    b->flags = c.take<uint32_t>(sort_flag_words(n, bits, t) > 0 ? sort_flag_words(n, bits, t) : 1);
+    // enough for a sort of any number of items up to n: fewer items can take smaller tiles
+    int64_t words = 1;
+    for (const int64_t m : {n, kTuneSmallN, kTuneMidN}) {
+        const int64_t w = m <= n ? sort_flag_words(m, bits, t) : 0;
+        words = w > words ? w : words;
+    }
+    b->flags = c.take<uint32_t>(words);
     b->tickets = c.take<uint32_t>(64);
 }
 
@@ -464,6 +470,7 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
     }
     SA_HIP(hipGetLastError());
     const int64_t tiles = sort_tiles(n, t);
+    const Tune shape = t.at(n);
     for (int p = 0; p < P; ++p) {
         const int lo = p * t.dbits;
         const int width = (bits - lo) < t.dbits ? (bits - lo) : t.dbits;
@@ -475,10 +482,10 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
         int rc = SA_OK;
         uint32_t *fl = b.flags + size_t(p) * tiles * R;
         switch (t.dbits) {
-            case 4: rc = launch_pass_d<4>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 8: rc = launch_pass_d<8>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 9: rc = launch_pass_d<9>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
-            case 11: rc = launch_pass_d<11>(t, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 4: rc = launch_pass_d<4>(shape, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 8: rc = launch_pass_d<8>(shape, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 9: rc = launch_pass_d<9>(shape, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
+            case 11: rc = launch_pass_d<11>(shape, n, s, b.keys[cur], vin, b.keys[cur ^ 1], b.vals[cur ^ 1], count_dev, uint32_t(n), shift, dmask, b.gbase + p * R, fl, b.tickets + p, b.err); break;
             default: rc = fail(SA_ERR_INVALID, "unsupported digit width");
         }
         ts.finish();

@@ -861,7 +861,9 @@ static int sa_build_batched_impl(const uint8_t *text, int64_t n, const int64_t *
     SA_TRY(resolve_batched(tune, &t, &pack));
     const int64_t need = sa_build_batched_ws_bytes(n, n_sets, set_off_h, tune);
     if (need < 0) return fail(SA_ERR_INVALID, "sa_build_batched: bad tuning");
-    sa_tuning inner{t.dbits, t.block, t.items, 0};
+    sa_tuning inner{};
+    if (tune) inner = *tune;
+    inner.seg_pack = 0;
     std::vector<int32_t> g = pack_groups(set_off_h, n_sets, pack);
     int32_t rounds_max = 0;
     for (size_t k = 0; k + 1 < g.size(); ++k) {
