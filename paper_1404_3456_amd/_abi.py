@@ -387,7 +387,7 @@ def sa_path(text, min_len: int, stream=None, ws=None):
         sa, isa_t, lcp = (torch.empty(n, dtype=torch.int32, device=t.device) for _ in range(3))
         _check(lib.sa_build(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(ws), ws.numel(), None, None, st))
         _check(lib.sa_lcp(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(lcp), _ptr(ws), ws.numel(), st))
-    cap = max(n // 64, 1024)
+    cap = _rows_guess(n)
     for _ in range(4):
         out = torch.empty((cap, 3), dtype=torch.int32, device=t.device)
         n_out = ctypes.c_int64(0)
@@ -545,14 +545,22 @@ def sa_lcp_plcp_min(min_n: int = -1) -> int:
 _ovl_ws_hint = {}
 
 
+def _rows_guess(n: int) -> int:
+    """Rows to make room for before their number is known (short reads at high coverage have
+    about one a dozen characters; too few only means a second call)."""
+    return max(n // 16, 1024)
+
+
 def sa_overlaps(text, sa, isa, lcp, min_len: int, stream=None):
     """(k, 3) int32 device tensor of rows (a, b, l), sorted by (a, b)."""
     torch = _torch()
     lib = load()
     t = _dev_text(text)
     n = t.numel()
-    need = max(_ovl_ws_hint.get(n, 0), sa_overlaps_ws_bytes(n, 1, 0))
-    cap = max(n // 64, 1024)
+    # room for reads of 32 characters and a candidate every 24: where that is too little, the
+    # call says what it needs, and a quarter more lets its first split of the space fit
+    need = max(_ovl_ws_hint.get(n, 0), sa_overlaps_ws_bytes(n, n // 32 + 1, n // 24 + 1024))
+    cap = _rows_guess(n)
     for _ in range(6):
         ws = _ws(need, t.device)
         out = torch.empty((cap, 3), dtype=torch.int32, device=t.device)
@@ -562,7 +570,7 @@ def sa_overlaps(text, sa, isa, lcp, min_len: int, stream=None):
                              cap, ctypes.byref(n_out), _ptr(ws), ws.numel(), ctypes.byref(needed),
                              _stream(stream))
         if rc == SA_ERR_NOMEM and needed.value > need:
-            need = int(needed.value)
+            need = int(needed.value) + int(needed.value) // 4
             _ovl_ws_hint[n] = need
             continue
         if rc == SA_ERR_CAPACITY and n_out.value > cap:

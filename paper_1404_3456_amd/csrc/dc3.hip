@@ -431,7 +431,6 @@ struct Dc3 {
 
     // Sorts items [0, count) already in sb.keys[cur]/vals[cur] over `bits` bits.
     int sort(int64_t count, int bits, int cur, int *cur_out) {
-        SA_TRY(sort_prepare(L.sb, count, bits, t, st));
         int nparts = 0;
         SA_TRY(launch_hist(L.sb, cur, count, 0, bits, t, st, &nparts));
         return sort_run(L.sb, cur, nullptr, count, 0, bits, t, nparts, st, cur_out);

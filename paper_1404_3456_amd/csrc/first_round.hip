@@ -631,9 +631,12 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V, uint32_t n, uint32_t lo_bit,
     uint32_t key_bits, uint32_t top_d, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, uint32_t *__restrict__ idx,
     int passes, uint32_t *__restrict__ hist, uint64_t *lbflags, uint32_t *tick, uint32_t *state,
-    uint32_t *err) {
+    uint32_t *err, uint32_t *clear, uint64_t nclear) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
+    // what the passes need cleared (a multiple of 4 words)
+    for (uint64_t i = blockIdx.x * kFxBlock + threadIdx.x; i < nclear / 4; i += gridDim.x * kFxBlock)
+        reinterpret_cast<uint4 *>(clear)[i] = make_uint4(0, 0, 0, 0);
     __shared__ uint64_t s_m[kFxRows + 4];  // starts per row, two rows of context on either side
     __shared__ uint64_t s_big[kFxRows];
     __shared__ uint32_t s_cnt[kFxRows];
@@ -720,8 +723,6 @@ static int launch_first_runs_t(const uint64_t *K, const uint32_t *V, const uint3
                                uint32_t *state, hipStream_t s) {
     const int64_t tiles = (n + Shape::kTile - 1) / Shape::kTile;
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
-    SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
-    SA_TRY(launch_fill_u32(tick, 1, 0, s));
     // per suffix: key 8 and position 4 read; rank 4, and sa 4 or slot and position 8, written;
     // 36 bytes of packed text per window of a suffix still in a group; lcp 4
     TimedScope ts("keyruns", double(n) * (lcp ? 28.0 : 24.0), s, double(n));
@@ -760,14 +761,15 @@ int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo
     SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
     SA_TRY(launch_fill_u32(tick, 1, 0, s));
     const size_t lds = size_t(P) * t.radix() * 4;
+    const uint64_t nclear = uint64_t(64 + sort_flag_words(n, key_bits, t));
     const uint32_t lb = uint32_t(lo_bit);
     // every key read; per item of a long run, its key, value and place written
     TimedScope ts("first_extract", double(n) * 8.0, s, double(n));
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_first_extract<4>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 8: hipLaunchKernelGGL(k_first_extract<8>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 9: hipLaunchKernelGGL(k_first_extract<9>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
-        case 11: hipLaunchKernelGGL(k_first_extract<11>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err); break;
+        case 4: hipLaunchKernelGGL(k_first_extract<4>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 8: hipLaunchKernelGGL(k_first_extract<8>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 9: hipLaunchKernelGGL(k_first_extract<9>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 11: hipLaunchKernelGGL(k_first_extract<11>, dim3(unsigned(grid)), dim3(kFxBlock), lds, s, K, V, uint32_t(n), lb, uint32_t(key_bits), uint32_t(top_d), b.keys[0], b.vals[0], idx, P, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();

@@ -166,19 +166,17 @@ struct SortBufs {
     uint32_t *vals[2];
     uint32_t *hist;     // [kHistParts][passes][radix] per-workgroup partial counts
     uint32_t *gbase;    // [passes][radix] exclusive bases
+    uint32_t *tickets;  // [passes]; cleared, with the flags, by the kernel that builds hist
     uint32_t *flags;    // [passes][tiles][radix] look-back words
-    uint32_t *tickets;  // [passes]
     uint32_t *err;
 };
 int sort_passes(int bits, const Tune &t);
 int64_t sort_flag_words(int64_t n, int bits, const Tune &t);
 void carve_sort(Carver &c, int64_t n, int bits, const Tune &t, SortBufs *b, bool with_items);
-// Clears histogram, flags and tickets for a sort of n items over `bits` bits.
-int sort_prepare(const SortBufs &b, int64_t n, int bits, const Tune &t, hipStream_t s);
 // Upper bound on the workgroups of a histogram-producing launch; each writes one partial
 // histogram (no global atomics) that the per-pass scan kernel reduces.
 constexpr int kHistParts = 1024;
-// Histogram of keys[cur] for all passes (when the producer did not build it); the number of
+// Histogram (and cleared tickets and flags) of keys[cur] for all passes (when the producer did not build it); the number of
 // partial histograms written goes to *nparts.
 int launch_hist(const SortBufs &b, int cur, int64_t n, int bit_lo, int bits, const Tune &t,
                 hipStream_t s, int *nparts);
@@ -206,6 +204,20 @@ constexpr int kStLcpLong = 12; // the LCP array needs Kasai's scan (launch_lcp_r
 constexpr int kStWords = 16;   // state words the host reads back
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
+// Pinned host words and events for reading device words without a full stream sync (one set
+// per host thread; two slots so one round's state can be in flight while the other is read,
+// and a third for read_words).
+struct PinnedState {
+    uint32_t *h = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    bool ok = false;
+    PinnedState();
+};
+PinnedState &pinned_state();
+// Copies kStWords device words to the host and waits for the stream: one copy to pinned memory
+// (a copy to pageable memory takes two more steps on the host).
+int read_words(const uint32_t *dev, uint32_t host[kStWords], hipStream_t s);
+
 // key builders (fused with the histogram of the sort that follows, over key bits
 // [lo_bit, key_bits)); a value is its item's index and is left to the first pass
 int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
@@ -213,7 +225,8 @@ int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int 
                 hipStream_t s, int *nparts);
 // First round (first_round.hip): from items ordered by key bits [lo_bit, key_bits), which tell
 // their first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the
-// items of runs too long for it, taken out.
+// items of runs too long for it, taken out.  The round's kernel needs its ticket and
+// look-back words (one per kFirstMinTile items) cleared.
 constexpr int kKeyLenShift = 55;          // a key's top 9 bits: distance to the separator, capped
 constexpr uint32_t kKeyLenMax = 511;
 constexpr int kExtStage = 57;             // bases one comparison of the extension takes

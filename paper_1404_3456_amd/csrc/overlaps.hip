@@ -15,8 +15,12 @@
 //   right walk: k = j+1, ...  while lcp[k] >= |b|; report (a, b, |b|) when suffix sa[k] has
 //               exactly |b| symbols before its separator and a != b.
 // A pair can be reported more than once (a read with periodic structure); the longest wins.
-// Candidates are counted, scanned, written as (a << 32 | b, l), sorted by a with the stable
-// radix sort (keeping b order within a), and reduced to one row per (a, b) with the largest l.
+// Candidates are written in order of b as (a << 32 | b, l), sorted by a with the stable radix
+// sort (keeping b order within a), and reduced to one row per (a, b) with the largest l.
+//
+// Each of these steps is one kernel whose prefix sums come from a look-back over its tiles
+// (separators to read ids and ends; candidates to their places; rows to theirs), so the host
+// waits twice: for the candidate count, which sizes the sort, and for the row count.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -29,119 +33,280 @@ __device__ __forceinline__ uint32_t read_of(const uint32_t *__restrict__ sepmask
     return uint32_t(sepcnt[w]) + __popc(before);
 }
 
-template <bool FILL>
-__global__ __launch_bounds__(256) void k_ovl_walk(
-    const int32_t *__restrict__ sa, const int32_t *__restrict__ isa,
-    const int32_t *__restrict__ lcp, const int32_t *__restrict__ read_end,
-    const uint32_t *__restrict__ sepmask, const int32_t *__restrict__ sepcnt, uint32_t n,
-    uint32_t m, int32_t min_len, uint32_t *__restrict__ counts, const int64_t *__restrict__ offs,
-    uint64_t *__restrict__ hkeys, uint32_t *__restrict__ hvals, uint32_t *err) {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= m) return;
-    const int32_t start = b == 0 ? 0 : read_end[b - 1] + 1;
-    const int32_t len = read_end[b] - start;
-    uint32_t c = 0;
-    int64_t o = FILL ? offs[b] : 0;
-    if (len >= min_len) {
-        const int32_t j = isa[start];
-        if (j < 0 || uint32_t(j) >= n) {
-            raise_err(err, kErrRange);
+// Device words of a call: error bits, lcp[0], reads, candidates and rows (64 bits each).
+constexpr int kOvErr = 0, kOvLcp0 = 1, kOvReads = 2, kOvHits = 4, kOvRows = 6;
+constexpr int kOvTick = 16;  // tickets of the three look-backs
+
+// Validates the text and finds its reads: separator bits and the separators before each word
+// of 32 positions, the read ends while they fit, and the read count.
+constexpr int kRdBlock = 256;
+constexpr int kRdTile = kRdBlock;  // words
+__global__ __launch_bounds__(kRdBlock) void k_ovl_reads(const uint8_t *__restrict__ text, int64_t n,
+                                                        const int32_t *__restrict__ lcp,
+                                                        uint32_t *__restrict__ sepmask,
+                                                        int32_t *__restrict__ sepcnt,
+                                                        int32_t *__restrict__ read_end,
+                                                        int64_t cap_reads, uint32_t nwords,
+                                                        uint64_t *lbflags, uint32_t *ctr) {
+    __shared__ uint32_t s_tile, s_excl;
+    __shared__ uint32_t s_w[kRdBlock / kWave];
+    if (threadIdx.x == 0) s_tile = ticket(ctr + kOvTick);
+    __syncthreads();
+    const uint32_t tile = s_tile, w = tile * uint32_t(kRdTile) + threadIdx.x;
+    const int64_t p0 = int64_t(w) * 32;
+    uint32_t sep = 0;
+    bool bad = false;
+    if (p0 < n) {
+        uint32_t c[8];  // four bytes each, position p0 in the low byte of the first
+        if (p0 + 32 <= n && (reinterpret_cast<uintptr_t>(text) & 15) == 0) {
+            const uint4 a = *reinterpret_cast<const uint4 *>(text + p0);
+            const uint4 b = *reinterpret_cast<const uint4 *>(text + p0 + 16);
+            c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w;
+            c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
         } else {
-            int32_t run = len;
-            for (int32_t k = j; k > 0; --k) {
-                const int32_t l = lcp[k];
-                run = l < run ? l : run;
-                if (run < min_len) break;
-                const uint32_t s = uint32_t(sa[k - 1]);
-                const uint32_t a = read_of(sepmask, sepcnt, s);
-                if (a >= m) { raise_err(err, kErrRange); break; }
-                if (read_end[a] - int32_t(s) == run && a != b) {
-                    if (FILL) {
-                        hkeys[o] = (uint64_t(a) << 32) | b;
-                        hvals[o] = uint32_t(run);
-                        ++o;
-                    }
-                    ++c;
-                }
-            }
-            for (uint32_t k = uint32_t(j) + 1; k < n && lcp[k] >= len; ++k) {
-                const uint32_t s = uint32_t(sa[k]);
-                const uint32_t a = read_of(sepmask, sepcnt, s);
-                if (a >= m) { raise_err(err, kErrRange); break; }
-                if (read_end[a] - int32_t(s) == len && a != b) {
-                    if (FILL) {
-                        hkeys[o] = (uint64_t(a) << 32) | b;
-                        hvals[o] = uint32_t(len);
-                        ++o;
-                    }
-                    ++c;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                c[j] = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t p = p0 + 4 * j + k;
+                    c[j] |= uint32_t(p < n ? text[p] : uint8_t('A')) << (8 * k);
                 }
             }
         }
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const uint32_t x = (c[j >> 2] >> (8 * (j & 3))) & 255u;
+            const bool is = x == '$';
+            bad |= !(is || x == 'A' || x == 'C' || x == 'G' || x == 'T');
+            sep |= uint32_t(is) << (31 - j);
+        }
+        if (p0 <= n - 1 && n - 1 < p0 + 32 && !((sep >> (31 - uint32_t(n - 1 - p0))) & 1u))
+            raise_err(ctr + kOvErr, kErrNoSepEnd);
     }
-    if (!FILL) counts[b] = c;
+    if (w < nwords) sepmask[w] = sep;
+    if (bad) raise_err(ctr + kOvErr, kErrAlphabet);
+    uint32_t total;
+    const uint32_t mine = block_excl_sum<kRdBlock>(uint32_t(__popc(sep)), s_w, &total);
+    if (threadIdx.x < kWave) {
+        const uint64_t ex = lookback_tile<SumOp>(lbflags, int(tile), total, ctr + kOvErr);
+        if (threadIdx.x == 0) s_excl = uint32_t(ex);
+    }
+    __syncthreads();
+    uint32_t k = s_excl + mine;
+    if (w < nwords) sepcnt[w] = int32_t(k);
+    while (sep) {
+        const int j = __clz(sep);  // bit 31-j <-> position 32w+j
+        if (int64_t(k) < cap_reads) read_end[k] = int32_t(p0 + j);
+        ++k;
+        sep &= ~(0x80000000u >> j);
+    }
+    if (threadIdx.x == 0 && (uint64_t(tile) + 1) * kRdTile >= nwords) {
+        ctr[kOvReads] = s_excl + total;
+        ctr[kOvLcp0] = uint32_t(lcp[0]);
+    }
 }
 
-// first[i] = 1 when row i starts a run of equal (a, b) keys
-__global__ __launch_bounds__(256) void k_run_heads(const uint64_t *__restrict__ keys, uint32_t r,
-                                                   uint32_t *__restrict__ first) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= r) return;
-    first[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1u : 0u;
+// The walks of a read's two sides; hit(a, l) for every suffix of another read a that equals
+// the first l symbols of read b.
+template <class F>
+__device__ __forceinline__ void walk_read(const int32_t *__restrict__ sa, const int32_t *__restrict__ isa,
+                                          const int32_t *__restrict__ lcp,
+                                          const int32_t *__restrict__ read_end,
+                                          const uint32_t *__restrict__ sepmask,
+                                          const int32_t *__restrict__ sepcnt, uint32_t n, uint32_t m,
+                                          int32_t min_len, uint32_t b, uint32_t *err, F hit) {
+    const int32_t start = b == 0 ? 0 : read_end[b - 1] + 1;
+    const int32_t len = read_end[b] - start;
+    if (len < min_len) return;
+    const int32_t j = isa[start];
+    if (j < 0 || uint32_t(j) >= n) {
+        raise_err(err, kErrRange);
+        return;
+    }
+    int32_t run = len;
+    for (int32_t k = j; k > 0; --k) {
+        const int32_t l = lcp[k];
+        run = l < run ? l : run;
+        if (run < min_len) break;
+        const uint32_t s = uint32_t(sa[k - 1]);
+        const uint32_t a = s < n ? read_of(sepmask, sepcnt, s) : m;
+        if (a >= m) {
+            raise_err(err, kErrRange);
+            break;
+        }
+        if (read_end[a] - int32_t(s) == run && a != b) hit(a, uint32_t(run));
+    }
+    for (uint32_t k = uint32_t(j) + 1; k < n && lcp[k] >= len; ++k) {
+        const uint32_t s = uint32_t(sa[k]);
+        const uint32_t a = s < n ? read_of(sepmask, sepcnt, s) : m;
+        if (a >= m) {
+            raise_err(err, kErrRange);
+            break;
+        }
+        if (read_end[a] - int32_t(s) == len && a != b) hit(a, uint32_t(len));
+    }
 }
 
-__global__ __launch_bounds__(256) void k_run_write(const uint64_t *__restrict__ keys,
-                                                   const uint32_t *__restrict__ vals, uint32_t r,
-                                                   const uint32_t *__restrict__ first,
-                                                   const int64_t *__restrict__ pos,
-                                                   int32_t *__restrict__ out) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= r || !first[i]) return;
-    const uint64_t k = keys[i];
-    uint32_t best = vals[i];
-    for (uint32_t j = i + 1; j < r && keys[j] == k; ++j) best = vals[j] > best ? vals[j] : best;
-    const int64_t o = pos[i];
-    out[3 * o] = int32_t(k >> 32);
-    out[3 * o + 1] = int32_t(k & 0xffffffffu);
-    out[3 * o + 2] = int32_t(best);
+// One read per thread, tiles by ticket (the read count is only on the device).  A thread keeps
+// its first kWkKeep matches in LDS while its tile's place is found; a read with more is walked
+// again.  Matches are written while they fit in cap_hits, the count always.  Nothing is walked
+// when the text or the LCP array is not valid.
+constexpr int kWkBlock = 256;
+constexpr int kWkKeep = 12;
+__global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
+    const int32_t *__restrict__ sa, const int32_t *__restrict__ isa,
+    const int32_t *__restrict__ lcp, const int32_t *__restrict__ read_end,
+    const uint32_t *__restrict__ sepmask, const int32_t *__restrict__ sepcnt, uint32_t n,
+    int64_t cap_reads, int32_t min_len, uint64_t *__restrict__ hkeys, uint32_t *__restrict__ hvals,
+    int64_t cap_hits, uint64_t *lbflags, uint32_t *ctr) {
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_excl;
+    __shared__ uint32_t s_w[kWkBlock / kWave];
+    __shared__ uint32_t s_a[kWkKeep][kWkBlock], s_l[kWkKeep][kWkBlock];
+    const uint32_t tid = threadIdx.x;
+    uint32_t *err = ctr + kOvErr;
+    const uint32_t reads = ctr[kOvReads];
+    // reads beyond the room for their ends are not walked: the host asks for more first
+    const bool valid = (ctr[kOvErr] & (kErrAlphabet | kErrNoSepEnd)) == 0 && ctr[kOvLcp0] == 0 &&
+                       int64_t(reads) <= cap_reads;
+    const uint32_t m = valid ? reads : 0u;
+    const uint32_t ntiles = (m + kWkBlock - 1) / kWkBlock;
+    while (true) {
+        __syncthreads();
+        if (tid == 0) s_tile = ticket(ctr + kOvTick + 1);
+        __syncthreads();
+        const uint32_t tile = s_tile;
+        if (tile >= ntiles) break;
+        const uint32_t b = tile * kWkBlock + tid;
+        uint32_t c = 0;
+        if (b < m)
+            walk_read(sa, isa, lcp, read_end, sepmask, sepcnt, n, m, min_len, b, err,
+                      [&](uint32_t a, uint32_t l) {
+                          if (c < uint32_t(kWkKeep)) {
+                              s_a[c][tid] = a;
+                              s_l[c][tid] = l;
+                          }
+                          ++c;
+                      });
+        uint32_t total;
+        const uint32_t mine = block_excl_sum<kWkBlock>(c, s_w, &total);
+        if (tid < kWave) {
+            const uint64_t ex = lookback_tile<SumOp>(lbflags, int(tile), total, err);
+            if (tid == 0) s_excl = ex;
+        }
+        __syncthreads();
+        uint64_t o = s_excl + mine;
+        if (tid == 0 && tile == ntiles - 1)
+            *reinterpret_cast<uint64_t *>(ctr + kOvHits) = s_excl + total;
+        if (c == 0 || o + c > uint64_t(cap_hits)) continue;
+        if (c <= uint32_t(kWkKeep)) {
+            for (uint32_t k = 0; k < c; ++k, ++o) {
+                hkeys[o] = (uint64_t(s_a[k][tid]) << 32) | b;
+                hvals[o] = s_l[k][tid];
+            }
+        } else {
+            walk_read(sa, isa, lcp, read_end, sepmask, sepcnt, n, m, min_len, b, err,
+                      [&](uint32_t a, uint32_t l) {
+                          hkeys[o] = (uint64_t(a) << 32) | b;
+                          hvals[o] = l;
+                          ++o;
+                      });
+        }
+    }
 }
 
+// Rows of the sorted candidates: one per run of equal (a, b) keys, with the longest length.
+constexpr int kRwBlock = 256;
+constexpr int kRwItems = 4;
+constexpr int kRwTile = kRwBlock * kRwItems;
+__global__ __launch_bounds__(kRwBlock) void k_ovl_rows(const uint64_t *__restrict__ keys,
+                                                       const uint32_t *__restrict__ vals, uint32_t r,
+                                                       int32_t *__restrict__ out, int64_t cap,
+                                                       uint64_t *lbflags, uint32_t *ctr) {
+    constexpr int W = kRwBlock / kWave;
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_excl;
+    __shared__ uint32_t s_cnt[kRwItems * W];
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    if (tid == 0) s_tile = ticket(ctr + kOvTick + 2);
+    __syncthreads();
+    const uint32_t tile = s_tile, base = tile * uint32_t(kRwTile);
+    uint64_t key[kRwItems], heads[kRwItems];
+#pragma unroll
+    for (int j = 0; j < kRwItems; ++j) {
+        const uint32_t i = base + j * kRwBlock + tid;
+        key[j] = i < r ? keys[i] : 0;
+        heads[j] = ballot(i < r && (i == 0 || keys[i - 1] != key[j]));
+        if (lane == 0) s_cnt[j * W + wave] = uint32_t(popc64(heads[j]));
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t c = lane < uint32_t(kRwItems * W) ? s_cnt[lane] : 0u;
+        const uint32_t inc = wave_incl_scan<Sum32>(c);
+        const uint64_t ex = lookback_tile<SumOp>(lbflags, int(tile), __shfl(inc, kWave - 1), ctr + kOvErr);
+        if (lane < uint32_t(kRwItems * W)) s_cnt[lane] = inc - c;
+        if (lane == 0) s_excl = ex;
+        if (lane == kWave - 1 && (uint64_t(tile) + 1) * kRwTile >= r)
+            *reinterpret_cast<uint64_t *>(ctr + kOvRows) = ex + inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRwItems; ++j) {
+        if (!((heads[j] >> lane) & 1u)) continue;
+        const uint32_t i = base + j * kRwBlock + tid;
+        const uint64_t o = s_excl + s_cnt[j * W + wave] + uint32_t(popc64(heads[j] & lanemask_lt()));
+        if (o >= uint64_t(cap)) continue;
+        uint32_t best = vals[i];
+        for (uint32_t y = i + 1; y < r && keys[y] == key[j]; ++y) best = vals[y] > best ? vals[y] : best;
+        out[3 * o] = int32_t(key[j] >> 32);
+        out[3 * o + 1] = int32_t(key[j] & 0xffffffffu);
+        out[3 * o + 2] = int32_t(best);
+    }
+}
+
+// Clears a call's words, with the active launch's look-back words.
+__global__ __launch_bounds__(256) void k_ovl_init(uint32_t *ctr, uint64_t *lb0, uint32_t n0,
+                                                  uint64_t *lb1, uint32_t n1) {
+    const uint32_t stride = gridDim.x * 256u;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n0; i += stride) lb0[i] = 0;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n1; i += stride) lb1[i] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 64) ctr[threadIdx.x] = 0;
+}
+
+// Text-sized part, read-sized part, candidates.
 struct OvlFixed {
-    uint32_t *sepmask, *wordcnt;
-    int32_t *sepcnt, *read_end;
-    uint32_t *counts;
-    int64_t *offs;
-    uint64_t *lbflags;
-    uint32_t *tick;
-    uint32_t *ctr;  // [0] err; [2..3] m (int32 at ctr+2); int64 totals at ctr+8, ctr+10
+    uint32_t *ctr, *sepmask;
+    int32_t *sepcnt;
+    uint64_t *lb_reads;
 };
-
-// Text-sized part (separator rank structure) then read-sized part (m reads).
-static void carve_fixed(Carver &c, int64_t n, int64_t m, OvlFixed *F) {
-    F->sepmask = c.take<uint32_t>(sepmask_words(n));
-    F->wordcnt = c.take<uint32_t>(sepmask_words(n));
-    F->sepcnt = c.take<int32_t>(sepmask_words(n));
-    F->tick = c.take<uint32_t>(64);
+static int64_t reads_tiles(int64_t n) { return (sepmask_words(n) + kRdTile - 1) / kRdTile; }
+static void carve_fixed(Carver &c, int64_t n, OvlFixed *F) {
     F->ctr = c.take<uint32_t>(64);
-    const int64_t scan_n = sepmask_words(n) > m + 1 ? sepmask_words(n) : m + 1;
-    F->lbflags = c.take<uint64_t>(scan_flags_words(scan_n) + 16);
-    F->read_end = c.take<int32_t>(m);
-    F->counts = c.take<uint32_t>(m + 1);
-    F->offs = c.take<int64_t>(m + 1);
+    F->sepmask = c.take<uint32_t>(sepmask_words(n));
+    F->sepcnt = c.take<int32_t>(sepmask_words(n));
+    F->lb_reads = c.take<uint64_t>(reads_tiles(n));
 }
-
+struct OvlReads {
+    int32_t *read_end;
+    uint64_t *lb_walk;
+};
+static void carve_reads(Carver &c, int64_t m, OvlReads *R) {
+    R->read_end = c.take<int32_t>(m);
+    R->lb_walk = c.take<uint64_t>((m + kWkBlock - 1) / kWkBlock + 1);
+}
+// keys[0] and vals[0], where the walks write, come first: their places do not depend on r
 struct OvlHits {
     SortBufs sb;
-    uint32_t *first;
-    int64_t *pos;
-    uint64_t *lbflags;
+    uint64_t *lb_rows;
 };
-
-static void carve_hits(Carver &c, int64_t r, const Tune &t, OvlHits *H) {
-    carve_sort(c, r, 32, t, &H->sb, true);
-    H->first = c.take<uint32_t>(r + 1);
-    H->pos = c.take<int64_t>(r + 1);
-    H->lbflags = c.take<uint64_t>(scan_flags_words(r + 1) + 16);
+static void carve_hits(Carver &c, int64_t hits, int64_t r, const Tune &t, OvlHits *H) {
+    H->sb.keys[0] = c.take<uint64_t>(hits);
+    H->sb.vals[0] = c.take<uint32_t>(hits);
+    H->sb.keys[1] = c.take<uint64_t>(r);
+    H->sb.vals[1] = c.take<uint32_t>(r);
+    H->lb_rows = c.take<uint64_t>((r + kRwTile - 1) / kRwTile + 1);
+    carve_sort(c, r, 32, t, &H->sb, false);
 }
 
 static int bits_for_u(int64_t v) {
@@ -161,18 +326,67 @@ extern "C" int64_t sa_overlaps_ws_bytes(int64_t n, int64_t m, int64_t candidates
     resolve_tuning(nullptr, &t);
     Carver c(nullptr, INT64_MAX);
     OvlFixed F;
-    carve_fixed(c, n, m, &F);
+    carve_fixed(c, n, &F);
+    OvlReads R;
+    carve_reads(c, m, &R);
     if (candidates > 0) {
         OvlHits H;
-        carve_hits(c, candidates, t, &H);
+        carve_hits(c, candidates, candidates, t, &H);
     }
     return c.off + 256;
 }
 
-extern "C" int sa_overlaps(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
-                           const int32_t *lcp, int32_t min_len, int32_t *out, int64_t cap,
-                           int64_t *n_out_h, void *ws, int64_t ws_bytes, int64_t *ws_needed_h,
-                           hipStream_t stream) {
+// The reads and, while they fit, the candidates of the text: kOv* words to host[].
+static int find_hits(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
+                     const int32_t *lcp, int32_t min_len, const OvlFixed &F, const OvlReads &R,
+                     int64_t cap_reads, uint64_t *keys, uint32_t *vals, int64_t cap_hits,
+                     uint32_t host[kStWords], hipStream_t s) {
+    const int64_t tag = timing_round_begin();
+    timing_scope_mode(kModeAny);
+    const int64_t rt = reads_tiles(n), wt = (cap_reads + kWkBlock - 1) / kWkBlock;
+    const int64_t most = rt > wt ? rt : wt;
+    hipLaunchKernelGGL(k_ovl_init, dim3(unsigned(most / 256 + 1 < 256 ? most / 256 + 1 : 256)), dim3(256), 0, s,
+                       F.ctr, F.lb_reads, uint32_t(rt), R.lb_walk, uint32_t(wt));
+    {
+        TimedScope ts("pack", double(n) + double(sepmask_words(n)) * 8.0, s, double(n));
+        hipLaunchKernelGGL(k_ovl_reads, dim3(unsigned(rt)), dim3(kRdBlock), 0, s, text, n, lcp, F.sepmask,
+                           F.sepcnt, R.read_end, cap_reads, uint32_t(sepmask_words(n)), F.lb_reads, F.ctr);
+        ts.finish();
+    }
+    {
+        TimedScope ts("overlap_walk", 0.0, 12.0, s);  // per read, counted below
+        // at most eight workgroups a CU, which take tiles until none is left
+        const unsigned g = unsigned(wt < 1 ? 1 : wt < 2048 ? wt : 2048);
+        hipLaunchKernelGGL(k_ovl_walk, dim3(g), dim3(kWkBlock), 0, s, sa, isa,
+                           lcp, R.read_end, F.sepmask, F.sepcnt, uint32_t(n), cap_reads, min_len, keys,
+                           vals, cap_hits, R.lb_walk, F.ctr);
+        ts.finish();
+    }
+    SA_HIP(hipGetLastError());
+    SA_TRY(read_words(F.ctr, host, s));
+    timing_round_items(tag, host[kOvReads], 0);
+    timing_flush();
+    // sa_lcp leaves a failure it found on the device in lcp[0] (0 in every valid array)
+    const int32_t lcp0 = int32_t(host[kOvLcp0]);
+    if (lcp0 < 0) return fail(lcp0 == SA_ERR_ALPHABET || lcp0 == SA_ERR_INVALID ? lcp0 : SA_ERR_HIP,
+                              "sa_overlaps: the LCP array carries a failure from sa_lcp");
+    if (lcp0 != 0) return fail(SA_ERR_INVALID, "sa_overlaps: lcp[0] must be 0");
+    const uint32_t e = host[kOvErr];
+    if (e & kErrAlphabet) return fail(SA_ERR_ALPHABET, "text holds a byte other than A, C, G, T, $");
+    if (e & kErrNoSepEnd) return fail(SA_ERR_INVALID, "text must end with '$'");
+    if (e) return fail(SA_ERR_HIP, "sa_overlaps: device consistency check failed (code " + std::to_string(e) + ")");
+    if (host[kOvReads] < 1 || int64_t(host[kOvReads]) > n) return fail(SA_ERR_HIP, "sa_overlaps: bad read count");
+    return SA_OK;
+}
+
+static int64_t words64(const uint32_t host[kStWords], int at) {
+    return int64_t((uint64_t(host[at + 1]) << 32) | host[at]);
+}
+
+static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
+                            const int32_t *lcp, int32_t min_len, int32_t *out, int64_t cap,
+                            int64_t *n_out_h, void *ws, int64_t ws_bytes, int64_t *ws_needed_h,
+                            hipStream_t s) {
     if (!text || !sa || !isa || !lcp || !ws || !n_out_h || (cap > 0 && !out))
         return fail(SA_ERR_INVALID, "sa_overlaps: NULL pointer");
     if (n < 1) return fail(SA_ERR_INVALID, "sa_overlaps: n must be >= 1");
@@ -185,104 +399,103 @@ extern "C" int sa_overlaps(const uint8_t *text, int64_t n, const int32_t *sa, co
     if (ws_bytes < fixed) return fail(SA_ERR_NOMEM, "sa_overlaps: workspace too small");
     Tune t;
     resolve_tuning(nullptr, &t);
-    hipStream_t s = stream;
+    // What the text-sized part leaves is split before the counts are known: a sixteenth is
+    // room for read ends and look-back words (under 5 bytes a read), and of the rest about a
+    // third for the candidates the walks find (12 of their 26 bytes and the sort's words).
+    // Where the counts do not fit that split, the search runs again with the sizes it found.
+    Carver c(ws, ws_bytes - 256);
     OvlFixed F;
-    {
-        Carver c0(ws, ws_bytes);
-        carve_fixed(c0, n, 1, &F);  // separators and counters only; read arrays carved below
+    carve_fixed(c, n, &F);
+    const int64_t left = ws_bytes - 256 - c.off;
+    int64_t cap_reads = left / 16 / 5 < n ? left / 16 / 5 : n, cap_hits = (left - left / 16) / 36;
+    if (cap_reads < 1) cap_reads = cap_hits = 0;
+    if (cap_hits > (int64_t(1) << 31)) cap_hits = int64_t(1) << 31;
+    const Carver at_reads = c;
+    OvlReads R{};
+    OvlHits H{};
+    uint32_t host[kStWords];
+    carve_reads(c, cap_reads, &R);
+    Carver at_hits = c;
+    H.sb.keys[0] = c.take<uint64_t>(cap_hits);
+    H.sb.vals[0] = c.take<uint32_t>(cap_hits);
+    if (!c.ok()) cap_hits = 0;
+    SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, cap_reads, H.sb.keys[0], H.sb.vals[0], cap_hits,
+                     host, s));
+    const int64_t m = host[kOvReads];
+    int64_t r = words64(host, kOvHits);
+    bool known = m <= cap_reads;  // the walks ran
+    if (!known || r > cap_hits) {
+        for (int again = 0;; ++again) {
+            const int64_t need = sa_overlaps_ws_bytes(n, m, known ? r : 0);
+            if (ws_needed_h) *ws_needed_h = need;
+            if (known && r >= kMaxN) return fail(SA_ERR_TOO_LARGE, "sa_overlaps: more than 2^31-2 candidate matches");
+            if (ws_bytes < need)
+                return fail(SA_ERR_NOMEM, known ? "sa_overlaps: workspace too small for " + std::to_string(r) + " candidates"
+                                                : "sa_overlaps: workspace too small for the reads");
+            if (again == 2) return fail(SA_ERR_HIP, "sa_overlaps: the candidate count changed between walks");
+            c = at_reads;
+            carve_reads(c, m, &R);
+            at_hits = c;
+            cap_hits = known ? r : 0;
+            H.sb.keys[0] = c.take<uint64_t>(cap_hits);
+            H.sb.vals[0] = c.take<uint32_t>(cap_hits);
+            SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H.sb.keys[0], H.sb.vals[0], cap_hits,
+                             host, s));
+            r = words64(host, kOvHits);
+            if (known && r <= cap_hits) break;
+            known = true;
+            if (r == 0) break;
+        }
     }
-    SA_TRY(launch_fill_u32(F.ctr, 64, 0, s));
-    SA_TRY(launch_pack(text, n, nullptr, F.sepmask, F.wordcnt, nullptr, F.ctr, s));
-    const int64_t nw = (n + 31) / 32;
-    SA_TRY(launch_scan_u32_i32(F.wordcnt, F.sepcnt, nw, reinterpret_cast<int32_t *>(F.ctr + 2),
-                               F.lbflags, F.tick, F.ctr, s));
-    uint32_t host[4];
-    int32_t lcp0 = 0;
-    SA_HIP(hipMemcpyAsync(host, F.ctr, 16, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipMemcpyAsync(&lcp0, lcp, 4, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
-    timing_flush();
-    // sa_lcp leaves a failure it found on the device in lcp[0] (0 in every valid array)
-    if (lcp0 < 0) return fail(lcp0 == SA_ERR_ALPHABET || lcp0 == SA_ERR_INVALID ? lcp0 : SA_ERR_HIP,
-                              "sa_overlaps: the LCP array carries a failure from sa_lcp");
-    if (lcp0 != 0) return fail(SA_ERR_INVALID, "sa_overlaps: lcp[0] must be 0");
-    if (host[0] & kErrAlphabet) return fail(SA_ERR_ALPHABET, "text holds a byte other than A, C, G, T, $");
-    if (host[0] & kErrNoSepEnd) return fail(SA_ERR_INVALID, "text must end with '$'");
-    if (host[0]) return fail(SA_ERR_HIP, "device consistency check failed");
-    const int64_t m = int32_t(host[2]);
-    if (m < 1 || m > n) return fail(SA_ERR_HIP, "sa_overlaps: bad read count");
-    {
-        const int64_t need_m = sa_overlaps_ws_bytes(n, m, 0);
-        if (ws_needed_h) *ws_needed_h = need_m;
-        if (ws_bytes < need_m) return fail(SA_ERR_NOMEM, "sa_overlaps: workspace too small for the reads");
-    }
-    Carver c(ws, ws_bytes);
-    carve_fixed(c, n, m, &F);  // same text-sized part; read arrays now sized by m
-    SA_TRY(launch_read_ends(F.sepmask, F.sepcnt, n, F.read_end, s));
-
-    // count candidates per read, then scan to offsets
-    const unsigned rgrid = unsigned((m + 255) / 256);
-    {
-        TimedScope ts("overlap_walk", double(m) * 12.0, s, double(m));
-        hipLaunchKernelGGL(k_ovl_walk<false>, dim3(rgrid), dim3(256), 0, s, sa, isa, lcp,
-                           F.read_end, F.sepmask, F.sepcnt, uint32_t(n), uint32_t(m), min_len,
-                           F.counts, nullptr, nullptr, nullptr, F.ctr);
-        ts.finish();
-        SA_HIP(hipGetLastError());
-    }
-    int64_t *tot = reinterpret_cast<int64_t *>(F.ctr + 8);
-    SA_TRY(launch_scan_u32_i64(F.counts, F.offs, m, tot, F.lbflags, F.tick, F.ctr, s));
-    int64_t r = 0;
-    uint32_t e = 0;
-    SA_HIP(hipMemcpyAsync(&r, tot, 8, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipMemcpyAsync(&e, F.ctr, 4, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
-    timing_flush();
-    if (e) return fail(SA_ERR_HIP, "sa_overlaps: device consistency check failed (code " + std::to_string(e) + ")");
+    if (ws_needed_h) *ws_needed_h = sa_overlaps_ws_bytes(n, m, r);
     if (r >= kMaxN) return fail(SA_ERR_TOO_LARGE, "sa_overlaps: more than 2^31-2 candidate matches");
-    const int64_t need = sa_overlaps_ws_bytes(n, m, r);
-    if (ws_needed_h) *ws_needed_h = need;
-    if (ws_bytes < need) return fail(SA_ERR_NOMEM, "sa_overlaps: workspace too small for " + std::to_string(r) + " candidates");
     if (r == 0) {
         *n_out_h = 0;
         return SA_OK;
     }
-    OvlHits H;
-    carve_hits(c, r, t, &H);
-    H.sb.err = F.ctr;
-    SA_TRY(launch_fill_u32(F.tick, 64, 0, s));
-    {
-        TimedScope ts("overlap_walk", double(m) * 12.0 + double(r) * 12.0, s, double(m));
-        hipLaunchKernelGGL(k_ovl_walk<true>, dim3(rgrid), dim3(256), 0, s, sa, isa, lcp,
-                           F.read_end, F.sepmask, F.sepcnt, uint32_t(n), uint32_t(m), min_len,
-                           nullptr, F.offs, H.sb.keys[0], H.sb.vals[0], F.ctr);
-        ts.finish();
-        SA_HIP(hipGetLastError());
+    c = at_hits;
+    carve_hits(c, cap_hits, r, t, &H);
+    if (!c.ok()) {  // the first split left too little for the sort: walk once more, exactly sized
+        const int64_t need = sa_overlaps_ws_bytes(n, m, r);
+        if (ws_bytes < need)
+            return fail(SA_ERR_NOMEM, "sa_overlaps: workspace too small for " + std::to_string(r) + " candidates");
+        c = at_reads;
+        carve_reads(c, m, &R);
+        carve_hits(c, r, r, t, &H);
+        const int64_t r0 = r;
+        SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H.sb.keys[0], H.sb.vals[0], r, host, s));
+        r = words64(host, kOvHits);
+        if (r != r0) return fail(SA_ERR_HIP, "sa_overlaps: the candidate count changed between walks");
     }
+    H.sb.err = F.ctr + kOvErr;
     int cur = 0;
     const int abits = bits_for_u(m - 1);
+    const int64_t row_tiles = (r + kRwTile - 1) / kRwTile;
     if (abits > 0) {
-        SA_TRY(sort_prepare(H.sb, r, abits, t, s));
         int nparts = 0;
         SA_TRY(launch_hist(H.sb, 0, r, 32, abits, t, s, &nparts));
         SA_TRY(sort_run(H.sb, 0, nullptr, r, 32, abits, t, nparts, s, &cur));
     }
-    const unsigned hgrid = unsigned((r + 255) / 256);
-    hipLaunchKernelGGL(k_run_heads, dim3(hgrid), dim3(256), 0, s, H.sb.keys[cur], uint32_t(r), H.first);
+    SA_TRY(launch_fill_u64(H.lb_rows, row_tiles, 0, s));
+    hipLaunchKernelGGL(k_ovl_rows, dim3(unsigned(row_tiles)), dim3(kRwBlock), 0, s, H.sb.keys[cur],
+                       H.sb.vals[cur], uint32_t(r), out, cap, H.lb_rows, F.ctr);
     SA_HIP(hipGetLastError());
-    int64_t *utot = reinterpret_cast<int64_t *>(F.ctr + 10);
-    SA_TRY(launch_scan_u32_i64(H.first, H.pos, r, utot, H.lbflags, F.tick, F.ctr, s));
-    int64_t u = 0;
-    SA_HIP(hipMemcpyAsync(&u, utot, 8, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipMemcpyAsync(&e, F.ctr, 4, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
+    SA_TRY(read_words(F.ctr, host, s));
     timing_flush();
-    if (e) return fail(SA_ERR_HIP, "sa_overlaps: device consistency check failed (code " + std::to_string(e) + ")");
+    if (host[kOvErr])
+        return fail(SA_ERR_HIP, "sa_overlaps: device consistency check failed (code " + std::to_string(host[kOvErr]) + ")");
+    const int64_t u = words64(host, kOvRows);
     *n_out_h = u;
     if (u > cap) return fail(SA_ERR_CAPACITY, "sa_overlaps: output holds " + std::to_string(cap) + " rows, need " + std::to_string(u));
-    hipLaunchKernelGGL(k_run_write, dim3(hgrid), dim3(256), 0, s, H.sb.keys[cur], H.sb.vals[cur],
-                       uint32_t(r), H.first, H.pos, out);
-    SA_HIP(hipGetLastError());
-    SA_HIP(hipStreamSynchronize(s));
     return SA_OK;
+}
+
+extern "C" int sa_overlaps(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
+                           const int32_t *lcp, int32_t min_len, int32_t *out, int64_t cap,
+                           int64_t *n_out_h, void *ws, int64_t ws_bytes, int64_t *ws_needed_h,
+                           hipStream_t stream) {
+    return guard<int>([&] {
+        return sa_overlaps_impl(text, n, sa, isa, lcp, min_len, out, cap, n_out_h, ws, ws_bytes,
+                                ws_needed_h, stream);
+    });
 }

@@ -53,16 +53,14 @@ void carve_sort(Carver &c, int64_t n, int bits, const Tune &t, SortBufs *b, bool
         const int64_t w = m <= n ? sort_flag_words(m, bits, t) : 0;
         words = w > words ? w : words;
     }
-    b->flags = c.take<uint32_t>(words);
-    b->tickets = c.take<uint32_t>(64);
+    b->tickets = c.take<uint32_t>(64 + words);  // one piece, cleared as one
+    b->flags = b->tickets ? b->tickets + 64 : nullptr;
 }
 
-int sort_prepare(const SortBufs &b, int64_t n, int bits, const Tune &t, hipStream_t s) {
-    const int P = sort_passes(bits, t);
-    if (P == 0) return SA_OK;
-    SA_TRY(launch_fill_u32(b.flags, sort_flag_words(n, bits, t), 0, s));
-    SA_TRY(launch_fill_u32(b.tickets, 64, 0, s));
-    return SA_OK;
+// Words that the kernel which builds a sort's histograms clears for its passes: the tickets and
+// the look-back words after them.
+static uint64_t sort_clear_words(int64_t n, int bits, const Tune &t) {
+    return sort_passes(bits, t) ? uint64_t(64 + sort_flag_words(n, bits, t)) : 0u;
 }
 
 // ---- digit histograms ---------------------------------------------------------------------
@@ -86,12 +84,22 @@ __device__ __forceinline__ void hist_flush(const uint32_t *s_h, uint32_t *part, 
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) dst[i] = s_h[i];
 }
 
+// Clears n words (a multiple of 4, 16-byte aligned) with the whole grid.
+__device__ __forceinline__ void clear_words(uint32_t *p, uint64_t n) {
+    uint4 *q = reinterpret_cast<uint4 *>(p);
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n / 4; i += stride)
+        q[i] = make_uint4(0, 0, 0, 0);
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void k_hist(const uint64_t *__restrict__ keys, uint32_t n,
                                               int bit_lo, int bits, int passes,
-                                              uint32_t *__restrict__ hist) {
+                                              uint32_t *__restrict__ hist, uint32_t *clear,
+                                              uint64_t nclear) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
+    clear_words(clear, nclear);
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
@@ -161,10 +169,67 @@ __global__ __launch_bounds__(kHsBlock) void k_hist_bases(uint32_t *__restrict__ 
     }
 }
 
+// Both steps in one workgroup per pass, for few partials: sums of each digit over them (by
+// 1024 / R slices of the partials, or several digits a thread), then the exclusive scan.
+constexpr int kHsFewParts = 64;
+template <int D>
+__global__ __launch_bounds__(kHsBlock) void k_hist_few(const uint32_t *__restrict__ part, int nparts,
+                                                       int passes, uint32_t *__restrict__ gbase) {
+    constexpr int R = 1 << D;
+    constexpr int DIG = R < kHsBlock ? R : kHsBlock;  // digits at a time
+    constexpr int SL = kHsBlock / DIG;
+    constexpr int PER = R / DIG;
+    __shared__ uint32_t s_part[kHsBlock];
+    __shared__ uint32_t s_tot[R];
+    __shared__ uint32_t s_w[kHsBlock / kWave];
+    const int tid = threadIdx.x, dl = tid % DIG, sl = tid / DIG;
+    const size_t stride = size_t(passes) * R;
+    for (int k = 0; k < PER; ++k) {
+        const uint32_t *src = part + size_t(blockIdx.x) * R + k * DIG + dl;
+        uint32_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+        int w = sl;
+        for (; w + 3 * SL < nparts; w += 4 * SL) {
+            a0 += src[size_t(w) * stride];
+            a1 += src[size_t(w + SL) * stride];
+            a2 += src[size_t(w + 2 * SL) * stride];
+            a3 += src[size_t(w + 3 * SL) * stride];
+        }
+        for (; w < nparts; w += SL) a0 += src[size_t(w) * stride];
+        s_part[tid] = a0 + a1 + a2 + a3;
+        __syncthreads();
+        if (sl == 0) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int q = 0; q < SL; ++q) c += s_part[q * DIG + dl];
+            s_tot[k * DIG + dl] = c;
+        }
+        __syncthreads();
+    }
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        v[j] = tid < DIG ? s_tot[tid * PER + j] : 0u;
+        sum += v[j];
+    }
+    uint32_t total;
+    uint32_t run = block_excl_sum<kHsBlock>(sum, s_w, &total);
+    if (tid < DIG) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            gbase[size_t(blockIdx.x) * R + tid * PER + j] = run;
+            run += v[j];
+        }
+    }
+}
+
 template <int D>
 static void launch_hist_scan(const uint32_t *hist, int nparts, int P, uint32_t *gbase,
                              hipStream_t s) {
     constexpr int R = 1 << D;
+    if (nparts <= kHsFewParts) {  // one launch instead of two; beyond, one workgroup reads too long
+        hipLaunchKernelGGL(k_hist_few<D>, dim3(unsigned(P)), dim3(kHsBlock), 0, s, hist, nparts, P, gbase);
+        return;
+    }
     hipLaunchKernelGGL(k_hist_sum<D>, dim3(unsigned(P), unsigned((R + kHsDigits - 1) / kHsDigits)),
                        dim3(kHsBlock), 0, s, hist, nparts, P, gbase);
     hipLaunchKernelGGL(k_hist_bases<D>, dim3(unsigned(P)), dim3(kHsBlock), 0, s, gbase);
@@ -183,11 +248,12 @@ int launch_hist(const SortBufs &b, int cur, int64_t n, int bit_lo, int bits, con
     *nparts = int(hist_grid(n));
     if (P == 0 || n == 0) return SA_OK;
     size_t lds = size_t(P) * t.radix() * 4;
+    const uint64_t nclear = sort_clear_words(n, bits, t);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_hist<4>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist); break;
-        case 8: hipLaunchKernelGGL(k_hist<8>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist); break;
-        case 9: hipLaunchKernelGGL(k_hist<9>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist); break;
-        case 11: hipLaunchKernelGGL(k_hist<11>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist); break;
+        case 4: hipLaunchKernelGGL(k_hist<4>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist, b.tickets, nclear); break;
+        case 8: hipLaunchKernelGGL(k_hist<8>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist, b.tickets, nclear); break;
+        case 9: hipLaunchKernelGGL(k_hist<9>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist, b.tickets, nclear); break;
+        case 11: hipLaunchKernelGGL(k_hist<11>, dim3(hist_grid(n)), dim3(256), lds, s, b.keys[cur], uint32_t(n), bit_lo, bits, P, b.hist, b.tickets, nclear); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     SA_HIP(hipGetLastError());
@@ -568,9 +634,11 @@ __global__ __launch_bounds__(kK0Block) void k_key0(const uint32_t *__restrict__ 
                                               uint32_t n_sets, int set_shift,
                                               uint64_t *__restrict__ keys, int lo_bit,
                                               uint64_t key_mask, int passes,
-                                              uint32_t *__restrict__ hist) {
+                                              uint32_t *__restrict__ hist, uint32_t *clear,
+                                              uint64_t nclear) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
+    clear_words(clear, nclear);
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
@@ -597,13 +665,14 @@ int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int 
     const int P = sort_passes(key_bits - lo_bit, t);
     *nparts = int(hist_grid(n));
     size_t lds = size_t(P) * t.radix() * 4;
+    const uint64_t nclear = sort_clear_words(n, key_bits - lo_bit, t);
     TimedScope ts("key0", double(n) * (8.0 + 0.375), s, double(n));
     const unsigned g = hist_grid(n);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
-        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
-        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
-        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist); break;
+        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
+        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
+        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
+        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();
@@ -637,9 +706,10 @@ __global__ __launch_bounds__(kBxBlock) void k_big_extract(
     const uint32_t *__restrict__ rank, uint32_t n, int rbits, uint64_t *__restrict__ keys,
     uint32_t *__restrict__ vals, uint32_t *__restrict__ bigidx, int passes,
     uint32_t *__restrict__ hist, uint64_t *lbflags, uint32_t *tick, uint32_t *state,
-    uint32_t *err) {
+    uint32_t *err, uint32_t *clear, uint64_t nclear) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
+    clear_words(clear, nclear);
     __shared__ uint64_t s_mask[kBxRows + 2];  // first-of-group bits per row; [0] and [kBxRows+1]: context
     __shared__ uint64_t s_bigm[kBxRows];      // large-group items per row
     __shared__ uint32_t s_cnt[kBxRows];       // their count, then the exclusive count
@@ -799,13 +869,14 @@ int launch_big_extract(const uint32_t *P, const uint32_t *S, const uint32_t *ran
     SA_TRY(launch_fill_u64(lbflags, tiles > 0 ? tiles : 1, 0, s));
     SA_TRY(launch_fill_u32(tick, 1, 0, s));
     size_t lds = size_t(P_) * t.radix() * 4;
+    const uint64_t nclear = sort_clear_words(a_bound, bits, t);
     // per large item: position, slot and rank[p + h] read (12), key, value and index written (16)
     TimedScope ts("keybuild", 0.0, 28.0, s);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_big_extract<4>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err); break;
-        case 8: hipLaunchKernelGGL(k_big_extract<8>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err); break;
-        case 9: hipLaunchKernelGGL(k_big_extract<9>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err); break;
-        case 11: hipLaunchKernelGGL(k_big_extract<11>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err); break;
+        case 4: hipLaunchKernelGGL(k_big_extract<4>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 8: hipLaunchKernelGGL(k_big_extract<8>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 9: hipLaunchKernelGGL(k_big_extract<9>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
+        case 11: hipLaunchKernelGGL(k_big_extract<11>, dim3(unsigned(grid)), dim3(kBxBlock), lds, s, P, S, rank, uint32_t(n), rbits, b.keys[0], b.vals[0], bigidx, P_, b.hist, lbflags, tick, state, b.err, b.tickets, nclear); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();
@@ -867,7 +938,6 @@ extern "C" int sa_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int32_t 
     b.err = c.take<uint32_t>(64);
     if (!c.ok()) return fail(SA_ERR_NOMEM, "sa_sort_pairs: workspace too small");
     SA_TRY(launch_fill_u32(b.err, 1, 0, stream));
-    SA_TRY(sort_prepare(b, n, bits, t, stream));
     int nparts = 0;
     SA_TRY(launch_hist(b, 0, n, bit_lo, bits, t, stream, &nparts));
     int cur = 0;

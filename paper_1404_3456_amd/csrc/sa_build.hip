@@ -212,6 +212,15 @@ __global__ __launch_bounds__(kRuBlock) void k_rank_update(
     }
 }
 
+// The state a build starts from, and cleared look-back words for its first round.
+__global__ __launch_bounds__(256) void k_build_init(uint32_t *state, uint32_t n, uint64_t *lbflags,
+                                                    uint32_t nlb, uint32_t *tick) {
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < nlb; i += gridDim.x * 256u) lbflags[i] = 0;
+    if (blockIdx.x != 0) return;
+    if (threadIdx.x < kStWords) state[threadIdx.x] = threadIdx.x == kStActive ? n : 0u;
+    if (threadIdx.x == kStWords) *tick = 0;
+}
+
 // Advances the round state after a rank update (one thread).  h_ext: symbols the first round's
 // groups are equal on unless it met one too large to be extended past h_first (0: none was).
 __global__ void k_round_end(uint32_t *state, uint32_t h_first, uint32_t h_ext) {
@@ -405,21 +414,24 @@ static int check_err(uint32_t e) {
     return SA_OK;
 }
 
-// Pinned host words and events for reading round state without a full stream sync (one set
-// per host thread; two slots so one round's state can be in flight while the other is read).
-struct PinnedState {
-    uint32_t *h = nullptr;
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    bool ok = false;
-    PinnedState() {
-        ok = hipHostMalloc(reinterpret_cast<void **>(&h), 2 * kStWords * 4, hipHostMallocDefault) == hipSuccess &&
-             hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) == hipSuccess &&
-             hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) == hipSuccess;
-    }
-};
-static PinnedState &pinned_state() {
+PinnedState::PinnedState() {
+    ok = hipHostMalloc(reinterpret_cast<void **>(&h), 3 * kStWords * 4, hipHostMallocDefault) == hipSuccess &&
+         hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) == hipSuccess &&
+         hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) == hipSuccess;
+}
+PinnedState &pinned_state() {
     static thread_local PinnedState ps;
     return ps;
+}
+
+int read_words(const uint32_t *dev, uint32_t host[kStWords], hipStream_t s) {
+    PinnedState &ps = pinned_state();
+    if (!ps.ok) return fail(SA_ERR_HIP, "no pinned host memory for device words");
+    uint32_t *h = ps.h + 2 * kStWords;
+    SA_HIP(hipMemcpyAsync(h, dev, kStWords * 4, hipMemcpyDeviceToHost, s));
+    SA_HIP(hipStreamSynchronize(s));
+    memcpy(host, h, kStWords * 4);
+    return SA_OK;
 }
 
 // One suffix-array build (plain: one text; batched: n_sets texts, set_off_h on the host).
@@ -458,10 +470,19 @@ struct Build {
     int first_sort(int lo_bit, int *cur) {
         const int64_t *set_off_dev = n_sets > 1 ? L.set_off : nullptr;
         const int bits = key0_bits - lo_bit;
-        SA_TRY(sort_prepare(L.sb, n, bits, t, s));
         int nparts = 0;
         SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev, n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
         return sort_run(L.sb, 0, nullptr, n, lo_bit, bits, t, nparts, s, cur, true);
+    }
+
+    int init() {
+        const int64_t nlb = (n + kLbMinTile - 1) / kLbMinTile;
+        if (nlb > L.lb_words) return fail(SA_ERR_HIP, "sa_build: look-back array too small");
+        const int64_t g = (nlb + 255) / 256 < 1024 ? (nlb + 255) / 256 : 1024;
+        hipLaunchKernelGGL(k_build_init, dim3(unsigned(g)), dim3(256), 0, s, L.state, uint32_t(n), L.lbflags,
+                           uint32_t(nlb), L.tickets);
+        SA_HIP(hipGetLastError());
+        return SA_OK;
     }
 
     int round_end() {
@@ -481,8 +502,7 @@ struct Build {
 
     // The first round, and the state after it (pinned slot 0, host[]).
     int round0(PinnedState &ps, uint32_t host[kStWords]) {
-        SA_TRY(launch_fill_u32(L.state, 64, 0, s));
-        SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
+        SA_TRY(init());
         SA_TRY(launch_pack(text, n, L.packed, L.sepmask, nullptr, nullptr, L.state + kStErr, s));
         if (n_sets > 1) {  // one text's end is checked by the packing
             SA_HIP(hipMemcpyAsync(L.set_off, set_off_h, size_t(n_sets + 1) * 8, hipMemcpyHostToDevice, s));
@@ -517,7 +537,6 @@ struct Build {
         b.vals[0] = L.sb.vals[cur ^ 1];
         b.keys[1] = reinterpret_cast<uint64_t *>(L.slots[0]);  // slots[0] and slots[1] in one
         b.vals[1] = L.pos;
-        SA_TRY(sort_prepare(b, n, key0_bits, t, s));
         int nparts = 0, bc = 0;
         const int64_t tag = timing_round_begin();
         timing_scope_mode(kModeRadix);
@@ -527,6 +546,8 @@ struct Build {
         SA_TRY(launch_big_place(b.keys[bc], b.vals[bc], L.bigidx, n, L.state, L.sb.keys[cur],
                                 L.sb.vals[cur], L.state + kStErr, s));
         timing_scope_mode(kModeAny);
+        SA_TRY(launch_fill_u64(L.lbflags, (n + kLbMinTile - 1) / kLbMinTile, 0, s));
+        SA_TRY(launch_fill_u32(L.tickets, 1, 0, s));
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, true, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end());
@@ -547,7 +568,6 @@ struct Build {
         int cur = 0;
         if (!runs_only) {
             const int bits = 2 * rbits;
-            SA_TRY(sort_prepare(L.sb, a_bound, bits, t, s));
             int nparts = 0;
             timing_scope_mode(kModeRadix);
             SA_TRY(launch_big_extract(L.pos, L.slots[sl], rank, n, rbits, a_bound, L.sb, L.bigidx,

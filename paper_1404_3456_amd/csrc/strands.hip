@@ -188,7 +188,6 @@ extern "C" int sa_strand_rows(const int32_t *rows, int64_t r, int64_t m, int32_t
                        W.sb.keys[0], W.sb.vals[0]);
     SA_HIP(hipGetLastError());
     const int bits = key_bits(m);
-    SA_TRY(sort_prepare(W.sb, u, bits, t, s));
     int nparts = 0, cur = 0;
     SA_TRY(launch_hist(W.sb, 0, u, 0, bits, t, s, &nparts));
     SA_TRY(sort_run(W.sb, 0, nullptr, u, 0, bits, t, nparts, s, &cur));
