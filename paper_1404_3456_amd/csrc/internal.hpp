@@ -155,9 +155,11 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
 // Finishes an LCP array whose negative entries are -1 - (symbols the suffix is known to share with
 // its predecessor), by comparing on in the text.  Sets *too_long, and may leave entries
 // negative, when some pair shares more than kLcpRestMax symbols past those (then Kasai's scan
-// is the way).
+// is the way).  list: the indices of `count` entries among which the negative ones are (NULL:
+// the first `count` entries).
 constexpr uint32_t kLcpRestMax = 2048;
-int launch_lcp_rest(const uint8_t *text, int64_t n, const int32_t *sa, int32_t *lcp, void *ws,
+int launch_lcp_rest(const uint8_t *text, const uint32_t *packed, const uint32_t *sepmask, int64_t n,
+                    const int32_t *sa, const uint32_t *list, int64_t count, int32_t *lcp, void *ws,
                     int64_t ws_bytes, uint32_t *too_long, uint32_t *err, hipStream_t s);
 
 // radix sort plumbing

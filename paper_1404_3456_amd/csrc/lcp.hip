@@ -117,14 +117,24 @@ __global__ __launch_bounds__(256) void k_lcp_gather(const int32_t *__restrict__ 
     }
 }
 
-// One entry per thread; see launch_lcp_rest.  A thread that finds the flag set stops: on a text
-// with many long matches the kernel then ends after its first workgroups.
+// One entry per thread (list: those, else every index); see launch_lcp_rest.  Many entries read
+// the text by window records (blk), whose lines hold codes and separators together; for a few
+// those are not worth building.  A thread that finds the flag set stops: on a text with many
+// long matches the kernel then ends after its first workgroups.
+template <bool BLK>
 __global__ __launch_bounds__(256) void k_lcp_rest(const uint4 *__restrict__ blk,
+                                                  const uint32_t *__restrict__ packed,
+                                                  const uint32_t *__restrict__ sepmask,
                                                   const int32_t *__restrict__ sa, uint32_t n,
+                                                  const uint32_t *__restrict__ list, uint32_t count,
                                                   int32_t *__restrict__ lcp, uint32_t *too_long,
                                                   uint32_t *err) {
-    for (uint64_t g = blockIdx.x * 256u + threadIdx.x; g < n; g += uint64_t(gridDim.x) * 256u) {
-        const uint32_t i = uint32_t(g);
+    for (uint64_t g = blockIdx.x * 256u + threadIdx.x; g < count; g += uint64_t(gridDim.x) * 256u) {
+        const uint32_t i = list ? list[g] : uint32_t(g);
+        if (i >= n) {
+            raise_err(err, kErrRange);
+            continue;
+        }
         const int32_t l = lcp[i];
         if (l >= 0 || i == 0) continue;
         if (ld_agent(too_long)) return;
@@ -140,9 +150,16 @@ __global__ __launch_bounds__(256) void k_lcp_rest(const uint4 *__restrict__ blk,
                 st_agent(too_long, 1u);
                 break;
             }
-            const Window a = window_at(blk, p + h), b = window_at(blk, q + h);
-            const uint64_t d = a.code ^ b.code;
-            const uint32_t sp = a.sep | b.sep;
+            uint64_t d;
+            uint32_t sp;
+            if (BLK) {
+                const Window a = window_at(blk, p + h), b = window_at(blk, q + h);
+                d = a.code ^ b.code;
+                sp = a.sep | b.sep;
+            } else {
+                d = codes_at(packed, p + h) ^ codes_at(packed, q + h);
+                sp = bits_at(sepmask, p + h) | bits_at(sepmask, q + h);
+            }
             const uint32_t md = d ? uint32_t(__clzll((long long)d)) >> 1 : 32u;
             const uint32_t ms = sp ? uint32_t(__clz(sp)) : 32u;
             const uint32_t kk = md < ms ? md : ms;
@@ -236,17 +253,26 @@ int lcp_run(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *is
     return SA_OK;
 }
 
-int launch_lcp_rest(const uint8_t *text, int64_t n, const int32_t *sa, int32_t *lcp, void *ws,
+int launch_lcp_rest(const uint8_t *text, const uint32_t *packed, const uint32_t *sepmask, int64_t n,
+                    const int32_t *sa, const uint32_t *list, int64_t count, int32_t *lcp, void *ws,
                     int64_t ws_bytes, uint32_t *too_long, uint32_t *err, hipStream_t s) {
-    if (ws_bytes < lcp_ws_bytes(n)) return fail(SA_ERR_NOMEM, "sa_lcp: workspace too small");
-    Carver c(ws, ws_bytes);
-    uint4 *blk = c.take<uint4>(sepmask_words(n));
-    SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, blk, err, s));
-    int64_t g = (n + 255) / 256;
+    int64_t g = (count + 255) / 256;
     if (g > 16384) g = 16384;
-    TimedScope ts("lcp_rest", double(n) * 4.0, s, double(n));
-    hipLaunchKernelGGL(k_lcp_rest, dim3(unsigned(g)), dim3(256), 0, s, blk, sa, uint32_t(n), lcp,
-                       too_long, err);
+    const dim3 grid{unsigned(g)};
+    uint4 *blk = nullptr;
+    if (!list) {
+        if (ws_bytes < lcp_ws_bytes(n)) return fail(SA_ERR_NOMEM, "sa_lcp: workspace too small");
+        Carver c(ws, ws_bytes);
+        blk = c.take<uint4>(sepmask_words(n));
+        SA_TRY(launch_pack(text, n, nullptr, nullptr, nullptr, blk, err, s));
+    }
+    TimedScope ts("lcp_rest", double(count) * 4.0, s, double(count));
+    if (list)
+        hipLaunchKernelGGL(k_lcp_rest<false>, grid, dim3(256), 0, s, blk, packed, sepmask, sa, uint32_t(n), list,
+                           uint32_t(count), lcp, too_long, err);
+    else
+        hipLaunchKernelGGL(k_lcp_rest<true>, grid, dim3(256), 0, s, blk, packed, sepmask, sa, uint32_t(n), list,
+                           uint32_t(count), lcp, too_long, err);
     ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;

@@ -625,12 +625,13 @@ struct Build {
     // The rest of the LCP array after the last round: *have_lcp when it is complete.  A build
     // whose first round left no group has it already; texts with matches far beyond the first
     // round's reach are left to Kasai's scan, whose work does not depend on their length.
-    int finish_lcp(PinnedState &ps, bool left, bool *have_lcp) {
+    int finish_lcp(PinnedState &ps, int64_t left, bool listed, bool *have_lcp) {
         if (!lcp || top_bits == 0) return SA_OK;
-        if (left) {
+        if (left > 0) {
             uint32_t host[kStWords];
-            SA_TRY(launch_lcp_rest(text, n, sa, lcp, L.lcp_ws, L.lcp_ws_bytes, L.state + kStLcpLong,
-                                   L.state + kStErr, s));
+            SA_TRY(launch_lcp_rest(text, L.packed, L.sepmask, n, sa, listed ? L.bigidx : nullptr,
+                                   listed ? left : n, lcp, L.lcp_ws, L.lcp_ws_bytes,
+                                   L.state + kStLcpLong, L.state + kStErr, s));
             SA_TRY(wait_state(ps, host));
             timing_flush();
             SA_TRY(check_err(host[kStErr]));
@@ -652,8 +653,13 @@ struct Build {
         SA_TRY(round0(ps, host));
         timing_poll();
         SA_TRY(check_err(host[kStErr]));
-        const bool left = host[kStActive] != 0;
-        if (!left) {
+        // Suffixes the first round left in groups: their slots are what the LCP array still
+        // lacks, kept where only rounds with large groups would write (those scan for them).
+        const int64_t left = host[kStActive];
+        const bool listed = lcp && top_bits && left > 0 && host[kStBig] == 0 && !use_graph;
+        if (listed)
+            SA_HIP(hipMemcpyAsync(L.bigidx, L.slots[0], size_t(left) * 4, hipMemcpyDeviceToDevice, s));
+        if (left == 0) {
             timing_flush();
         } else if (use_graph) {
             int64_t A = host[kStActive];
@@ -743,7 +749,7 @@ struct Build {
             }
         }
         if (rounds_out) *rounds_out = int(host[kStRounds]);
-        return finish_lcp(ps, left, have_lcp);
+        return finish_lcp(ps, left, listed, have_lcp);
     }
 };
 

@@ -24,24 +24,27 @@ __device__ __forceinline__ uint8_t complement(uint8_t c) {
     }
 }
 
-// Thread i: out[i] = text[i]; out[n + i] = complement(text[n - 2 - i]) for i < n - 1, and
-// out[2n - 1] = '$'.  Adds the separators of text to *m_dev.
+// out[i] = text[i]; out[n + i] = complement(text[n - 2 - i]) for i < n - 1, and out[2n - 1] = '$'.
+// Adds the separators of text to *m_dev: one addition a workgroup of a grid that strides over
+// the text (one for every 256 characters serialised on that word: 246 us at 10 M characters,
+// now 12).
+constexpr int kRcGrid = 1024;
 __global__ __launch_bounds__(256) void k_revcomp(const uint8_t *__restrict__ text, int64_t n,
                                                  uint8_t *__restrict__ out,
                                                  unsigned long long *m_dev) {
     __shared__ uint32_t s_cnt;
     if (threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    bool sep = false;
-    if (i < n) {
+    uint32_t cnt = 0;
+    const int64_t stride = int64_t(gridDim.x) * 256;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += stride) {
         const uint8_t c = text[i];
         out[i] = c;
-        sep = c == '$';
+        cnt += c == '$';
         out[n + i] = i < n - 1 ? complement(text[n - 2 - i]) : uint8_t('$');
     }
-    const uint64_t b = ballot(sep);
-    if (lane_id() == 0 && b) atomicAdd(&s_cnt, uint32_t(popc64(b)));
+    for (int o = 1; o < kWave; o <<= 1) cnt += __shfl_xor(cnt, o);
+    if (lane_id() == 0 && cnt) atomicAdd(&s_cnt, cnt);
     __syncthreads();
     if (threadIdx.x == 0 && s_cnt) atomicAdd(m_dev, (unsigned long long)s_cnt);
 }
@@ -133,7 +136,8 @@ extern "C" int sa_revcomp_text(const uint8_t *text, int64_t n, uint8_t *out, int
     Carver c(ws, ws_bytes);
     unsigned long long *m_dev = c.take<unsigned long long>(1);
     SA_TRY(launch_fill_u64(reinterpret_cast<uint64_t *>(m_dev), 1, 0, stream));
-    hipLaunchKernelGGL(k_revcomp, dim3(unsigned((n + 255) / 256)), dim3(256), 0, stream, text, n,
+    const int64_t g = (n + 255) / 256 < kRcGrid ? (n + 255) / 256 : kRcGrid;
+    hipLaunchKernelGGL(k_revcomp, dim3(unsigned(g)), dim3(256), 0, stream, text, n,
                        out, m_dev);
     SA_HIP(hipGetLastError());
     unsigned long long m = 0;

@@ -26,6 +26,13 @@ __device__ __forceinline__ Window window_at(const uint4 *__restrict__ blk, uint3
     return w;
 }
 
+// Separator bits of positions a .. a+31 (position a in bit 31); reads words a/32 and a/32 + 1.
+__device__ __forceinline__ uint32_t bits_at(const uint32_t *__restrict__ sepmask, uint32_t a) {
+    const uint32_t o = a & 31;
+    const uint32_t x = sepmask[a >> 5], y = sepmask[(a >> 5) + 1];
+    return o ? (x << o) | (y >> (32 - o)) : x;
+}
+
 // 32 bases of a packed code array (16 per word, base 0 in the top bits) from base a; reads
 // words a/16 .. a/16 + 2.
 __device__ __forceinline__ uint64_t codes_at(const uint32_t *__restrict__ packed, uint64_t a) {
