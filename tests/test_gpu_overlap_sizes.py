@@ -83,3 +83,31 @@ def test_many_empty_reads(lib):
     rng = np.random.default_rng([synth.SEED_BASE, 804])
     reads = [""] * 30_000 + ["ACGTTGCA"[int(rng.integers(0, 4)):] for _ in range(300)]
     every_workspace(lib, synth.text_from_strings([reads[i] for i in rng.permutation(len(reads))]), 3)
+
+
+@pytest.mark.parametrize("bad", [(), (0,), (2, 3), (0, 1, 2, 3, 4)])
+def test_borrowed_jobs_checked_on_the_device(lib, bad):
+    """Borrowed texts of odd lengths in one batch, some with a foreign byte at their first or
+    last base: those (only) are refused, the others' results are their own."""
+    import time
+    texts = [synth.genome_reads(9700 + k, 300 + 17 * k, 20 + k, 41 + k) for k in range(5)]
+    jobs = [t.copy() for t in texts]
+    for k in bad:
+        jobs[k][0 if k % 2 else jobs[k].size - 2] = ord("N")
+    with lib.AsmServer(1 << 30, max_jobs_per_batch=8, workers=1) as srv:
+        first = srv.asm_submit(texts[0], 15, borrow=True)  # the others queue up behind it
+        ids = [srv.asm_submit(t, 15, borrow=True) for t in jobs]
+        end = time.time() + 60
+        while any(srv.asm_poll(j) is None for j in [first] + ids):
+            assert time.time() < end
+            time.sleep(0.001)
+        assert srv.asm_poll(first)["status"] == lib.SA_OK
+        for k, j in enumerate(ids):
+            r = srv.asm_poll(j)
+            if k in bad:
+                assert r["status"] == lib.SA_ERR_ALPHABET
+                continue
+            want = oracle.suffix_array(texts[k])
+            assert r["status"] == lib.SA_OK and r["m"] == int((texts[k] == synth.SEP).sum())
+            assert np.array_equal(r["sa"].cpu().numpy(), want)
+            assert np.array_equal(r["ovl"].cpu().numpy(), oracle.overlaps(texts[k], 15))
