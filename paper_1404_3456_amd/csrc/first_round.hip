@@ -1,22 +1,22 @@
 // first_round.hip -- the first round of a suffix-array build, from suffixes ordered by the top
-// bits of their first-round keys to groups equal on h0 + kExtBases symbols.
+// bits of their first-round keys to groups equal on top_d + kExtBases symbols.
 //
-// Sec. IV sorts integer keys by radix passes, one digit at a time.  A first-round key holds 29
-// bases (63 bits, seven 9-bit passes), but two or three passes over its top bits already leave
-// runs of equal top bits that are about as short as the final groups: the reads of a 10x
-// coverage put about ten copies of a genome stretch side by side, and that is what a run
-// holds.  So only the top bits go through passes over HBM; the rest of the key is sorted run by
-// run in LDS here, and each group still equal on all of it is sorted by the next kExtBases
-// symbols read from the packed text.  The same kernel then finishes the round: it labels
-// groups, writes the ranks and the final suffixes, and compacts the rest for the doubling
-// rounds, which start at h0 + kExtBases symbols instead of h0.
+// Sec. IV sorts integer keys by radix passes, one digit at a time.  A key of 29 bases (63 bits)
+// takes seven 9-bit passes, but two or three passes over its top bits already leave runs of
+// equal top bits that are about as short as the final groups: the reads of a 10x coverage put
+// about ten copies of a genome stretch side by side, and that is what a run holds.  So only the
+// top bits go through passes over HBM; each run is then sorted in LDS by the next kExtBases
+// symbols, read from the packed text.  The same kernel finishes the round: it labels groups,
+// writes the ranks, the final suffixes and the common prefixes it saw, and compacts the rest
+// for the doubling rounds, which start at top_d + kExtBases symbols instead of 29.
 //
 // A run is a stretch of equal top bits, that is, of suffixes equal on their first top_d bases
 // (suffixes that end before top_d bases share theirs only with their equals and are runs of
-// their own).  Runs of more than kFrRun suffixes (repeats) do not fit the context a tile loads.  The plain
-// form of the kernel only reports them; the host then has their items taken out, sorted by
-// radix passes over the whole key and put back in place (k_first_extract, k_big_place), and
-// runs the other form, which takes such runs as sorted.
+// their own).  Runs of more than kFrRun suffixes (repeats) do not fit the context a tile loads.
+// The plain form of the kernel only reports them; the host then has their items taken out,
+// sorted by radix passes over the whole key and put back in place (k_first_extract,
+// k_big_place), and runs the other form, which takes such runs as sorted by h0 symbols and
+// first sorts the others by them too.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -138,7 +138,7 @@ __device__ __forceinline__ uint32_t add_below(uint32_t c, uint64_t q0, uint64_t 
     return c;
 }
 __device__ __forceinline__ uint32_t add_below2(uint32_t c, uint64_t q0, uint64_t q1, uint64_t k0,
-                                               uint64_t k1, uint64_t in) {
+                                                uint64_t k1, uint64_t in) {
     uint32_t t;
     asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
         "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
@@ -170,7 +170,7 @@ __device__ __forceinline__ int count_below(const uint64_t *s, int st, int en, ui
 
 // The same for two-word keys.
 __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *s1, int st, int en,
-                                            uint64_t k0, uint64_t k1) {
+                                             uint64_t k0, uint64_t k1) {
     uint32_t c = 0;
     for (int y = st; y < en; y += 4) {
         uint64_t q0[4], q1[4];
@@ -235,6 +235,16 @@ constexpr int64_t kFrFewItems = int64_t(1) << 21;
 // LCP: also writes lcp[i] of every suffix told apart from its predecessor here (the keys and
 // windows compared hold their common prefix); for the others, which leave in groups, the
 // negative of one more than the symbols they are known to share.
+// What bounds it: the comparisons in LDS (about ten items a run are compared with each other
+// twice a window) and, per window, one gather of 36 bytes of packed text an item.  3.0 ms for
+// the 50.1 M suffixes of 10x reads, of which a copy of what it reads and writes would take
+// 0.3 ms.  The four passes, rank updates, sorts of runs and Kasai's scan it took the place of
+// were 8.1 ms.
+// The plain form's windows follow the run's top bits at once: sorting by the rest of the key
+// first costs 18.0 ms against 16.8 over a batch of 210 M suffixes in small sets, and 3.0 either
+// way at 50.1 M.  The mixed form does sort by it: repeats make its runs long (40 items and more),
+// and comparing one word of the key instead of two of the text tells most of them apart: 23.5
+// against 28.7 ms at 400 M suffixes with planted repeats.
 template <class Shape, bool MIXED, bool LCP>
 __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     const uint64_t *__restrict__ K, const uint32_t *__restrict__ V,
@@ -252,9 +262,10 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     __shared__ int16_t s_l[LCP ? kFrSpan : 1];   // lcp entries
     uint16_t *const s_at = s_list;               // where a sorted item's words lie
     __shared__ uint32_t s_cnt[kFrRows];
-    __shared__ uint64_t s_m0w[kFrReach + kFrRows], s_mw[kFrReach + kFrRows];
-    uint64_t *const s_m0 = s_m0w + kFrReach;     // starts of runs
+    __shared__ uint64_t s_mw[kFrReach + kFrRows];
     uint64_t *const s_m = s_mw + kFrReach;       // starts of groups
+    __shared__ uint64_t s_m0w[MIXED ? kFrReach + kFrRows : 1];
+    uint64_t *const s_m0 = MIXED ? s_m0w + kFrReach : s_m;  // starts of runs
     __shared__ uint64_t s_u[MIXED ? kFrRows : 1];  // starts of what a tile takes as a whole
     __shared__ uint64_t s_row[kFrRows];   // (count, last start) before each row
     __shared__ uint32_t s_tile, s_quit;
@@ -273,111 +284,104 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     }
     const int64_t lo = int64_t(tile) * kFrTile;
     const uint64_t kmask = (uint64_t(1) << key_bits) - 1;  // key_bits <= kKeyLenShift
-    uint64_t k[kFrItems];
-    uint32_t v[kFrItems];
+    {
+        uint64_t k[kFrItems];
+        uint32_t v[kFrItems];
 #pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int64_t gi = lo + j * kFrBlock + tid;
-        const bool in = gi >= 0 && gi < int64_t(n);
-        k[j] = in ? K[gi] : 0;
-        v[j] = in ? V[gi] : 0;
-    }
-    // a run is ordered by the bits below lo_bit (31 at most), equal ones by item
-    const uint64_t rest = (uint64_t(1) << lo_bit) - 1;
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        s_k[x] = k[j];
-        s_c[x] = ((k[j] & rest) << 32) | uint32_t(x);
-    }
-    // the rows before the span: their starts (in a long run, in order, also of its groups)
-    if (wave < uint32_t(kFrReach)) {
-        const int64_t gi = lo - kFrRun + int64_t(tid);
-        bool h = gi <= 0, g = gi <= 0;
-        if (!h) {
-            const uint64_t a = K[gi], d = (a ^ K[gi - 1]) & kmask;
-            h = d >> lo_bit || (a & 31u) < uint64_t(top_d);
-            g = d != 0 || (a & 31u) < uint64_t(h0);
+        for (int j = 0; j < kFrItems; ++j) {
+            const int64_t gi = lo + j * kFrBlock + tid;
+            const bool in = gi < int64_t(n);
+            k[j] = in ? K[gi] : 0;
+            v[j] = in ? V[gi] : 0;
         }
-        const uint64_t mh = ballot(h), mg = ballot(g);
-        if (lane == 0) {
-            s_m0w[wave] = mh;
-            s_mw[wave] = mg;
-        }
-    }
-    __syncthreads();
-    // starts of runs (positions outside the array count as runs of their own, and so does a
-    // suffix of fewer than top_d bases: it shares its top bits only with its equals, which are
-    // in position order)
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        const int64_t gi = lo + x;
-        bool h = gi <= 0 || gi >= int64_t(n);
-        if (!h) {
-            const uint64_t prev = x > 0 ? s_k[x - 1] : K[gi - 1];
-            h = ((k[j] ^ prev) & kmask) >> lo_bit || (k[j] & 31u) < uint64_t(top_d);
-        }
-        const uint64_t m = ballot(h);
-        if (lane == 0) s_m0[x >> 6] = m;
-    }
-    __syncthreads();
-    // each run in order of the whole key (equal keys keep their order)
-    int pos[kFrItems];
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        const int x = j * kFrBlock + tid;
-        int st, en;
-        pos[j] = x;
-        if (run_bounds(s_m0, kFrRows, x, &st, &en)) {
-            if (st >= 0 && en - st > 1) pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
-        } else if (!MIXED && x < kFrTile) {
-            s_quit = 1;
-        }
-    }
-    __syncthreads();
-    if (!MIXED && s_quit) {
-        if (tid == 0) {
-            st_agent(state + kStLongRun, 1u);
-            st_agent(lbflags + tile, kLb64Inc);
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < kFrItems; ++j) {
-        s_k[pos[j]] = k[j];
-        s_v[pos[j]] = v[j];
-        s_reach[pos[j]] = uint16_t(k[j] >> kKeyLenShift);
-    }
-    __syncthreads();
-    if (LCP) {  // the keys' codes, for the common prefixes of neighbours
+        const uint64_t rest = (uint64_t(1) << lo_bit) - 1;  // 31 bits at most
 #pragma unroll
         for (int j = 0; j < kFrItems; ++j) {
             const int x = j * kFrBlock + tid;
-            s_c[x] = key_codes(s_k[x], lo_bit, top_d, h0, err);
+            s_k[x] = k[j];
+            if (MIXED) {
+                s_c[x] = ((k[j] & rest) << 32) | uint32_t(x);
+            } else {
+                s_v[x] = v[j];
+                s_reach[x] = uint16_t(k[j] >> kKeyLenShift);
+                if (LCP) s_c[x] = key_codes(k[j], lo_bit, top_d, h0, err);  // for neighbours
+            }
+        }
+        // the rows before the span: their starts (in a long run, in order, also of its groups)
+        if (wave < uint32_t(kFrReach)) {
+            const int64_t gi = lo - kFrRun + int64_t(tid);
+            bool h = gi <= 0, g = gi <= 0;
+            if (!h) {
+                const uint64_t a = K[gi], d = (a ^ K[gi - 1]) & kmask;
+                h = d >> lo_bit || (a & 31u) < uint64_t(top_d);
+                g = d != 0 || (a & 31u) < uint64_t(h0);
+            }
+            const uint64_t mh = ballot(h), mg = ballot(g);
+            if (lane == 0) {
+                s_m0[int(wave) - kFrReach] = mh;
+                if (MIXED) s_mw[wave] = mg;
+            }
         }
         __syncthreads();
+        if (MIXED) {
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                const int x = j * kFrBlock + tid;
+                const int64_t gi = lo + x;
+                bool h = gi <= 0 || gi >= int64_t(n);
+                if (!h) {
+                    const uint64_t prev = x > 0 ? s_k[x - 1] : K[gi - 1];
+                    h = ((k[j] ^ prev) & kmask) >> lo_bit || (k[j] & 31u) < uint64_t(top_d);
+                }
+                const uint64_t m = ballot(h);
+                if (lane == 0) s_m0[x >> 6] = m;
+            }
+            __syncthreads();
+            int pos[kFrItems];
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                const int x = j * kFrBlock + tid;
+                int st, en;
+                pos[j] = x;
+                if (run_bounds(s_m0, kFrRows, x, &st, &en)) {  // equal keys keep their order
+                    if (st >= 0 && en - st > 1)
+                        pos[j] = st + count_below(s_c, st, en, ((k[j] & rest) << 32) | uint32_t(x));
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kFrItems; ++j) {
+                s_k[pos[j]] = k[j];
+                s_v[pos[j]] = v[j];
+                s_reach[pos[j]] = uint16_t(k[j] >> kKeyLenShift);
+                if (LCP) s_c[pos[j]] = key_codes(k[j], lo_bit, top_d, h0, err);
+            }
+            __syncthreads();
+        }
     }
-    // starts of groups equal on the whole key; a key of fewer than h0 symbols is a suffix that
-    // ended at its separator, alone in its group
+    // Starts of the groups that the windows begin with.  Positions outside the array count as
+    // groups of their own, and so does a suffix of fewer than depth0 bases: it shares its key
+    // only with its equals, which are in position order.
+    const uint32_t depth0 = MIXED ? h0 : top_d;  // symbols a group shares
 #pragma unroll
     for (int j = 0; j < kFrItems; ++j) {
         const int x = j * kFrBlock + tid;
         const int64_t gi = lo + x;
         const uint64_t key = s_k[x];
-        bool h = gi <= 0 || gi >= int64_t(n);
-        const bool first = h;
+        const bool edge = gi <= 0 || gi >= int64_t(n);
         // before the span: the last item of another run, which differs in its top bits whatever
         // its order, or one of the same long run, in order
-        const uint64_t prev = first ? 0 : x > 0 ? s_k[x - 1] : K[gi - 1];
-        if (!first) h = ((key ^ prev) & kmask) != 0 || (key & 31u) < uint64_t(h0);
+        const uint64_t prev = edge ? 0 : x > 0 ? s_k[x - 1] : K[gi - 1];
+        const uint64_t d = (key ^ prev) & kmask;
+        const bool h = edge || (MIXED ? d : d >> lo_bit) != 0 || (key & 31u) < uint64_t(depth0);
         if (LCP) {
-            int l = -1 - int(h0);
-            if (h && !first) {
+            int l = -1 - int(depth0);
+            if (edge) {
+                l = 0;
+            } else if (h) {
                 const uint64_t before = x > 0 ? s_c[x - 1] : key_codes(prev, lo_bit, top_d, h0, err);
                 l = int(key_lcp(before, s_c[x], uint32_t(prev), uint32_t(key), h0));
             }
-            if (first) l = 0;
             s_l[x] = int16_t(l);
         }
         const uint64_t m = ballot(h);
@@ -402,38 +406,58 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     }
     const int own0 = first_start(unit, kFrRows, 0), own1 = first_start(unit, kFrRows, kFrTile);
     // Groups of the tile are told apart by the text: windows of two stages, kExtStage bases
-    // each, while there are such groups.  Each window starts by listing their items, so that a
-    // window few items need takes few waves.
+    // each, while there are such groups.  Each window takes a list of their items, so that one
+    // which few items need takes few waves.
     uint32_t *const s_m32 = reinterpret_cast<uint32_t *>(s_m);
-#pragma unroll 1
-    for (int w = 0; w < kExtWindows; ++w) {
-        // opaque in the loop: what hangs on it is cheaper made again than kept in registers
-        uint32_t id = tid;
-        asm volatile("" : "+v"(id));
-        uint64_t in[kFrItems];
+    const auto list_items = [&](const uint64_t (&in)[kFrItems], const uint32_t (&place)[kFrItems]) {
+        // the places of the lanes of in[j], in the order of j and the threads; how many
 #pragma unroll
-        for (int j = 0; j < kFrItems; ++j) {
-            const int x = j * kFrBlock + int(id);
-            int st, en;
-            const bool small = run_bounds(s_m, kFrRows, x, &st, &en);
-            if (MIXED && !small && x >= own0 && x < own1) state[kStNoExt] = 1u;
-            in[j] = ballot(small && en - st > 1 && st >= own0 && st < own1);
-            if (lane == 0) s_cnt[x >> 6] = uint32_t(popc64(in[j]));
-        }
+        for (int j = 0; j < kFrItems; ++j)
+            if (lane == 0) s_cnt[j * kFrWaves + wave] = uint32_t(popc64(in[j]));
         __syncthreads();
         const uint32_t cnt = lane < uint32_t(kFrRows) ? s_cnt[lane] : 0u;
         const uint32_t inc = wave_incl_scan<Sum32>(cnt);
-        const uint32_t total = __shfl(inc, kFrRows - 1);
 #pragma unroll
         for (int j = 0; j < kFrItems; ++j) {
-            const int row = j * kFrWaves + int(id / kWave);
-            const uint32_t before = __shfl(inc - cnt, row);
+            const uint32_t before = __shfl(inc - cnt, j * kFrWaves + int(wave));
             if ((in[j] >> lane) & 1u)
-                s_list[before + uint32_t(popc64(in[j] & lanemask_lt()))] = uint16_t(row * 64 + int(lane));
+                s_list[before + uint32_t(popc64(in[j] & lanemask_lt()))] = uint16_t(place[j]);
         }
-        if (total == 0) break;  // the same for every wave
+        const uint32_t total = __shfl(inc, kFrRows - 1);
         __syncthreads();
-        const uint32_t depth = h0 + uint32_t(w) * 2 * kExtStage;
+        return total;
+    };
+    uint32_t total;
+    {
+        uint64_t in[kFrItems];
+        uint32_t place[kFrItems];
+#pragma unroll
+        for (int j = 0; j < kFrItems; ++j) {
+            const int x = j * kFrBlock + tid;
+            int st, en;
+            const bool small = run_bounds(s_m, kFrRows, x, &st, &en);
+            if (!small && x < kFrTile) {
+                if (!MIXED) s_quit = 1;
+                else if (x >= own0 && x < own1) state[kStNoExt] = 1u;
+            }
+            in[j] = ballot(small && en - st > 1 && st >= own0 && st < own1);
+            place[j] = uint32_t(x);
+        }
+        total = list_items(in, place);
+        if (!MIXED && s_quit) {
+            if (tid == 0) {
+                st_agent(state + kStLongRun, 1u);
+                st_agent(lbflags + tile, kLb64Inc);
+            }
+            return;
+        }
+    }
+#pragma unroll 1
+    for (int w = 0; w < kExtWindows && total > 0; ++w) {
+        // opaque in the loop: what hangs on it is cheaper made again than kept in registers
+        uint32_t id = tid;
+        asm volatile("" : "+v"(id));
+        const uint32_t depth = depth0 + uint32_t(w) * 2 * kExtStage;
         // an item of the thread: its place, where its position and reach lie (its place at the
         // window's start) and its group's bounds in one word each, 11 bits a place; and the
         // second stage's words.  What a barrier separates is read again from LDS: registers
@@ -510,10 +534,9 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
                 }
             }
             __syncthreads();
-            if (stage == 1) continue;
 #pragma unroll
             for (int j = 0; j < kFrItems; ++j) {
-                if (at[j] == kFrNone) continue;
+                if (at[j] == kFrNone || !grp[j]) continue;
                 const int x = int(at[j] & 0xffffu);
                 const uint32_t st = uint32_t(run_start(s_m, x)), en = uint32_t(run_end(s_m, kFrRows, x));
                 grp[j] = en - st > 1 ? st | (en << 16) : 0u;  // 0: alone
@@ -527,13 +550,16 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
             r2[j] = s_reach[at[j] >> 16];
         }
         __syncthreads();
+        uint64_t in[kFrItems];
 #pragma unroll
         for (int j = 0; j < kFrItems; ++j) {
+            in[j] = ballot(at[j] != kFrNone && grp[j] != 0);
             if (at[j] == kFrNone) continue;
-            s_v[at[j] & 0xffffu] = v2[j];
-            s_reach[at[j] & 0xffffu] = uint16_t(r2[j]);
+            at[j] &= 0xffffu;
+            s_v[at[j]] = v2[j];
+            s_reach[at[j]] = uint16_t(r2[j]);
         }
-        __syncthreads();
+        total = list_items(in, at);
     }
     __syncthreads();
     // Wave 0: per row of 64, the tile's suffixes still in groups (not both they and the next

@@ -485,9 +485,10 @@ struct Build {
         return SA_OK;
     }
 
-    int round_end() {
+    // shared: symbols the suffixes of a group share when the text's windows begin
+    int round_end(int shared = 0) {
         hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, L.state, uint32_t(h0),
-                           top_bits ? uint32_t(h0 + kExtBases) : 0u);
+                           shared ? uint32_t(shared + kExtBases) : 0u);
         SA_HIP(hipGetLastError());
         return SA_OK;
     }
@@ -523,7 +524,7 @@ struct Build {
         SA_TRY(first_sort(lo_bit, &cur));
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, false, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
-        SA_TRY(round_end());
+        SA_TRY(round_end(top_d));
         SA_TRY(wait_state(ps, host));
         if (host[kStLongRun] == 0) return SA_OK;
         // Some run of equal top bits is too long for the run sort: its items are taken out,
@@ -550,7 +551,7 @@ struct Build {
         SA_TRY(launch_fill_u32(L.tickets, 1, 0, s));
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, true, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
-        SA_TRY(round_end());
+        SA_TRY(round_end(h0));
         SA_TRY(wait_state(ps, host));
         timing_round_items(tag, n, host[kStBigLast]);
         return SA_OK;
