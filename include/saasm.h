@@ -230,7 +230,8 @@ int64_t sa_lcp_plcp_min(int64_t min_n);
 /* fragment -- is a prefix of a suffix of the text).                                          */
 /* ---------------------------------------------------------------------------------------- */
 
-/* Workspace bytes for sa_lookup on a text of n bytes with patterns of pat_total bytes in all. */
+/* Workspace bytes for sa_lookup on a text of n bytes with patterns of pat_total bytes in all.
+ * (It takes up to 4 MiB less too, without the samples of the array its search starts from.) */
 int64_t sa_lookup_ws_bytes(int64_t n, int64_t pat_total);
 
 /* sa_lookup: for each pattern P_i = pat[pat_off[i] .. pat_off[i+1]) over A, C, G, T, the
