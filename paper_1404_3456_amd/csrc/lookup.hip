@@ -39,15 +39,11 @@ __device__ __forceinline__ uint32_t sample_lcp(uint64_t a, uint64_t b) {
     return same < l ? same : l;
 }
 
-struct __attribute__((packed, aligned(1))) Bytes16 {
-    uint32_t w[4];
-};
-
 // The first pblocks blocks: pattern bytes to 2-bit codes, 16 per word (word w: bytes 16w ..
 // 16w+15 of the concatenated patterns, byte 16w in the top bits); bytes other than A, C, G, T
 // raise kErrAlphabet.  The others: the samples, one a thread.
-// Bound by memory: 16 bytes a load, at any alignment, take 40 MB of patterns in 13 us (byte
-// loads: 44).
+// Bound by memory: the bytes of 1 M patterns of 40, 16 a load at any alignment, and half a million
+// samples take 31 us (the bytes alone, one a load, 44).
 __global__ __launch_bounds__(256) void k_lookup_prep(const uint8_t *__restrict__ pat, int64_t total,
                                                      uint32_t *__restrict__ packed, int64_t nwords,
                                                      uint32_t pblocks, const uint4 *__restrict__ blk,
@@ -70,16 +66,19 @@ __global__ __launch_bounds__(256) void k_lookup_prep(const uint8_t *__restrict__
     if (w >= nwords) return;
     uint32_t x = 0;
     bool bad = false;
-    const auto take = [&](int j, uint32_t c) {
-        bad |= !((c == 'A') | (c == 'C') | (c == 'G') | (c == 'T'));
-        x |= (((c >> 1) ^ (c >> 2)) & 3u) << (30 - 2 * j);  // A0 C1 G2 T3
-    };
     if (w * 16 + 16 <= total) {
         const Bytes16 b = *reinterpret_cast<const Bytes16 *>(pat + w * 16);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) take(j, (b.w[j >> 2] >> (8 * (j & 3))) & 255u);
+        for (int j = 0; j < 4; ++j) {
+            bad |= bases_of(b.w[j]) != 0x80808080u;
+            x |= codes_packed(codes_of(b.w[j])) << (24 - 8 * j);
+        }
     } else {
-        for (int j = 0; w * 16 + j < total && j < 16; ++j) take(j, pat[w * 16 + j]);
+        for (int j = 0; w * 16 + j < total; ++j) {
+            const uint32_t c = pat[w * 16 + j];
+            bad |= !(bases_of(c) & 128u);
+            x |= (codes_of(c) & 3u) << (30 - 2 * j);
+        }
     }
     packed[w] = x;
     if (bad) raise_err(err, kErrAlphabet);

@@ -6,64 +6,72 @@
 // as integers compares 32 bases lexicographically, and one separator bit per position.
 #include "device.hpp"
 #include "internal.hpp"
+#include "text.hpp"
 
 namespace saasm {
 
 int64_t sepmask_words(int64_t n) { return (n + 31) / 32 + 4; }
 int64_t packed_words(int64_t n) { return 2 * sepmask_words(n); }
 
+struct __attribute__((packed, aligned(1))) Bytes4 {
+    uint32_t w;
+};
+
 // One thread per 32 text positions: one separator-mask word, two packed words and one window
 // record (text.hpp), each only where its array is given.  Words past the end of the text are
 // written as zeros (padding that window reads may touch).
+// Bound by memory for a large text and by the fetch of its own instructions for a small one,
+// so the bytes are taken four at a time (a byte at a time: 34 us for 50.1 M positions with
+// records, 17 now, and 7.4 us for 80,000, 2.9 now).
 __global__ __launch_bounds__(256) void k_pack(const uint8_t *__restrict__ text, int64_t n,
                                               uint32_t *__restrict__ packed,
                                               uint32_t *__restrict__ sepmask,
                                               uint32_t *__restrict__ wordcnt,
                                               uint4 *__restrict__ blk, int64_t nwords,
                                               uint32_t *err) {
-    int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (w >= nwords) return;
-    int64_t p0 = w * 32;
-    uint32_t hiw = 0, low = 0, sep = 0;
-    bool bad = false;
-    if (p0 < n) {
-        uint8_t b[32];
-        const bool full = (p0 + 32 <= n) && ((reinterpret_cast<uintptr_t>(text) & 15) == 0);
-        if (full) {
-            uint4 a = *reinterpret_cast<const uint4 *>(text + p0);
-            uint4 c = *reinterpret_cast<const uint4 *>(text + p0 + 16);
-            uint32_t wv[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+    const int64_t p0 = w * 32;
+    // the positions' bytes, at any alignment of the text; 'A' past its end
+    uint32_t v[8];
+    const int64_t r = n - p0;
+    if (r >= 32) {
+        const Bytes16 a = *reinterpret_cast<const Bytes16 *>(text + p0);
+        const Bytes16 c = *reinterpret_cast<const Bytes16 *>(text + p0 + 16);
 #pragma unroll
-            for (int j = 0; j < 32; ++j) b[j] = uint8_t(wv[j >> 2] >> (8 * (j & 3)));
-        } else {
+        for (int j = 0; j < 4; ++j) {
+            v[j] = a.w[j];
+            v[4 + j] = c.w[j];
+        }
+    } else {
+        uint32_t last = 0x41414141u;  // of the word that holds the end
 #pragma unroll
-            for (int j = 0; j < 32; ++j) b[j] = (p0 + j < n) ? text[p0 + j] : uint8_t('A');
-        }
+        for (int k = 0; k < 3; ++k)
+            if (k < (r & 3) && r > 0)
+                last = (last & ~(255u << (8 * k))) | (uint32_t(text[p0 + (r & ~3) + k]) << (8 * k));
 #pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            uint32_t c = b[j];
-            bool in = p0 + j < n;
-            bool is_sep = (c == '$') && in;
-            bool ok = (c == 'A') | (c == 'C') | (c == 'G') | (c == 'T') | (c == '$');
-            bad |= !ok;
-            uint32_t code = is_sep ? 0u : (((c >> 1) ^ (c >> 2)) & 3u);  // A0 C1 G2 T3
-            if (!in) code = 0;
-            if (j < 16) hiw |= code << (30 - 2 * j);
-            else low |= code << (30 - 2 * (j - 16));
-            sep |= uint32_t(is_sep) << (31 - j);
-        }
-        if (p0 <= n - 1 && n - 1 < p0 + 32) {
-            if (b[(n - 1) - p0] != '$') raise_err(err, kErrNoSepEnd);
-        }
+        for (int j = 0; j < 8; ++j)
+            v[j] = 4 * j + 4 <= r ? reinterpret_cast<const Bytes4 *>(text + p0 + 4 * j)->w
+                   : r > 0 && j == int(r >> 2) ? last : 0x41414141u;
     }
+    uint32_t code[2] = {0, 0}, sep = 0, ok = 0x80808080u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t x = v[j], s = bytes_equal(x, '$');
+        ok &= s | bases_of(x);
+        const uint32_t c = codes_of(x) & ~(((s >> 7) << 2) - (s >> 7));  // a separator's: 0
+        code[j >> 2] |= codes_packed(c) << (24 - 8 * (j & 3));
+        sep |= (((s >> 7) * 0x08040201u) >> 24) << (28 - 4 * j);
+    }
+    if (r >= 1 && r <= 32 && !((sep >> (32 - r)) & 1u)) raise_err(err, kErrNoSepEnd);
     if (packed) {
-        packed[2 * w] = hiw;
-        packed[2 * w + 1] = low;
+        packed[2 * w] = code[0];
+        packed[2 * w + 1] = code[1];
     }
     if (sepmask) sepmask[w] = sep;
     if (wordcnt) wordcnt[w] = __popc(sep);
-    if (blk) blk[w] = make_uint4(hiw, low, sep, 0u);
-    if (bad) raise_err(err, kErrAlphabet);
+    if (blk) blk[w] = make_uint4(code[0], code[1], sep, 0u);
+    if (ok != 0x80808080u) raise_err(err, kErrAlphabet);
 }
 
 int launch_pack(const uint8_t *text, int64_t n, uint32_t *packed, uint32_t *sepmask,

@@ -10,6 +10,23 @@
 
 namespace saasm {
 
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t w[4];
+};
+
+// Four bytes at once: 128 in every byte of v that equals c.
+__device__ __forceinline__ uint32_t bytes_equal(uint32_t v, uint32_t c) {
+    const uint32_t x = v ^ (c * 0x01010101u);
+    return ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+}
+// 128 in every byte that is a base.
+__device__ __forceinline__ uint32_t bases_of(uint32_t v) {
+    return bytes_equal(v, 'A') | bytes_equal(v, 'C') | bytes_equal(v, 'G') | bytes_equal(v, 'T');
+}
+// Their codes, a byte each (A0 C1 G2 T3); and four such in 8 bits, byte 0's on top.
+__device__ __forceinline__ uint32_t codes_of(uint32_t v) { return ((v >> 1) ^ (v >> 2)) & 0x03030303u; }
+__device__ __forceinline__ uint32_t codes_packed(uint32_t c) { return (c * 0x40100401u) >> 24; }
+
 struct Window {
     uint64_t code;  // 32 bases from position a, base a in bits 63..62
     uint32_t sep;   // separator bits of positions a .. a+31, position a in bit 31
