@@ -192,4 +192,23 @@ __device__ __forceinline__ uint32_t block_excl_sum(uint32_t v, uint32_t *lds, ui
     return before + inc - v;
 }
 
+// Counts the digits of f (D bits each) of the calling lanes in the LDS histogram s_h, items in
+// order over the lanes, one add for every stretch of lanes with the same digit: long groups
+// hold the same upper digits throughout, and 64 adds to one word take their turns.
+template <int D>
+__device__ __forceinline__ void hist_add_streaks(uint32_t *s_h, uint64_t f, int passes) {
+    constexpr int R = 1 << D;
+    const uint32_t lane = lane_id();
+    const uint64_t act = ballot(true);
+    const bool follows = lane > 0 && ((act >> (lane - 1)) & 1u);
+    const uint64_t above = lane == 63 ? 0 : ~uint64_t(0) << (lane + 1);
+    for (int p = 0; p < passes; ++p) {
+        const uint32_t d = uint32_t(f >> (p * D)) & (R - 1);
+        const uint32_t up = __shfl_up(d, 1);
+        const bool head = !(follows && up == d);
+        const uint64_t ends = (ballot(head) | ~act) & above;
+        if (head) atomicAdd(&s_h[p * R + d], (ends ? uint32_t(__ffsll((long long)ends)) - 1u : 64u) - lane);
+    }
+}
+
 }  // namespace saasm

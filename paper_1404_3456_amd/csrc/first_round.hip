@@ -270,18 +270,18 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     __shared__ uint64_t s_row[kFrRows];   // (count, last start) before each row
     __shared__ uint32_t s_tile, s_quit;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    // Once a long run is known no workgroup takes another ticket (all take them from one word,
+    // one every 11 ns, 3.3 ms for the tiles of 400 M suffixes, 0.2 without): tiles look back at
+    // lower tickets only, and every one taken is published.
     if (tid == 0) {
-        s_tile = ticket(tick);
         s_quit = MIXED ? 0u : ld_agent(state + kStLongRun);
+        if (!s_quit) s_tile = ticket(tick);
     }
     __syncthreads();
+    if (s_quit) return;
     const uint32_t tile = s_tile;
     const uint32_t ntiles = (n + kFrTile - 1) / kFrTile;
     if (tile >= ntiles) return;
-    if (s_quit) {  // later tiles look back at this one: publish something and stop
-        if (tid == 0) st_agent(lbflags + tile, kLb64Inc);
-        return;
-    }
     const int64_t lo = int64_t(tile) * kFrTile;
     const uint64_t kmask = (uint64_t(1) << key_bits) - 1;  // key_bits <= kKeyLenShift
     {
@@ -642,14 +642,19 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     }
 }
 
-// The items of runs (as in k_first_runs) of more than kFrRun items, in order, with their whole keys and
-// their places in the list, and the digit counts of the passes that sort them.  The runs'
-// starts come from masks of 64 items: an item's run is long when the distance back to its
+// The items of runs (as in k_first_runs) of more than kFrRun items, in order, with their whole
+// keys and their places in the list, and the digit counts of the passes that sort them.  The
+// runs' starts come from masks of 64 items: an item's run is long when the distance back to its
 // start plus the distance on to the next, each sought two rows away, exceeds kFrRun.
+// Bound by the waves in flight (keys read, and a look-back a tile): 1.9 ms over 400 M suffixes,
+// 0.6 for the read alone.  One row at a time 2.1, four 2.3 (fewer waves fit); with one LDS add
+// an item for the counts, 1.3 ms more: a long run's items share their upper digits.
 constexpr int kFxBlock = 512;
 constexpr int kFxWaves = kFxBlock / kWave;
 constexpr int kFxRows = 128;                  // rows of 64 items per tile
 constexpr int kFxTile = kFxRows * kWave;
+constexpr int kFxLoad = 2;                    // rows a wave has on their way
+static_assert(kFxRows % (kFxLoad * kFxWaves) == 0, "whole steps over a tile's rows");
 static_assert(kFxTile >= kFirstMinTile, "look-back words are sized for tiles of kFirstMinTile items");
 
 template <int D>
@@ -679,15 +684,26 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
         const uint32_t tile = s_tile;
         if (tile >= ntiles) break;
         const int64_t tbase = int64_t(tile) * kFxTile;
-        for (int r = int(wave); r < kFxRows + 4; r += kFxWaves) {
-            const int64_t i = tbase + int64_t(r - 2) * kWave + lane;
-            bool h = i <= 0 || i >= int64_t(n);
-            if (!h) {
-                const uint64_t k = K[i];
-                h = ((k ^ K[i - 1]) & kmask) >> lo_bit || (k & 31u) < uint64_t(top_d);
+        for (int r0 = int(wave); r0 < kFxRows + 4; r0 += kFxLoad * kFxWaves) {
+            uint64_t k[kFxLoad], q[kFxLoad];  // the row's keys; the one before it, in lane 0
+#pragma unroll
+            for (int j = 0; j < kFxLoad; ++j) {
+                const int r = r0 + j * kFxWaves;
+                const int64_t i = tbase + int64_t(r - 2) * kWave + lane;
+                const bool in = r < kFxRows + 4 && i >= 0 && i < int64_t(n);
+                k[j] = in ? K[i] : 0;
+                q[j] = in && lane == 0 && i > 0 ? K[i - 1] : 0;
             }
-            const uint64_t m = ballot(h);
-            if (lane == 0) s_m[r] = m;
+#pragma unroll
+            for (int j = 0; j < kFxLoad; ++j) {
+                const int r = r0 + j * kFxWaves;
+                const int64_t i = tbase + int64_t(r - 2) * kWave + lane;
+                const uint64_t up = __shfl_up((unsigned long long)k[j], 1);
+                const uint64_t d = (k[j] ^ (lane ? up : q[j])) & kmask;
+                const uint64_t m = ballot(i <= 0 || i >= int64_t(n) || d >> lo_bit ||
+                                          (k[j] & 31u) < uint64_t(top_d));
+                if (lane == 0 && r < kFxRows + 4) s_m[r] = m;
+            }
         }
         __syncthreads();
         for (int r = int(wave); r < kFxRows; r += kFxWaves) {
@@ -719,21 +735,32 @@ __global__ __launch_bounds__(kFxBlock) void k_first_extract(
             if (lane == 0 && tile == ntiles - 1) state[kStRadixN] = uint32_t(before + agg);
         }
         __syncthreads();
-        for (int r = int(wave); r < kFxRows; r += kFxWaves) {
-            const uint64_t b = s_big[r];
-            if (!((b >> lane) & 1u)) continue;
-            const uint32_t i = uint32_t(tbase) + uint32_t(r) * kWave + lane;
-            const uint32_t j = s_cnt[r] + uint32_t(popc64(b & lanemask_lt()));
-            if (j >= n) {
-                raise_err(err, kErrRange);
-                continue;
+        for (int r0 = int(wave); r0 < kFxRows; r0 += kFxLoad * kFxWaves) {
+            uint64_t k[kFxLoad];
+            uint32_t v[kFxLoad];
+#pragma unroll
+            for (int j = 0; j < kFxLoad; ++j) {
+                const int r = r0 + j * kFxWaves;
+                if (!((s_big[r] >> lane) & 1u)) continue;
+                const int64_t i = tbase + int64_t(r) * kWave + lane;
+                k[j] = K[i];
+                v[j] = V[i];
             }
-            keys[j] = K[i];
-            vals[j] = V[i];
-            idx[j] = i;
-            const uint64_t key = K[i] & kmask;
-            for (int p = 0; p < passes; ++p)
-                atomicAdd(&s_h[p * R + uint32_t((key >> (p * D)) & (R - 1))], 1u);
+#pragma unroll
+            for (int j = 0; j < kFxLoad; ++j) {
+                const int r = r0 + j * kFxWaves;
+                const uint64_t b = s_big[r];
+                if (!((b >> lane) & 1u)) continue;
+                const uint32_t at = s_cnt[r] + uint32_t(popc64(b & lanemask_lt()));
+                if (at >= n) {
+                    raise_err(err, kErrRange);
+                    continue;
+                }
+                keys[at] = k[j];
+                vals[at] = v[j];
+                idx[at] = uint32_t(tbase) + uint32_t(r) * kWave + lane;
+                hist_add_streaks<D>(s_h, k[j] & kmask, passes);
+            }
         }
     }
     __syncthreads();

@@ -820,7 +820,7 @@ __global__ __launch_bounds__(kBxBlock) void k_big_extract(
             keys[j] = key;
             vals[j] = p;
             bigidx[j] = i;
-            hist_add<D>(s_h, key, passes);
+            hist_add_streaks<D>(s_h, key, passes);
         }
     }
     __syncthreads();
