@@ -74,13 +74,29 @@ __device__ __forceinline__ uint32_t name_index(uint32_t pos, uint32_t n1) {
     return pos % 3u == 1u ? pos / 3u : n1 + pos / 3u;
 }
 
+// What the naming that follows needs cleared, by the kernel that makes its keys: the look-back
+// words of its tiles, its ticket, and the three zeros past the end of the level's ranks and of
+// its name string (launches of their own took 5 us each).
+struct D3Clear {
+    uint64_t *lbflags;
+    uint32_t nlb;
+    uint32_t *tick, *rank_end, *R_end;
+};
+__device__ __forceinline__ void d3_clear(const D3Clear &z) {
+    const uint32_t x = blockIdx.x * kD3Block + threadIdx.x;
+    for (uint32_t i = x; i < z.nlb; i += gridDim.x * kD3Block) z.lbflags[i] = 0;
+    if (x == 0) *z.tick = 0;
+    if (x < 3) z.rank_end[x] = z.R_end[x] = 0;
+}
+
 // ---- step 1: sample keys --------------------------------------------------------------------
 // Top level: three 3-bit symbols, those after a separator set to 0; a key whose last symbol
 // is 0 holds a separator.
 __global__ __launch_bounds__(kD3Block) void k_d3_keys_top(const uint8_t *__restrict__ text,
                                                           uint32_t n, uint32_t n12,
                                                           uint64_t *__restrict__ keys,
-                                                          uint32_t *__restrict__ vals) {
+                                                          uint32_t *__restrict__ vals, D3Clear z) {
+    d3_clear(z);
     for (uint32_t j = blockIdx.x * kD3Block + threadIdx.x; j < n12; j += gridDim.x * kD3Block) {
         const uint32_t p = sample_pos(j);
         uint32_t c0 = text_sym(text[p]);
@@ -96,7 +112,8 @@ __global__ __launch_bounds__(kD3Block) void k_d3_keys_top(const uint8_t *__restr
 __global__ __launch_bounds__(kD3Block) void k_d3_keys(const uint32_t *__restrict__ s,
                                                       uint32_t n12, int b, int mode,
                                                       uint64_t *__restrict__ keys,
-                                                      uint32_t *__restrict__ vals) {
+                                                      uint32_t *__restrict__ vals, D3Clear z) {
+    d3_clear(z);
     for (uint32_t j = blockIdx.x * kD3Block + threadIdx.x; j < n12; j += gridDim.x * kD3Block) {
         const uint32_t p = sample_pos(j);
         uint64_t k;
@@ -124,19 +141,22 @@ __global__ __launch_bounds__(kD3Block) void k_d3_rekey(const uint32_t *__restric
 constexpr int kNsItems = 16;                      // sorted samples per thread of the name scan
 constexpr int kNsTile = kD3Block * kNsItems;
 
-// Names in sorted order: nm[j] = number of distinct triples among sorted samples 0..j.  A
+// Names: the j-th sorted sample's is the number of distinct triples among samples 0..j, written
+// to its place in the name string (read where names repeat: the recursion ranks the samples).  A
 // sample starts a new name when its key differs from its predecessor's (at the top level also
 // when its triple holds a separator; with two sorts also when the last names differ).  One
 // pass: head flags, a workgroup scan and a decoupled look-back over tiles; the last tile
 // writes the name count to *total.  A tile is kNsItems rows of kD3Block consecutive samples,
-// each row read and written by the whole workgroup (coalesced); a row's heads are counted
-// with one ballot per wave.
+// each row read by the whole workgroup (coalesced); a row's heads are counted with one ballot
+// per wave.  Bound by the scattered words: 109 us for 6.7 M samples, 139 with the names written
+// in order first and scattered by a kernel of their own.
 template <bool TOP>
 __global__ __launch_bounds__(kD3Block) void k_d3_name_scan(const uint64_t *__restrict__ keys,
                                                            const uint32_t *__restrict__ vals,
                                                            const uint32_t *__restrict__ s,
-                                                           uint32_t n12, int two_sort,
-                                                           uint32_t *__restrict__ nm,
+                                                           uint32_t n12, uint32_t n1,
+                                                           int two_sort,
+                                                           uint32_t *__restrict__ R,
                                                            uint32_t *total, uint64_t *lbflags,
                                                            uint32_t *tick, uint32_t *err) {
     constexpr int W = kD3Block / kWave;
@@ -149,15 +169,17 @@ __global__ __launch_bounds__(kD3Block) void k_d3_name_scan(const uint64_t *__res
     const uint32_t base = tile * uint32_t(kNsTile) + tid;
     uint32_t heads = 0;
     uint32_t below[kNsItems];  // heads of lower lanes of this wave in the same row
+    uint32_t pos[kNsItems];
 #pragma unroll
     for (int r = 0; r < kNsItems; ++r) {
         const uint32_t i = base + uint32_t(r) * kD3Block;
         bool head = false;
+        pos[r] = i < n12 ? vals[i] : 0u;
         if (i < n12) {
             const uint64_t k = keys[i];
             head = i == 0 || k != keys[i - 1];
             if constexpr (TOP) head = head || (k & 7u) == 0;  // holds a separator
-            else if (two_sort && !head) head = s[vals[i] + 2] != s[vals[i - 1] + 2];
+            else if (two_sort && !head) head = s[pos[r] + 2] != s[vals[i - 1] + 2];
         }
         const uint64_t m = ballot(head);
         below[r] = uint32_t(popc64(m & lanemask_lt()));
@@ -187,29 +209,20 @@ __global__ __launch_bounds__(kD3Block) void k_d3_name_scan(const uint64_t *__res
             row += c;
         }
         const uint32_t i = base + uint32_t(r) * kD3Block;
-        if (i < n12) nm[i] = row_base + before + below[r] + ((heads >> r) & 1u);
+        if (i < n12) R[name_index(pos[r], n1)] = row_base + before + below[r] + ((heads >> r) & 1u);
         row_base += row;
     }
     if (tid == 0 && (tile + 1) * uint64_t(kNsTile) >= n12) *total = s_excl + tile_total;
 }
 
-// Names of the sorted samples to where the next step reads them: into the name string when
-// names repeat (the recursion ranks the samples), else the ranks themselves (name = j + 1)
-// and the sample order.
-__global__ __launch_bounds__(kD3Block) void k_d3_scatter(const uint32_t *__restrict__ vals,
-                                                         const uint32_t *__restrict__ nm,
-                                                         uint32_t n12, uint32_t n1, int unique,
-                                                         uint32_t *__restrict__ R,
-                                                         uint32_t *__restrict__ sa12,
-                                                         uint32_t *__restrict__ rank) {
+// Every name is one sample's: the samples' order and ranks are those of the sort.
+__global__ __launch_bounds__(kD3Block) void k_d3_ranks(const uint32_t *__restrict__ vals,
+                                                       uint32_t n12, uint32_t *__restrict__ sa12,
+                                                       uint32_t *__restrict__ rank) {
     for (uint32_t j = blockIdx.x * kD3Block + threadIdx.x; j < n12; j += gridDim.x * kD3Block) {
         const uint32_t p = vals[j];
-        if (unique) {
-            rank[p] = j + 1u;
-            sa12[j] = p;
-        } else {
-            R[name_index(p, n1)] = nm[j];
-        }
+        rank[p] = j + 1u;
+        sa12[j] = p;
     }
 }
 
@@ -278,23 +291,34 @@ __device__ __forceinline__ bool d3_less(const Rec &a, uint32_t ap, const Rec &b,
 }
 
 // Merge-path split of every tile boundary: split[t] = how many of the first t * kMgTile
-// outputs come from A (the 0 mod 3 list).
+// outputs come from A (the 0 mod 3 list).  Bound by the chain of its reads, so kSpLanes lanes
+// look at as many points at once: 7 steps for 3.3 M positions instead of 22 (23 us, 45 with
+// one lane).
+constexpr int kSpLanes = 8;
 __global__ __launch_bounds__(kD3Block) void k_d3_split(const uint4 *__restrict__ rec, uint32_t n,
                                                        const uint32_t *__restrict__ A, uint32_t na,
                                                        const uint32_t *__restrict__ B, uint32_t nb,
                                                        uint32_t ntiles,
                                                        uint32_t *__restrict__ split) {
-    for (uint32_t t = blockIdx.x * kD3Block + threadIdx.x; t <= ntiles; t += gridDim.x * kD3Block) {
+    const uint32_t lane = lane_id(), k = lane % kSpLanes, first = lane - k;
+    const uint32_t groups = gridDim.x * (kD3Block / kSpLanes);
+    for (uint32_t t = (blockIdx.x * kD3Block + threadIdx.x) / kSpLanes; t <= ntiles; t += groups) {
         const uint64_t dd = uint64_t(t) * kMgTile;
         const uint32_t d = dd < n ? uint32_t(dd) : n;
         uint32_t lo = d > nb ? d - nb : 0u, hi = d < na ? d : na;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
+        while (lo < hi) {  // the same for the lanes of a group
+            const auto point = [&](uint32_t j) {
+                return lo + uint32_t(uint64_t(hi - lo) * (j + 1) / (kSpLanes + 1));
+            };
+            const uint32_t mid = point(k);
             const uint32_t ap = A[mid], bp = B[d - 1 - mid];
-            if (d3_less(load_rec(rec, ap), ap, load_rec(rec, bp), bp)) lo = mid + 1;
-            else hi = mid;
+            const uint64_t m = ballot(d3_less(load_rec(rec, ap), ap, load_rec(rec, bp), bp)) >> first;
+            const uint32_t less = uint32_t(__ffsll((long long)~(m & ((1u << kSpLanes) - 1)))) - 1u;
+            const uint32_t l = less ? point(less - 1) + 1 : lo;  // a point that is less
+            if (less < uint32_t(kSpLanes)) hi = point(less);     // and the next, which is not
+            lo = l;
         }
-        split[t] = lo;
+        if (k == 0) split[t] = lo;
     }
 }
 
@@ -380,7 +404,6 @@ struct Level {
 
 struct Layout {
     std::vector<Level> lev;
-    uint32_t *nm = nullptr;     // [n12 of the top] names in sorted order
     uint4 *rec = nullptr;       // [n of the top] comparison records
     uint64_t *lbflags = nullptr;
     uint32_t *tick = nullptr;
@@ -414,7 +437,6 @@ void carve_dc3(Carver &c, int64_t n, const Tune &t, uint32_t *top_out, Layout *L
     }
     const int64_t n12 = L->lev[0].n12 > 0 ? L->lev[0].n12 : 1;
     const int64_t items = std::max<int64_t>(n12, L->lev[0].n0);
-    L->nm = c.take<uint32_t>(n12);
     L->rec = c.take<uint4>(n);
     L->lbflags = c.take<uint64_t>(n12 / kNsTile + 16);
     L->tick = c.take<uint32_t>(64);
@@ -436,9 +458,8 @@ struct Dc3 {
         return sort_run(L.sb, cur, nullptr, count, 0, bits, t, nparts, st, cur_out);
     }
 
-    int read_words(uint32_t host[2]) {
-        SA_HIP(hipMemcpyAsync(host, L.state, 8, hipMemcpyDeviceToHost, st));
-        SA_HIP(hipStreamSynchronize(st));
+    int read_state(uint32_t host[kStWords]) {
+        SA_TRY(read_words(L.state, host, st));
         timing_poll();
         return SA_OK;
     }
@@ -451,17 +472,19 @@ struct Dc3 {
         const unsigned g = grid_for(v.n12);
         int cur = 0, bits = 0;
         bool two = false;
+        const int64_t ntiles = (v.n12 + kNsTile - 1) / kNsTile;
+        const D3Clear z = {L.lbflags, uint32_t(ntiles), L.tick, v.rank + v.n, v.R + v.n12};
         {
             TimedScope ts("dc3_keys", double(v.n12) * (top ? 15.0 : 24.0), st);
             if (top) {
                 hipLaunchKernelGGL(k_d3_keys_top, dim3(g), dim3(kD3Block), 0, st, text,
-                                   uint32_t(v.n), n12, L.sb.keys[0], L.sb.vals[0]);
+                                   uint32_t(v.n), n12, L.sb.keys[0], L.sb.vals[0], z);
                 bits = 9;
             } else {
                 const int b = bits_for(v.K);
                 two = 3 * b > 64;
                 hipLaunchKernelGGL(k_d3_keys, dim3(g), dim3(kD3Block), 0, st, v.s, n12, b,
-                                   two ? 1 : 0, L.sb.keys[0], L.sb.vals[0]);
+                                   two ? 1 : 0, L.sb.keys[0], L.sb.vals[0], z);
                 bits = two ? b : 3 * b;
             }
             ts.finish();
@@ -477,41 +500,34 @@ struct Dc3 {
             SA_HIP(hipGetLastError());
             SA_TRY(sort(v.n12, 2 * b, cur, &cur));
         }
-        const int64_t ntiles = (v.n12 + kNsTile - 1) / kNsTile;
-        SA_TRY(launch_fill_u64(L.lbflags, ntiles, 0, st));
-        SA_TRY(launch_fill_u32(L.tick, 1, 0, st));
         {
-            // keys 8 (+ 8 for the first two names' comparison with two sorts) + names 4
-            TimedScope ts("dc3_names", double(v.n12) * (two ? 20.0 : 12.0), st);
+            // keys 8 (+ 8 for the last names' comparison with two sorts), positions 4, names 4
+            TimedScope ts("dc3_names", double(v.n12) * (two ? 24.0 : 16.0), st);
             if (top)
                 hipLaunchKernelGGL(k_d3_name_scan<true>, dim3(unsigned(ntiles)), dim3(kD3Block), 0,
-                                   st, L.sb.keys[cur], L.sb.vals[cur], v.s, n12, 0, L.nm,
+                                   st, L.sb.keys[cur], L.sb.vals[cur], v.s, n12, uint32_t(v.n1), 0, v.R,
                                    L.state + 1, L.lbflags, L.tick, L.state);
             else
                 hipLaunchKernelGGL(k_d3_name_scan<false>, dim3(unsigned(ntiles)), dim3(kD3Block), 0,
-                                   st, L.sb.keys[cur], L.sb.vals[cur], v.s, n12, two ? 1 : 0, L.nm,
+                                   st, L.sb.keys[cur], L.sb.vals[cur], v.s, n12, uint32_t(v.n1), two ? 1 : 0, v.R,
                                    L.state + 1, L.lbflags, L.tick, L.state);
             ts.finish();
             SA_HIP(hipGetLastError());
         }
-        uint32_t host[2];
-        SA_TRY(read_words(host));
+        uint32_t host[kStWords];
+        SA_TRY(read_state(host));
         if (host[0]) return fail(host[0] & kErrAlphabet ? SA_ERR_ALPHABET : SA_ERR_HIP,
                                  "sa_build_dc3: device check failed (code " + std::to_string(host[0]) + ")");
         if (host[1] < 1 || host[1] > n12) return fail(SA_ERR_HIP, "sa_build_dc3: bad name count");
         *descend = host[1] < n12;
         if (*descend) {
             L.lev[d + 1].K = host[1];
-            SA_TRY(launch_fill_u32(v.R + v.n12, 3, 0, st));
+            return SA_OK;
         }
-        {
-            // positions 4 + names 4 (descending) or sample order 4; one scattered word
-            TimedScope ts("dc3_names", double(v.n12) * 12.0, st);
-            hipLaunchKernelGGL(k_d3_scatter, dim3(g), dim3(kD3Block), 0, st, L.sb.vals[cur], L.nm,
-                               n12, uint32_t(v.n1), *descend ? 0 : 1, v.R, v.sa12, v.rank);
-            ts.finish();
-            SA_HIP(hipGetLastError());
-        }
+        TimedScope ts("dc3_names", double(v.n12) * 12.0, st);
+        hipLaunchKernelGGL(k_d3_ranks, dim3(g), dim3(kD3Block), 0, st, L.sb.vals[cur], n12, v.sa12, v.rank);
+        ts.finish();
+        SA_HIP(hipGetLastError());
         return SA_OK;
     }
 
@@ -559,7 +575,7 @@ struct Dc3 {
         }
         {
             TimedScope ts("dc3_merge", double(ntiles + 1) * 4.0, st);
-            hipLaunchKernelGGL(k_d3_split, dim3(grid_for(ntiles + 1)), dim3(kD3Block), 0, st, L.rec,
+            hipLaunchKernelGGL(k_d3_split, dim3(grid_for((int64_t(ntiles) + 1) * kSpLanes)), dim3(kD3Block), 0, st, L.rec,
                                uint32_t(v.n), A, uint32_t(v.n0), v.sa12, uint32_t(v.n12), ntiles,
                                L.split);
             ts.finish();
@@ -582,8 +598,10 @@ struct Dc3 {
         int depth = 0;
         for (;; ++depth) {
             Level &v = L.lev[depth];
-            SA_TRY(launch_fill_u32(v.rank + v.n, 3, 0, st));
-            if (v.n12 == 0) break;
+            if (v.n12 == 0) {
+                SA_TRY(launch_fill_u32(v.rank + v.n, 3, 0, st));
+                break;
+            }
             bool descend = false;
             SA_TRY(name_samples(depth, &descend));
             if (!descend) break;
@@ -592,8 +610,8 @@ struct Dc3 {
             v.recursed = true;
         }
         for (int d = depth; d >= 0; --d) SA_TRY(finish(d));
-        uint32_t host[2];
-        SA_TRY(read_words(host));
+        uint32_t host[kStWords];
+        SA_TRY(read_state(host));
         if (host[0] & kErrAlphabet)
             return fail(SA_ERR_ALPHABET, "text holds a byte other than A, C, G, T, $");
         if (host[0] & kErrNoSepEnd) return fail(SA_ERR_INVALID, "the text must end with '$'");
