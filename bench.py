@@ -762,7 +762,7 @@ def main():
         step()
     torch.cuda.synchronize()
     pkg.sa_timing_enable(False)
-    kern = kernel_table(pkg, KEYS + (("dc3_keys", "dc3_names", "dc3_lift", "dc3_recs",
+    kern = kernel_table(pkg, KEYS + (("dc3_keys", "dc3_names", "dc3_recs",
                                        "dc3_merge") if args.sa_algo == "dc3" else ()), ks)
     dom = max((k for k in kern if k in KERNEL_NAMES), key=lambda k: kern[k]["ms_per_step"])
     d = kern[dom]

@@ -42,8 +42,9 @@ namespace saasm {
 namespace {
 
 constexpr int kD3Block = 256;
-constexpr int kMgItems = 8;                      // outputs per merge thread
-constexpr int kMgTile = kD3Block * kMgItems;     // outputs per merge workgroup
+constexpr int kMgBlock = 512;
+constexpr int kMgItems = 4;                      // outputs per merge thread
+constexpr int kMgTile = kMgBlock * kMgItems;     // outputs per merge workgroup
 
 unsigned grid_for(int64_t n, int per_block = kD3Block) {
     int64_t g = (n + per_block - 1) / per_block;
@@ -226,19 +227,6 @@ __global__ __launch_bounds__(kD3Block) void k_d3_ranks(const uint32_t *__restric
     }
 }
 
-// ---- step 2: sample order from the suffix array of the name string ------------------------
-__global__ __launch_bounds__(kD3Block) void k_d3_lift(const uint32_t *__restrict__ saR,
-                                                      uint32_t n12, uint32_t n1,
-                                                      uint32_t *__restrict__ sa12,
-                                                      uint32_t *__restrict__ rank) {
-    for (uint32_t k = blockIdx.x * kD3Block + threadIdx.x; k < n12; k += gridDim.x * kD3Block) {
-        const uint32_t r = saR[k];
-        const uint32_t p = r < n1 ? 3u * r + 1u : 3u * (r - n1) + 2u;
-        sa12[k] = p;
-        rank[p] = k + 1u;
-    }
-}
-
 // ---- step 3: keys of the suffixes at positions 0 mod 3 --------------------------------------
 // (symbol, rank of the next suffix); a separator at the top level orders by its position.
 template <bool TOP>
@@ -323,19 +311,27 @@ __global__ __launch_bounds__(kD3Block) void k_d3_split(const uint4 *__restrict__
 }
 
 // One tile of kMgTile outputs: the tile's runs of A and B with their comparison records go to
-// LDS, each thread finds its own split by merge path and merges kMgItems outputs, and the
-// tile is written out contiguously.
-__global__ __launch_bounds__(kD3Block) void k_d3_merge(const uint4 *__restrict__ rec, uint32_t n,
+// LDS, each thread finds its own split by merge path and merges kMgItems outputs.  The k-th
+// output of the top level is suffix array entry k, and the k of its position the inverse; of a
+// deeper level it is a place of the name string above, so that level's k-th sample, of rank
+// k + 1 (step 2).
+// Bound by one random 16-byte read and one scattered word an output: at 10 M outputs 325 us; 408
+// with the scattered words left to a kernel of their own.
+struct D3Into {
+    uint32_t *out;         // [k]: the top's suffix array, the samples in order elsewhere
+    uint32_t *where;       // [position]: k (the inverse; may be NULL), k + 1 (ranks) elsewhere
+    uint32_t n1;           // of the level above
+    bool top;
+};
+__global__ __launch_bounds__(kMgBlock) void k_d3_merge(const uint4 *__restrict__ rec, uint32_t n,
                                                        const uint32_t *__restrict__ A,
                                                        uint32_t na_all,
                                                        const uint32_t *__restrict__ B,
                                                        uint32_t nb_all,
                                                        const uint32_t *__restrict__ split,
-                                                       uint32_t *__restrict__ out,
-                                                       uint32_t *err) {
+                                                       D3Into to, uint32_t *err) {
     __shared__ uint32_t s_pos[kMgTile];
     __shared__ Rec s_rec[kMgTile];
-    __shared__ uint32_t s_out[kMgTile];
     const uint32_t t = blockIdx.x, tid = threadIdx.x;
     const uint32_t d0 = t * uint32_t(kMgTile);
     const uint32_t d1 = (n - d0) < uint32_t(kMgTile) ? n : d0 + kMgTile;
@@ -349,13 +345,25 @@ __global__ __launch_bounds__(kD3Block) void k_d3_merge(const uint4 *__restrict__
     }
     const uint32_t b0 = d0 - a0;
     const uint32_t na = a1 - a0, nb = cnt - na;
-    for (uint32_t i = tid; i < cnt; i += kD3Block) {
-        const uint32_t x = i < na ? A[a0 + i] : B[b0 + (i - na)];
-        s_pos[i] = x;
-        s_rec[i] = load_rec(rec, x);
+    {
+        uint32_t x[kMgItems];  // all of a thread's reads on their way together
+        uint4 v[kMgItems];
+#pragma unroll
+        for (int j = 0; j < kMgItems; ++j) {
+            const uint32_t i = tid + j * kMgBlock;
+            x[j] = i >= cnt ? 0u : i < na ? A[a0 + i] : B[b0 + (i - na)];
+        }
+#pragma unroll
+        for (int j = 0; j < kMgItems; ++j) v[j] = rec[x[j]];
+#pragma unroll
+        for (int j = 0; j < kMgItems; ++j) {
+            s_pos[tid + j * kMgBlock] = x[j];
+            s_rec[tid + j * kMgBlock] = Rec{v[j].x, v[j].y, v[j].z, v[j].w};
+        }
     }
     __syncthreads();
     const uint32_t k = tid * kMgItems;
+    uint32_t got[kMgItems];
     if (k < cnt) {
         uint32_t lo = k > nb ? k - nb : 0u, hi = k < na ? k : na;
         while (lo < hi) {
@@ -365,23 +373,32 @@ __global__ __launch_bounds__(kD3Block) void k_d3_merge(const uint4 *__restrict__
             else hi = mid;
         }
         uint32_t ai = lo, bi = k - lo;
-        const uint32_t kend = (k + kMgItems) < cnt ? k + kMgItems : cnt;
-        for (uint32_t o = k; o < kend; ++o) {
+#pragma unroll
+        for (int j = 0; j < kMgItems; ++j) {
+            if (k + j >= cnt) break;
             bool takeA;
             if (bi >= nb) takeA = true;
             else if (ai >= na) takeA = false;
             else takeA = d3_less(s_rec[ai], s_pos[ai], s_rec[na + bi], s_pos[na + bi]);
-            s_out[o] = takeA ? s_pos[ai++] : s_pos[na + bi++];
+            got[j] = takeA ? s_pos[ai++] : s_pos[na + bi++];
         }
     }
     __syncthreads();
-    for (uint32_t i = tid; i < cnt; i += kD3Block) out[d0 + i] = s_out[i];
-}
-
-__global__ __launch_bounds__(kD3Block) void k_d3_inverse(const uint32_t *__restrict__ sa,
-                                                         uint32_t n, int32_t *__restrict__ isa) {
-    for (uint32_t k = blockIdx.x * kD3Block + threadIdx.x; k < n; k += gridDim.x * kD3Block)
-        isa[sa[k]] = int32_t(k);
+#pragma unroll
+    for (int j = 0; j < kMgItems; ++j)
+        if (k + j < cnt) s_pos[k + j] = got[j];
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += kMgBlock) {
+        const uint32_t x = s_pos[i], k = d0 + i;
+        if (to.top) {
+            to.out[k] = x;
+            if (to.where) to.where[x] = k;
+        } else {
+            const uint32_t p = x < to.n1 ? 3u * x + 1u : 3u * (x - to.n1) + 2u;
+            to.out[k] = p;
+            to.where[p] = k + 1u;
+        }
+    }
 }
 
 int bits_for(int64_t v) {  // bits needed to hold 0..v
@@ -394,12 +411,10 @@ int bits_for(int64_t v) {  // bits needed to hold 0..v
 struct Level {
     int64_t n = 0, n0 = 0, n1 = 0, n12 = 0;
     uint32_t *s = nullptr;     // [n + 3] symbols (levels below the top)
-    uint32_t *out = nullptr;   // [n] this level's suffix array
     uint32_t *rank = nullptr;  // [n + 3]
     uint32_t *sa12 = nullptr;  // [n12] sorted samples
     uint32_t *R = nullptr;     // [n12 + 3] name string = next level's s
     uint32_t K = 0;            // largest symbol of s (the top: 4)
-    bool recursed = false;
 };
 
 struct Layout {
@@ -412,7 +427,7 @@ struct Layout {
     SortBufs sb{};
 };
 
-void carve_dc3(Carver &c, int64_t n, const Tune &t, uint32_t *top_out, Layout *L) {
+void carve_dc3(Carver &c, int64_t n, const Tune &t, Layout *L) {
     L->lev.clear();
     int64_t m = n;
     for (int depth = 0; m > 0; ++depth) {
@@ -421,12 +436,7 @@ void carve_dc3(Carver &c, int64_t n, const Tune &t, uint32_t *top_out, Layout *L
         v.n0 = (m + 2) / 3;
         v.n1 = (m + 1) / 3;
         v.n12 = m - v.n0;
-        if (depth > 0) {
-            v.s = L->lev.back().R;
-            v.out = c.take<uint32_t>(m);
-        } else {
-            v.out = top_out;
-        }
+        if (depth > 0) v.s = L->lev.back().R;
         v.rank = c.take<uint32_t>(m + 3);
         if (v.n12 > 0) {
             v.sa12 = c.take<uint32_t>(v.n12);
@@ -447,6 +457,7 @@ void carve_dc3(Carver &c, int64_t n, const Tune &t, uint32_t *top_out, Layout *L
 
 struct Dc3 {
     const uint8_t *text;
+    uint32_t *sa, *isa;  // the inverse may be NULL
     Tune t;
     Layout L;
     hipStream_t st;
@@ -535,13 +546,6 @@ struct Dc3 {
     int finish(int d) {
         Level &v = L.lev[d];
         const bool top = d == 0;
-        if (v.recursed) {
-            TimedScope ts("dc3_lift", double(v.n12) * 16.0, st);
-            hipLaunchKernelGGL(k_d3_lift, dim3(grid_for(v.n12)), dim3(kD3Block), 0, st,
-                               L.lev[d + 1].out, uint32_t(v.n12), uint32_t(v.n1), v.sa12, v.rank);
-            ts.finish();
-            SA_HIP(hipGetLastError());
-        }
         const int cb = top ? 3 : bits_for(v.K);
         const int rb = bits_for(std::max<int64_t>(v.n - 1, v.n12));
         {
@@ -582,10 +586,12 @@ struct Dc3 {
             SA_HIP(hipGetLastError());
         }
         {
-            // list entry 4 + its 16-byte record + output 4
-            TimedScope ts("dc3_merge", double(v.n) * 24.0, st);
-            hipLaunchKernelGGL(k_d3_merge, dim3(ntiles), dim3(kD3Block), 0, st, L.rec, uint32_t(v.n),
-                               A, uint32_t(v.n0), v.sa12, uint32_t(v.n12), L.split, v.out, L.state);
+            // list entry 4 + its 16-byte record + output 4 + its scattered word 4
+            TimedScope ts("dc3_merge", double(v.n) * (top && !isa ? 24.0 : 28.0), st);
+            const D3Into to = top ? D3Into{sa, isa, 0, true}
+                                  : D3Into{L.lev[d - 1].sa12, L.lev[d - 1].rank, uint32_t(L.lev[d - 1].n1), false};
+            hipLaunchKernelGGL(k_d3_merge, dim3(ntiles), dim3(kMgBlock), 0, st, L.rec, uint32_t(v.n),
+                               A, uint32_t(v.n0), v.sa12, uint32_t(v.n12), L.split, to, L.state);
             ts.finish();
             SA_HIP(hipGetLastError());
         }
@@ -607,7 +613,6 @@ struct Dc3 {
             if (!descend) break;
             if (depth + 1 >= int(L.lev.size()))
                 return fail(SA_ERR_HIP, "sa_build_dc3: recursion deeper than its levels");
-            v.recursed = true;
         }
         for (int d = depth; d >= 0; --d) SA_TRY(finish(d));
         uint32_t host[kStWords];
@@ -633,7 +638,7 @@ extern "C" int64_t sa_build_dc3_ws_bytes(int64_t n, const sa_tuning *tune) {
     if (n < 1 || n >= kMaxN || resolve_tuning(tune, &t) != SA_OK) return -1;
     Carver c(nullptr, INT64_MAX);
     Layout L;
-    carve_dc3(c, n, t, nullptr, &L);
+    carve_dc3(c, n, t, &L);
     return c.off + 256;
 }
 
@@ -651,14 +656,11 @@ static int sa_build_dc3_impl(const uint8_t *text, int64_t n, int32_t *sa, int32_
     D.text = text;
     D.st = stream;
     Carver c(ws, ws_bytes);
-    carve_dc3(c, n, D.t, reinterpret_cast<uint32_t *>(sa), &D.L);
+    D.sa = reinterpret_cast<uint32_t *>(sa);
+    D.isa = reinterpret_cast<uint32_t *>(isa_or_null);
+    carve_dc3(c, n, D.t, &D.L);
     D.L.sb.err = D.L.state;
     SA_TRY(D.run(n, levels_h));
-    if (isa_or_null) {
-        hipLaunchKernelGGL(k_d3_inverse, dim3(grid_for(n)), dim3(kD3Block), 0, stream,
-                           reinterpret_cast<const uint32_t *>(sa), uint32_t(n), isa_or_null);
-        SA_HIP(hipGetLastError());
-    }
     return SA_OK;
 }
 
