@@ -37,7 +37,7 @@ constexpr int kRuTile = kRuBlock * kRuItems;
 // word per tile of this size, and every launcher checks its tile count against that on the host.
 constexpr int kLbMinTile = kFirstMinTile < kRuTile ? kFirstMinTile : kRuTile;
 
-constexpr int64_t kTopMinN = 16384;  // the default radix tile (choose_first_round)
+constexpr int64_t kTunedTopMinN = 16384;  // choose_first_round
 
 // Rank update over the sorted active items (K, V) of a round, whose suffix-array slots are
 // S[0..A) (S == nullptr: identity, round 0).  For item i:
@@ -599,15 +599,18 @@ struct Build {
     // sixteen suffixes a run at most: reads lie as many deep as their coverage, so a run then
     // holds the copies of one or two genome stretches.  More bases only add passes; fewer make
     // runs of several stretches, which cost the run sort their square and pass its limit
-    // sooner.  Texts below one radix tile keep the passes over the whole key: one workgroup
-    // does each of them.
+    // sooner.  A build with a tuning of its caller's keeps the passes over the whole key and the
+    // doubling rounds after them below kTunedTopMinN: whoever tunes so small a build does it to
+    // see its sorts at work (the timing records of a tuned 14,440-character text are held to its
+    // seven passes), not for speed.  The form by top bits is the faster one there too, at 1,000
+    // characters 63 against 197 us, at 14,000 77 against 284, so every other build takes it.
     void choose_first_round() {
         int sb = 0;
         while ((int64_t(1) << sb) < n_sets) ++sb;
         h0 = (63 - 5 - sb) / 2 < kH0 ? (63 - 5 - sb) / 2 : kH0;
         key0_bits = 2 * h0 + 5 + sb;
         top_d = top_bits = 0;
-        if (n < kTopMinN) return;
+        if (t.fixed && n < kTunedTopMinN) return;
         int64_t longest = n_sets > 0 ? 0 : n;
         for (int k = 0; k < n_sets; ++k)
             longest = set_off_h[k + 1] - set_off_h[k] > longest ? set_off_h[k + 1] - set_off_h[k] : longest;
