@@ -432,13 +432,14 @@ def bench_lookup(args, pkg, torch, np):
     Lk, kms, _ = pkg.sa_timing_get("lookup")
     res = res.cpu().numpy()
     found = int((res[:, 1] > res[:, 0]).sum())
-    # modelled bytes per lookup: one joint search of ceil(log2 n) steps, plus for a pattern
-    # that occurs cnt times the two searches inside its split interval (2 ceil(log2(cnt + 1))
-    # steps); each step touches one 64-byte line of the suffix array and one of the text
-    # records.  The kernel is bound by each thread's chain of dependent loads, not by this
-    # traffic: the figure shows how far from the bandwidth roof that leaves it.
+    # modelled bytes per lookup: one joint search of ceil(log2 stride) steps between two samples
+    # of the array (one for every two patterns, 4,096 to 2^19, at most a sixteenth of it), plus
+    # for a pattern that occurs cnt times the two searches inside its split interval
+    # (2 ceil(log2(cnt + 1)) steps); each step touches one 64-byte line of the suffix array and
+    # one of the text records.
     cnt = (res[:, 1] - res[:, 0]).astype(np.int64)
-    steps = int(np.ceil(np.log2(r.n))) * len(pats) + int(
+    ns = min(max(4096, len(pats) // 2), r.n // 16 + 1, 1 << 19)
+    steps = int(np.ceil(np.log2(-(-r.n // ns) + 1))) * len(pats) + int(
         (2 * np.ceil(np.log2(cnt[cnt > 0] + 1))).sum())
     model = steps * 128.0
     kern_s = kms * 1e-3 / Lk
@@ -455,7 +456,7 @@ def bench_lookup(args, pkg, torch, np):
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(model / kern_s / 1e9 / HBM_PEAK_GBS, 4), "traffic": None,
                      "kernel": "k_lookup",
-                     "model": "(ceil(log2 n) + 2*ceil(log2(count+1)) if found) steps x 128 B per lookup; latency-bound"},
+                     "model": "(ceil(log2 sample stride) + 2*ceil(log2(count+1)) if found) steps x 128 B per lookup"},
     }), flush=True)
 
 
@@ -549,8 +550,8 @@ KERNEL_NAMES = {
     "key0": "k_key0 (first-round keys + digit histograms)",
     "overlap_walk": "k_ovl_walk (LCP-interval walks)",
 }
-KEYS = ("pack", "key0", "radix_pass", "keybuild", "keyruns", "rank_update", "kasai",
-        "lcp_gather", "overlap_walk")
+KEYS = ("pack", "key0", "radix_pass", "first_extract", "keybuild", "keyruns", "rank_update", "kasai",
+        "lcp_gather", "lcp_rest", "overlap_walk")
 BUILD_KEYS = ("pack", "key0", "radix_pass", "keybuild", "keyruns", "rank_update")
 
 
@@ -578,10 +579,11 @@ def traffic_for(args, key, tuning):
     only for the sources the counters were taken on and the default tuning."""
     import hashlib
     sources = {"radix_pass": ("radix.hip", "device.hpp"),
-               "sa_build": ("sa_build.hip", "radix.hip", "pack.hip", "device.hpp", "internal.hpp"),
+               "sa_build": ("sa_build.hip", "first_round.hip", "radix.hip", "pack.hip", "device.hpp",
+                            "internal.hpp"),
                "rank_update": ("sa_build.hip", "device.hpp", "internal.hpp"),
                "kasai": ("lcp.hip", "text.hpp", "device.hpp", "internal.hpp"),
-               "keyruns": ("sa_build.hip", "device.hpp", "internal.hpp")}
+               "keyruns": ("first_round.hip", "sa_build.hip", "device.hpp", "internal.hpp")}
     tpath = os.path.join(args.traffic_dir, f"{key}_traffic.json")
     if key not in sources or not os.path.exists(tpath) or tuning is not None:
         return None

@@ -235,11 +235,11 @@ constexpr int64_t kFrFewItems = int64_t(1) << 21;
 // LCP: also writes lcp[i] of every suffix told apart from its predecessor here (the keys and
 // windows compared hold their common prefix); for the others, which leave in groups, the
 // negative of one more than the symbols they are known to share.
-// What bounds it: the comparisons in LDS (about ten items a run are compared with each other
-// twice a window) and, per window, one gather of 36 bytes of packed text an item.  3.0 ms for
-// the 50.1 M suffixes of 10x reads, of which a copy of what it reads and writes would take
-// 0.3 ms.  The four passes, rank updates, sorts of runs and Kasai's scan it took the place of
-// were 8.1 ms.
+// What bounds it: the lines of its gathers, 36 bytes of packed text an item and window, and of the
+// ranks it scatters (11.6 GB counted beyond L2 for the 50.1 M suffixes of 10x reads, 3.9 TB/s in
+// 3.0 ms, where a copy reaches 5.1), and beside them the comparisons in LDS (about ten items a
+// run are compared with each other twice a window).  The four passes, rank updates, sorts of
+// runs and Kasai's scan it took the place of were 8.1 ms.
 // The plain form's windows follow the run's top bits at once: sorting by the rest of the key
 // first costs 18.0 ms against 16.8 over a batch of 210 M suffixes in small sets, and 3.0 either
 // way at 50.1 M.  The mixed form does sort by it: repeats make its runs long (40 items and more),

@@ -167,6 +167,8 @@ __device__ __forceinline__ void walk_read(const int32_t *__restrict__ sa, const 
 // its first kWkKeep matches in LDS while its tile's place is found; a read with more is walked
 // again.  Matches are written while they fit in cap_hits, the count always.  Nothing is walked
 // when the text or the LCP array is not valid.
+// Bound by each walk's chain of reads: 72 us for 100,000 reads in 50.1 M suffixes, where a walk
+// to count, a scan and a walk to write took 90.
 constexpr int kWkBlock = 256;
 constexpr int kWkKeep = 12;
 __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
