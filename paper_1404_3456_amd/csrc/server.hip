@@ -224,8 +224,8 @@ __global__ void k_rows_shift(int32_t *__restrict__ rows, int64_t nrows,
 
 // Separators of every job's text, and a flag for any byte outside A, C, G, T, $: workgroups of
 // row y share job y's text.  A borrowed text is checked here, after its upload: the host's scan
-// of the same bytes (scan_text, for texts copied at submission) takes about as long as ten
-// builds of them (35 M characters: 17 ms against under 0.1).
+// of the same bytes (scan_text, for texts copied at submission) takes longer than the whole build
+// of them (35 M characters: 17 ms, under 0.1 here; the build 3).
 constexpr int kJsGrid = 64;
 constexpr int kJsRows = 32768;  // jobs a launch takes (a grid's second size ends at 65535)
 __global__ __launch_bounds__(256) void k_job_scan(const uint8_t *__restrict__ text,
