@@ -63,73 +63,22 @@ bool parallel_chunks(int64_t n, F f) {
     return !failed.load();
 }
 
-// Whether sa and isa are inverse permutations of [0, n), found on host threads of its own while
-// the search runs: 10 M entries take 5 ms, half of the search's time.  The search reads no entry
-// outside the arrays whatever they hold, stops when they are known to fail, and writes its
-// outcome only if they pass.
-class InverseCheck {
-  public:
-    InverseCheck(const int32_t *sa, const int32_t *isa, int64_t n) {
-        auto run = [this, sa, isa, n] {
-            ran_ = parallel_chunks(n, [&](int64_t lo, int64_t hi, int) {
-                for (int64_t i = lo; i < hi; ++i)
-                    if (sa[i] < 0 || sa[i] >= n || isa[sa[i]] != i) {
-                        bad_.store(true, std::memory_order_relaxed);
-                        return;
-                    }
-            });
-        };
-        try {
-            th_ = std::thread(run);
-        } catch (...) {
-            run();
-        }
-    }
-    ~InverseCheck() {
-        if (th_.joinable()) th_.join();
-    }
-    bool failed() const { return bad_.load(std::memory_order_relaxed); }
-    int status() {
-        if (th_.joinable()) th_.join();
-        if (!ran_) return fail(SA_ERR_NOMEM, "sa_reconstruct: host thread failed");
-        if (bad_.load()) return fail(SA_ERR_INVALID, "sa_reconstruct: sa/isa are not inverse permutations");
-        return SA_OK;
-    }
-
-  private:
-    std::thread th_;
-    std::atomic<bool> bad_{false};
-    bool ran_ = false;
-};
-
 struct Recon {
     const uint8_t *t;
     int64_t n;
     const int32_t *sa, *isa, *lcp;
-    const InverseCheck *check;
     std::vector<int64_t> start, len;  // per fragment
-    std::vector<int32_t> near;        // first fragment that starts at or after position p, at p / 256
+    std::vector<int32_t> frag_at;     // fragment id whose first base is position p, else -1
     std::vector<char> used;
     int64_t min_len = 0;
-
-    // Fragment whose first base is position p, else -1.  (An array over all positions told this
-    // before: 7 ms to fill for 10 M.)
-    int32_t frag_at(int64_t p) const {
-        if (p < 0 || p >= n || (p > 0 && t[p - 1] != '$')) return -1;
-        size_t f = size_t(near[size_t(p >> 8)]);
-        while (start[f] < p) ++f;  // p is a start, so this ends there
-        return int32_t(f);
-    }
 
     // Fragments f (unused) whose text agrees with the suffix at q for min(|f|, rlen) bases,
     // |f| != rlen unless `final_ok`; in increasing id.
     void candidates(int64_t q, int64_t rlen, bool final_ok, std::vector<int32_t> &out) const {
         out.clear();
         const int64_t i = isa[q];
-        if (i < 0 || i >= n) return;  // the check fails
-        const auto stop = [&](int64_t k) { return (k & 1023) == 0 && check->failed(); };
         auto consider = [&](int64_t k, int64_t run) {
-            const int32_t f = frag_at(sa[k]);
+            const int32_t f = frag_at[sa[k]];
             if (f < 0 || used[f]) return;
             const int64_t lf = len[f];
             if (lf == rlen && !final_ok) return;
@@ -140,13 +89,13 @@ struct Recon {
         int64_t run = INT64_MAX;
         for (int64_t k = i - 1; k >= 0; --k) {
             run = std::min<int64_t>(run, lcp[k + 1]);
-            if (run < floor || stop(k)) break;
+            if (run < floor) break;
             consider(k, run);
         }
         run = INT64_MAX;
         for (int64_t k = i + 1; k < n; ++k) {
             run = std::min<int64_t>(run, lcp[k]);
-            if (run < floor || stop(k)) break;
+            if (run < floor) break;
             consider(k, run);
         }
         std::sort(out.begin(), out.end());
@@ -170,8 +119,48 @@ struct Frame {
 
 using namespace saasm;
 
-static int search(Recon &R, InverseCheck &check, const uint8_t *text_h, int64_t m, int32_t *order_h,
-                  uint8_t *rs_h, int64_t rs_cap, int64_t *rs_len_h, int64_t max_steps) {
+static int reconstruct_impl(const uint8_t *text_h, int64_t n, const int32_t *sa_h,
+                            const int32_t *isa_h, const int32_t *lcp_h, int32_t *order_h,
+                            uint8_t *rs_h, int64_t rs_cap, int64_t *rs_len_h, int64_t max_steps) {
+    if (!text_h || !sa_h || !isa_h || !lcp_h || !order_h || !rs_len_h)
+        return fail(SA_ERR_INVALID, "sa_reconstruct: NULL pointer");
+    if (n < 1 || text_h[n - 1] != '$') return fail(SA_ERR_INVALID, "sa_reconstruct: text must end with '$'");
+    if (n >= kMaxN) return fail(SA_ERR_TOO_LARGE, "sa_reconstruct: n >= 2^31-2");
+    Recon R;
+    R.t = text_h;
+    R.n = n;
+    R.sa = sa_h;
+    R.isa = isa_h;
+    R.lcp = lcp_h;
+    R.frag_at.resize(size_t(n));
+    if (!parallel_chunks(n, [&](int64_t lo, int64_t hi, int) {
+            std::fill(R.frag_at.begin() + lo, R.frag_at.begin() + hi, -1);
+        }))
+        return fail(SA_ERR_NOMEM, "sa_reconstruct: host thread failed");
+    for (int64_t s0 = 0; s0 < n;) {  // fragment by fragment: the next separator after s0
+        const void *q = memchr(text_h + s0, '$', size_t(n - s0));
+        const int64_t p = static_cast<const uint8_t *>(q) - text_h;  // text_h[n-1] is '$'
+        if (p == s0) return fail(SA_ERR_INVALID, "sa_reconstruct: empty fragment");
+        R.frag_at[size_t(s0)] = int32_t(R.start.size());
+        R.start.push_back(s0);
+        R.len.push_back(p - s0);
+        s0 = p + 1;
+    }
+    const int64_t m = int64_t(R.start.size());
+    if (m < 2) return fail(SA_ERR_INVALID, "sa_reconstruct: need at least two fragments");
+    R.min_len = *std::min_element(R.len.begin(), R.len.end());
+    R.used.assign(size_t(m), 0);
+    std::atomic<bool> bad{false};
+    if (!parallel_chunks(n, [&](int64_t lo, int64_t hi, int) {
+            for (int64_t i = lo; i < hi; ++i)
+                if (sa_h[i] < 0 || sa_h[i] >= n || isa_h[sa_h[i]] != i) {
+                    bad.store(true, std::memory_order_relaxed);
+                    return;
+                }
+        }))
+        return fail(SA_ERR_NOMEM, "sa_reconstruct: host thread failed");
+    if (bad.load()) return fail(SA_ERR_INVALID, "sa_reconstruct: sa/isa are not inverse permutations");
+
     std::vector<uint8_t> rs;      // the sequence so far
     std::vector<int32_t> order;   // fragments in placement order
     State st;
@@ -185,7 +174,6 @@ static int search(Recon &R, InverseCheck &check, const uint8_t *text_h, int64_t 
     };
     auto done = [&]() { return int64_t(st.placed) == m && st.e_lo == st.e_hi; };
     auto finish = [&]() -> int {
-        SA_TRY(check.status());
         if (rs_h && int64_t(rs.size()) > rs_cap)
             return fail(SA_ERR_CAPACITY, "sa_reconstruct: rs buffer too small");
         if (rs_h) memcpy(rs_h, rs.data(), rs.size());
@@ -240,7 +228,6 @@ static int search(Recon &R, InverseCheck &check, const uint8_t *text_h, int64_t 
         stack.clear();
         push_frame();
         while (!stack.empty()) {
-            if (check.failed()) return check.status();
             if (++steps > max_steps) return fail(SA_ERR_NOTFOUND, "sa_reconstruct: step limit reached");
             Frame &F = stack.back();
             restore(F.saved);  // undo whatever the last choice under this frame placed
@@ -268,39 +255,6 @@ static int search(Recon &R, InverseCheck &check, const uint8_t *text_h, int64_t 
         }
     }
     return fail(SA_ERR_NOTFOUND, "sa_reconstruct: no reconstruction from two cuttings");
-}
-
-static int reconstruct_impl(const uint8_t *text_h, int64_t n, const int32_t *sa_h,
-                            const int32_t *isa_h, const int32_t *lcp_h, int32_t *order_h,
-                            uint8_t *rs_h, int64_t rs_cap, int64_t *rs_len_h, int64_t max_steps) {
-    if (!text_h || !sa_h || !isa_h || !lcp_h || !order_h || !rs_len_h)
-        return fail(SA_ERR_INVALID, "sa_reconstruct: NULL pointer");
-    if (n < 1 || text_h[n - 1] != '$') return fail(SA_ERR_INVALID, "sa_reconstruct: text must end with '$'");
-    if (n >= kMaxN) return fail(SA_ERR_TOO_LARGE, "sa_reconstruct: n >= 2^31-2");
-    Recon R;
-    R.t = text_h;
-    R.n = n;
-    R.sa = sa_h;
-    R.isa = isa_h;
-    R.lcp = lcp_h;
-    for (int64_t s0 = 0; s0 < n;) {  // fragment by fragment: the next separator after s0
-        const void *q = memchr(text_h + s0, '$', size_t(n - s0));
-        const int64_t p = static_cast<const uint8_t *>(q) - text_h;  // text_h[n-1] is '$'
-        if (p == s0) return fail(SA_ERR_INVALID, "sa_reconstruct: empty fragment");
-        while (int64_t(R.near.size()) * 256 <= s0) R.near.push_back(int32_t(R.start.size()));
-        R.start.push_back(s0);
-        R.len.push_back(p - s0);
-        s0 = p + 1;
-    }
-    const int64_t m = int64_t(R.start.size());
-    if (m < 2) return fail(SA_ERR_INVALID, "sa_reconstruct: need at least two fragments");
-    R.min_len = *std::min_element(R.len.begin(), R.len.end());
-    R.used.assign(size_t(m), 0);
-    InverseCheck check(sa_h, isa_h, n);
-    R.check = &check;
-    const int found = search(R, check, text_h, m, order_h, rs_h, rs_cap, rs_len_h, max_steps);
-    const int inverse = check.status();
-    return inverse != SA_OK ? inverse : found;
 }
 
 extern "C" int sa_reconstruct(const uint8_t *text_h, int64_t n, const int32_t *sa_h,

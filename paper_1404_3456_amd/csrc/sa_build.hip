@@ -309,7 +309,8 @@ static void carve_build(Carver &c, int64_t n, int n_sets, const Tune &t, BuildLa
 // set, and raise kErrRange otherwise.  Tiles of kKrTile items, loaded with kRunMax items of
 // context on either side, so every run of at most kRunMax items that meets the tile lies inside
 // the loaded range.  The active count and h come from state[kStActive] and state[kStH]; a count
-// of 0 makes the launch a no-op.
+// of 0 makes the launch a no-op but for the look-back words and the ticket of the rank update that
+// follows, which it clears whatever the count (two launches of their own took 8 us a round).
 constexpr int kKrBlock = 256;
 constexpr int kKrTile = 2048;
 constexpr int kKrSpan = kKrTile + 2 * kRunMax;
@@ -317,10 +318,15 @@ constexpr int kKrSpan = kKrTile + 2 * kRunMax;
 __global__ __launch_bounds__(kKrBlock) void k_keys_runs(
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ S,
     const uint32_t *__restrict__ rank, uint32_t n, int rbits, const uint32_t *state,
-    uint64_t *__restrict__ K, uint32_t *__restrict__ V, uint32_t *err) {
+    uint64_t *__restrict__ K, uint32_t *__restrict__ V, uint64_t *lbflags, uint32_t nlb,
+    uint32_t *tick, uint32_t *err) {
     __shared__ uint32_t s_p[kKrSpan];   // position | first-of-run bit; outside [0, A): the bit alone
     __shared__ uint32_t s_r2[kKrSpan];  // rank[p + h]
     __shared__ uint32_t s_lab[kKrSpan]; // slot (the label, on a run's first member)
+    if (threadIdx.x == 0) {
+        if (blockIdx.x < nlb) lbflags[blockIdx.x] = 0;  // no more of them than workgroups
+        if (blockIdx.x == 0) *tick = 0;
+    }
     const uint32_t A = state[kStActive];
     const uint32_t h = state[kStH];
     const bool mixed = state[kStBig] != 0;  // longer runs exist and are sorted elsewhere
@@ -371,15 +377,24 @@ __global__ __launch_bounds__(kKrBlock) void k_keys_runs(
     }
 }
 
+// Tiles of a rank update of at most a_bound items.
+static int64_t ru_tiles(int64_t a_bound) {
+    return a_bound > 0 ? (a_bound + kRuTile - 1) / kRuTile : 1;
+}
+
 static int launch_keys_runs(const uint32_t *P, const uint32_t *S, const uint32_t *rank,
                             int64_t a_bound, int64_t n, int rbits, const uint32_t *state,
-                            uint64_t *K, uint32_t *V, uint32_t *err, hipStream_t s) {
+                            uint64_t *K, uint32_t *V, uint64_t *lbflags, int64_t lb_words,
+                            uint32_t *tick, uint32_t *err, hipStream_t s) {
     int64_t tiles = (a_bound + kKrTile - 1) / kKrTile;
     if (tiles < 1) tiles = 1;
+    static_assert(kKrTile <= kRuTile, "a workgroup for every look-back word");
+    const int64_t nlb = ru_tiles(a_bound);
+    if (nlb > lb_words) return fail(SA_ERR_HIP, "run sort: look-back array too small");
     // algorithmic bytes per item: read P, S and rank[p + h] (4 each); write K (8) and V (4)
     TimedScope ts("keyruns", 0.0, 24.0, s);
     hipLaunchKernelGGL(k_keys_runs, dim3(unsigned(tiles)), dim3(kKrBlock), 0, s, P, S, rank,
-                       uint32_t(n), rbits, state, K, V, err);
+                       uint32_t(n), rbits, state, K, V, lbflags, uint32_t(nlb), tick, err);
     ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;
@@ -390,11 +405,8 @@ static int launch_rank_update(const uint64_t *K, const uint32_t *V, const uint32
                               int32_t *sa, uint32_t *rank, uint32_t *S_new, uint32_t *P_new,
                               uint64_t *lbflags, int64_t lb_words, uint32_t *tick,
                               uint32_t *state, hipStream_t s) {
-    int64_t tiles = (a_bound + kRuTile - 1) / kRuTile;
-    if (tiles < 1) tiles = 1;
+    const int64_t tiles = ru_tiles(a_bound);
     if (tiles > lb_words) return fail(SA_ERR_HIP, "rank update: look-back array too small");
-    SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
-    SA_TRY(launch_fill_u32(tick, 1, 0, s));
     // algorithmic bytes: read K (8) + V (4) + S (4 when present); write sa (4) + rank (4) +
     // S_new (4) + P_new (4) (upper bounds)
     TimedScope ts = S ? TimedScope("rank_update", 0.0, 32.0, s)
@@ -580,7 +592,7 @@ struct Build {
         uint32_t *V = L.sb.vals[cur ^ 1];
         timing_scope_mode(kModeRuns);
         SA_TRY(launch_keys_runs(L.pos, L.slots[sl], rank, a_bound, n, rbits, L.state, K, V,
-                                L.state + kStErr, s));
+                                L.lbflags, L.lb_words, L.tickets, L.state + kStErr, s));
         if (!runs_only) {
             timing_scope_mode(kModeRadix);
             SA_TRY(launch_big_place(L.sb.keys[cur], L.sb.vals[cur], L.bigidx, a_bound, L.state, K, V,
