@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <memory>
 #include <thread>
 #include <vector>
 
@@ -68,7 +69,7 @@ struct Recon {
     int64_t n;
     const int32_t *sa, *isa, *lcp;
     std::vector<int64_t> start, len;  // per fragment
-    std::vector<int32_t> frag_at;     // fragment id whose first base is position p, else -1
+    std::unique_ptr<int32_t[]> frag_at;  // fragment id whose first base is position p, else -1
     std::vector<char> used;
     int64_t min_len = 0;
 
@@ -132,9 +133,11 @@ static int reconstruct_impl(const uint8_t *text_h, int64_t n, const int32_t *sa_
     R.sa = sa_h;
     R.isa = isa_h;
     R.lcp = lcp_h;
-    R.frag_at.resize(size_t(n));
+    // Not a vector: its zeros would touch every page on this thread first (7 of 26 ms on the host
+    // for 10 M positions).
+    R.frag_at.reset(new int32_t[size_t(n)]);
     if (!parallel_chunks(n, [&](int64_t lo, int64_t hi, int) {
-            std::fill(R.frag_at.begin() + lo, R.frag_at.begin() + hi, -1);
+            std::fill(R.frag_at.get() + lo, R.frag_at.get() + hi, -1);
         }))
         return fail(SA_ERR_NOMEM, "sa_reconstruct: host thread failed");
     for (int64_t s0 = 0; s0 < n;) {  // fragment by fragment: the next separator after s0

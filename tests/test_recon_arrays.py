@@ -1,5 +1,5 @@
 """sa_reconstruct on arrays that are no suffix array and its inverse: refused, with nothing written;
-and on fragments that start at every distance from the multiples of 256 its lookup counts in."""
+and on fragments that start all over a sequence."""
 import ctypes
 
 import numpy as np
