@@ -122,35 +122,80 @@ __device__ __forceinline__ void stage_key(uint64_t w0, uint64_t w1, uint32_t l, 
     *c1 = w1 | (uint64_t(l) << 7);
 }
 
-// c + 1 in the lanes of `in` whose (q0, q1) is below (k0, k1): the borrow of one 32-bit
-// subtraction chain.  As comparisons this is four 64-bit ones and their logic, twice the
-// instructions, and the compiler turns the chain in C back into them.
-__device__ __forceinline__ uint32_t add_below(uint32_t c, uint64_t q0, uint64_t k0, uint64_t in) {
+// How many of four words q[i], in the lanes of in[i], are below k, added to c: the borrows of
+// 32-bit subtraction chains.  As comparisons a two-word key takes four 64-bit ones and their logic,
+// twice the instructions, and the compiler turns a chain in C back into them.  The four chains
+// take turns, each with its borrow in a register pair of its own: gfx950 wants two wait states
+// between a vector instruction that writes a carry and the one that takes it in (the compiler
+// puts s_nop 1 there, but looks into no inline assembly), and three instructions lie between.
+__device__ __forceinline__ uint32_t add_below(uint32_t c, const uint64_t (&q)[4], uint64_t k,
+                                              const uint64_t (&in)[4]) {
     uint32_t t;
-    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
-        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
-        "s_and_b64 vcc, vcc, %6\n\t"
-        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
-        : "=&v"(t), "+v"(c)
-        : "v"(uint32_t(q0)), "v"(uint32_t(k0)), "v"(uint32_t(q0 >> 32)), "v"(uint32_t(k0 >> 32)),
-          "s"(in)
-        : "vcc");
+    uint64_t b1, b2, b3;
+    asm("v_sub_co_u32_e64 %[t], vcc, %[q0l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b1], %[q1l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b2], %[q2l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b3], %[q3l], %[kl]\n\t"
+        "v_subb_co_u32_e64 %[t], vcc, %[q0h], %[kh], vcc\n\t"
+        "v_subb_co_u32_e64 %[t], %[b1], %[q1h], %[kh], %[b1]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b2], %[q2h], %[kh], %[b2]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b3], %[q3h], %[kh], %[b3]\n\t"
+        "s_and_b64 vcc, vcc, %[i0]\n\t"
+        "s_and_b64 %[b1], %[b1], %[i1]\n\t"
+        "s_and_b64 %[b2], %[b2], %[i2]\n\t"
+        "s_and_b64 %[b3], %[b3], %[i3]\n\t"
+        "v_addc_co_u32_e64 %[c], vcc, 0, %[c], vcc\n\t"
+        "v_addc_co_u32_e64 %[c], %[b1], 0, %[c], %[b1]\n\t"
+        "v_addc_co_u32_e64 %[c], %[b2], 0, %[c], %[b2]\n\t"
+        "v_addc_co_u32_e64 %[c], %[b3], 0, %[c], %[b3]"
+        : [t] "=&v"(t), [c] "+&v"(c), [b1] "=&s"(b1), [b2] "=&s"(b2), [b3] "=&s"(b3)
+        : [q0l] "v"(uint32_t(q[0])), [q0h] "v"(uint32_t(q[0] >> 32)), [q1l] "v"(uint32_t(q[1])),
+          [q1h] "v"(uint32_t(q[1] >> 32)), [q2l] "v"(uint32_t(q[2])), [q2h] "v"(uint32_t(q[2] >> 32)),
+          [q3l] "v"(uint32_t(q[3])), [q3h] "v"(uint32_t(q[3] >> 32)), [kl] "v"(uint32_t(k)),
+          [kh] "v"(uint32_t(k >> 32)), [i0] "s"(in[0]), [i1] "s"(in[1]), [i2] "s"(in[2]), [i3] "s"(in[3])
+        : "vcc", "scc");
     return c;
 }
-__device__ __forceinline__ uint32_t add_below2(uint32_t c, uint64_t q0, uint64_t q1, uint64_t k0,
-                                                uint64_t k1, uint64_t in) {
+// The same for two-word keys (q0, q1) and (k0, k1).
+__device__ __forceinline__ uint32_t add_below2(uint32_t c, const uint64_t (&q0)[4],
+                                               const uint64_t (&q1)[4], uint64_t k0, uint64_t k1,
+                                               const uint64_t (&in)[4]) {
     uint32_t t;
-    asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
-        "v_subb_co_u32 %0, vcc, %4, %5, vcc\n\t"
-        "v_subb_co_u32 %0, vcc, %6, %7, vcc\n\t"
-        "v_subb_co_u32 %0, vcc, %8, %9, vcc\n\t"
-        "s_and_b64 vcc, vcc, %10\n\t"
-        "v_addc_co_u32 %1, vcc, 0, %1, vcc"
-        : "=&v"(t), "+v"(c)
-        : "v"(uint32_t(q1)), "v"(uint32_t(k1)), "v"(uint32_t(q1 >> 32)), "v"(uint32_t(k1 >> 32)),
-          "v"(uint32_t(q0)), "v"(uint32_t(k0)), "v"(uint32_t(q0 >> 32)), "v"(uint32_t(k0 >> 32)),
-          "s"(in)
-        : "vcc");
+    uint64_t b1, b2, b3;
+    asm("v_sub_co_u32_e64 %[t], vcc, %[q0l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b1], %[q1l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b2], %[q2l], %[kl]\n\t"
+        "v_sub_co_u32_e64 %[t], %[b3], %[q3l], %[kl]\n\t"
+        "v_subb_co_u32_e64 %[t], vcc, %[q0m], %[km], vcc\n\t"
+        "v_subb_co_u32_e64 %[t], %[b1], %[q1m], %[km], %[b1]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b2], %[q2m], %[km], %[b2]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b3], %[q3m], %[km], %[b3]\n\t"
+        "v_subb_co_u32_e64 %[t], vcc, %[q0n], %[kn], vcc\n\t"
+        "v_subb_co_u32_e64 %[t], %[b1], %[q1n], %[kn], %[b1]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b2], %[q2n], %[kn], %[b2]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b3], %[q3n], %[kn], %[b3]\n\t"
+        "v_subb_co_u32_e64 %[t], vcc, %[q0h], %[kh], vcc\n\t"
+        "v_subb_co_u32_e64 %[t], %[b1], %[q1h], %[kh], %[b1]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b2], %[q2h], %[kh], %[b2]\n\t"
+        "v_subb_co_u32_e64 %[t], %[b3], %[q3h], %[kh], %[b3]\n\t"
+        "s_and_b64 vcc, vcc, %[i0]\n\t"
+        "s_and_b64 %[b1], %[b1], %[i1]\n\t"
+        "s_and_b64 %[b2], %[b2], %[i2]\n\t"
+        "s_and_b64 %[b3], %[b3], %[i3]\n\t"
+        "v_addc_co_u32_e64 %[c], vcc, 0, %[c], vcc\n\t"
+        "v_addc_co_u32_e64 %[c], %[b1], 0, %[c], %[b1]\n\t"
+        "v_addc_co_u32_e64 %[c], %[b2], 0, %[c], %[b2]\n\t"
+        "v_addc_co_u32_e64 %[c], %[b3], 0, %[c], %[b3]"
+        : [t] "=&v"(t), [c] "+&v"(c), [b1] "=&s"(b1), [b2] "=&s"(b2), [b3] "=&s"(b3)
+        : [q0l] "v"(uint32_t(q1[0])), [q0m] "v"(uint32_t(q1[0] >> 32)), [q0n] "v"(uint32_t(q0[0])),
+          [q0h] "v"(uint32_t(q0[0] >> 32)), [q1l] "v"(uint32_t(q1[1])), [q1m] "v"(uint32_t(q1[1] >> 32)),
+          [q1n] "v"(uint32_t(q0[1])), [q1h] "v"(uint32_t(q0[1] >> 32)), [q2l] "v"(uint32_t(q1[2])),
+          [q2m] "v"(uint32_t(q1[2] >> 32)), [q2n] "v"(uint32_t(q0[2])), [q2h] "v"(uint32_t(q0[2] >> 32)),
+          [q3l] "v"(uint32_t(q1[3])), [q3m] "v"(uint32_t(q1[3] >> 32)), [q3n] "v"(uint32_t(q0[3])),
+          [q3h] "v"(uint32_t(q0[3] >> 32)), [kl] "v"(uint32_t(k1)), [km] "v"(uint32_t(k1 >> 32)),
+          [kn] "v"(uint32_t(k0)), [kh] "v"(uint32_t(k0 >> 32)), [i0] "s"(in[0]), [i1] "s"(in[1]),
+          [i2] "s"(in[2]), [i3] "s"(in[3])
+        : "vcc", "scc");
     return c;
 }
 
@@ -159,11 +204,13 @@ __device__ __forceinline__ uint32_t add_below2(uint32_t c, uint64_t q0, uint64_t
 __device__ __forceinline__ int count_below(const uint64_t *s, int st, int en, uint64_t k) {
     uint32_t c = 0;
     for (int y = st; y < en; y += 4) {
-        uint64_t q[4];
+        uint64_t q[4], in[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] = s[y + i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c = add_below(c, q[i], k, ballot(y + i < en));
+        for (int i = 0; i < 4; ++i) {
+            q[i] = s[y + i];
+            in[i] = ballot(y + i < en);
+        }
+        c = add_below(c, q, k, in);
     }
     return int(c);
 }
@@ -173,14 +220,14 @@ __device__ __forceinline__ int count_below2(const uint64_t *s0, const uint64_t *
                                              uint64_t k0, uint64_t k1) {
     uint32_t c = 0;
     for (int y = st; y < en; y += 4) {
-        uint64_t q0[4], q1[4];
+        uint64_t q0[4], q1[4], in[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             q0[i] = s0[y + i];
             q1[i] = s1[y + i];
+            in[i] = ballot(y + i < en);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c = add_below2(c, q0[i], q1[i], k0, k1, ballot(y + i < en));
+        c = add_below2(c, q0, q1, k0, k1, in);
     }
     return int(c);
 }
