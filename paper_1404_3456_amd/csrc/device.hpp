@@ -14,8 +14,9 @@ constexpr uint32_t kErrSpin = 4u;       // a look-back wait exceeded its bound
 constexpr uint32_t kErrRange = 8u;      // an index a kernel derived fell outside its array
 
 // Upper bound on look-back polls before a wait gives up (sets kErrSpin and continues).  A
-// predecessor tile always publishes without waiting on anything, so the bound is never
-// reached by a correct launch; it only guarantees that every wave exits.
+// predecessor tile always publishes without waiting on anything and after work bounded by its
+// tile's size (no kernel looks back after a search as long as its input makes it), so the bound
+// is never reached by a correct launch; it only guarantees that every wave exits.
 constexpr uint32_t kSpinLimit = 1u << 24;
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }

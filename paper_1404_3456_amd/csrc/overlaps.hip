@@ -18,9 +18,10 @@
 // Candidates are written in order of b as (a << 32 | b, l), sorted by a with the stable radix
 // sort (keeping b order within a), and reduced to one row per (a, b) with the largest l.
 //
-// Each of these steps is one kernel whose prefix sums come from a look-back over its tiles
-// (separators to read ids and ends; candidates to their places; rows to theirs), so the host
-// waits twice: for the candidate count, which sizes the sort, and for the row count.
+// Prefix sums come from look-backs over tiles (separators to read ids and ends; candidates to
+// their places; rows to theirs), so the host waits twice: for the candidate count, which sizes
+// the sort, and for the row count.  The walks are a kernel without one: a look-back's wait is
+// bounded, and a walk is as long as its input makes it.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -35,7 +36,7 @@ __device__ __forceinline__ uint32_t read_of(const uint32_t *__restrict__ sepmask
 
 // Device words of a call: error bits, lcp[0], reads, candidates and rows (64 bits each).
 constexpr int kOvErr = 0, kOvLcp0 = 1, kOvReads = 2, kOvHits = 4, kOvRows = 6;
-constexpr int kOvTick = 16;  // tickets of the three look-backs
+constexpr int kOvTick = 16;  // tickets of the reads, the walks, the rows and the placing
 
 // Validates the text and finds its reads: separator bits and the separators before each word
 // of 32 positions, the read ends while they fit, and the read count.
@@ -163,12 +164,21 @@ __device__ __forceinline__ void walk_read(const int32_t *__restrict__ sa, const 
     }
 }
 
+// The matches of a tile of reads: how many, and where among the unplaced ones they lie.
+struct OvlTile {
+    uint64_t count, at;
+};
+
 // One read per thread, tiles by ticket (the read count is only on the device).  A thread keeps
-// its first kWkKeep matches in LDS while its tile's place is found; a read with more is walked
-// again.  Matches are written while they fit in cap_hits, the count always.  Nothing is walked
-// when the text or the LCP array is not valid.
-// Bound by each walk's chain of reads: 72 us for 100,000 reads in 50.1 M suffixes, where a walk
-// to count, a scan and a walk to write took 90.
+// its first kWkKeep matches in LDS while its tile takes room for all of its own, one addition to
+// the count; a read with more is walked again.  A tile's matches are written together, in order,
+// if they fit in cap_hits; k_ovl_place puts the tiles in order.  Nothing is walked when the text
+// or the LCP array is not valid.
+// No workgroup waits for another: the matches of one read can take seconds to find (a short
+// read of one letter beside a read of millions of it), longer than a look-back polls.
+// Bound by each walk's chain of reads: 46 us for 100,000 reads in 50.1 M suffixes, and 12 to place
+// their matches (72 in one kernel that looked back between the two; a walk to count, a scan and
+// a walk to write took 90).
 constexpr int kWkBlock = 256;
 constexpr int kWkKeep = 12;
 __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
@@ -176,10 +186,10 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
     const int32_t *__restrict__ lcp, const int32_t *__restrict__ read_end,
     const uint32_t *__restrict__ sepmask, const int32_t *__restrict__ sepcnt, uint32_t n,
     int64_t cap_reads, int32_t min_len, uint64_t *__restrict__ hkeys, uint32_t *__restrict__ hvals,
-    int64_t cap_hits, uint64_t *lbflags, uint32_t *ctr) {
+    int64_t cap_hits, OvlTile *__restrict__ tiles, uint32_t *ctr) {
     __shared__ uint32_t s_tile;
-    __shared__ uint64_t s_excl;
-    __shared__ uint32_t s_w[kWkBlock / kWave];
+    __shared__ uint64_t s_at;
+    __shared__ uint64_t s_w[kWkBlock / kWave];
     __shared__ uint32_t s_a[kWkKeep][kWkBlock], s_l[kWkKeep][kWkBlock];
     const uint32_t tid = threadIdx.x;
     uint32_t *err = ctr + kOvErr;
@@ -189,6 +199,7 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
                        int64_t(reads) <= cap_reads;
     const uint32_t m = valid ? reads : 0u;
     const uint32_t ntiles = (m + kWkBlock - 1) / kWkBlock;
+    if (blockIdx.x >= ntiles) return;  // the others are enough (a ticket takes 11 ns of all)
     while (true) {
         __syncthreads();
         if (tid == 0) s_tile = ticket(ctr + kOvTick + 1);
@@ -206,17 +217,24 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
                           }
                           ++c;
                       });
-        uint32_t total;
-        const uint32_t mine = block_excl_sum<kWkBlock>(c, s_w, &total);
-        if (tid < kWave) {
-            const uint64_t ex = lookback_tile<SumOp>(lbflags, int(tile), total, err);
-            if (tid == 0) s_excl = ex;
+        const uint64_t inc = wave_incl_scan<SumOp>(uint64_t(c));
+        if (lane_id() == kWave - 1) s_w[tid / kWave] = inc;
+        __syncthreads();
+        uint64_t before = inc - c, total = 0;
+#pragma unroll
+        for (int w = 0; w < kWkBlock / kWave; ++w) {
+            if (uint32_t(w) < tid / kWave) before += s_w[w];
+            total += s_w[w];
+        }
+        if (tid == 0) {
+            s_at = total ? __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(ctr + kOvHits), total,
+                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                         : 0;
+            tiles[tile] = OvlTile{total, s_at};
         }
         __syncthreads();
-        uint64_t o = s_excl + mine;
-        if (tid == 0 && tile == ntiles - 1)
-            *reinterpret_cast<uint64_t *>(ctr + kOvHits) = s_excl + total;
-        if (c == 0 || o + c > uint64_t(cap_hits)) continue;
+        if (c == 0 || s_at + total > uint64_t(cap_hits)) continue;
+        uint64_t o = s_at + before;
         if (c <= uint32_t(kWkKeep)) {
             for (uint32_t k = 0; k < c; ++k, ++o) {
                 hkeys[o] = (uint64_t(s_a[k][tid]) << 32) | b;
@@ -233,10 +251,47 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
     }
 }
 
-// Rows of the sorted candidates: one per run of equal (a, b) keys, with the longest length.
-constexpr int kRwBlock = 256;
+// The tiles' matches, put in the order of the tiles, and the rows' look-back words cleared;
+// nothing when they did not all fit in cap_hits.  Bound by memory (24 bytes a match).
+constexpr int kPlBlock = 256;
+constexpr int kRwBlock = 256;  // of the rows' kernel
 constexpr int kRwItems = 4;
 constexpr int kRwTile = kRwBlock * kRwItems;
+__global__ __launch_bounds__(kPlBlock) void k_ovl_place(
+    const OvlTile *__restrict__ tiles, const uint64_t *__restrict__ hkeys,
+    const uint32_t *__restrict__ hvals, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
+    int64_t cap_hits, uint64_t *__restrict__ lb_rows, uint64_t *lbflags, uint32_t *ctr) {
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_to;
+    const uint64_t hits = *reinterpret_cast<const uint64_t *>(ctr + kOvHits);
+    if (hits == 0 || hits > uint64_t(cap_hits)) return;  // 0 too where nothing was walked
+    const uint32_t ntiles = (ctr[kOvReads] + kWkBlock - 1) / kWkBlock;
+    if (blockIdx.x >= ntiles) return;
+    const uint32_t groups = gridDim.x < ntiles ? gridDim.x : ntiles;  // those that go on
+    for (uint64_t i = blockIdx.x * kPlBlock + threadIdx.x; i * kRwTile < hits; i += groups * kPlBlock)
+        lb_rows[i] = 0;
+    while (true) {
+        __syncthreads();
+        if (threadIdx.x == 0) s_tile = ticket(ctr + kOvTick + 3);
+        __syncthreads();
+        const uint32_t tile = s_tile;
+        if (tile >= ntiles) break;
+        const OvlTile t = tiles[tile];
+        if (threadIdx.x < kWave) {
+            const uint64_t to = lookback_tile<SumOp>(lbflags, int(tile), t.count, ctr + kOvErr);
+            if (threadIdx.x == 0) s_to = to;
+        }
+        __syncthreads();
+        const uint64_t to = s_to;
+        if (to + t.count > hits) continue;  // a look-back that gave up: reported
+        for (uint64_t i = threadIdx.x; i < t.count; i += kPlBlock) {
+            keys[to + i] = hkeys[t.at + i];
+            vals[to + i] = hvals[t.at + i];
+        }
+    }
+}
+
+// Rows of the sorted candidates: one per run of equal (a, b) keys, with the longest length.
 __global__ __launch_bounds__(kRwBlock) void k_ovl_rows(const uint64_t *__restrict__ keys,
                                                        const uint32_t *__restrict__ vals, uint32_t r,
                                                        int32_t *__restrict__ out, int64_t cap,
@@ -306,23 +361,30 @@ static void carve_fixed(Carver &c, int64_t n, OvlFixed *F) {
 }
 struct OvlReads {
     int32_t *read_end;
-    uint64_t *lb_walk;
+    uint64_t *lb_place;
+    OvlTile *tiles;
 };
 static void carve_reads(Carver &c, int64_t m, OvlReads *R) {
     R->read_end = c.take<int32_t>(m);
-    R->lb_walk = c.take<uint64_t>((m + kWkBlock - 1) / kWkBlock + 1);
+    R->lb_place = c.take<uint64_t>((m + kWkBlock - 1) / kWkBlock + 1);
+    R->tiles = c.take<OvlTile>((m + kWkBlock - 1) / kWkBlock + 1);
 }
-// keys[0] and vals[0], where the walks write, come first: their places do not depend on r
+// The rows' look-back words, and keys[0] and vals[0], where the matches are placed, come first:
+// their places do not depend on r.  The sort's other half, which follows, holds the matches
+// before that.
 struct OvlHits {
     SortBufs sb;
     uint64_t *lb_rows;
 };
-static void carve_hits(Carver &c, int64_t hits, int64_t r, const Tune &t, OvlHits *H) {
+static void take_hits(Carver &c, int64_t hits, int64_t r, OvlHits *H) {
+    H->lb_rows = c.take<uint64_t>((hits + kRwTile - 1) / kRwTile + 1);
     H->sb.keys[0] = c.take<uint64_t>(hits);
     H->sb.vals[0] = c.take<uint32_t>(hits);
     H->sb.keys[1] = c.take<uint64_t>(r);
     H->sb.vals[1] = c.take<uint32_t>(r);
-    H->lb_rows = c.take<uint64_t>((r + kRwTile - 1) / kRwTile + 1);
+}
+static void carve_hits(Carver &c, int64_t hits, int64_t r, const Tune &t, OvlHits *H) {
+    take_hits(c, hits, r, H);
     carve_sort(c, r, 32, t, &H->sb, false);
 }
 
@@ -356,14 +418,14 @@ extern "C" int64_t sa_overlaps_ws_bytes(int64_t n, int64_t m, int64_t candidates
 // The reads and, while they fit, the candidates of the text: kOv* words to host[].
 static int find_hits(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
                      const int32_t *lcp, int32_t min_len, const OvlFixed &F, const OvlReads &R,
-                     int64_t cap_reads, uint64_t *keys, uint32_t *vals, int64_t cap_hits,
+                     int64_t cap_reads, const OvlHits &H, int64_t cap_hits,
                      uint32_t host[kStWords], hipStream_t s) {
     const int64_t tag = timing_round_begin();
     timing_scope_mode(kModeAny);
     const int64_t rt = reads_tiles(n), wt = (cap_reads + kWkBlock - 1) / kWkBlock;
     const int64_t most = rt > wt ? rt : wt;
     hipLaunchKernelGGL(k_ovl_init, dim3(unsigned(most / 256 + 1 < 256 ? most / 256 + 1 : 256)), dim3(256), 0, s,
-                       F.ctr, F.lb_reads, uint32_t(rt), R.lb_walk, uint32_t(wt));
+                       F.ctr, F.lb_reads, uint32_t(rt), R.lb_place, uint32_t(wt));
     {
         TimedScope ts("pack", double(n) + double(sepmask_words(n)) * 8.0, s, double(n));
         hipLaunchKernelGGL(k_ovl_reads, dim3(unsigned(rt)), dim3(kRdBlock), 0, s, text, n, lcp, F.sepmask,
@@ -375,8 +437,10 @@ static int find_hits(const uint8_t *text, int64_t n, const int32_t *sa, const in
         // at most eight workgroups a CU, which take tiles until none is left
         const unsigned g = unsigned(wt < 1 ? 1 : wt < 2048 ? wt : 2048);
         hipLaunchKernelGGL(k_ovl_walk, dim3(g), dim3(kWkBlock), 0, s, sa, isa,
-                           lcp, R.read_end, F.sepmask, F.sepcnt, uint32_t(n), cap_reads, min_len, keys,
-                           vals, cap_hits, R.lb_walk, F.ctr);
+                           lcp, R.read_end, F.sepmask, F.sepcnt, uint32_t(n), cap_reads, min_len,
+                           H.sb.keys[1], H.sb.vals[1], cap_hits, R.tiles, F.ctr);
+        hipLaunchKernelGGL(k_ovl_place, dim3(g), dim3(kPlBlock), 0, s, R.tiles, H.sb.keys[1],
+                           H.sb.vals[1], H.sb.keys[0], H.sb.vals[0], cap_hits, H.lb_rows, R.lb_place, F.ctr);
         ts.finish();
     }
     SA_HIP(hipGetLastError());
@@ -417,8 +481,9 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
     Tune t;
     resolve_tuning(nullptr, &t);
     // What the text-sized part leaves is split before the counts are known: a sixteenth is
-    // room for read ends and look-back words (under 5 bytes a read), and of the rest about a
-    // third for the candidates the walks find (12 of their 26 bytes and the sort's words).
+    // room for read ends and tile words (under 5 bytes a read), and of the rest about two
+    // thirds for the candidates the walks find (24 of their 26 bytes and the sort's words, so at
+    // 36 a candidate the rest of a workspace holds them twice).
     // Where the counts do not fit that split, the search runs again with the sizes it found.
     Carver c(ws, ws_bytes - 256);
     OvlFixed F;
@@ -433,11 +498,9 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
     uint32_t host[kStWords];
     carve_reads(c, cap_reads, &R);
     Carver at_hits = c;
-    H.sb.keys[0] = c.take<uint64_t>(cap_hits);
-    H.sb.vals[0] = c.take<uint32_t>(cap_hits);
+    take_hits(c, cap_hits, cap_hits, &H);
     if (!c.ok()) cap_hits = 0;
-    SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, cap_reads, H.sb.keys[0], H.sb.vals[0], cap_hits,
-                     host, s));
+    SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, cap_reads, H, cap_hits, host, s));
     const int64_t m = host[kOvReads];
     int64_t r = words64(host, kOvHits);
     bool known = m <= cap_reads;  // the walks ran
@@ -454,10 +517,8 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
             carve_reads(c, m, &R);
             at_hits = c;
             cap_hits = known ? r : 0;
-            H.sb.keys[0] = c.take<uint64_t>(cap_hits);
-            H.sb.vals[0] = c.take<uint32_t>(cap_hits);
-            SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H.sb.keys[0], H.sb.vals[0], cap_hits,
-                             host, s));
+            take_hits(c, cap_hits, cap_hits, &H);
+            SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H, cap_hits, host, s));
             r = words64(host, kOvHits);
             if (known && r <= cap_hits) break;
             known = true;
@@ -480,7 +541,7 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
         carve_reads(c, m, &R);
         carve_hits(c, r, r, t, &H);
         const int64_t r0 = r;
-        SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H.sb.keys[0], H.sb.vals[0], r, host, s));
+        SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, m, H, r, host, s));
         r = words64(host, kOvHits);
         if (r != r0) return fail(SA_ERR_HIP, "sa_overlaps: the candidate count changed between walks");
     }
@@ -493,7 +554,6 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
         SA_TRY(launch_hist(H.sb, 0, r, 32, abits, t, s, &nparts));
         SA_TRY(sort_run(H.sb, 0, nullptr, r, 32, abits, t, nparts, s, &cur));
     }
-    SA_TRY(launch_fill_u64(H.lb_rows, row_tiles, 0, s));
     hipLaunchKernelGGL(k_ovl_rows, dim3(unsigned(row_tiles)), dim3(kRwBlock), 0, s, H.sb.keys[cur],
                        H.sb.vals[cur], uint32_t(r), out, cap, H.lb_rows, F.ctr);
     SA_HIP(hipGetLastError());

@@ -1,0 +1,50 @@
+"""sa_overlaps over many tiles of reads: tiles whose walks differ a hundredfold in length, more
+tiles than workgroups walk at once, and tiles with and without matches.  Exact against the
+oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1404_3456_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+LETTERS = np.frombuffer(b"ACGT", dtype=np.uint8)
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_1404_3456_amd as p
+    p.load()
+    return p
+
+
+def check(lib, text, min_len):
+    t = torch.from_numpy(text).cuda()
+    sa, isa = lib.sa_build(t)
+    rows = lib.sa_overlaps(t, sa, isa, lib.sa_lcp(t, sa, isa), min_len).cpu().numpy()
+    assert np.array_equal(rows, oracle.overlaps(text, min_len))
+    return rows.shape[0]
+
+
+@pytest.mark.parametrize("at", [0, 300, 700])
+def test_one_long_walk(lib, at):
+    """A read of one letter whose interval holds the suffixes of a long read of it."""
+    rng = np.random.default_rng([synth.SEED_BASE, 805, at])
+    genome = rng.choice(LETTERS, 4000).tobytes().decode()
+    reads = [genome[k:k + 60] for k in rng.integers(0, 3940, 700)]
+    reads[at:at] = ["A" * 30]
+    assert check(lib, synth.text_from_strings(reads + ["A" * 5000, "C" + "A" * 40]), 12) > 700
+
+
+@pytest.mark.parametrize("m", [2047 * 256, 2048 * 256 + 1, 2051 * 256 - 1])
+def test_more_tiles_than_walk_at_once(lib, m):
+    """The edges of 2,048 tiles of 256 reads; every other stretch of 1,024 reads, of one base, has
+    no match."""
+    rng = np.random.default_rng([synth.SEED_BASE, 806, m])
+    some = rng.choice(LETTERS, (m, 10))
+    some[:, 9] = ord("$")
+    keep = np.ones(some.shape, dtype=bool)
+    keep[(np.arange(m) // 1024) % 2 == 1, 1:9] = False
+    assert check(lib, some[keep], 8) > 0
