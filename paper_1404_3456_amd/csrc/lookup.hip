@@ -100,7 +100,8 @@ struct Pattern {
 // Compares P with the suffix at p, whose first k bases are known to equal P's.  Returns < 0 when
 // the suffix sorts below P without starting with it, 0 when it starts with P, > 0 when it sorts
 // above P; *l = their common prefix (<= P.m).  One record of the text a step: most suffixes
-// differ from P within the first.  The text ends with a separator, so no record past it is read.
+// differ from P within the first.  The text ends with a separator (k_lookup does not search one
+// that does not), so no record past it is read.
 __device__ __forceinline__ int cmp_suffix(const uint4 *__restrict__ blk,
                                           const uint32_t *__restrict__ ppk, const Pattern &P,
                                           uint32_t p, uint32_t k, uint32_t *l) {
@@ -139,6 +140,10 @@ __global__ __launch_bounds__(256) void k_lookup(const uint4 *__restrict__ blk,
                                                 uint32_t ns, uint32_t stride,
                                                 int32_t *__restrict__ lohi, uint32_t *err) {
     __shared__ uint64_t s_top[kTopSamples];
+    // Without a separator at its end nothing stops a comparison there: a long pattern would be
+    // compared with whatever follows the text's records.  (Found by the packing, so the same for
+    // every thread; the call fails.)
+    if (ld_agent(err) & kErrNoSepEnd) return;
     const uint32_t step = (ns + kTopSamples - 1) / kTopSamples;  // samples per held one
     const uint32_t nt = ns ? (ns + step - 1) / step : 0;
     for (uint32_t t = threadIdx.x; t < nt; t += 256) s_top[t] = samples[t * step];
