@@ -206,16 +206,16 @@ constexpr int kStLcpLong = 12; // the LCP array needs Kasai's scan (launch_lcp_r
 constexpr int kStWords = 16;   // state words the host reads back
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
-// Pinned host words and events for reading device words without a full stream sync (one set
-// per host thread; two slots so one round's state can be in flight while the other is read,
-// and a third for read_words).
+// Pinned host words and events for reading device words without a full stream sync (two slots so
+// one round's state can be in flight while the other is read, and a third for read_words).
 struct PinnedState {
     uint32_t *h = nullptr;
     hipEvent_t ev[2] = {nullptr, nullptr};
-    bool ok = false;
-    PinnedState();
+    int device = 0;
+    PinnedState *next = nullptr;
 };
-PinnedState &pinned_state();
+// The calling thread's for the current device, until the thread ends; NULL when none can be made.
+PinnedState *pinned_state();
 // Copies kStWords device words to the host and waits for the stream: one copy to pinned memory
 // (a copy to pageable memory takes two more steps on the host).
 int read_words(const uint32_t *dev, uint32_t host[kStWords], hipStream_t s);

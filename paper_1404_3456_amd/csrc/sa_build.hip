@@ -23,6 +23,8 @@
 // suffixes then form one block of the order, labels of different texts never mix, and the
 // block of text s is exactly the suffix array of text s (in concatenated coordinates).
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <vector>
 
 #include "device.hpp"
@@ -426,20 +428,75 @@ static int check_err(uint32_t e) {
     return SA_OK;
 }
 
-PinnedState::PinnedState() {
-    ok = hipHostMalloc(reinterpret_cast<void **>(&h), 3 * kStWords * 4, hipHostMallocDefault) == hipSuccess &&
-         hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) == hipSuccess &&
-         hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) == hipSuccess;
+// The states of threads that have ended, for others to take: a state is a page of pinned memory,
+// and a program with a thread for every request would otherwise hold one for each it ever had.
+// So there are as many as threads have held at once.  Never destroyed: threads can end after the
+// static destructors have run.
+namespace {
+struct PinnedPool {
+    std::mutex mu;
+    PinnedState *idle = nullptr;
+};
+PinnedPool &pinned_pool() {
+    static PinnedPool *pool = new PinnedPool;
+    return *pool;
 }
-PinnedState &pinned_state() {
-    static thread_local PinnedState ps;
-    return ps;
+struct PinnedHold {  // a thread's states, one for each device it calls on
+    PinnedState *mine = nullptr;
+    ~PinnedHold() {
+        if (!mine) return;
+        PinnedPool &pool = pinned_pool();
+        std::lock_guard<std::mutex> lock(pool.mu);
+        while (PinnedState *p = mine) {
+            mine = p->next;
+            p->next = pool.idle;
+            pool.idle = p;
+        }
+    }
+};
+
+PinnedState *take_pinned(int device) {
+    PinnedPool &pool = pinned_pool();
+    {
+        std::lock_guard<std::mutex> lock(pool.mu);
+        for (PinnedState **at = &pool.idle; *at; at = &(*at)->next) {
+            if ((*at)->device != device) continue;
+            PinnedState *p = *at;
+            *at = p->next;
+            return p;
+        }
+    }
+    std::unique_ptr<PinnedState> p(new PinnedState);
+    p->device = device;
+    if (hipHostMalloc(reinterpret_cast<void **>(&p->h), 3 * kStWords * 4, hipHostMallocDefault) != hipSuccess)
+        return nullptr;
+    if (hipEventCreateWithFlags(&p->ev[0], hipEventDisableTiming) == hipSuccess) {
+        if (hipEventCreateWithFlags(&p->ev[1], hipEventDisableTiming) == hipSuccess) return p.release();
+        (void)hipEventDestroy(p->ev[0]);
+    }
+    (void)hipHostFree(p->h);
+    return nullptr;
+}
+}  // namespace
+
+PinnedState *pinned_state() {
+    static thread_local PinnedHold hold;
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    for (PinnedState *p = hold.mine; p; p = p->next)
+        if (p->device == device) return p;
+    PinnedState *p = take_pinned(device);
+    if (p) {
+        p->next = hold.mine;
+        hold.mine = p;
+    }
+    return p;
 }
 
 int read_words(const uint32_t *dev, uint32_t host[kStWords], hipStream_t s) {
-    PinnedState &ps = pinned_state();
-    if (!ps.ok) return fail(SA_ERR_HIP, "no pinned host memory for device words");
-    uint32_t *h = ps.h + 2 * kStWords;
+    PinnedState *ps = pinned_state();
+    if (!ps) return fail(SA_ERR_HIP, "no pinned host memory for device words");
+    uint32_t *h = ps->h + 2 * kStWords;
     SA_HIP(hipMemcpyAsync(h, dev, kStWords * 4, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
     memcpy(host, h, kStWords * 4);
@@ -657,12 +714,21 @@ struct Build {
         return SA_OK;
     }
 
+    // A build that fails waits for what it has enqueued: a state copy among it would land in
+    // pinned words that the next build, of this thread or another, reads.
     int run(bool use_graph, int *rounds_out, bool *have_lcp) {
+        const int rc = rounds(use_graph, rounds_out, have_lcp);
+        if (rc != SA_OK) (void)hipStreamSynchronize(s);
+        return rc;
+    }
+
+    int rounds(bool use_graph, int *rounds_out, bool *have_lcp) {
         rbits = bits_for(n - 1);
         choose_first_round();
         if (h0 < 1) return fail(SA_ERR_INVALID, "too many texts in one batch");
-        PinnedState &ps = pinned_state();
-        if (!ps.ok) return fail(SA_ERR_HIP, "sa_build: no pinned host memory for round state");
+        PinnedState *const pinned = pinned_state();
+        if (!pinned) return fail(SA_ERR_HIP, "sa_build: no pinned host memory for round state");
+        PinnedState &ps = *pinned;
         uint32_t host[kStWords];
         // Round 1 waits for round 0's state: whether its groups are all small (then no round
         // needs the radix passes again), and how many suffixes are left.
