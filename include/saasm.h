@@ -126,8 +126,8 @@ int sa_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int32_t bit_lo, int
 int64_t sa_build_ws_bytes(int64_t n, const sa_tuning *tune_or_null);
 
 /* One workspace for the whole path on a text of n bytes with at most n_reads_upper reads
- * (<= 0: assume n): the largest of what sa_build (default tuning), sa_lcp and sa_overlaps need,
- * the last with room for up to n candidate matches of its walks (a text with more makes
+ * (<= 0: assume n): the largest of what sa_build (default tuning; sa_build_batched of the one
+ * text, with its LCP array, needs no more), sa_lcp and sa_overlaps need, the last with room for up to n candidate matches of its walks (a text with more makes
  * sa_overlaps return SA_ERR_NOMEM with the size it needs).  The calls may share it because each
  * finishes with it before the next starts on the same stream.  -1 for n < 1. */
 int64_t sa_workspace_bytes(int64_t n, int64_t n_reads_upper);

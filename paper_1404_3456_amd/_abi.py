@@ -371,22 +371,17 @@ def _index(t, ws, stream):
 
 
 def sa_path(text, min_len: int, stream=None, ws=None):
-    """The whole path -- suffix array, LCP array, overlaps -- through one workspace (allocated
-    here unless `ws` is given; sa_workspace_bytes(n, reads) bytes are enough): (sa, isa, lcp,
+    """The whole path -- suffix array, LCP array, overlaps -- through one workspace of
+    sa_workspace_bytes(n, reads) bytes (allocated here unless `ws` is given): (sa, isa, lcp,
     overlap rows)."""
     torch = _torch()
     lib = load()
     t = _dev_text(text)
     n = t.numel()
     if ws is None:
-        ws = _ws(max(sa_workspace_bytes(n, 0), _index_ws_bytes(n)), t.device)
+        ws = _ws(sa_workspace_bytes(n, 0), t.device)
     st = _stream(stream)
-    if ws.numel() >= _index_ws_bytes(n):
-        sa, isa_t, lcp = _index(t, ws, stream)
-    else:  # a workspace of the three calls' size without the room a build's own LCP takes
-        sa, isa_t, lcp = (torch.empty(n, dtype=torch.int32, device=t.device) for _ in range(3))
-        _check(lib.sa_build(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(ws), ws.numel(), None, None, st))
-        _check(lib.sa_lcp(_ptr(t), n, _ptr(sa), _ptr(isa_t), _ptr(lcp), _ptr(ws), ws.numel(), st))
+    sa, isa_t, lcp = _index(t, ws, stream)
     cap = _rows_guess(n)
     for _ in range(4):
         out = torch.empty((cap, 3), dtype=torch.int32, device=t.device)

@@ -275,7 +275,8 @@ struct BuildLayout {
     uint32_t *tickets;
     uint32_t *state;       // kSt* words
     int64_t *set_off;      // batched builds: [n_sets + 1]
-    void *lcp_ws;          // batched builds: workspace of the LCP computed after the build
+    void *lcp_ws;          // batched builds: workspace of the LCP computed after the build,
+                           // in the sort's buffers, which are idle then
     int64_t lcp_ws_bytes;
 };
 
@@ -289,14 +290,16 @@ static void carve_build(Carver &c, int64_t n, int n_sets, const Tune &t, BuildLa
     L->slots[1] = L->slots[0] ? L->slots[0] + n64 : nullptr;
     L->pos = c.take<uint32_t>(n);
     L->bigidx = c.take<uint32_t>(n);
+    const int64_t sort_at = (c.off + 255) & ~int64_t(255);
     carve_sort(c, n, bits, t, &L->sb, true);
+    L->lcp_ws = L->sb.keys[0];
+    L->lcp_ws_bytes = c.off - sort_at;
     L->lb_words = (n + kLbMinTile - 1) / kLbMinTile + 16;
     L->lbflags = c.take<uint64_t>(L->lb_words);
     L->tickets = c.take<uint32_t>(64);
     L->state = c.take<uint32_t>(64);
-    L->set_off = c.take<int64_t>(n_sets + 1);
-    L->lcp_ws_bytes = n_sets > 0 ? lcp_ws_bytes(n) : 0;
-    L->lcp_ws = n_sets > 0 ? c.take<char>(L->lcp_ws_bytes) : nullptr;
+    // not used for one text, which so needs the same in a batch of its own
+    L->set_off = c.take<int64_t>(n_sets > 1 ? n_sets + 1 : 1);
 }
 
 // Keys of a doubling round built in the previous round's sorted order and sorted group by
@@ -858,8 +861,7 @@ static int build_common(const uint8_t *text, int64_t n, const int64_t *set_off_h
     carve_build(c, n, n_sets, t, &B.L);
     B.L.sb.err = B.L.state + kStErr;
     B.rank = isa_or_null ? reinterpret_cast<uint32_t *>(isa_or_null) : B.L.rank;
-    if (lcp_or_null && (n_sets < 1 || !B.L.lcp_ws))
-        return fail(SA_ERR_INVALID, "LCP output needs a batched build");
+    if (lcp_or_null && n_sets < 1) return fail(SA_ERR_INVALID, "LCP output needs a batched build");
     B.lcp = lcp_or_null;
     int rounds = 0;
     bool have_lcp = false;  // the array is complete
@@ -1011,7 +1013,8 @@ extern "C" int sa_build_batched(const uint8_t *text, int64_t n, const int64_t *s
     return guard<int>([&] { return sa_build_batched_impl(text, n, set_off_h, n_sets, sa, isa_or_null, lcp_or_null, ws, ws_bytes, tune, use_graph, rounds_h, stream); });
 }
 
-// One workspace for sa_build, sa_lcp and sa_overlaps (up to n candidate matches).
+// One workspace for sa_build, or sa_build_batched of the one text (the same size), sa_lcp and
+// sa_overlaps (up to n candidate matches).
 extern "C" int64_t sa_workspace_bytes(int64_t n, int64_t n_reads_upper) {
     if (n < 1) return -1;
     const int64_t m = n_reads_upper <= 0 || n_reads_upper > n ? n : n_reads_upper;
