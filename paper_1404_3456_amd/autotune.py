@@ -18,8 +18,10 @@ from . import _abi
 DEFAULT_CACHE = os.path.join(os.environ.get("XDG_CACHE_HOME", os.path.expanduser("~/.cache")),
                              "saasm", "autotune.json")
 
-# (digit_bits, block_threads, items_per_thread)
-TILE_CANDIDATES = [(8, 1024, 16), (9, 1024, 16), (8, 512, 16), (9, 512, 16), (8, 256, 16),
+# (digit_bits, block_threads, items_per_thread).  The first is the untuned default, whose tile
+# follows each sort's number of items and whose small builds start by top bits: no choice is then
+# slower than none.
+TILE_CANDIDATES = [(0, 0, 0), (8, 1024, 16), (9, 1024, 16), (8, 512, 16), (9, 512, 16), (8, 256, 16),
                    (8, 512, 8), (11, 512, 16), (4, 1024, 16)]
 
 
