@@ -537,6 +537,8 @@ SURVEY_BYTES = {
     "radix_pass": 24.0,   # read and write an 8-byte key and a 4-byte value
     "keybuild": 20.0,     # doubling keys, per large-group item (read rank[p+h]; write key, value)
     "keyruns": 20.0,      # the same keys, built and ordered run by run
+    "first_extract": 8.0, # read the key, per suffix
+    "first_runs": 20.0,   # read key 8 + value 4, write the rank 4 and the SA entry 4, per suffix
     "rank_update": 16.0,  # read key 8 + SA 4, write the rank 4, per active suffix
     "kasai": 12.0,        # isa 4 + the gathered sa 4 + the lcp write 4, per suffix
     "lcp_gather": 0.0,    # second half of the position-ordered LCP form (inside Kasai's 12)
@@ -545,23 +547,37 @@ KERNEL_NAMES = {
     "radix_pass": "k_onesweep (one LSD radix pass)",
     "rank_update": "k_rank_update (group labels; random 4-byte scatter)",
     "kasai": "k_kasai (LCP; random gathers)",
-    "keyruns": "k_first_runs, k_keys_runs (keys sorted run by run in LDS)",
+    "first_runs": "k_first_runs (the first round's keys sorted run by run in LDS)",
+    "keyruns": "k_keys_runs (doubling keys sorted group by group in LDS)",
     "keybuild": "k_big_extract (doubling keys of the large groups' items)",
     "key0": "k_key0 (first-round keys + digit histograms)",
     "overlap_walk": "k_ovl_walk (LCP-interval walks)",
 }
-KEYS = ("pack", "key0", "radix_pass", "first_extract", "keybuild", "keyruns", "rank_update", "kasai",
-        "lcp_gather", "lcp_rest", "overlap_walk")
-BUILD_KEYS = ("pack", "key0", "radix_pass", "keybuild", "keyruns", "rank_update")
+KEYS = ("pack", "key0", "radix_pass", "first_extract", "first_runs", "keybuild", "keyruns",
+        "rank_update", "kasai", "lcp_gather", "lcp_rest", "overlap_walk")
+BUILD_KEYS = ("pack", "key0", "radix_pass", "first_extract", "first_runs", "keybuild", "keyruns",
+              "rank_update")
+
+
+def timed_launches(pkg, key):
+    """(launches, ms, bytes, units) under a key; of "keyruns" those of the doubling rounds' kernel
+    alone (the library files the first round's there too, and by itself as "first_runs")."""
+    L, ms, by = pkg.sa_timing_get(key)
+    items = pkg.sa_timing_items(key)
+    if key == "keyruns":
+        fL, fms, fby = pkg.sa_timing_get("first_runs")
+        if fL == L:
+            return 0, 0.0, 0.0, 0.0
+        return L - fL, ms - fms, by - fby, items - (pkg.sa_timing_items("first_runs") if fL else 0.0)
+    return L, ms, by, items
 
 
 def kernel_table(pkg, keys, steps):
     out = {}
     for key in keys:
-        L, ms, by = pkg.sa_timing_get(key)
+        L, ms, by, items = timed_launches(pkg, key)
         if not L:
             continue
-        items = pkg.sa_timing_items(key)
         e = {"launches_per_step": round(L / steps, 2), "ms_per_step": round(ms / steps, 4),
              "avg_us": round(ms * 1000.0 / L, 3), "units_per_step": round(items / steps),
              "impl_bytes_per_step": round(by / steps), "impl_GBs": round(by / (ms * 1e-3) / 1e9, 1)}
@@ -575,15 +591,16 @@ def kernel_table(pkg, keys, steps):
 
 
 def traffic_for(args, key, tuning):
-    """Counter-measured HBM bytes per launch (<kernel key>_traffic.json under profiles/), valid
-    only for the sources the counters were taken on and the default tuning."""
+    """Counter-measured bytes per launch at the L2's memory side (<kernel key>_traffic.json under
+    profiles/), valid only for the sources the counters were taken on and the default tuning."""
     import hashlib
     sources = {"radix_pass": ("radix.hip", "device.hpp"),
                "sa_build": ("sa_build.hip", "first_round.hip", "radix.hip", "pack.hip", "device.hpp",
                             "internal.hpp"),
                "rank_update": ("sa_build.hip", "device.hpp", "internal.hpp"),
                "kasai": ("lcp.hip", "text.hpp", "device.hpp", "internal.hpp"),
-               "keyruns": ("first_round.hip", "sa_build.hip", "device.hpp", "internal.hpp")}
+               "first_runs": ("first_round.hip", "device.hpp", "internal.hpp"),
+               "keyruns": ("sa_build.hip", "device.hpp", "internal.hpp")}
     tpath = os.path.join(args.traffic_dir, f"{key}_traffic.json")
     if key not in sources or not os.path.exists(tpath) or tuning is not None:
         return None
@@ -768,8 +785,7 @@ def main():
                                        "dc3_merge") if args.sa_algo == "dc3" else ()), ks)
     dom = max((k for k in kern if k in KERNEL_NAMES), key=lambda k: kern[k]["ms_per_step"])
     d = kern[dom]
-    L, ms, by = pkg.sa_timing_get(dom)
-    items = pkg.sa_timing_items(dom)
+    L, ms, by, items = timed_launches(pkg, dom)
     avg_s = ms * 1e-3 / L
     per_unit = SURVEY_BYTES.get(dom)
     alg = items / L * per_unit if per_unit is not None else by / L

@@ -432,6 +432,7 @@ int asm_server_destroy(asm_server *server);
 /* Per-kernel timing with HIP events recorded on the launch stream around every instrumented
  * launch.  Keys: "radix_pass", "key0" (first-round keys), "keybuild" (doubling keys of
  * large groups), "keyruns" (keys sorted run by run, the first round's and the doubling rounds'),
+ * "first_runs" (the first round's part of "keyruns" by itself),
  * "first_extract" (first-round items in runs too long for that), "rank_update", "kasai", "lcp_gather",
  * "overlap_walk", "pack", "lookup".
  * sa_timing_get returns launches, summed duration (ms) and summed algorithmic bytes (the
@@ -441,7 +442,7 @@ int sa_timing_reset(void);
 int sa_timing_get(const char *key, int64_t *launches_h, double *total_ms_h, double *bytes_h);
 
 /* sa_timing_items: summed units of work of the timed launches under `key` (suffixes for
- * "pack", "key0", "first_extract", "kasai" and "lcp_gather"; items sorted for "radix_pass";
+ * "pack", "key0", "first_extract", "first_runs", "kasai" and "lcp_gather"; items sorted for "radix_pass";
  * active suffixes for "rank_update", "keyruns" and "keybuild"; reads for
  * "overlap_walk"; patterns for "lookup"), so that bytes per unit of any other model can be
  * applied to the same launches. */

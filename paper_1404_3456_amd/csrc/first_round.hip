@@ -825,12 +825,15 @@ static int launch_first_runs_t(const uint64_t *K, const uint32_t *V, const uint3
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
     // per suffix: key 8 and position 4 read; rank 4, and sa 4 or slot and position 8, written;
     // 36 bytes of packed text per window of a suffix still in a group; lcp 4
-    TimedScope ts("keyruns", double(n) * (lcp ? 28.0 : 24.0), s, double(n));
+    // (counted by the caller, who learns whether the launch gave up)
+    TimedScope ts("keyruns", 0.0, lcp ? 28.0 : 24.0, s);
+    TimedScope own("first_runs", 0.0, lcp ? 28.0 : 24.0, s);
     auto k = mixed ? (lcp ? k_first_runs<Shape, true, true> : k_first_runs<Shape, true, false>)
                    : (lcp ? k_first_runs<Shape, false, true> : k_first_runs<Shape, false, false>);
     hipLaunchKernelGGL(k, dim3(unsigned(tiles)), dim3(Shape::kBlock), 0, s, K, V, packed, uint32_t(n),
                        uint32_t(lo_bit), uint32_t(key_bits), uint32_t(top_d), uint32_t(h0), sa, rank,
                        S_new, P_new, lcp, lbflags, tick, state, state + kStErr);
+    own.finish();
     ts.finish();
     SA_HIP(hipGetLastError());
     return SA_OK;

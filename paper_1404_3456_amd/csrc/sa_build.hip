@@ -594,10 +594,13 @@ struct Build {
         }
         const int lo_bit = key0_bits - top_bits;
         SA_TRY(first_sort(lo_bit, &cur));
+        const int64_t plain = timing_round_begin();
+        timing_scope_mode(kModeAny);
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, false, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end(top_d));
         SA_TRY(wait_state(ps, host));
+        timing_round_items(plain, host[kStLongRun] ? 0 : n, 0);
         if (host[kStLongRun] == 0) return SA_OK;
         // Some run of equal top bits is too long for the run sort: its items are taken out,
         // sorted by their whole keys and put back, and the round's end runs again.  The passes
