@@ -16,9 +16,12 @@
 // The plain form of the kernel only reports them; the host then has their items taken out,
 // sorted by radix passes over the whole key and put back in place (k_first_extract,
 // k_big_place), and runs the other form, which takes such runs as sorted by h0 symbols and
-// first sorts the others by them too.
+// first sorts the others by them too.  Where nearly all runs are that long, all of this is in vain: a
+// sample of the suffixes tells before the first pass (k_sample_runs), and the round sorts by
+// whole keys alone.
 #include "device.hpp"
 #include "internal.hpp"
+#include "text.hpp"
 
 namespace saasm {
 
@@ -689,6 +692,77 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
     }
 }
 
+// What share of sampled suffixes have an equal among the positions looked at, on their first
+// top_d bases (and in the same text of a batch); see launch_sample_runs.  A thread looks at
+// kSampleRow positions in a row, somewhere in its part of the text, and takes those of which
+// skip bits of a hash are zero: the members of a run are taken or left together, so that few of
+// them tell as much of the runs' sizes as all would.  Each taken takes a slot of an open-addressed
+// table of (31 bits of the hash, "met twice") words; one that finds its word there, and marked
+// already, needs no atomic, so a text of one repeated base does not serialise on one word.  The
+// last workgroup decides.
+// Bound by latency, so the taken are listed in LDS first and then probe all at once: 11 us at 20 M
+// and at 50 M suffixes (54 to 61 with the probes in the loop over the row; 20 to 53 with every
+// position taken of 2^16 to 2^18).
+__global__ __launch_bounds__(kSampleBlock) void k_sample_runs(
+    const uint32_t *__restrict__ packed, const uint32_t *__restrict__ sepmask, uint32_t n,
+    uint32_t top_d, const int64_t *__restrict__ set_off, uint32_t n_sets, uint32_t part,
+    uint32_t skip, float enough, uint32_t *table, uint32_t *state) {
+    constexpr int kFirst = 21, kSecond = 42;  // fields of the counts: paired, taken, workgroups
+    static_assert(kMaxLooked < int64_t(1) << kFirst, "counts fit their fields");
+    static_assert(kSampleSlots <= 1 << 14, "slots come from 14 bits of the hash");
+    static_assert(kSampleRow - 1 + 24 < 32, "a row's bases lie in one word");
+    __shared__ uint32_t s_h[kSampleStep];
+    __shared__ uint32_t s_taken, s_paired;
+    if (threadIdx.x == 0) s_taken = s_paired = 0;
+    __syncthreads();
+    const uint32_t t = blockIdx.x * kSampleBlock + threadIdx.x;
+    // part positions a thread, at least 2 kSampleRow; (t + 1) * part <= n
+    const uint32_t a = t * part + uint32_t((uint64_t(t * 2654435769u) * (part - kSampleRow)) >> 32);
+    const uint64_t codes = codes_at(packed, a);
+    const uint32_t sep = bits_at(sepmask, a);
+#pragma unroll
+    for (int j = 0; j < kSampleRow; ++j) {
+        if ((sep << j) >> (32 - top_d)) continue;  // ends before top_d <= 24 bases
+        uint64_t h = (codes << (2 * j)) >> (64 - 2 * top_d);
+        h = (h ^ (h >> 29)) * 0x9e3779b97f4a7c15ull;
+        if (skip && h >> (64 - skip)) continue;
+        if (set_off) h += uint64_t(set_of(set_off, n_sets, a + j)) * 0xd1342543de82ef95ull;
+        h = (h ^ (h >> 32)) * 0x9e3779b97f4a7c15ull;
+        s_h[atomicAdd(&s_taken, 1u)] = uint32_t(h >> 32);
+    }
+    __syncthreads();
+    const uint32_t taken = s_taken;
+    uint32_t paired = 0;
+    for (uint32_t i = threadIdx.x; i < taken; i += kSampleBlock) {
+        const uint32_t tag = (s_h[i] | 2u) & ~1u;
+        uint32_t at = (tag >> 18) & uint32_t(kSampleSlots - 1);
+        for (int k = 0; k < 64; ++k, at = (at + 1) & uint32_t(kSampleSlots - 1)) {
+            uint32_t w = ld_agent(table + at);
+            if (w == 0) {
+                w = atomicCAS(table + at, 0u, tag);
+                if (w == 0) break;  // the first
+            }
+            if ((w & ~1u) != tag) continue;
+            // the second counts for the first too
+            paired += (w & 1u) || (atomicOr(table + at, 1u) & 1u) ? 1u : 2u;
+            break;
+        }
+    }
+    for (int o = 1; o < kWave; o <<= 1) paired += __shfl_xor(paired, o);
+    if (lane_id() == 0 && paired) atomicAdd(&s_paired, paired);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const uint64_t mine = (uint64_t(1) << kSecond) | (uint64_t(taken) << kFirst) | s_paired;
+    const uint64_t all = mine + __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(state + kStSample), mine,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (all >> kSecond != gridDim.x) return;
+    const uint32_t field = (1u << kFirst) - 1;
+    const uint32_t pairs = uint32_t(all) & field, of = uint32_t(all >> kFirst) & field;
+    if (of < 256 || float(pairs) < enough * float(of)) return;
+    st_agent(state + kStTopN, 0u);
+    st_agent(state + kStLongRun, 1u);
+}
+
 // The items of runs (as in k_first_runs) of more than kFrRun items, in order, with their whole
 // keys and their places in the list, and the digit counts of the passes that sort them.  The
 // runs' starts come from masks of 64 items: an item's run is long when the distance back to its
@@ -849,6 +923,21 @@ int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *pack
                                             S_new, P_new, lcp, lbflags, lb_words, tick, state, s);
     return launch_first_runs_t<FrLarge>(K, V, packed, n, lo_bit, key_bits, top_d, h0, mixed, sa, rank,
                                         S_new, P_new, lcp, lbflags, lb_words, tick, state, s);
+}
+
+int launch_sample_runs(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int top_d,
+                       const int64_t *set_off_dev, int n_sets, int64_t looked, double enough,
+                       uint32_t *table, uint32_t *state, hipStream_t s) {
+    const int64_t part = looked > 0 ? n / (looked / kSampleRow) : 0;
+    if (looked % kSampleStep || looked > kMaxLooked || part < 2 * kSampleRow || top_d < 1 || top_d > 24)
+        return fail(SA_ERR_HIP, "first round: bad sample");
+    uint32_t skip = 0;  // half as many hashes while half of the slots would be taken
+    while ((looked >> skip) >= kSampleSlots / 2) ++skip;
+    hipLaunchKernelGGL(k_sample_runs, dim3(unsigned(looked / kSampleStep)), dim3(kSampleBlock), 0, s, packed,
+                       sepmask, uint32_t(n), uint32_t(top_d), set_off_dev, uint32_t(n_sets),
+                       uint32_t(part), skip, float(enough), table, state);
+    SA_HIP(hipGetLastError());
+    return SA_OK;
 }
 
 int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,

@@ -203,6 +203,8 @@ constexpr int kStBigLast = 9;  // kStRadixN of the round that ended (read back f
 constexpr int kStLongRun = 10; // first round: a run of equal top key bits is too long for LDS
 constexpr int kStNoExt = 11;   // first round: some group is equal on the h0 symbols of its key only
 constexpr int kStLcpLong = 12; // the LCP array needs Kasai's scan (launch_lcp_rest)
+constexpr int kStTopN = 13;    // first round: items its passes over the top bits sort (n, or 0)
+constexpr int kStSample = 14;  // launch_sample_runs: its counts (64 bits)
 constexpr int kStWords = 16;   // state words the host reads back
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
@@ -241,6 +243,18 @@ int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *pack
                       uint32_t *rank, uint32_t *S_new, uint32_t *P_new, int32_t *lcp_or_null,
                       uint64_t *lbflags, int64_t lb_words, uint32_t *tick, uint32_t *state,
                       hipStream_t s);
+// Samples the text's suffixes at random, some 2^12 to 2^13 (all positions looked at, `looked`, a
+// multiple of kSampleStep and at most kMaxLooked, that fall into a part of the hashes), and sets
+// state[kStTopN] to 0 and state[kStLongRun] to 1 when the share of them that are equal to another
+// position looked at on top_d bases is at least `enough`.  table: kSampleSlots cleared words.
+constexpr int kSampleBlock = 256;
+constexpr int kSampleRow = 8;  // positions in a row a thread looks at
+constexpr int64_t kSampleStep = int64_t(kSampleBlock) * kSampleRow;
+constexpr int64_t kMaxLooked = int64_t(1) << 20;
+constexpr int64_t kSampleSlots = int64_t(1) << 14;
+int launch_sample_runs(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int top_d,
+                       const int64_t *set_off_dev, int n_sets, int64_t looked, double enough,
+                       uint32_t *table, uint32_t *state, hipStream_t s);
 int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo_bit, int top_d,
                          int key_bits,
                          const SortBufs &b, uint32_t *idx, uint64_t *lbflags, int64_t lb_words,

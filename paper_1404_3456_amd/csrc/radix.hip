@@ -554,7 +554,7 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
         const uint32_t shift = uint32_t(bit_lo + lo);
         const uint32_t dmask = (1u << width) - 1u;
         const uint32_t *vin = index_vals && p == 0 ? nullptr : b.vals[cur];
-        TimedScope ts = count_dev ? TimedScope("radix_pass", 0.0, 24.0, s)
+        TimedScope ts = count_dev ? TimedScope("radix_pass", 0.0, vin ? 24.0 : 20.0, s)
                                   : TimedScope("radix_pass", double(n) * (vin ? 24.0 : 20.0), s, double(n));
         int rc = SA_OK;
         uint32_t *fl = b.flags + size_t(p) * tiles * R;
@@ -620,18 +620,6 @@ __device__ __forceinline__ uint32_t sep_distance(const uint32_t *__restrict__ se
     const uint32_t next = __shfl(mine, int(k) + 2);  // every lane takes part
     if (here) return uint32_t(__clzll((long long)here));
     return later ? 64u - lane + 32u * k + uint32_t(__clz(next)) : 512u;
-}
-
-// Index of the text of a batch that holds position p: largest s with set_off[s] <= p.
-__device__ __forceinline__ uint32_t set_of(const int64_t *__restrict__ set_off, uint32_t n_sets,
-                                           uint32_t p) {
-    uint32_t lo = 0, hi = n_sets;  // invariant: set_off[lo] <= p < set_off[hi]
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (set_off[mid] <= int64_t(p)) lo = mid;
-        else hi = mid;
-    }
-    return lo;
 }
 
 // First-round keys of every suffix and the digit counts of the passes to come.  Bound by issue (67 M

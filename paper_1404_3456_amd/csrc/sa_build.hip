@@ -22,6 +22,7 @@
 // concatenation, with each text's index placed above the first-round key: every text's
 // suffixes then form one block of the order, labels of different texts never mix, and the
 // block of text s is exactly the suffix array of text s (in concatenated coordinates).
+#include <cmath>
 #include <cstring>
 #include <memory>
 #include <mutex>
@@ -40,6 +41,7 @@ constexpr int kRuTile = kRuBlock * kRuItems;
 constexpr int kLbMinTile = kFirstMinTile < kRuTile ? kFirstMinTile : kRuTile;
 
 constexpr int64_t kTunedTopMinN = 16384;  // choose_first_round
+constexpr int64_t kSampleMinN = int64_t(1) << 21;  // sample_looked
 
 // Rank update over the sorted active items (K, V) of a round, whose suffix-array slots are
 // S[0..A) (S == nullptr: identity, round 0).  For item i:
@@ -214,12 +216,15 @@ __global__ __launch_bounds__(kRuBlock) void k_rank_update(
     }
 }
 
-// The state a build starts from, and cleared look-back words for its first round.
+// The state a build starts from, and cleared look-back and table words for its first round.
 __global__ __launch_bounds__(256) void k_build_init(uint32_t *state, uint32_t n, uint64_t *lbflags,
-                                                    uint32_t nlb, uint32_t *tick) {
+                                                    uint32_t nlb, uint32_t *table, uint32_t ntable,
+                                                    uint32_t *tick) {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < nlb; i += gridDim.x * 256u) lbflags[i] = 0;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < ntable; i += gridDim.x * 256u) table[i] = 0;
     if (blockIdx.x != 0) return;
-    if (threadIdx.x < kStWords) state[threadIdx.x] = threadIdx.x == kStActive ? n : 0u;
+    if (threadIdx.x < kStWords)
+        state[threadIdx.x] = threadIdx.x == kStActive || threadIdx.x == kStTopN ? n : 0u;
     if (threadIdx.x == kStWords) *tick = 0;
 }
 
@@ -539,20 +544,21 @@ struct Build {
 
     // Keys and the passes over their bits [lo_bit, key0_bits): the sorted items end up in
     // buffer *cur.
-    int first_sort(int lo_bit, int *cur) {
-        const int64_t *set_off_dev = n_sets > 1 ? L.set_off : nullptr;
+    const int64_t *set_off_dev() const { return n_sets > 1 ? L.set_off : nullptr; }
+    int first_sort(int lo_bit, const uint32_t *count_dev, int *cur) {
         const int bits = key0_bits - lo_bit;
         int nparts = 0;
-        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev, n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
-        return sort_run(L.sb, 0, nullptr, n, lo_bit, bits, t, nparts, s, cur, true);
+        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev(), n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
+        return sort_run(L.sb, 0, count_dev, n, lo_bit, bits, t, nparts, s, cur, true);
     }
 
     int init() {
         const int64_t nlb = (n + kLbMinTile - 1) / kLbMinTile;
         if (nlb > L.lb_words) return fail(SA_ERR_HIP, "sa_build: look-back array too small");
         const int64_t g = (nlb + 255) / 256 < 1024 ? (nlb + 255) / 256 : 1024;
+        static_assert(kSampleSlots <= kSampleMinN, "the table lies in bigidx");
         hipLaunchKernelGGL(k_build_init, dim3(unsigned(g)), dim3(256), 0, s, L.state, uint32_t(n), L.lbflags,
-                           uint32_t(nlb), L.tickets);
+                           uint32_t(nlb), L.bigidx, sample_looked() ? uint32_t(kSampleSlots) : 0u, L.tickets);
         SA_HIP(hipGetLastError());
         return SA_OK;
     }
@@ -573,6 +579,17 @@ struct Build {
         return SA_OK;
     }
 
+    // A first round by passes over the whole key.
+    int round0_whole(PinnedState &ps, uint32_t host[kStWords]) {
+        int cur = 0;
+        SA_TRY(first_sort(0, nullptr, &cur));
+        SA_TRY(launch_rank_update(L.sb.keys[cur], L.sb.vals[cur], nullptr, n, n, true, h0, rbits,
+                                  sa, rank, L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets,
+                                  L.state, s));
+        SA_TRY(round_end());
+        return wait_state(ps, host);
+    }
+
     // The first round, and the state after it (pinned slot 0, host[]).
     int round0(PinnedState &ps, uint32_t host[kStWords]) {
         SA_TRY(init());
@@ -583,25 +600,30 @@ struct Build {
                                text, L.set_off, uint32_t(n_sets), L.state + kStErr);
             SA_HIP(hipGetLastError());
         }
-        int cur = 0;
-        if (top_bits == 0) {
-            SA_TRY(first_sort(0, &cur));
-            SA_TRY(launch_rank_update(L.sb.keys[cur], L.sb.vals[cur], nullptr, n, n, true, h0, rbits,
-                                      sa, rank, L.slots[0], L.pos, L.lbflags, L.lb_words, L.tickets,
-                                      L.state, s));
-            SA_TRY(round_end());
-            return wait_state(ps, host);
-        }
+        if (top_bits == 0) return round0_whole(ps, host);
+        const int64_t looked = sample_looked();
+        if (looked)
+            SA_TRY(launch_sample_runs(L.packed, L.sepmask, n, top_d, set_off_dev(), n_sets, looked,
+                                      sample_enough(looked), L.bigidx, L.state, s));
         const int lo_bit = key0_bits - top_bits;
-        SA_TRY(first_sort(lo_bit, &cur));
-        const int64_t plain = timing_round_begin();
+        int cur = 0;
+        const int64_t sorted = timing_round_begin();
         timing_scope_mode(kModeAny);
+        SA_TRY(first_sort(lo_bit, looked ? L.state + kStTopN : nullptr, &cur));
+        const int64_t plain = timing_round_begin();
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, false, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end(top_d));
         SA_TRY(wait_state(ps, host));
+        timing_round_items(sorted, host[kStTopN], 0);
         timing_round_items(plain, host[kStLongRun] ? 0 : n, 0);
         if (host[kStLongRun] == 0) return SA_OK;
+        if (host[kStTopN] == 0) {  // the passes and the run sort did nothing
+            SA_TRY(launch_fill_u32(L.state + 1, kStWords - 1, 0, s));
+            SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
+            whole_keys();
+            return round0_whole(ps, host);
+        }
         // Some run of equal top bits is too long for the run sort: its items are taken out,
         // sorted by their whole keys and put back, and the round's end runs again.  The passes
         // work between the idle half of the sort's buffers and the slot and position arrays,
@@ -668,6 +690,37 @@ struct Build {
         return round_end();
     }
 
+    int set_bits() const {  // of the text's index above a first-round key
+        int sb = 0;
+        while ((int64_t(1) << sb) < n_sets) ++sb;
+        return sb;
+    }
+    void whole_keys() {
+        const int sb = set_bits();
+        h0 = (63 - 5 - sb) / 2 < kH0 ? (63 - 5 - sb) / 2 : kH0;
+        key0_bits = 2 * h0 + 5 + sb;
+        top_d = top_bits = 0;
+    }
+
+    // Positions to look at before a first round by top bits (one in 128, the longest run that the
+    // run sort takes, so that such a run has one there on average), and the share of the sampled
+    // ones among them that must find an equal for it to sort by whole keys instead: what a text
+    // of runs of kDenseRun would have, and no less than four in ten.  Where runs are longer the
+    // passes over the top bits come on top of all others: 150-base reads at 150x coverage take
+    // 3.8 ms by top bits and 5.0 by whole keys (20 M suffixes), at 160x 4.5 and 5.0, at 200x 6.2
+    // and 5.0, at 300x 6.2 and 5.0, copies of one read 9.4 and 8.1; at 300x 50 M 13.7 and 11.3, 200 M
+    // 62.7 and 54.7.  Up to kSampleMinN top bits are the faster way at any coverage (0.3 M at
+    // 300x: 0.91 and 1.06), as fewer, larger launches count for more than passes.
+    static constexpr double kDenseRun = 130, kDenseShare = 0.4;
+    int64_t sample_looked() const {
+        if (top_bits == 0 || n <= kSampleMinN) return 0;
+        return (n / 128 < kMaxLooked ? n / 128 : kMaxLooked) / kSampleStep * kSampleStep;
+    }
+    double sample_enough(int64_t looked) const {
+        const double share = 1 - std::exp(-double(looked) * kDenseRun / double(n));
+        return share > kDenseShare ? share : kDenseShare;
+    }
+
     // How the first round sorts: by the first top_d bases of every key by passes over HBM and
     // by the rest run by run in LDS, where a run is the suffixes equal on those bases.  Whole
     // digits' worth of bases, so many that a random text of the longest one's size would hold
@@ -680,11 +733,8 @@ struct Build {
     // seven passes), not for speed.  The form by top bits is the faster one there too, at 1,000
     // characters 63 against 197 us, at 14,000 77 against 284, so every other build takes it.
     void choose_first_round() {
-        int sb = 0;
-        while ((int64_t(1) << sb) < n_sets) ++sb;
-        h0 = (63 - 5 - sb) / 2 < kH0 ? (63 - 5 - sb) / 2 : kH0;
-        key0_bits = 2 * h0 + 5 + sb;
-        top_d = top_bits = 0;
+        whole_keys();
+        const int sb = set_bits();
         if (t.fixed && n < kTunedTopMinN) return;
         int64_t longest = n_sets > 0 ? 0 : n;
         for (int k = 0; k < n_sets; ++k)

@@ -61,4 +61,16 @@ __device__ __forceinline__ uint64_t codes_at(const uint32_t *__restrict__ packed
     return x;
 }
 
+// Index of the text of a batch that holds position p: largest s with set_off[s] <= p.
+__device__ __forceinline__ uint32_t set_of(const int64_t *__restrict__ set_off, uint32_t n_sets,
+                                           uint32_t p) {
+    uint32_t lo = 0, hi = n_sets;  // invariant: set_off[lo] <= p < set_off[hi]
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (set_off[mid] <= int64_t(p)) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 }  // namespace saasm
