@@ -265,19 +265,37 @@ __global__ __launch_bounds__(256) void k_job_scan(const uint8_t *__restrict__ te
     }
 }
 
-// One branch-free pass (vectorisable): count separators, flag any byte outside A,C,G,T,$.
+// One branch-free pass: count separators, flag any byte outside A,C,G,T,$.  By 64 bytes at a time,
+// with a count and a flag of 8 bits for each of them, which the host compiler turns into byte
+// vectors (100,000 characters in 9 us of a host core; one 64-bit count took 125, and submission, not the
+// device, then sets how many jobs a batch finds queued).
 static bool scan_text(const uint8_t *t, int64_t n, int64_t *m_out) {
-    int64_t m = 0;
-    uint32_t bad = 0;
-    for (int64_t i = 0; i < n; ++i) {
+    constexpr int kLanes = 64;
+    int64_t m = 0, i = 0;
+    uint8_t bad[kLanes] = {0};
+    while (n - i >= kLanes) {
+        uint8_t seps[kLanes] = {0};
+        int64_t steps = (n - i) / kLanes;
+        if (steps > 255) steps = 255;  // a count holds so many
+        for (int64_t k = 0; k < steps; ++k, i += kLanes)
+            for (int l = 0; l < kLanes; ++l) {
+                const uint8_t c = t[i + l];
+                const uint8_t sep = c == '$';
+                const uint8_t base = uint8_t(c == 'A') | uint8_t(c == 'C') | uint8_t(c == 'G') | uint8_t(c == 'T');
+                seps[l] = uint8_t(seps[l] + sep);
+                bad[l] |= uint8_t((sep | base) ^ 1u);
+            }
+        for (int l = 0; l < kLanes; ++l) m += seps[l];
+    }
+    uint8_t any = 0;
+    for (int l = 0; l < kLanes; ++l) any |= bad[l];
+    for (; i < n; ++i) {
         const uint8_t c = t[i];
-        const uint32_t sep = c == '$';
-        const uint32_t base = (c == 'A') | (c == 'C') | (c == 'G') | (c == 'T');
-        m += sep;
-        bad |= (sep | base) ^ 1u;
+        m += c == '$';
+        any |= !(c == '$' || c == 'A' || c == 'C' || c == 'G' || c == 'T');
     }
     *m_out = m;
-    return bad == 0;
+    return any == 0;
 }
 
 static int64_t arena_alloc(asm_server *S, int64_t bytes, bool high = false) {
