@@ -36,7 +36,7 @@ __device__ __forceinline__ uint32_t read_of(const uint32_t *__restrict__ sepmask
 
 // Device words of a call: error bits, lcp[0], reads, candidates and rows (64 bits each).
 constexpr int kOvErr = 0, kOvLcp0 = 1, kOvReads = 2, kOvHits = 4, kOvRows = 6;
-constexpr int kOvTick = 16;  // tickets of the reads, the walks, the rows and the placing
+constexpr int kOvTick = 16;  // tickets of the reads, the placing and the rows
 
 // Validates the text and finds its reads: separator bits and the separators before each word
 // of 32 positions, the read ends while they fit, and the read count.
@@ -146,8 +146,8 @@ __device__ __forceinline__ void walk_read(const int32_t *__restrict__ sa, const 
         run = l < run ? l : run;
         if (run < min_len) break;
         const uint32_t s = uint32_t(sa[k - 1]);
-        const uint32_t a = s < n ? read_of(sepmask, sepcnt, s) : m;
-        if (a >= m) {
+        const uint32_t a = read_of(sepmask, sepcnt, s < n ? s : n - 1);
+        if (a >= m || s >= n) {
             raise_err(err, kErrRange);
             break;
         }
@@ -155,8 +155,8 @@ __device__ __forceinline__ void walk_read(const int32_t *__restrict__ sa, const 
     }
     for (uint32_t k = uint32_t(j) + 1; k < n && lcp[k] >= len; ++k) {
         const uint32_t s = uint32_t(sa[k]);
-        const uint32_t a = s < n ? read_of(sepmask, sepcnt, s) : m;
-        if (a >= m) {
+        const uint32_t a = read_of(sepmask, sepcnt, s < n ? s : n - 1);
+        if (a >= m || s >= n) {
             raise_err(err, kErrRange);
             break;
         }
@@ -169,9 +169,9 @@ struct OvlTile {
     uint64_t count, at;
 };
 
-// One read per thread, tiles by ticket (the read count is only on the device).  A thread keeps
-// its first kWkKeep matches in LDS while its tile takes room for all of its own, one addition to
-// the count; a read with more is walked again.  A tile's matches are written together, in order,
+// One read per thread, tiles dealt out in turn (the read count is only on the device).  A thread
+// keeps its first kWkKeep matches in LDS while its tile takes room for all of its own, one addition
+// to the count; a read with more is walked again.  A tile's matches are written together, in order,
 // if they fit in cap_hits; k_ovl_place puts the tiles in order.  Nothing is walked when the text
 // or the LCP array is not valid.
 // No workgroup waits for another: the matches of one read can take seconds to find (a short
@@ -187,7 +187,6 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
     const uint32_t *__restrict__ sepmask, const int32_t *__restrict__ sepcnt, uint32_t n,
     int64_t cap_reads, int32_t min_len, uint64_t *__restrict__ hkeys, uint32_t *__restrict__ hvals,
     int64_t cap_hits, OvlTile *__restrict__ tiles, uint32_t *ctr) {
-    __shared__ uint32_t s_tile;
     __shared__ uint64_t s_at;
     __shared__ uint64_t s_w[kWkBlock / kWave];
     __shared__ uint32_t s_a[kWkKeep][kWkBlock], s_l[kWkKeep][kWkBlock];
@@ -199,13 +198,8 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
                        int64_t(reads) <= cap_reads;
     const uint32_t m = valid ? reads : 0u;
     const uint32_t ntiles = (m + kWkBlock - 1) / kWkBlock;
-    if (blockIdx.x >= ntiles) return;  // the others are enough (a ticket takes 11 ns of all)
-    while (true) {
-        __syncthreads();
-        if (tid == 0) s_tile = ticket(ctr + kOvTick + 1);
-        __syncthreads();
-        const uint32_t tile = s_tile;
-        if (tile >= ntiles) break;
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        __syncthreads();  // what the tile before left in LDS has been read
         const uint32_t b = tile * kWkBlock + tid;
         uint32_t c = 0;
         if (b < m)
@@ -252,8 +246,12 @@ __global__ __launch_bounds__(kWkBlock) void k_ovl_walk(
 }
 
 // The tiles' matches, put in the order of the tiles, and the rows' look-back words cleared;
-// nothing when they did not all fit in cap_hits.  Bound by memory (24 bytes a match).
+// nothing when they did not all fit in cap_hits.  Units of work by ticket, one for about
+// kPlUnit matches: all tiles are cut into as many slices, and the first slice of a tile looks
+// back for the others, which wait for what it publishes (26 M matches of two tiles of reads: 0.2
+// ms, a tile a workgroup 36).  Bound by memory (24 bytes a match).
 constexpr int kPlBlock = 256;
+constexpr uint32_t kPlUnit = 2048;
 constexpr int kRwBlock = 256;  // of the rows' kernel
 constexpr int kRwItems = 4;
 constexpr int kRwTile = kRwBlock * kRwItems;
@@ -261,30 +259,45 @@ __global__ __launch_bounds__(kPlBlock) void k_ovl_place(
     const OvlTile *__restrict__ tiles, const uint64_t *__restrict__ hkeys,
     const uint32_t *__restrict__ hvals, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
     int64_t cap_hits, uint64_t *__restrict__ lb_rows, uint64_t *lbflags, uint32_t *ctr) {
-    __shared__ uint32_t s_tile;
+    __shared__ uint32_t s_unit;
     __shared__ uint64_t s_to;
     const uint64_t hits = *reinterpret_cast<const uint64_t *>(ctr + kOvHits);
     if (hits == 0 || hits > uint64_t(cap_hits)) return;  // 0 too where nothing was walked
     const uint32_t ntiles = (ctr[kOvReads] + kWkBlock - 1) / kWkBlock;
-    if (blockIdx.x >= ntiles) return;
-    const uint32_t groups = gridDim.x < ntiles ? gridDim.x : ntiles;  // those that go on
+    const uint32_t slices = uint32_t(hits / (uint64_t(ntiles) * kPlUnit)) + 1u;
+    const uint32_t units = ntiles * slices;  // at most ntiles + hits / kPlUnit
+    if (blockIdx.x >= units) return;  // the others are enough (a ticket takes 11 ns of all)
+    const uint32_t groups = gridDim.x < units ? gridDim.x : units;  // those that go on
     for (uint64_t i = blockIdx.x * kPlBlock + threadIdx.x; i * kRwTile < hits; i += groups * kPlBlock)
         lb_rows[i] = 0;
     while (true) {
         __syncthreads();
-        if (threadIdx.x == 0) s_tile = ticket(ctr + kOvTick + 3);
+        if (threadIdx.x == 0) s_unit = ticket(ctr + kOvTick + 1);
         __syncthreads();
-        const uint32_t tile = s_tile;
-        if (tile >= ntiles) break;
+        const uint32_t tile = s_unit / slices, slice = s_unit % slices;
+        if (s_unit >= units) break;
         const OvlTile t = tiles[tile];
-        if (threadIdx.x < kWave) {
-            const uint64_t to = lookback_tile<SumOp>(lbflags, int(tile), t.count, ctr + kOvErr);
-            if (threadIdx.x == 0) s_to = to;
+        if (slice == 0) {
+            if (threadIdx.x < kWave) {
+                const uint64_t to = lookback_tile<SumOp>(lbflags, int(tile), t.count, ctr + kOvErr);
+                if (threadIdx.x == 0) s_to = to;
+            }
+        } else if (threadIdx.x == 0) {
+            uint64_t v = ld_agent(lbflags + tile);  // of a lower ticket
+            for (uint32_t spins = 0; v >> 62 != 2; v = ld_agent(lbflags + tile)) {
+                if (++spins > kSpinLimit) {
+                    raise_err(ctr + kOvErr, kErrSpin);
+                    v = kLb64Inc | (hits + t.count + 1);  // out of range below
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            s_to = (v & kLb64Val) - t.count;
         }
         __syncthreads();
         const uint64_t to = s_to;
-        if (to + t.count > hits) continue;  // a look-back that gave up: reported
-        for (uint64_t i = threadIdx.x; i < t.count; i += kPlBlock) {
+        if (to + t.count > hits) continue;  // a wait that gave up: reported
+        for (uint64_t i = uint64_t(slice) * kPlBlock + threadIdx.x; i < t.count; i += slices * kPlBlock) {
             keys[to + i] = hkeys[t.at + i];
             vals[to + i] = hvals[t.at + i];
         }
@@ -388,6 +401,23 @@ static void carve_hits(Carver &c, int64_t hits, int64_t r, const Tune &t, OvlHit
     carve_sort(c, r, 32, t, &H->sb, false);
 }
 
+// Bytes to find, place and sort r candidates; the most of them that fit in so many bytes.
+static int64_t hits_bytes(int64_t r, const Tune &t) {
+    Carver c(nullptr, INT64_MAX);
+    OvlHits H;
+    carve_hits(c, r, r, t, &H);
+    return c.off;
+}
+static int64_t hits_in(int64_t bytes, const Tune &t) {
+    int64_t lo = 0, hi = bytes / 24 < int64_t(1) << 31 ? bytes / 24 : int64_t(1) << 31;
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo + 1) / 2;
+        if (hits_bytes(mid, t) <= bytes) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 static int bits_for_u(int64_t v) {
     int b = 0;
     while ((int64_t(1) << b) <= v) ++b;
@@ -434,12 +464,12 @@ static int find_hits(const uint8_t *text, int64_t n, const int32_t *sa, const in
     }
     {
         TimedScope ts("overlap_walk", 0.0, 12.0, s);  // per read, counted below
-        // at most eight workgroups a CU, which take tiles until none is left
+        // at most eight workgroups a CU
         const unsigned g = unsigned(wt < 1 ? 1 : wt < 2048 ? wt : 2048);
         hipLaunchKernelGGL(k_ovl_walk, dim3(g), dim3(kWkBlock), 0, s, sa, isa,
                            lcp, R.read_end, F.sepmask, F.sepcnt, uint32_t(n), cap_reads, min_len,
                            H.sb.keys[1], H.sb.vals[1], cap_hits, R.tiles, F.ctr);
-        hipLaunchKernelGGL(k_ovl_place, dim3(g), dim3(kPlBlock), 0, s, R.tiles, H.sb.keys[1],
+        hipLaunchKernelGGL(k_ovl_place, dim3(1024), dim3(kPlBlock), 0, s, R.tiles, H.sb.keys[1],
                            H.sb.vals[1], H.sb.keys[0], H.sb.vals[0], cap_hits, H.lb_rows, R.lb_place, F.ctr);
         ts.finish();
     }
@@ -480,26 +510,25 @@ static int sa_overlaps_impl(const uint8_t *text, int64_t n, const int32_t *sa, c
     if (ws_bytes < fixed) return fail(SA_ERR_NOMEM, "sa_overlaps: workspace too small");
     Tune t;
     resolve_tuning(nullptr, &t);
-    // What the text-sized part leaves is split before the counts are known: a sixteenth is
-    // room for read ends and tile words (under 5 bytes a read), and of the rest about two
-    // thirds for the candidates the walks find (24 of their 26 bytes and the sort's words, so at
-    // 36 a candidate the rest of a workspace holds them twice).
-    // Where the counts do not fit that split, the search runs again with the sizes it found.
+    // What the text-sized part leaves is split before the counts are known: of what a sort needs
+    // for however few candidates (8 MB of digit counts) and more, an eighth of the rest is room
+    // for read ends and tile words (under 5 bytes a read), all else for candidates.  Where the
+    // counts do not fit that split, the search runs again with the sizes it found; where every
+    // read has some candidates, a workspace a quarter larger than it asks for spares that.
     Carver c(ws, ws_bytes - 256);
     OvlFixed F;
     carve_fixed(c, n, &F);
-    const int64_t left = ws_bytes - 256 - c.off;
-    int64_t cap_reads = left / 16 / 5 < n ? left / 16 / 5 : n, cap_hits = (left - left / 16) / 36;
-    if (cap_reads < 1) cap_reads = cap_hits = 0;
-    if (cap_hits > (int64_t(1) << 31)) cap_hits = int64_t(1) << 31;
+    const int64_t left = ws_bytes - 256 - c.off, least = hits_bytes(1, t);
+    const int64_t reads_room = (left > least ? left - least : left) / 8;
+    int64_t cap_reads = reads_room / 5 < n ? reads_room / 5 : n, cap_hits = 0;
     const Carver at_reads = c;
     OvlReads R{};
     OvlHits H{};
     uint32_t host[kStWords];
     carve_reads(c, cap_reads, &R);
     Carver at_hits = c;
+    if (cap_reads > 0) cap_hits = hits_in(ws_bytes - 256 - ((c.off + 255) & ~int64_t(255)), t);
     take_hits(c, cap_hits, cap_hits, &H);
-    if (!c.ok()) cap_hits = 0;
     SA_TRY(find_hits(text, n, sa, isa, lcp, min_len, F, R, cap_reads, H, cap_hits, host, s));
     const int64_t m = host[kOvReads];
     int64_t r = words64(host, kOvHits);

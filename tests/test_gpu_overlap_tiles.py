@@ -48,3 +48,39 @@ def test_more_tiles_than_walk_at_once(lib, m):
     keep = np.ones(some.shape, dtype=bool)
     keep[(np.arange(m) // 1024) % 2 == 1, 1:9] = False
     assert check(lib, some[keep], 8) > 0
+
+
+@pytest.mark.parametrize("kind", ["few", "copies", "homopolymers", "10x"])
+def test_one_search_in_a_roomy_workspace(lib, kind):
+    """In a workspace a quarter larger than the call asks for, the text is searched once, however
+    many candidates a read has (the timing records show the launches)."""
+    import ctypes
+    rng = np.random.default_rng([synth.SEED_BASE, 812])
+    word = lambda k: rng.choice(LETTERS, k).tobytes().decode()  # noqa: E731
+    text = {"few": lambda: synth.genome_reads(9990, 100_000, 3000, 100),
+            "copies": lambda: synth.text_from_strings([word(60)] * 400),
+            "homopolymers": lambda: synth.text_from_strings(["A" * 90] * 60),
+            "10x": lambda: synth.genome_reads(9991, 20_000, 1000, 200, err=0.0)}[kind]()
+    t = torch.from_numpy(text).cuda()
+    sa, isa = lib.sa_build(t)
+    lcp = lib.sa_lcp(t, sa, isa)
+    want = oracle.overlaps(text, 20)
+    c, n = lib.load(), text.size
+    P = lambda x: ctypes.c_void_p(x.data_ptr())  # noqa: E731
+    out = torch.empty((want.shape[0] + 1, 3), dtype=torch.int32, device="cuda")
+    k, need = ctypes.c_int64(-1), ctypes.c_int64(-1)
+    size, calls = int(lib.sa_overlaps_ws_bytes(n, 1, 0)), 0
+    while True:
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        lib.sa_timing_reset()
+        lib.sa_timing_enable(True)
+        rc = c.sa_overlaps(P(t), n, P(sa), P(isa), P(lcp), 20, P(out), out.shape[0], ctypes.byref(k), P(ws),
+                           size, ctypes.byref(need), None)
+        lib.sa_timing_enable(False)
+        if rc == lib.SA_OK and size * 4 >= need.value * 5:
+            break
+        assert rc in (lib.SA_OK, lib.SA_ERR_NOMEM) and calls < 4
+        size, calls = need.value * 5 // 4, calls + 1
+    assert lib.sa_timing_get("overlap_walk")[0] == 1
+    assert k.value == want.shape[0] and np.array_equal(out.cpu().numpy()[:k.value], want)
