@@ -950,8 +950,6 @@ int launch_first_extract(const uint64_t *K, const uint32_t *V, int64_t n, int lo
     if (tiles > lb_words) return fail(SA_ERR_HIP, "first round: look-back array too small");
     int64_t grid = kHistParts < tiles ? kHistParts : tiles;
     *nparts = int(grid);
-    SA_TRY(launch_fill_u64(lbflags, tiles, 0, s));
-    SA_TRY(launch_fill_u32(tick, 1, 0, s));
     const size_t lds = size_t(P) * t.radix() * 4;
     const uint64_t nclear = uint64_t(64 + sort_flag_words(n, key_bits, t));
     const uint32_t lb = uint32_t(lo_bit);

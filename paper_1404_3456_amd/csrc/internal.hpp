@@ -229,8 +229,8 @@ int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int 
                 hipStream_t s, int *nparts);
 // First round (first_round.hip): from items ordered by key bits [lo_bit, key_bits), which tell
 // their first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the
-// items of runs too long for it, taken out.  The round's kernel needs its ticket and
-// look-back words (one per kFirstMinTile items) cleared.
+// items of runs too long for it, taken out.  Both need their ticket and look-back words (one
+// per kFirstMinTile items) cleared.
 constexpr int kKeyLenShift = 55;          // a key's top 9 bits: distance to the separator, capped
 constexpr uint32_t kKeyLenMax = 511;
 constexpr int kExtStage = 57;             // bases one comparison of the extension takes

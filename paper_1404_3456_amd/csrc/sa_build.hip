@@ -216,14 +216,14 @@ __global__ __launch_bounds__(kRuBlock) void k_rank_update(
     }
 }
 
-// The state a build starts from, and cleared look-back and table words for its first round.
+// Cleared look-back words, table words and ticket; state (if given) as a first round starts from it.
 __global__ __launch_bounds__(256) void k_build_init(uint32_t *state, uint32_t n, uint64_t *lbflags,
                                                     uint32_t nlb, uint32_t *table, uint32_t ntable,
                                                     uint32_t *tick) {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < nlb; i += gridDim.x * 256u) lbflags[i] = 0;
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < ntable; i += gridDim.x * 256u) table[i] = 0;
     if (blockIdx.x != 0) return;
-    if (threadIdx.x < kStWords)
+    if (state && threadIdx.x < kStWords)
         state[threadIdx.x] = threadIdx.x == kStActive || threadIdx.x == kStTopN ? n : 0u;
     if (threadIdx.x == kStWords) *tick = 0;
 }
@@ -552,13 +552,13 @@ struct Build {
         return sort_run(L.sb, 0, count_dev, n, lo_bit, bits, t, nparts, s, cur, true);
     }
 
-    int init() {
+    int clear_first_round(uint32_t *state, int64_t table_words) {
         const int64_t nlb = (n + kLbMinTile - 1) / kLbMinTile;
         if (nlb > L.lb_words) return fail(SA_ERR_HIP, "sa_build: look-back array too small");
         const int64_t g = (nlb + 255) / 256 < 1024 ? (nlb + 255) / 256 : 1024;
         static_assert(kSampleSlots <= kSampleMinN, "the table lies in bigidx");
-        hipLaunchKernelGGL(k_build_init, dim3(unsigned(g)), dim3(256), 0, s, L.state, uint32_t(n), L.lbflags,
-                           uint32_t(nlb), L.bigidx, sample_looked() ? uint32_t(kSampleSlots) : 0u, L.tickets);
+        hipLaunchKernelGGL(k_build_init, dim3(unsigned(g)), dim3(256), 0, s, state, uint32_t(n), L.lbflags,
+                           uint32_t(nlb), L.bigidx, uint32_t(table_words), L.tickets);
         SA_HIP(hipGetLastError());
         return SA_OK;
     }
@@ -592,7 +592,7 @@ struct Build {
 
     // The first round, and the state after it (pinned slot 0, host[]).
     int round0(PinnedState &ps, uint32_t host[kStWords]) {
-        SA_TRY(init());
+        SA_TRY(clear_first_round(L.state, sample_looked() ? kSampleSlots : 0));
         SA_TRY(launch_pack(text, n, L.packed, L.sepmask, nullptr, nullptr, L.state + kStErr, s));
         if (n_sets > 1) {  // one text's end is checked by the packing
             SA_HIP(hipMemcpyAsync(L.set_off, set_off_h, size_t(n_sets + 1) * 8, hipMemcpyHostToDevice, s));
@@ -618,9 +618,9 @@ struct Build {
         timing_round_items(sorted, host[kStTopN], 0);
         timing_round_items(plain, host[kStLongRun] ? 0 : n, 0);
         if (host[kStLongRun] == 0) return SA_OK;
+        SA_TRY(check_err(host[kStErr]));  // cleared now with the rest of the state
+        SA_TRY(clear_first_round(L.state, 0));
         if (host[kStTopN] == 0) {  // the passes and the run sort did nothing
-            SA_TRY(launch_fill_u32(L.state + 1, kStWords - 1, 0, s));
-            SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
             whole_keys();
             return round0_whole(ps, host);
         }
@@ -628,8 +628,6 @@ struct Build {
         // sorted by their whole keys and put back, and the round's end runs again.  The passes
         // work between the idle half of the sort's buffers and the slot and position arrays,
         // which nothing has filled yet.
-        SA_TRY(launch_fill_u32(L.state + 1, kStWords - 1, 0, s));
-        SA_TRY(launch_fill_u32(L.state + kStActive, 1, uint32_t(n), s));
         SortBufs b = L.sb;
         b.keys[0] = L.sb.keys[cur ^ 1];
         b.vals[0] = L.sb.vals[cur ^ 1];
@@ -644,8 +642,7 @@ struct Build {
         SA_TRY(launch_big_place(b.keys[bc], b.vals[bc], L.bigidx, n, L.state, L.sb.keys[cur],
                                 L.sb.vals[cur], L.state + kStErr, s));
         timing_scope_mode(kModeAny);
-        SA_TRY(launch_fill_u64(L.lbflags, (n + kLbMinTile - 1) / kLbMinTile, 0, s));
-        SA_TRY(launch_fill_u32(L.tickets, 1, 0, s));
+        SA_TRY(clear_first_round(nullptr, 0));
         SA_TRY(launch_first_runs(L.sb.keys[cur], L.sb.vals[cur], L.packed, n, lo_bit, key0_bits, top_d, h0, true, sa, rank,
                                  L.slots[0], L.pos, lcp, L.lbflags, L.lb_words, L.tickets, L.state, s));
         SA_TRY(round_end(h0));
