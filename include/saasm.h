@@ -55,8 +55,8 @@ enum {
  *                    1024 only with 16 items and digit_bits <= 9; default 1024, or 512 for
  *                    11-bit digits)
  *   items_per_thread 8 or 16 keys per thread (tile = block_threads * items_per_thread;
- *                    default 16).  With both left 0, sorts of up to 2^20 items take 512 x 8
- *                    and of up to 2^21 items 512 x 16
+ *                    default 16).  With both left 0, sorts of up to 2^20 items (2^19 with
+ *                    11-bit digits) take 512 x 8 and of up to 2^21 items 512 x 16
  *   seg_pack         sa_build_batched only: at most this many characters per build
  *                    (consecutive texts are packed greedily; 0 = all texts in one build);
  *                    must be 0 for the other entry points                                 */

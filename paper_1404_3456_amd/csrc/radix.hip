@@ -49,7 +49,7 @@ void carve_sort(Carver &c, int64_t n, int bits, const Tune &t, SortBufs *b, bool
     b->gbase = c.take<uint32_t>(int64_t(P) * t.radix());
     // enough for a sort of any number of items up to n: fewer items can take smaller tiles
     int64_t words = 1;
-    for (const int64_t m : {n, kTuneSmallN, kTuneMidN}) {
+    for (const int64_t m : {n, t.small_n(), kTuneMidN}) {
         const int64_t w = m <= n ? sort_flag_words(m, bits, t) : 0;
         words = w > words ? w : words;
     }
