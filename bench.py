@@ -594,13 +594,11 @@ def traffic_for(args, key, tuning):
     """Counter-measured bytes per launch at the L2's memory side (<kernel key>_traffic.json under
     profiles/), valid only for the sources the counters were taken on and the default tuning."""
     import hashlib
-    sources = {"radix_pass": ("radix.hip", "device.hpp"),
-               "sa_build": ("sa_build.hip", "first_round.hip", "radix.hip", "pack.hip", "device.hpp",
-                            "internal.hpp"),
-               "rank_update": ("sa_build.hip", "device.hpp", "internal.hpp"),
-               "kasai": ("lcp.hip", "text.hpp", "device.hpp", "internal.hpp"),
-               "first_runs": ("first_round.hip", "device.hpp", "internal.hpp"),
-               "keyruns": ("sa_build.hip", "device.hpp", "internal.hpp")}
+    sources = {"sa_build": ("sa_build.hip", "first_round.hip", "radix.hip", "pack.hip", "text.hpp",
+                            "device.hpp", "internal.hpp"),
+               "first_runs": ("first_round.hip", "text.hpp", "device.hpp", "internal.hpp"),
+               "radix_pass": ("radix.hip", "text.hpp", "device.hpp", "internal.hpp"),
+               "kasai": ("lcp.hip", "text.hpp", "device.hpp", "internal.hpp")}
     tpath = os.path.join(args.traffic_dir, f"{key}_traffic.json")
     if key not in sources or not os.path.exists(tpath) or tuning is not None:
         return None

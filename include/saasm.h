@@ -318,7 +318,9 @@ int64_t sa_overlaps_ws_bytes(int64_t n, int64_t m, int64_t candidates);
  *   n_out_h       host out: number of rows
  *   ws_needed_h   host out, may be NULL: workspace bytes this text needs
  * Returns SA_ERR_NOMEM (with *ws_needed_h set) when ws_bytes is too small -- call again with a
- * larger workspace -- and SA_ERR_CAPACITY (with *n_out_h set) when cap < rows.
+ * larger workspace; where that is a quarter larger than asked for, the text is as a rule searched
+ * once and not twice -- and SA_ERR_CAPACITY (with *n_out_h set, and the first cap rows written)
+ * when cap < rows.
  * Synchronises the stream. */
 int sa_overlaps(const uint8_t *text, int64_t n, const int32_t *sa, const int32_t *isa,
                 const int32_t *lcp, int32_t min_len, int32_t *out, int64_t cap,

@@ -196,7 +196,6 @@ int sort_run(const SortBufs &b, int cur, const uint32_t *count_dev, int64_t n, i
 // Device-side round state of a suffix-array build (words of a uint32 array).
 constexpr int kStErr = 0;      // error bits
 constexpr int kStActive = 1;   // suffixes in non-singleton groups entering the next round
-constexpr int kStKeys = 2;     // keys written by the round's key build (== kStActive)
 constexpr int kStH = 3;        // prefix length the groups are sorted by
 constexpr int kStRounds = 4;   // rounds completed
 constexpr int kStNext = 5;     // active count produced by the round's rank update
