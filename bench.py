@@ -592,7 +592,8 @@ def kernel_table(pkg, keys, steps):
 
 def traffic_for(args, key, tuning):
     """Counter-measured bytes per launch at the L2's memory side (<kernel key>_traffic.json under
-    profiles/), valid only for the sources the counters were taken on and the default tuning."""
+    profiles/), valid only for the workload and the sources the counters were taken on and the
+    default tuning."""
     import hashlib
     sources = {"sa_build": ("sa_build.hip", "first_round.hip", "radix.hip", "pack.hip", "text.hpp",
                             "device.hpp", "internal.hpp"),
@@ -609,7 +610,7 @@ def traffic_for(args, key, tuning):
         tr = json.load(open(tpath))
     except (OSError, ValueError):
         return None
-    if tr.get("source_sha256") != h or args.sa_algo != "doubling":
+    if tr.get("source_sha256") != h or tr.get("workload") != args.workload or args.sa_algo != "doubling":
         return None
     return tr.get("bytes_per_launch")
 

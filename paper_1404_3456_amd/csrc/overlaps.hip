@@ -176,7 +176,7 @@ struct OvlTile {
 // or the LCP array is not valid.
 // No workgroup waits for another: the matches of one read can take seconds to find (a short
 // read of one letter beside a read of millions of it), longer than a look-back polls.
-// Bound by each walk's chain of reads: 46 us for 100,000 reads in 50.1 M suffixes, and 12 to place
+// Bound by each walk's chain of reads: 43 us for 100,000 reads in 50.1 M suffixes, and 12 to place
 // their matches (72 in one kernel that looked back between the two; a walk to count, a scan and
 // a walk to write took 90).
 constexpr int kWkBlock = 256;

@@ -49,3 +49,23 @@ def test_build_keys():
     bench = load_bench()
     assert {"first_extract", "first_runs"} <= set(bench.BUILD_KEYS) <= set(bench.KEYS)
     assert all(bench.SURVEY_BYTES[k] > 0 for k in bench.BUILD_KEYS)
+
+
+def test_traffic_records_are_of_one_workload_and_its_sources(tmp_path):
+    import hashlib
+    import json
+    from types import SimpleNamespace
+    bench = load_bench()
+    csrc = os.path.join(ROOT, "paper_1404_3456_amd", "csrc")
+    files = ("first_round.hip", "text.hpp", "device.hpp", "internal.hpp")
+    h = hashlib.sha256(b"".join(open(os.path.join(csrc, f), "rb").read() for f in files)).hexdigest()
+    record = {"bytes_per_launch": 7, "source_sha256": h, "workload": "plain-large-5M"}
+    args = SimpleNamespace(traffic_dir=str(tmp_path), workload="plain-large-5M", sa_algo="doubling")
+    path = tmp_path / "first_runs_traffic.json"
+    path.write_text(json.dumps(record))
+    assert bench.traffic_for(args, "first_runs", None) == 7
+    args.workload = "repeat-stress-40M"
+    assert bench.traffic_for(args, "first_runs", None) is None
+    args.workload = "plain-large-5M"
+    path.write_text(json.dumps({**record, "source_sha256": "0"}))
+    assert bench.traffic_for(args, "first_runs", None) is None
