@@ -140,14 +140,14 @@ __global__ __launch_bounds__(256) void k_lookup(const uint4 *__restrict__ blk,
                                                 uint32_t ns, uint32_t stride,
                                                 int32_t *__restrict__ lohi, uint32_t *err) {
     __shared__ uint64_t s_top[kTopSamples];
-    // Without a separator at its end nothing stops a comparison there: a long pattern would be
-    // compared with whatever follows the text's records.  (Found by the packing, so the same for
-    // every thread; the call fails.)
-    if (ld_agent(err) & kErrNoSepEnd) return;
+    const uint32_t found = *err;  // by the packing
     const uint32_t step = (ns + kTopSamples - 1) / kTopSamples;  // samples per held one
     const uint32_t nt = ns ? (ns + step - 1) / step : 0;
     for (uint32_t t = threadIdx.x; t < nt; t += 256) s_top[t] = samples[t * step];
     __syncthreads();
+    // Without a separator at its end nothing stops a comparison there: a long pattern would be
+    // compared with whatever follows the text's records.  (The call fails.)
+    if (found & kErrNoSepEnd) return;
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= npat) return;
     const int64_t a = off[i], b = off[i + 1];
