@@ -699,7 +699,8 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
 // them tell as much of the runs' sizes as all would.  Each taken takes a slot of an open-addressed
 // table of (31 bits of the hash, "met twice") words; one that finds its word there, and marked
 // already, needs no atomic, so a text of one repeated base does not serialise on one word.  The
-// last workgroup decides.
+// last workgroup decides, by the share or because far fewer were taken than should be (the few
+// different strings of a tandem repeat may all fall into another part).
 // Bound by latency, so the taken are listed in LDS first and then probe all at once: 11 to 13 us at
 // 20 M and 50 M suffixes, 16 at 400 M (54 to 61 with the probes in the loop over the row; 20 to 53
 // with every position taken of 2^16 to 2^18).
@@ -712,17 +713,19 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_runs(
     static_assert(kSampleSlots <= 1 << 14, "slots come from 14 bits of the hash");
     static_assert(kSampleRow - 1 + 24 < 32, "a row's bases lie in one word");
     __shared__ uint32_t s_h[kSampleStep];
-    __shared__ uint32_t s_taken, s_paired;
-    if (threadIdx.x == 0) s_taken = s_paired = 0;
+    __shared__ uint32_t s_taken, s_paired, s_valid;
+    if (threadIdx.x == 0) s_taken = s_paired = s_valid = 0;
     __syncthreads();
     const uint32_t t = blockIdx.x * kSampleBlock + threadIdx.x;
     // part positions a thread, at least 2 kSampleRow; (t + 1) * part <= n
     const uint32_t a = t * part + uint32_t((uint64_t(t * 2654435769u) * (part - kSampleRow)) >> 32);
     const uint64_t codes = codes_at(packed, a);
     const uint32_t sep = bits_at(sepmask, a);
+    uint32_t valid = 0;
 #pragma unroll
     for (int j = 0; j < kSampleRow; ++j) {
         if ((sep << j) >> (32 - top_d)) continue;  // ends before top_d <= 24 bases
+        ++valid;
         uint64_t h = (codes << (2 * j)) >> (64 - 2 * top_d);
         h = (h ^ (h >> 29)) * 0x9e3779b97f4a7c15ull;
         if (skip && h >> (64 - skip)) continue;
@@ -748,17 +751,29 @@ __global__ __launch_bounds__(kSampleBlock) void k_sample_runs(
             break;
         }
     }
-    for (int o = 1; o < kWave; o <<= 1) paired += __shfl_xor(paired, o);
-    if (lane_id() == 0 && paired) atomicAdd(&s_paired, paired);
+    for (int o = 1; o < kWave; o <<= 1) {
+        paired += __shfl_xor(paired, o);
+        valid += __shfl_xor(valid, o);
+    }
+    if (lane_id() == 0) {
+        atomicAdd(&s_paired, paired);
+        atomicAdd(&s_valid, valid);
+    }
     __syncthreads();
     if (threadIdx.x != 0) return;
+    __hip_atomic_fetch_add(state + kStValid, s_valid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();  // before this workgroup counts as ended
     const uint64_t mine = (uint64_t(1) << kSecond) | (uint64_t(taken) << kFirst) | s_paired;
     const uint64_t all = mine + __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(state + kStSample), mine,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (all >> kSecond != gridDim.x) return;
     const uint32_t field = (1u << kFirst) - 1;
     const uint32_t pairs = uint32_t(all) & field, of = uint32_t(all >> kFirst) & field;
-    if (of < 256 || float(pairs) < enough * float(of)) return;
+    __threadfence();
+    const uint32_t could = ld_agent(state + kStValid);
+    // far fewer taken than a part of the hashes should hold: a text of a few bases over and over
+    const bool few = could >= 1024 && (of << skip) < could / 4;
+    if (!few && (of < 256 || float(pairs) < enough * float(of))) return;
     st_agent(state + kStTopN, 0u);
     st_agent(state + kStLongRun, 1u);
 }

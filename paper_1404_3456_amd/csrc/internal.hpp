@@ -209,6 +209,8 @@ constexpr int kStLcpLong = 12; // the LCP array needs Kasai's scan (launch_lcp_r
 constexpr int kStTopN = 13;    // first round: items its passes over the top bits sort (n, or 0)
 constexpr int kStSample = 14;  // launch_sample_runs: its counts (64 bits)
 constexpr int kStWords = 16;   // state words the host reads back
+constexpr int kStValid = 16;   // launch_sample_runs: positions that could be sampled
+constexpr int kStAll = 17;     // state words
 constexpr int kRunMax = 32;    // largest group the run sort handles
 
 // Pinned host words and events for reading device words without a full stream sync (two slots so
@@ -226,10 +228,11 @@ PinnedState *pinned_state();
 int read_words(const uint32_t *dev, uint32_t host[kStWords], hipStream_t s);
 
 // key builders (fused with the histogram of the sort that follows, over key bits
-// [lo_bit, key_bits)); a value is its item's index and is left to the first pass
+// [lo_bit, key_bits)); a value is its item's index and is left to the first pass.  count_dev: the
+// count that the passes read, if they do; no keys are made where it is 0
 int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
-                int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
-                hipStream_t s, int *nparts);
+                int n_sets, int lo_bit, int key_bits, const uint32_t *count_dev, const SortBufs &b, int cur,
+                const Tune &t, hipStream_t s, int *nparts);
 // First round (first_round.hip): from items ordered by key bits [lo_bit, key_bits), which tell
 // their first top_d bases apart, to labelled groups equal on h0 + kExtBases symbols; and the
 // items of runs too long for it, taken out.  Both need their ticket and look-back words (one
@@ -249,7 +252,8 @@ int launch_first_runs(const uint64_t *K, const uint32_t *V, const uint32_t *pack
 // Samples the text's suffixes at random, some 2^12 to 2^13 (all positions looked at, `looked`, a
 // multiple of kSampleStep and at most kMaxLooked, that fall into a part of the hashes), and sets
 // state[kStTopN] to 0 and state[kStLongRun] to 1 when the share of them that are equal to another
-// position looked at on top_d bases is at least `enough`.  table: kSampleSlots cleared words.
+// position looked at on top_d bases is at least `enough`, or most positions hold so few different
+// bases that the sample misses them.  table: kSampleSlots cleared words.
 constexpr int kSampleBlock = 256;
 constexpr int kSampleRow = 8;  // positions in a row a thread looks at
 constexpr int64_t kSampleStep = int64_t(kSampleBlock) * kSampleRow;

@@ -636,11 +636,13 @@ __global__ __launch_bounds__(kK0Block) void k_key0(const uint32_t *__restrict__ 
                                               uint32_t n_sets, int set_shift,
                                               uint64_t *__restrict__ keys, int lo_bit,
                                               uint64_t key_mask, int passes,
-                                              uint32_t *__restrict__ hist, uint32_t *clear,
+                                              uint32_t *__restrict__ hist,
+                                              const uint32_t *count_dev, uint32_t *clear,
                                               uint64_t nclear) {
     constexpr int R = 1 << D;
     extern __shared__ uint32_t s_h[];
     clear_words(clear, nclear);
+    if (count_dev && *count_dev == 0) return;  // passes that sort nothing follow
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
@@ -660,8 +662,8 @@ __global__ __launch_bounds__(kK0Block) void k_key0(const uint32_t *__restrict__ 
 }
 
 int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int h0, int top_d, const int64_t *set_off_dev,
-                int n_sets, int lo_bit, int key_bits, const SortBufs &b, int cur, const Tune &t,
-                hipStream_t s, int *nparts) {
+                int n_sets, int lo_bit, int key_bits, const uint32_t *count_dev, const SortBufs &b, int cur,
+                const Tune &t, hipStream_t s, int *nparts) {
     const int set_shift = 2 * h0 + 5 + (top_d ? 1 : 0);
     const uint64_t key_mask = (uint64_t(1) << key_bits) - 1;  // key_bits <= 63
     const int P = sort_passes(key_bits - lo_bit, t);
@@ -671,10 +673,10 @@ int launch_key0(const uint32_t *packed, const uint32_t *sepmask, int64_t n, int 
     TimedScope ts("key0", double(n) * (8.0 + 0.375), s, double(n));
     const unsigned g = hist_grid(n);
     switch (t.dbits) {
-        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
-        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
-        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
-        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, b.tickets, nclear); break;
+        case 4: hipLaunchKernelGGL(k_key0<4>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, count_dev, b.tickets, nclear); break;
+        case 8: hipLaunchKernelGGL(k_key0<8>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, count_dev, b.tickets, nclear); break;
+        case 9: hipLaunchKernelGGL(k_key0<9>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, count_dev, b.tickets, nclear); break;
+        case 11: hipLaunchKernelGGL(k_key0<11>, dim3(g), dim3(kK0Block), lds, s, packed, sepmask, uint32_t(sepmask_words(n)), uint32_t(n), uint32_t(h0), uint32_t(top_d), set_off_dev, uint32_t(n_sets), set_shift, b.keys[cur], lo_bit, key_mask, P, b.hist, count_dev, b.tickets, nclear); break;
         default: return fail(SA_ERR_INVALID, "unsupported digit width");
     }
     ts.finish();

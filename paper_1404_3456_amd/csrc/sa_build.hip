@@ -223,9 +223,9 @@ __global__ __launch_bounds__(256) void k_build_init(uint32_t *state, uint32_t n,
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < nlb; i += gridDim.x * 256u) lbflags[i] = 0;
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < ntable; i += gridDim.x * 256u) table[i] = 0;
     if (blockIdx.x != 0) return;
-    if (state && threadIdx.x < kStWords)
+    if (state && threadIdx.x < kStAll)
         state[threadIdx.x] = threadIdx.x == kStActive || threadIdx.x == kStTopN ? n : 0u;
-    if (threadIdx.x == kStWords) *tick = 0;
+    if (threadIdx.x == kStAll) *tick = 0;
 }
 
 // Advances the round state after a rank update (one thread).  h_ext: symbols the first round's
@@ -548,7 +548,7 @@ struct Build {
     int first_sort(int lo_bit, const uint32_t *count_dev, int *cur) {
         const int bits = key0_bits - lo_bit;
         int nparts = 0;
-        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev(), n_sets, lo_bit, key0_bits, L.sb, 0, t, s, &nparts));
+        SA_TRY(launch_key0(L.packed, L.sepmask, n, h0, top_d, set_off_dev(), n_sets, lo_bit, key0_bits, count_dev, L.sb, 0, t, s, &nparts));
         return sort_run(L.sb, 0, count_dev, n, lo_bit, bits, t, nparts, s, cur, true);
     }
 

@@ -34,6 +34,8 @@ def text_of(kind, n):
     text = {"10x": lambda: cover(n, 10), "60x": lambda: cover(n, 60), "400x": lambda: cover(n, 400),
             "error-free 400x": lambda: cover(n, 400, err=0.0), "copies": lambda: copies,
             "tenth copies": lambda: np.concatenate([cover(n - n // 10, 10), copies[: n // 10]]),
+            "tandem": lambda: np.resize(np.append(np.resize(rng.choice(LETTERS, 7), 700), np.uint8(synth.SEP)), n),
+            "homopolymer": lambda: np.resize(np.append(np.full(900, ord("C")), synth.SEP).astype(np.uint8), n),
             "short reads": lambda: cover(n, 400, read=9)}[kind]().copy()
     text[-1] = synth.SEP
     return text
@@ -60,6 +62,7 @@ def check(lib, text, off, whole_keys):
 @pytest.mark.parametrize("n", [MIN_N + 1, MIN_N + 70_001])
 @pytest.mark.parametrize("kind, whole_keys", [("10x", False), ("60x", False), ("400x", True),
                                               ("error-free 400x", True), ("copies", True),
+                                              ("tandem", True), ("homopolymer", True),
                                               ("tenth copies", False)])
 def test_route_above_the_least_size(lib, kind, whole_keys, n):
     text = text_of(kind, n)
