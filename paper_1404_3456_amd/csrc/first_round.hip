@@ -701,8 +701,8 @@ __global__ __launch_bounds__(Shape::kBlock, Shape::kOcc) void k_first_runs(
 // already, needs no atomic, so a text of one repeated base does not serialise on one word.  The
 // last workgroup decides, by the share or because far fewer were taken than should be (the few
 // different strings of a tandem repeat may all fall into another part).
-// Bound by latency, so the taken are listed in LDS first and then probe all at once: 11 to 13 us at
-// 20 M and 50 M suffixes, 16 at 400 M (54 to 61 with the probes in the loop over the row; 20 to 53
+// Bound by latency, so the taken are listed in LDS first and then probe all at once: 12 to 14 us at
+// 20 M and 50 M suffixes, 19 at 400 M (54 to 61 with the probes in the loop over the row; 20 to 53
 // with every position taken of 2^16 to 2^18).
 __global__ __launch_bounds__(kSampleBlock) void k_sample_runs(
     const uint32_t *__restrict__ packed, const uint32_t *__restrict__ sepmask, uint32_t n,
