@@ -756,16 +756,26 @@ struct Build {
         const double more = double(after[kStH]) - double(before[kStH]);
         lcp_steps += more / 64 * (double(before[kStActive]) + double(after[kStActive]));
     }
-    // Such a comparison takes 0.024 ns at 20 M suffixes and 0.036 at 200 M, a position of Kasai's
-    // scan 0.044 and 0.058 (copies of a 500-base read 3.5 against 0.8 ms, error-free reads of
-    // 1,000 2.3 against 0.95 and of 600 0.34 against 0.88; 400 M with repeats 4.1 against 21.2).
-    static constexpr double kScanSteps = 1.75;
+    // The estimate above which Kasai's scan is the shorter way, in comparisons a suffix.  The
+    // scan's 0.038 to 0.050 ns a position hardly depend on the text.  Where the groups were all
+    // small (listed) the estimate is about twice the comparisons made, as of two suffixes that
+    // end in the round the shorter one counts; a comparison takes 0.025 to 0.03 ns while the packed
+    // text and its mask (3 / 8 of a byte a character) fit an XCD's 4 MiB of L2, and 0.035 to 0.05
+    // above.  With window records (not listed) it takes 0.014 to 0.020 ns at any size.  Entry by
+    // entry and by the scan, in ms, error-free reads at 11x: 10 M suffixes of 650 bases
+    // (estimate 2.2) 0.16 and 0.40, of 800 (3.4) 0.42 and 0.42, of 1,000 (5.1) 0.85 and 0.43; 60 M
+    // of 650 1.52 and 2.43, of 700 (2.7) 2.27 and 2.44, of 800 4.08 and 2.48; not listed, 10 M of
+    // which half are copies of one read of 200 bases (1.7) 0.20 and 0.35, of 300 (2.7) 0.40 and 0.36,
+    // of 500 (4.5) 0.65 and 0.38; 400 M with repeats 4.1 and 21.2.
+    double scan_steps(bool listed) const {
+        return !listed ? 2.4 : n <= (int64_t(4) << 20) * 8 / 3 ? 3.6 : 2.9;
+    }
 
     // The rest of the LCP array after the last round: *have_lcp when it is complete.  A build
     // whose first round left no group has it already; texts with many or long matches beyond the
     // first round's reach are left to Kasai's scan, whose work does not depend on them.
     int finish_lcp(PinnedState &ps, int64_t left, bool listed, bool *have_lcp) {
-        if (!lcp || top_bits == 0 || double(left) + lcp_steps > kScanSteps * double(n)) return SA_OK;
+        if (!lcp || top_bits == 0 || double(left) + lcp_steps > scan_steps(listed) * double(n)) return SA_OK;
         if (left > 0) {
             uint32_t host[kStWords];
             SA_TRY(launch_lcp_rest(text, L.packed, L.sepmask, n, sa, listed ? L.bigidx : nullptr,
