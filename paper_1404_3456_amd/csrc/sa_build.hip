@@ -41,7 +41,7 @@ constexpr int kRuTile = kRuBlock * kRuItems;
 constexpr int kLbMinTile = kFirstMinTile < kRuTile ? kFirstMinTile : kRuTile;
 
 constexpr int64_t kTunedTopMinN = 16384;  // choose_first_round
-constexpr int64_t kSampleMinN = int64_t(1) << 21;  // sample_looked
+constexpr int64_t kSampleMinN = int64_t(1) << 23;  // sample_looked
 
 // Rank update over the sorted active items (K, V) of a round, whose suffix-array slots are
 // S[0..A) (S == nullptr: identity, round 0).  For item i:
@@ -706,8 +706,10 @@ struct Build {
     // passes over the top bits come on top of all others: 150-base reads at 150x coverage take
     // 3.8 ms by top bits and 5.0 by whole keys (20 M suffixes), at 160x 4.5 and 5.0, at 200x 6.2
     // and 5.0, at 300x 6.2 and 5.0, copies of one read 9.4 and 8.1; at 300x 50 M 13.7 and 11.3, 200 M
-    // 62.7 and 54.7.  Up to kSampleMinN top bits are the faster way at any coverage (0.3 M at
-    // 300x: 0.91 and 1.06), as fewer, larger launches count for more than passes.
+    // 62.7 and 54.7.  Up to kSampleMinN no sample is taken: its 12 to 18 us would be more than a
+    // 75th of the whole path (batch of 5.6 M at 5x to 18x: 835 us, 848 with it), for texts of which
+    // whole keys save little (5 M at 300x: 2.03 and 1.90 ms; 16 M 5.03 and 4.12) or nothing (0.3 M
+    // 0.91 and 1.06), as fewer, larger launches count for more than passes.
     static constexpr double kDenseRun = 130, kDenseShare = 0.4;
     int64_t sample_looked() const {
         if (top_bits == 0 || n <= kSampleMinN) return 0;
@@ -768,7 +770,7 @@ struct Build {
     // which half are copies of one read of 200 bases (1.7) 0.20 and 0.35, of 300 (2.7) 0.40 and 0.36,
     // of 500 (4.5) 0.65 and 0.38; 400 M with repeats 4.1 and 21.2.
     double scan_steps(bool listed) const {
-        return !listed ? 2.4 : n <= (int64_t(4) << 20) * 8 / 3 ? 3.6 : 2.9;
+        return !listed ? 3.0 : n <= (int64_t(4) << 20) * 8 / 3 ? 3.6 : 2.9;
     }
 
     // The rest of the LCP array after the last round: *have_lcp when it is complete.  A build

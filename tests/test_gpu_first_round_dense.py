@@ -11,7 +11,7 @@ from tests import checks
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-MIN_N = 1 << 21
+MIN_N = 1 << 23
 LETTERS = np.frombuffer(b"ACGT", dtype=np.uint8)
 
 
